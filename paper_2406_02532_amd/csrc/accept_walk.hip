@@ -1,235 +1,678 @@
 // Acceptance walk (Alg. 1, main loop): sequential sampling from the target model, served from the
 // tree of precomputed distributions for as long as the sampled tokens stay on a tree path.
 //
-// One workgroup walks the tree; every step is data-parallel over the V logits of the current
-// node.  The row is read once per step and kept as exp((x - max)/t) in registers (V <= 32768) or
-// in a caller-provided scratch row (larger V).  Nucleus and draw are found with bitwise searches
-// whose probes are block reductions in a fixed order, so a given input always gives the same path:
-//   * nucleus threshold: the largest float bit pattern K with  sum{e >= K} >= top_p * Z;
-//   * draw: the largest id Y with  sum{nucleus, id < Y} <= u * mass  (inverse CDF in id order).
+// One workgroup walks the tree; every step is data-parallel over the V logits of the current node.
+// What bounds it: the chain of a step -- a row (128 KB at V = 32000) through one compute unit, barriers, the search for
+// the child -- times the number of steps.  So a step makes two passes over the row and works on little after that:
+//   1. the row maximum M;
+//   2. with e = exp((x - M)/t): elements below (1 - top_p)/2V are less than half of what the nucleus may leave out, even
+//      all of them together (the sum Z is at least 1); they only count towards Z.  The others are listed, with peaked
+//      rows a few out of V;
+//   3. at most 64 of them are finished by one wave in registers: the nucleus threshold, the largest bit pattern K with
+//      sum{e >= K} >= top_p * Z, ties, nucleus mass, and the draw, the largest id Y with  sum{nucleus, id < Y} <= u * mass
+//      (inverse CDF in id order).  Longer lists are cut by histograms over the bits of e, lists that do not fit
+//      (flat rows, top_p = 1) by the same histograms over the whole row, re-read from L2.
+// All sums but that of the small elements are integers: e in units of 2^-44 (at most 2^17 elements of at most 1, so 61
+// bits; what an element loses to truncation is below 2^-44, 7e-9 of Z in all, an order below what fp32 partial sums
+// lose).  Integer sums do not depend on the order in which LDS atomics arrive, so a given input always gives the same path.
+// The form before this one searched threshold and draw bit by bit, 48 block-wide sums per step of about 1 us each (at
+// V > 32768 each a pass over 512 KB in L2).  Three walks of 7 to 14 steps at V = 32000: 564 us each on average, now 62
+// (8 us a step: 2.4 the row, 2.4 the two passes, 1.2 the candidates, 0.9 the child); of 10 to 14 steps at V = 128256
+// with draft probabilities: 6950 us, now 192.
 //
 // With draft probabilities (SI = true) the same kernel runs the comparison system of Sect. 4.1 instead:
 // a drafted child with token x is accepted with probability P_target(x) / P_draft(x), capped at one.  The
-// warped target distribution p of the current node is then a normalised vector in the scratch row; the
-// children are tried in index order, child j of the position accepted when r_j q[x] < p[x]; a rejection
-// replaces p by the renormalised positive part of p - q; after the last rejection the token is drawn
-// from what p has become and the walk ends.
+// warped target distribution p of the current node is then kept normalised -- the nucleus in order of id, in the
+// registers of one wave (at most 64 elements), as a list in LDS, or as a whole scratch row where it is larger; the
+// children are tried in index order, child j of the position accepted when r_j q[x] < p[x]; a rejection replaces p by
+// the renormalised positive part of p - q; after the last rejection the token is drawn from what p has become and the
+// walk ends.
 #include "kernels.h"
 
 namespace {
 
-__device__ __forceinline__ float uniform01(unsigned long long seed, long long position) {
-  unsigned long long z = seed + (unsigned long long)(position + 1) * 0x9E3779B97F4A7C15ull;
+typedef unsigned long long u64;
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+
+constexpr int kBins = 1024;      // histogram bins: bits 20.. of the pattern of e <= 1, then bits 10..19 and 0..9; ids by blocks of 128
+constexpr int kListCap = 1024;   // elements kept in LDS
+constexpr int kStageNodes = 4096;  // the parents of trees up to this size are read once, into LDS
+
+__device__ __forceinline__ u64 mix24(u64 seed, long long position) {  // the uniform of a position, in units of 2^-24
+  u64 z = seed + (u64)(position + 1) * 0x9E3779B97F4A7C15ull;
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
   z = z ^ (z >> 31);
-  return (float)(z >> 40) * 5.9604644775390625e-08f;  // 2^-24
+  return z >> 40;
 }
-
 // the uniform of the trial-th decision at one position (the ratio test needs several per position)
-__device__ __forceinline__ float trial_uniform(unsigned long long seed, long long position, int trial) {
-  return uniform01(seed + (unsigned long long)(trial + 1) * 0xD6E8FEB86659FD93ull, position);
+__device__ __forceinline__ u64 trial24(u64 seed, long long position, int trial) {
+  return mix24(seed + (u64)(trial + 1) * 0xD6E8FEB86659FD93ull, position);
+}
+// floor(mass * u), u in units of 2^-24
+__device__ __forceinline__ u64 scaled(u64 mass, u64 u24) {
+  return (__umul64hi(mass, u24) << 40) | ((mass * u24) >> 24);
+}
+// a float in [0, 1], given by its bits, in units of 2^-44 (rounded down; anything else, a NaN included, counts nothing)
+__device__ __forceinline__ u64 fix44(unsigned bits) {
+  if (bits > 0x3F800000u) return 0;
+  const int s = (int)(bits >> 23) - 106;
+  const unsigned m = (bits & 0x7FFFFFu) | 0x800000u;
+  return s >= 0 ? (u64)m << s : (u64)(s > -24 ? m >> -s : 0u);
+}
+__device__ __forceinline__ u64 wave_sum_u64(u64 v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+__device__ __forceinline__ unsigned lane_u32(unsigned v, int j) { return __builtin_amdgcn_readlane(v, j); }
+__device__ __forceinline__ u64 lane_u64(u64 v, int j) {
+  return ((u64)lane_u32((unsigned)(v >> 32), j) << 32) | lane_u32((unsigned)v, j);
 }
 
-// ITEMS > 0: lane holds elements j*NT + tid, j < ITEMS, in registers.  ITEMS == 0: elements live in ebuf.
-// SI (only with ITEMS == 0): acceptance by the ratio of target and draft probability, see the header.
-template <int NT, int ITEMS, bool SI>
+// max / min over the wave inside the vector unit (row shifts, then two row broadcasts; lane 63 ends up with the result):
+// six instructions, where exchanges through LDS cost a round trip each
+#define SX_WAVE_REDUCE(NAME, OP, NEUTRAL)                                                                    \
+  __device__ __forceinline__ unsigned NAME(unsigned v) {                                                    \
+    v = OP(v, (unsigned)__builtin_amdgcn_update_dpp((int)NEUTRAL, (int)v, 0x111, 0xf, 0xf, false));          \
+    v = OP(v, (unsigned)__builtin_amdgcn_update_dpp((int)NEUTRAL, (int)v, 0x112, 0xf, 0xf, false));          \
+    v = OP(v, (unsigned)__builtin_amdgcn_update_dpp((int)NEUTRAL, (int)v, 0x114, 0xf, 0xf, false));          \
+    v = OP(v, (unsigned)__builtin_amdgcn_update_dpp((int)NEUTRAL, (int)v, 0x118, 0xf, 0xf, false));          \
+    v = OP(v, (unsigned)__builtin_amdgcn_update_dpp((int)NEUTRAL, (int)v, 0x142, 0xa, 0xf, false));          \
+    v = OP(v, (unsigned)__builtin_amdgcn_update_dpp((int)NEUTRAL, (int)v, 0x143, 0xc, 0xf, false));          \
+    return lane_u32(v, 63);                                                                                  \
+  }
+SX_WAVE_REDUCE(wave_max_u32, max, 0u)
+SX_WAVE_REDUCE(wave_min_u32, min, 0xFFFFFFFFu)
+#undef SX_WAVE_REDUCE
+
+// INLDS: the row fits the LDS (V <= 32768) and is copied there by loads that write LDS; otherwise every pass reads it
+// from memory, after the first one from L2.  (Held in registers the row cost more than it saved: 32 unrolled copies of
+// every pass's body outgrew the instruction cache, and the rest of the kernel spilled.)  SI: acceptance by the ratio of
+// target and draft probability.
+template <int N>
+struct Const {
+  static constexpr int value = N;
+};
+
+template <int NT, bool INLDS, bool SI>
 __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict__ logits,
                                                          const float* __restrict__ draft_probs,
                                                          const int* __restrict__ tokens,
                                                          const int* __restrict__ parent, int T, int V,
-                                                         float temperature, float top_p, unsigned long long seed,
+                                                         float temperature, float top_p, u64 seed,
                                                          int pos0, int* __restrict__ path_out,
                                                          int* __restrict__ tokens_out, int* __restrict__ n_out,
                                                          float* __restrict__ ebuf, int* __restrict__ status) {
-  static_assert(!SI || ITEMS == 0, "the ratio test keeps its distribution in the scratch row");
   constexpr int NW = NT / 64;
-  constexpr int R = ITEMS > 0 ? ITEMS : 1;
+  constexpr int BPT = kBins / NT;  // bins per lane in a scan
+  __shared__ u64 hist[kBins];
+  __shared__ u64 list[kListCap];   // id << 32 | bits of e
+  __shared__ float plist[SI ? kListCap : 1];
+  __shared__ short s_par[kStageNodes];
+  extern __shared__ __attribute__((aligned(1024))) float row[];  // INLDS: V rounded up to 4 NT
   __shared__ float redf[16];
   __shared__ int redi[16];
-  const int tid = threadIdx.x;
+  __shared__ u64 s_wsum[NW];
+  __shared__ u64 s_low, s_above;
+  __shared__ int s_n, s_nl, s_bin, s_token, s_child;
+  __shared__ float s_px;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float NEG_INF = -__builtin_huge_valf();
 
   if (tid == 0) status[0] = (parent[0] != -1) ? SX_ERR_TREE : SX_OK;  // node 0 must be the root
+  const bool staged = T <= kStageNodes;
+  if (staged)
+    for (int j = tid; j < T; j += NT) s_par[j] = (short)max(min(parent[j], T), -1);  // (a parent past the end is nobody's)
+  auto par_of = [&](int j) { return staged ? (int)s_par[j] : parent[j]; };
+  const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
 
-  float ev[R];
-  // sum of e over elements selected by pred(bits(e), id)
-  auto sum_if = [&](auto pred) -> float {
-    float a = 0.f;
-    if constexpr (ITEMS > 0) {
+  // sum of hist over the bins before this lane's first (ascending order of r; bin = r or kBins - 1 - r), and over all
+  auto scan = [&](bool desc, u64& total) -> u64 {
+    u64 mine = 0;
 #pragma unroll
-      for (int j = 0; j < ITEMS; ++j) {
-        const int id = j * NT + tid;
-        a += pred(__float_as_uint(ev[j]), id) ? ev[j] : 0.f;  // padding holds e = 0
-      }
-    } else {
-      for (int id = tid; id < V; id += NT) {
-        const float e = ebuf[id];
-        a += pred(__float_as_uint(e), id) ? e : 0.f;
-      }
+    for (int i = 0; i < BPT; ++i) {
+      const int r = tid * BPT + i;
+      mine += hist[desc ? kBins - 1 - r : r];
     }
-    return block_sum<NW>(a, redf);
+    u64 incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const u64 t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) s_wsum[wave] = incl;
+    __syncthreads();
+    u64 before = 0, all = 0;
+#pragma unroll 4
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) before += s_wsum[w];
+      all += s_wsum[w];
+    }
+    total = all;
+    return before + incl - mine;
   };
-  auto count_if = [&](auto pred) -> int {
-    int c = 0;
-    if constexpr (ITEMS > 0) {
+  // the first r whose running sum (from `start`) reaches `need`: its bin to s_bin, the sum before it to s_above
+  auto find = [&](bool desc, u64 start, u64 need) {
 #pragma unroll
-      for (int j = 0; j < ITEMS; ++j) {
-        const int id = j * NT + tid;
-        c += (id < V && pred(__float_as_uint(ev[j]), id)) ? 1 : 0;
+    for (int i = 0; i < BPT; ++i) {
+      const int r = tid * BPT + i, b = desc ? kBins - 1 - r : r;
+      const u64 h = hist[b];
+      if (start < need && start + h >= need) {
+        s_bin = b;
+        s_above = start;
       }
-    } else {
-      for (int id = tid; id < V; id += NT) c += pred(__float_as_uint(ebuf[id]), id) ? 1 : 0;
+      start += h;
     }
-    return block_sum_i<NW>(c, redi);
+    __syncthreads();
+  };
+  auto clear_hist = [&]() {
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) hist[i * NT + tid] = 0;
+    if (tid == 0) {
+      s_bin = 0;
+      s_above = 0;
+    }
+    __syncthreads();
+  };
+  // id of the first element, in id order, at which the running sum of weight(bits, id) over `each` exceeds `target`
+  auto first_beyond = [&](auto each, auto weight, u64 target) -> int {
+    __syncthreads();
+    clear_hist();
+    each([&](unsigned b, int id) {
+      const u64 f = weight(b, id);
+      if (f) atomicAdd(&hist[(unsigned)id >> 7], f);
+    });
+    __syncthreads();
+    u64 total;
+    u64 start = scan(false, total);
+    find(false, start, target + 1);
+    const int block = s_bin;
+    const u64 base = s_above;
+    __syncthreads();
+    clear_hist();
+    each([&](unsigned b, int id) {
+      if ((id >> 7) == block) {
+        const u64 f = weight(b, id);
+        if (f) atomicAdd(&hist[id & 127], f);
+      }
+    });
+    __syncthreads();
+    start = base + scan(false, total);
+    find(false, start, target + 1);
+    return min(block * 128 + s_bin, V - 1);
   };
 
+  __syncthreads();
   int cur = 0, depth = 0, n = 0;
   for (int step = 0; step < T; ++step) {
     const float* x = logits + (size_t)cur * (size_t)V;
+    // f(four consecutive elements, id of the first) over the row, in the same number of rounds for every lane; past the
+    // end x reads as -inf.  A lane always takes the same quads, so in LDS it reads what its own wave has copied.
+    auto edge = [&](float v, int id) { return id < V ? v : NEG_INF; };
+    auto sweep_by = [&](auto quads, auto f) {
+      if constexpr (INLDS) {
+        int id = tid * 4;
+        for (; id - tid * 4 + 4 * NT <= V; id += 4 * NT) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(row + id);
+          f(v[0], v[1], v[2], v[3], id);
+        }
+        if (id - tid * 4 < V) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(row + id);
+          f(edge(v[0], id), edge(v[1], id + 1), edge(v[2], id + 2), edge(v[3], id + 3), id);
+        }
+      } else {
+        constexpr int U = decltype(quads)::value;  // quads in flight per lane
+        if (vec) {  // quads lie inside the row or past its end
+          for (int b0 = 0; b0 < V; b0 += U * 4 * NT) {
+            f32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              v[u] = *reinterpret_cast<const f32x4*>(x + min(b0 + (u * NT + tid) * 4, V - 4));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const int id = b0 + (u * NT + tid) * 4;
+              const bool in = id < V;
+              f(in ? v[u][0] : NEG_INF, in ? v[u][1] : NEG_INF, in ? v[u][2] : NEG_INF, in ? v[u][3] : NEG_INF, id);
+            }
+          }
+          return;
+        }
+        for (int b0 = 0; b0 < V; b0 += U * 4 * NT) {
+          float v[U][4];
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[u][c] = x[(unsigned)min(b0 + (u * NT + tid) * 4 + c, V - 1)];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int id = b0 + (u * NT + tid) * 4;
+            f(edge(v[u][0], id), edge(v[u][1], id + 1), edge(v[u][2], id + 2), edge(v[u][3], id + 3), id);
+          }
+        }
+      }
+    };
+    auto sweep = [&](auto f) { sweep_by(Const<4>{}, f); };
+    if constexpr (INLDS) {  // copies past the end of the row write zeros
+      const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, V * 4, 0x00020000);
+      if (vec) {
+        for (int b0 = 0; b0 < V; b0 += 4 * NT)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void_ptr)(row + b0 + wave * 256), 16, (b0 + tid * 4) * 4, 0, 0, 0);
+      } else {
+        for (int b0 = 0; b0 < V; b0 += 4 * NT)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(res, (lds_void_ptr)(row + b0 + wave * 256 + c * 64), 4,
+                                                     (b0 + wave * 256 + c * 64 + lane) * 4, 0, 0, 0);
+      }
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0x0070);  // all of this wave's copies are in
+      asm volatile("" ::: "memory");
+    }
+    const long long pos = (long long)pos0 + depth + 1;
     // ---- row maximum (and the greedy answer) ------------------------------------------------------
     float tm = NEG_INF;
-    if constexpr (ITEMS > 0) {
+    sweep_by(Const<8>{}, [&](float v0, float v1, float v2, float v3, int) { tm = fmaxf(tm, fmaxf(fmaxf(v0, v1), fmaxf(v2, v3))); });
 #pragma unroll
-      for (int j = 0; j < ITEMS; ++j) {
-        const int id = j * NT + tid;
-        ev[j] = id < V ? x[id] : NEG_INF;
-        tm = fmaxf(tm, ev[j]);
-      }
-    } else {
-      for (int id = tid; id < V; id += NT) tm = fmaxf(tm, x[id]);
+    for (int i = 0; i < BPT; ++i) hist[i * NT + tid] = 0;
+    if (tid == 0) {
+      s_low = 0;
+      s_n = 0;
+      s_bin = 0;
+      s_above = 0;
+      s_token = 0;
+      s_child = 0x7FFFFFFF;
     }
     const float M = block_max<NW>(tm, redf);
     int token;
+    int nl = -1;          // SI: entries of the nucleus list; -1: the distribution is in ebuf
     if (temperature == 0.f) {
       int best = 0x7FFFFFFF;
-      if constexpr (ITEMS > 0) {
+      sweep([&](float v0, float v1, float v2, float v3, int id) {
+        const float v[4] = {v0, v1, v2, v3};
 #pragma unroll
-        for (int j = ITEMS - 1; j >= 0; --j) {
-          const int id = j * NT + tid;
-          if (id < V && ev[j] == M) best = id;
-        }
-      } else {
-        for (int id = tid; id < V; id += NT)
-          if (x[id] == M) best = min(best, id);
-      }
+        for (int c = 0; c < 4; ++c)
+          if (v[c] == M && id + c < V) best = min(best, id + c);
+      });
       token = block_min_i<NW>(best, redi);
       if constexpr (SI) {  // p = all mass on the argmax
-        __syncthreads();
-        for (int id = tid; id < V; id += NT) ebuf[id] = id == token ? 1.0f : 0.f;
+        if (tid == 0) {
+          list[0] = (u64)(unsigned)min(token, V - 1) << 32;
+          plist[0] = 1.0f;
+        }
+        nl = 1;
         __syncthreads();
       }
     } else {
-      // ---- e = exp((x - max)/t), Z ------------------------------------------------------------
+      // ---- the elements that can be in the nucleus, and the sum of the others ---------------------------------
       const float inv_t = 1.0f / temperature;
-      float zs = 0.f;
-      if constexpr (ITEMS > 0) {
+      auto e_bits = [&](float v) { return __float_as_uint(expf((v - M) * inv_t)); };
+      // the x below which e is certainly under `e` (the slack covers the roundings of this line and of e_bits)
+      auto x_below = [&](float e) {
+        const float l = logf(e);
+        return M + temperature * (l - 1e-4f * (1.0f - l)) - 1e-6f * fabsf(M);
+      };
+      // appends (id, payload) of the lanes that hit; entries past the end of the list are counted only
+      auto append = [&](bool hit, int id, unsigned payload) {
+        const u64 who = __builtin_amdgcn_ballot_w64(hit);
+        if (who == 0) return;
+        const int leader = __builtin_ctzll(who);
+        int slot = 0;
+        if (lane == leader) slot = atomicAdd(&s_n, __builtin_popcountll(who));
+        slot = __builtin_amdgcn_readlane(slot, leader) + __builtin_popcountll(who & ((1ull << lane) - 1ull));
+        if (hit && slot < kListCap) list[slot] = ((u64)(unsigned)id << 32) | payload;
+      };
+      const float x_cut = x_below(0.4f * (1.0f - top_p) / (float)V);
+      const float c2 = inv_t * 1.4426950408889634f, mc2 = -M * c2;
+      // e below 2^-46 counts nothing, as in fix44: with peaked rows that skips most exponentials
+      const float x_zero = fminf(x_cut, x_below(1.4210854715202004e-14f));
+      float lowf = 0.f;
+      sweep([&](float v0, float v1, float v2, float v3, int id) {
+        const float m4 = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
+        if (__builtin_amdgcn_ballot_w64(m4 >= x_zero) == 0) return;
+        const float v[4] = {v0, v1, v2, v3};
+        if (__builtin_amdgcn_ballot_w64(m4 >= x_cut) == 0) {
 #pragma unroll
-        for (int j = 0; j < ITEMS; ++j) {
-          const int id = j * NT + tid;
-          ev[j] = id < V ? expf((ev[j] - M) * inv_t) : 0.f;
-          zs += ev[j];
+          for (int c = 0; c < 4; ++c) lowf += __builtin_amdgcn_exp2f(fmaf(v[c], c2, mc2));  // exp2(-inf) = 0 past the end
+          return;
         }
-      } else {
-        for (int id = tid; id < V; id += NT) {
-          const float e = expf((x[id] - M) * inv_t);
-          ebuf[id] = e;
-          zs += e;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const bool hit = v[c] >= x_cut;
+          if (!hit) lowf += __builtin_amdgcn_exp2f(fmaf(v[c], c2, mc2));
+          append(hit && id + c < V, id + c, __float_as_uint(v[c]));
         }
-        __syncthreads();
-      }
-      const float Z = block_sum<NW>(zs, redf);
-      const float thr = top_p * Z;
-      // ---- nucleus: largest bit pattern K with sum{e >= K} >= thr --------------------------------
-      unsigned K = 0;
-      for (int bit = 30; bit >= 0; --bit) {
-        const unsigned trial = K | (1u << bit);
-        const float S = sum_if([&](unsigned b, int) { return b >= trial; });
-        if (S >= thr) K = trial;
-      }
-      const float S_gt = sum_if([&](unsigned b, int) { return b > K; });
-      const int n_tie = count_if([&](unsigned b, int) { return b == K; });
-      const float eK = __uint_as_float(K);
-      int m = 1;  // ties (equal probabilities) enter in id order until the mass reaches thr
-      while (m < n_tie && S_gt + (float)m * eK < thr) ++m;
-      unsigned Ytie = 0xFFFFFFFFu;
-      if (m < n_tie) {  // largest Y with #(tie, id < Y) <= m
-        Ytie = 0;
-        for (int bit = 17; bit >= 0; --bit) {
-          const unsigned trial = Ytie | (1u << bit);
-          const int c = count_if([&](unsigned b, int id) { return b == K && (unsigned)id < trial; });
-          if (c <= m) Ytie = trial;
-        }
-      }
-      auto member = [&](unsigned b, int id) { return b > K || (b == K && (unsigned)id < Ytie); };
-      const float mass = sum_if(member);
-      if constexpr (SI) {  // p = the nucleus, normalised; the draw below is not taken in this mode
-        const float inv_mass = 1.0f / mass;
-        __syncthreads();
-        for (int id = tid; id < V; id += NT) {
-          const float e = ebuf[id];
-          ebuf[id] = member(__float_as_uint(e), id) ? e * inv_mass : 0.f;
-        }
-        __syncthreads();
-      }
+      });
+      const u64 low = wave_sum_u64(fix44(__float_as_uint(lowf)));
+      if (lane == 0 && low) atomicAdd(&s_low, low);
+      __syncthreads();
+      const u64 u24 = mix24(seed, pos);
+      int nc = s_n;
+      const bool overflow = nc > kListCap;
+      u64 thr = 0;
+      unsigned K = 0, Ytie = 0xFFFFFFFFu;  // the nucleus: e > K, or e == K and id < Ytie
+      u64 mass = 0;
       token = 0;
-      if constexpr (!SI) {
-        const float u = uniform01(seed, (long long)pos0 + depth + 1);
-        const float target = u * mass;
-        // ---- inverse CDF in id order: largest Y <= V with sum{member, id < Y} <= target ---------
-        unsigned Y = 0;
-        for (int bit = 17; bit >= 0; --bit) {
-          const unsigned trial = Y | (1u << bit);
-          if (trial > (unsigned)V) continue;  // uniform across the block
-          const float G = sum_if([&](unsigned b, int id) { return (unsigned)id < trial && member(b, id); });
-          if (G <= target) Y = trial;
+      auto threshold = [&](u64 Z) -> u64 {
+        const u64 t = (u64)ceil((double)top_p * (double)Z);
+        return t > Z ? Z : (t < 1 ? 1 : t);
+      };
+      // at most 64 candidates in `list` (payload: bits of e), one per lane of one wave; `thr` known (have_thr) or made
+      // from their sum and the small elements'
+      auto few = [&](int cnt, bool have_thr) {
+        const u64 entry = lane < cnt ? list[lane] : 0xFFFFFFFF00000000ull;
+        const unsigned b = (unsigned)entry, id = (unsigned)(entry >> 32);
+        const u64 f = fix44(b);
+        u64 ge = 0;       // sum over elements at least as large
+        u64 all = 0;
+        int earlier = 0;  // equal ones with a lower id
+        for (int j = 0; j < cnt; ++j) {
+          const unsigned bj = lane_u32(b, j), idj = lane_u32(id, j);
+          const u64 fj = lane_u64(f, j);
+          all += fj;
+          ge += bj >= b ? fj : 0;
+          earlier += (bj == b && idj < id) ? 1 : 0;
         }
-        token = (int)Y;
-        if (Y >= (unsigned)V) {  // only by rounding: fall back to the last nucleus token
-          int last = -1;
-          if constexpr (ITEMS > 0) {
-#pragma unroll
-            for (int j = 0; j < ITEMS; ++j) {
-              const int id = j * NT + tid;
-              if (id < V && member(__float_as_uint(ev[j]), id)) last = id;
-            }
-          } else {
-            for (int id = tid; id < V; id += NT)
-              if (member(__float_as_uint(ebuf[id]), id)) last = id;
+        const u64 need = have_thr ? thr : threshold(s_low + all);
+        unsigned k = lane < cnt && ge >= need ? b : 0u;
+        k = wave_max_u32(k);
+        const u64 ties = __builtin_amdgcn_ballot_w64(lane < cnt && b == k);
+        int m = 1;  // ties (equal probabilities) enter in id order until the mass reaches the threshold
+        u64 sum = 0;
+        if (ties) {
+          const int tl0 = __builtin_ctzll(ties), n_tie = __builtin_popcountll(ties);
+          const u64 fk = lane_u64(f, tl0), gt = lane_u64(ge, tl0) - (u64)n_tie * fk;
+          while (m < n_tie && gt + (u64)m * fk < need) ++m;
+          sum = gt + (u64)m * fk;
+        }
+        const bool member = lane < cnt && (b > k || (b == k && earlier < m));
+        const u64 fm = member ? f : 0;
+        u64 cum = 0;    // sum over members up to this one, in id order
+        int place = 0;  // members with a lower id
+        for (int j = 0; j < cnt; ++j) {
+          const u64 fj = lane_u64(fm, j);
+          const unsigned idj = lane_u32(id, j);
+          cum += idj <= id ? fj : 0;
+          place += (fj != 0 && idj < id) ? 1 : 0;
+        }
+        if constexpr (SI) {  // the nucleus in order of id, normalised (a member of weight 0 is one that p rounds to 0)
+          const float inv_mass = (float)(17592186044416.0 / (double)sum);  // 2^44 / mass
+          if (fm != 0) {
+            list[place] = entry;
+            plist[place] = __uint_as_float(b) * inv_mass;
           }
-          token = -block_min_i<NW>(-last, redi);
+          const u64 kept = __builtin_amdgcn_ballot_w64(fm != 0);
+          if (lane == 0) s_nl = __builtin_popcountll(kept);
+        } else {
+          const u64 target = scaled(sum, u24);
+          unsigned t = member && cum > target ? id : 0x7FFFFFFFu;
+          t = wave_min_u32(t);
+          if (lane == 0) s_token = t < (unsigned)V ? (int)t : 0;
         }
+      };
+      bool done = false;
+      if (nc <= 64) {
+        if (wave == 0) {
+          if (lane < nc) list[lane] = (list[lane] & 0xFFFFFFFF00000000ull) | e_bits(__uint_as_float((unsigned)list[lane]));
+          few(nc, false);
+        }
+        done = true;
+      } else {
+        // ---- more: bin of the threshold by a histogram over the top bits of e (8 bins per octave) ---------------
+        auto each_x = [&](auto f) {
+          if (!overflow) {
+            for (int i = tid; i < nc; i += NT) f(__uint_as_float((unsigned)list[i]), (int)(list[i] >> 32));
+          } else {
+            sweep([&](float v0, float v1, float v2, float v3, int id) {
+              if (id < V) f(v0, id);
+              if (id + 1 < V) f(v1, id + 1);
+              if (id + 2 < V) f(v2, id + 2);
+              if (id + 3 < V) f(v3, id + 3);
+            });
+          }
+        };
+        each_x([&](float v, int) {
+          if (v >= x_cut) {
+            const unsigned b = e_bits(v);
+            const u64 f = fix44(b);
+            if (f) atomicAdd(&hist[min(b >> 20, (unsigned)(kBins - 1))], f);
+          }
+        });
+        __syncthreads();
+        u64 total;
+        const u64 start = scan(true, total);
+        thr = threshold(total + s_low);
+        find(true, start, thr);
+        const unsigned floor_bits = (unsigned)s_bin << 20;
+        u64 above = s_above;
+        // ---- the elements of that bin and above ---------------------------------------------------------------
+        if (!overflow) {  // in place: every lane takes its entries before anyone writes
+          u64 mine[kListCap / NT];
+#pragma unroll
+          for (int i = 0; i < kListCap / NT; ++i) mine[i] = i * NT + tid < nc ? list[i * NT + tid] : 0;
+          __syncthreads();
+          if (tid == 0) s_n = 0;
+          __syncthreads();
+#pragma unroll
+          for (int i = 0; i < kListCap / NT; ++i) {
+            const unsigned b = e_bits(__uint_as_float((unsigned)mine[i]));
+            append(i * NT + tid < nc && b >= floor_bits && b <= 0x3F800000u, (int)(mine[i] >> 32), b);
+          }
+        } else {
+          __syncthreads();
+          if (tid == 0) s_n = 0;
+          __syncthreads();
+          const float x_floor = floor_bits ? x_below(__uint_as_float(floor_bits)) : NEG_INF;
+          sweep([&](float v0, float v1, float v2, float v3, int id) {
+            const float v[4] = {v0, v1, v2, v3};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const bool maybe = id + c < V && v[c] >= x_floor;
+              if (__builtin_amdgcn_ballot_w64(maybe) == 0) continue;
+              const unsigned b = e_bits(v[c]);
+              append(maybe && b >= floor_bits && b <= 0x3F800000u, id + c, b);
+            }
+          });
+        }
+        __syncthreads();
+        nc = s_n;
+        if (nc <= 64) {
+          if (wave == 0) few(nc, true);
+          done = true;
+        } else {
+          // ---- still many: the lower bits of the threshold by two more histograms, the draw by blocks of ids -----
+          auto each = [&](auto f) {
+            if (nc <= kListCap) {
+              for (int i = tid; i < nc; i += NT) f((unsigned)list[i], (int)(list[i] >> 32));
+            } else {
+              sweep([&](float v0, float v1, float v2, float v3, int id) {
+                if (id < V) f(e_bits(v0), id);
+                if (id + 1 < V) f(e_bits(v1), id + 1);
+                if (id + 2 < V) f(e_bits(v2), id + 2);
+                if (id + 3 < V) f(e_bits(v3), id + 3);
+              });
+            }
+          };
+          unsigned prefix = floor_bits >> 20;
+          for (int shift = 10; shift >= 0; shift -= 10) {
+            __syncthreads();
+            clear_hist();
+            each([&](unsigned b, int) {
+              if (b <= 0x3F800000u && (b >> (shift + 10)) == prefix) {
+                const u64 f = fix44(b);
+                if (f) atomicAdd(&hist[(b >> shift) & (kBins - 1)], f);
+              }
+            });
+            __syncthreads();
+            u64 t2;
+            const u64 st = above + scan(true, t2);
+            find(true, st, thr);
+            prefix = (prefix << 10) | (unsigned)s_bin;
+            above = s_above;
+          }
+          K = prefix;
+          const u64 fk = fix44(K);
+          const u64 tie_sum = hist[K & (kBins - 1)];  // the last histogram's bin holds the elements equal to K alone
+          mass = above;
+          if (fk > 0) {
+            const u64 n_tie = tie_sum / fk;
+            u64 m = thr > above ? (thr - above + fk - 1) / fk : 1;
+            m = m < 1 ? 1 : (m > n_tie ? n_tie : m);
+            mass = above + m * fk;
+            if (m < n_tie)
+              Ytie = (unsigned)first_beyond(each, [&](unsigned b, int) { return (u64)(b == K ? 1 : 0); }, m);
+          }
+          if constexpr (!SI)
+            token = first_beyond(each,
+                                 [&](unsigned b, int id) {
+                                   return b <= 0x3F800000u && (b > K || (b == K && (unsigned)id < Ytie)) ? fix44(b) : 0;
+                                 },
+                                 scaled(mass, u24));
+        }
+      }
+      if (done) {
+        __syncthreads();
+        if constexpr (SI) nl = s_nl;
+        else token = s_token;
+      }
+      if (SI && !done) {  // p = the nucleus, normalised
+        auto member = [&](unsigned b, unsigned id) { return b > K || (b == K && id < Ytie); };
+        const float inv_mass = (float)(17592186044416.0 / (double)mass);  // 2^44 / mass
+        __syncthreads();
+        if (nc <= kListCap) {
+          // in order of id: sums over the list then have one order, whatever order the atomics filled it in
+          const int np2 = next_pow2(nc < 2 ? 2 : nc);
+          int mine = 0;
+          for (int i = tid; i < np2; i += NT) {
+            const bool in = i < nc && member((unsigned)list[i], (unsigned)(list[i] >> 32));
+            if (!in) list[i] = ~0ull;
+            mine += in ? 1 : 0;
+          }
+          nl = block_sum_i<NW>(mine, redi);
+          block_bitonic_sort_u64<NT>(list, np2);
+          for (int i = tid; i < nl; i += NT) plist[i] = __uint_as_float((unsigned)list[i]) * inv_mass;
+        } else {
+          for (int id = tid; id < V; id += NT) {
+            const unsigned b = e_bits(x[id]);
+            ebuf[id] = member(b, (unsigned)id) ? __uint_as_float(b) * inv_mass : 0.f;
+          }
+        }
+        __syncthreads();
       }
     }
     if constexpr (SI) {
       // ---- ratio test over the children of cur, in index order ------------------------------------------
       const float* q = draft_probs + (size_t)cur * (size_t)V;
-      const long long pos = (long long)pos0 + depth + 1;
+      if (nl >= 0 && nl <= 64 && staged) {
+        // one wave holds the distribution: p and q of an element per lane, in order of id.  (A token that p gives no mass is
+        // rejected whatever q is.)
+        if (wave == 0) {
+          const unsigned id = lane < nl ? (unsigned)(list[lane] >> 32) : 0xFFFFFFFFu;
+          float pv = lane < nl ? plist[lane] : 0.f;
+          const float qv = lane < nl ? q[id] : 0.f;
+          int trial = 0, found = -1;
+          for (int j0 = cur + 1; j0 < T && found < 0; j0 += 64) {
+            const int j = j0 + lane;
+            const bool kid = j < T && s_par[min(j, T - 1)] == cur;
+            u64 kids = __builtin_amdgcn_ballot_w64(kid);
+            const int tj = kid ? tokens[j] : 0;
+            while (kids) {
+              const int l = __builtin_ctzll(kids);
+              kids &= kids - 1;
+              const int xt = __builtin_amdgcn_readlane(tj, l);
+              const u64 here = __builtin_amdgcn_ballot_w64(lane < nl && (int)id == xt);
+              if (xt < 0 || xt >= V) {  // not a token: nothing to accept, nothing the draft could have covered
+                if (lane == 0) status[0] = SX_ERR_TREE;
+                ++trial;
+                continue;
+              }
+              const float r = (float)trial24(seed, pos, trial) * 5.9604644775390625e-08f;  // 2^-24
+              if (__builtin_amdgcn_ballot_w64((here >> lane & 1) && r * qv < pv)) {
+                found = j0 + l;
+                break;
+              }
+              ++trial;
+              const float d = fmaxf(pv - qv, 0.f);
+              const float Zr = wave_sum(d);
+              if (Zr > 0.f) pv = d * (1.0f / Zr);
+            }
+          }
+          int last = 0;
+          if (found < 0) {  // every child rejected: draw from what p has become
+            const u64 f = fix44(min(__float_as_uint(pv), 0x3F800000u));
+            u64 incl = f;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+              const u64 t = __shfl_up(incl, o, 64);
+              if (lane >= o) incl += t;
+            }
+            const u64 target = scaled(lane_u64(incl, 63), trial24(seed, pos, trial));
+            const u64 beyond = __builtin_amdgcn_ballot_w64(lane < nl && incl > target);
+            if (beyond) last = (int)lane_u32(id, __builtin_ctzll(beyond));
+          }
+          if (lane == 0) {
+            s_child = found;
+            s_token = last;
+          }
+        }
+        __syncthreads();
+        const int next = s_child;
+        if (tid == 0) {
+          path_out[n] = cur;
+          tokens_out[n] = next >= 0 ? tokens[next] : s_token;
+        }
+        __syncthreads();  // everybody has read it before the next step clears it
+        ++n;
+        if (next < 0) break;
+        cur = next;
+        ++depth;
+        continue;
+      }
       int after = cur, trial = 0, accepted = -1;
       while (true) {
         int c = 0x7FFFFFFF;
         for (int j = after + 1 + tid; j < T; j += NT)
-          if (parent[j] == cur) c = min(c, j);
+          if (par_of(j) == cur) c = min(c, j);
         c = block_min_i<NW>(c, redi);
         if (c == 0x7FFFFFFF) break;
-        const int x = tokens[c];
+        const int xt = tokens[c];
         after = c;
-        if (x < 0 || x >= V) {  // not a token: nothing to accept, nothing the draft could have covered
+        if (xt < 0 || xt >= V) {  // not a token: nothing to accept, nothing the draft could have covered
           if (tid == 0) status[0] = SX_ERR_TREE;
           ++trial;
           continue;
         }
-        if (trial_uniform(seed, pos, trial) * q[x] < ebuf[x]) {
+        float px;
+        if (nl >= 0) {
+          if (tid == 0) s_px = 0.f;
+          __syncthreads();
+          for (int i = tid; i < nl; i += NT)
+            if ((int)(list[i] >> 32) == xt) s_px = plist[i];
+          __syncthreads();
+          px = s_px;
+        } else {
+          px = ebuf[xt];
+        }
+        const float r = (float)trial24(seed, pos, trial) * 5.9604644775390625e-08f;  // 2^-24
+        if (r * q[xt] < px) {
           accepted = c;
           break;
         }
         ++trial;
         float z = 0.f;
-        for (int id = tid; id < V; id += NT) z += fmaxf(ebuf[id] - q[id], 0.f);
-        const float Zr = block_sum<NW>(z, redf);  // its barriers also order the reads of ebuf[x] above before the writes
+        if (nl >= 0) {
+          for (int i = tid; i < nl; i += NT) z += fmaxf(plist[i] - q[list[i] >> 32], 0.f);
+        } else {
+          for (int id = tid; id < V; id += NT) z += fmaxf(ebuf[id] - q[id], 0.f);
+        }
+        const float Zr = block_sum<NW>(z, redf);  // its barriers also order the reads of p[x] above before the writes
         if (Zr > 0.f) {
           const float inv = 1.0f / Zr;
-          for (int id = tid; id < V; id += NT) ebuf[id] = fmaxf(ebuf[id] - q[id], 0.f) * inv;
+          if (nl >= 0) {
+            for (int i = tid; i < nl; i += NT) plist[i] = fmaxf(plist[i] - q[list[i] >> 32], 0.f) * inv;
+          } else {
+            for (int id = tid; id < V; id += NT) ebuf[id] = fmaxf(ebuf[id] - q[id], 0.f) * inv;
+          }
         }
         __syncthreads();
       }
@@ -244,22 +687,24 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         continue;
       }
       // ---- every child rejected: draw from what p has become, then stop ----------------------------------
-      const float S = sum_if([&](unsigned, int) { return true; });
-      const float target = trial_uniform(seed, pos, trial) * S;
-      unsigned Y = 0;
-      for (int bit = 17; bit >= 0; --bit) {
-        const unsigned t2 = Y | (1u << bit);
-        if (t2 > (unsigned)V) continue;
-        const float G = sum_if([&](unsigned, int id) { return (unsigned)id < t2; });
-        if (G <= target) Y = t2;
-      }
-      token = (int)Y;
-      if (Y >= (unsigned)V) {  // only by rounding: the last token with mass
-        int last = -1;
-        for (int id = tid; id < V; id += NT)
-          if (ebuf[id] > 0.f) last = id;
-        token = -block_min_i<NW>(-last, redi);
-      }
+      // (p is at most 1 up to the rounding of its normalisation; a value above 1 counts as 1)
+      auto weight = [&](unsigned b, int) { return fix44(min(b, 0x3F800000u)); };
+      auto each = [&](auto f) {
+        if (nl >= 0) {
+          for (int i = tid; i < nl; i += NT) f(__float_as_uint(plist[i]), (int)(list[i] >> 32));
+        } else {
+          for (int id = tid; id < V; id += NT) f(__float_as_uint(ebuf[id]), id);
+        }
+      };
+      u64 part = 0;
+      each([&](unsigned b, int id) { part += weight(b, id); });
+      part = wave_sum_u64(part);
+      __syncthreads();
+      if (tid == 0) s_low = 0;
+      __syncthreads();
+      if (lane == 0 && part) atomicAdd(&s_low, part);
+      __syncthreads();
+      token = first_beyond(each, weight, scaled(s_low, trial24(seed, pos, trial)));
       if (tid == 0) {
         path_out[n] = cur;
         tokens_out[n] = token;
@@ -275,13 +720,53 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
     // ---- cache lookup: lowest-index child of cur carrying the sampled token -------------------------
     int child = 0x7FFFFFFF;
     for (int j = cur + 1 + tid; j < T; j += NT)
-      if (parent[j] == cur && tokens[j] == token) child = min(child, j);
-    child = block_min_i<NW>(child, redi);
+      if (par_of(j) == cur && tokens[j] == token) child = min(child, j);
+    if (child != 0x7FFFFFFF) atomicMin(&s_child, child);
+    __syncthreads();
+    child = s_child;
+    __syncthreads();  // everybody has read it before the next step clears it
     if (child == 0x7FFFFFFF) break;
     cur = child;
     ++depth;
   }
   if (tid == 0) n_out[0] = n;
+}
+
+}  // namespace
+
+namespace {
+
+struct WalkArgs {
+  const float *logits, *draft_probs;
+  const int *tokens, *parent;
+  int T, V;
+  float temperature, top_p;
+  u64 seed;
+  int pos0;
+  int *path_out, *tokens_out, *n_out;
+  float* ebuf;
+  int* status;
+};
+
+template <int NT, bool INLDS, bool SI>
+int launch_walk(const WalkArgs& a, hipStream_t st) {
+  const size_t row_bytes = INLDS ? sx_align_up((size_t)a.V * 4, (size_t)NT * 16) : 0;
+  if (INLDS) {  // above the default limit of dynamic LDS: allowed once per device
+    static bool configured[64] = {};
+    int dev = 0;
+    SX_HIP_TRY(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) return SX_ERR_HIP;
+    if (!configured[dev]) {
+      SX_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&accept_walk_kernel<NT, INLDS, SI>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)sx_align_up((NT == 256 ? 4096 : 32768) * 4, (size_t)NT * 16)));
+      configured[dev] = true;
+    }
+  }
+  accept_walk_kernel<NT, INLDS, SI><<<1, NT, row_bytes, st>>>(a.logits, a.draft_probs, a.tokens, a.parent, a.T, a.V,
+                                                              a.temperature, a.top_p, a.seed, a.pos0, a.path_out,
+                                                              a.tokens_out, a.n_out, a.ebuf, a.status);
+  SX_LAUNCH_CHECK();
+  return SX_OK;
 }
 
 }  // namespace
@@ -303,18 +788,17 @@ extern "C" int sx_accept_walk(const float* logits, const float* draft_probs, con
   hipStream_t st = (hipStream_t)stream;
   int* status = reinterpret_cast<int*>(workspace);
   float* ebuf = reinterpret_cast<float*>(static_cast<char*>(workspace) + SX_WS_HEADER);
-#define SX_WALK(NT, ITEMS, SI)                                                                                        \
-  accept_walk_kernel<NT, ITEMS, SI><<<1, NT, 0, st>>>(logits, draft_probs, tree_tokens, parent_idx, T, V, temperature, \
-                                                      top_p, (unsigned long long)seed, pos0, path_out, tokens_out,    \
-                                                      n_out, ebuf, status)
+  const WalkArgs a = {logits, draft_probs, tree_tokens, parent_idx, T, V, temperature, top_p, (u64)seed, pos0, path_out,
+                      tokens_out, n_out, ebuf, status};
   sx_prof_begin(SX_K_WALK, st);
-  if (draft_probs) SX_WALK(1024, 0, true);
-  else if (V <= 1024) SX_WALK(512, 2, false);
-  else if (V <= 8192) SX_WALK(512, 16, false);
-  else if (V <= 32768) SX_WALK(512, 64, false);
-  else SX_WALK(1024, 0, false);
-#undef SX_WALK
+  int rc;
+  // the row in LDS while it fits; small rows with fewer waves to meet at the barriers
+  if (V <= 4096)
+    rc = draft_probs ? launch_walk<256, true, true>(a, st) : launch_walk<256, true, false>(a, st);
+  else if (V <= 32768)
+    rc = draft_probs ? launch_walk<1024, true, true>(a, st) : launch_walk<1024, true, false>(a, st);
+  else
+    rc = draft_probs ? launch_walk<1024, false, true>(a, st) : launch_walk<1024, false, false>(a, st);
   sx_prof_end(st);
-  SX_LAUNCH_CHECK();
-  return SX_OK;
+  return rc;
 }

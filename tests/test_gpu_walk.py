@@ -98,6 +98,39 @@ def test_nucleus_with_tied_probabilities(sx):
         assert toks == ref["tokens"] and toks[0] in (5, 100)      # token 200 ties with 100 but has the higher id
 
 
+@pytest.mark.parametrize("V,top_p", [(1023, 0.9), (4097, 0.75), (32767, 0.9), (40001, 0.66), (128256, 1.0)])
+@pytest.mark.parametrize("tied", [False, True])
+def test_walk_with_any_number_of_candidates(sx, V, top_p, tied):
+    """Rows whose nucleus comes from c likely tokens over a floor too low to matter, c on both sides of what the kernel
+    finishes in one wave (64), in its list (1024) and with the whole row; rows that are no multiple of four long."""
+    r = np.random.default_rng(V)
+    checked = 0
+    for c in (1, 3, 63, 64, 65, 200, 1000, 1024, 1025, 3000):
+        if c > V:
+            continue
+        lg = np.full((1, V), -40.0, np.float32)
+        ids = r.choice(V, size=c, replace=False)
+        lg[0, ids] = 1.0 if tied else r.uniform(0.0, 3.0, size=c).astype(np.float32)
+        lg[0, V - 1] = lg[0, ids[0]]
+        tok, par = np.array([3], np.int32), np.array([-1], np.int32)
+        ld, td, pd = to_dev(lg), to_dev(tok), to_dev(par)
+        qd = to_dev(np.full((1, V), 1.0 / V, np.float32))
+        for seed in range(6):
+            ref = oracle.accept_walk(lg, tok, par, 0.8, top_p, seed=seed, pos0=9)
+            m = ref["margins"][0]
+            if min(m["m_p"], m["m_u"]) > 1e-5:      # sums of at most 3000 terms: fp32 terms are good to 3e-7 of the mass
+                path, toks, _ = _walk(sx, ld, td, pd, 0.8, top_p, seed, 9)
+                assert path == [0] and toks == ref["tokens"], (c, seed)
+                checked += 1
+            ref = oracle.specinfer_walk(lg, np.full((1, V), 1.0 / V), tok, par, 0.8, top_p, seed=seed, pos0=9)
+            if min(ref["margins"][0]["m_acc"], ref["margins"][0]["m_u"]) > 1e-5 and m["m_p"] > 1e-5:
+                _, toks, n, _ = sx.accept_walk(ld, td, pd, 0.8, top_p, seed, 9, draft_probs=qd)
+                torch.cuda.synchronize()
+                assert int(n.item()) == 1 and int(toks[0].item()) == ref["tokens"][0], (c, seed)
+                checked += 1
+    assert checked >= 12
+
+
 def test_duplicate_siblings_and_single_node(sx):
     tok = np.array([5, 3, 3, 9], np.int32)
     par = np.array([-1, 0, 0, 1], np.int32)
