@@ -428,124 +428,292 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
   }
 }
 
-// One workgroup of 1024 lanes; lane t owns the flat candidates [t*per, (t+1)*per).
-// REG = true keeps the (<= 64) keys of a lane in registers.
+// One workgroup of 1024 lanes picks the Bsel best of n candidates and orders them.  What bounds it is a chain of block-wide
+// steps on one compute unit, so there are few of them:
+//   threshold   with d = (largest order key) - (order key), the smallest D with #(d <= D) >= Bsel, by histograms of d in
+//               LDS: 4096 bins of 2^14 keys (1024 per octave of the scores, 8 octaves below the best; bins of an eighth of
+//               an octave made a row's candidates meet in one bin, and their atomics queue), then bins of 4, then single
+//               keys, as far as needed.  Scores further apart (-inf among the winners) take bins over all 32 bits;
+//   order       the winners fall into 4096 buckets of equal key range (two per bucket at most on average), are placed
+//               by a scan of the bucket counts and ranked inside their bucket by counting smaller entries.  Where one
+//               bucket holds more than kBucketMax (many equal scores) they go through a sorting network instead.
+// Before, the threshold was a search over 32 bits with a block-wide count each and the order a sorting network of 66
+// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 48 and 14 (of the 48 four passes over 256 KB by one compute unit are 33).
+// QUADS > 0 (up to 16384 candidates): lane t holds the keys of the candidates 4 (j 1024 + t) .. + 3, j < QUADS, in
+// registers; 0: they are re-read, which beyond that costs less than the code it takes to hold them.
 constexpr int kSelThreads = 1024;
+constexpr int kSelBins = 4096;
+constexpr unsigned kBucketMax = 32;
+// order key of a candidate: never 0, which marks the slots past the end (only one NaN pattern would map there)
+__device__ __forceinline__ unsigned select_key(float v) { return max(f32_order_key(v), 1u); }
 
-template <bool REG>
+template <int QUADS>
 __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float* __restrict__ score,
                                                                     const int* __restrict__ topk_idx, int n, int k,
-                                                                    int B, int per, int* __restrict__ out_row,
+                                                                    int B, int* __restrict__ out_row,
                                                                     int* __restrict__ out_token,
                                                                     float* __restrict__ out_score,
                                                                     int* __restrict__ n_out) {
   constexpr int NW = kSelThreads / 64;
-  constexpr int RK = 64;  // keys a lane can hold in registers
-  extern __shared__ unsigned long long sbuf[];
-  __shared__ int redi[16];
-  __shared__ int s_wave_ties[NW];
-  __shared__ int s_probe[2][NW];
-  __shared__ int s_pos;
+  constexpr int BPT = kSelBins / kSelThreads;
+  constexpr int R = QUADS > 0 ? QUADS * 4 : 1;
+  extern __shared__ unsigned long long sbuf[];  // winners, then room to place them: 2 x next_pow2(Bsel)
+  __shared__ __attribute__((aligned(16))) unsigned hist[kSelBins];
+  __shared__ int s_wave[NW];
+  __shared__ unsigned s_max, s_big;
+  __shared__ int s_pos, s_bin, s_above;
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int Bsel = min(B, n);
 
-  // ---- threshold: K = largest order key with #(key >= K) >= Bsel, by bitwise search --------------------
-  // For the search a lane holds the keys tid, tid + 1024, ... (coalesced); slots past n hold key 0,
-  // below every real key.
-  unsigned key[REG ? RK : 1];
-  if (REG) {
+  // f(four order keys, flat index of the first) over the candidates in memory, U quads in flight per lane.  (A rolled
+  // loop on purpose: with 64 keys a lane in registers every pass is 64 copies of its body, and a workgroup that runs
+  // through them once waits for instructions: 63 us against 48.)
+  auto stream = [&](auto f) {
+    constexpr int U = 4;
+    for (int i0 = 0; i0 < n; i0 += U * 4 * kSelThreads) {
+      f32x4 v[U];
 #pragma unroll
-    for (int e = 0; e < RK; ++e) {
-      const int i = e * kSelThreads + tid;
-      key[e] = i < n ? f32_order_key(score[i]) : 0u;
-    }
-  }
-  unsigned K = 0;
-  if (n > Bsel) {
-    // One barrier per probe: the per-wave counts alternate between two LDS rows, so the next probe's
-    // writers can never overtake this probe's readers.
-    for (int bit = 31; bit >= 0; --bit) {
-      const unsigned trial = K | (1u << bit);
-      int c = 0;
-      if (REG) {
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + (u * kSelThreads + tid) * 4;
+        if (i + 4 <= n) {
+          v[u] = *reinterpret_cast<const f32x4*>(score + i);
+        } else {
 #pragma unroll
-        for (int e = 0; e < RK; ++e) c += (key[e] >= trial) ? 1 : 0;
-      } else {
-        for (int i = tid; i < n; i += kSelThreads) c += (f32_order_key(score[i]) >= trial) ? 1 : 0;
+          for (int c = 0; c < 4; ++c) v[u][c] = i + c < n ? score[i + c] : 0.f;
+        }
       }
-      c = wave_sum_i(c);
-      int* row = s_probe[bit & 1];
-      if ((tid & 63) == 0) row[tid >> 6] = c;
-      __syncthreads();
-      int total = 0;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) total += row[w];
-      if (total >= Bsel) K = trial;
-    }
-  }
-
-  // ---- winners: every key > K, and of the keys == K the `need` lowest flat indices -----------------------
-  int gt = 0, eq = 0;
-  if (REG) {
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + (u * kSelThreads + tid) * 4;
+        unsigned t[4];
 #pragma unroll
-    for (int e = 0; e < RK; ++e) {
-      gt += (key[e] > K) ? 1 : 0;
-      eq += (key[e] == K) ? 1 : 0;
+        for (int c = 0; c < 4; ++c) t[c] = i + c < n ? select_key(v[u][c]) : 0u;
+        f(t[0], t[1], t[2], t[3], i);
+      }
     }
-  } else {
-    for (int i = tid; i < n; i += kSelThreads) {
-      const unsigned kk = f32_order_key(score[i]);
-      gt += kk > K;
-      eq += kk == K;
-    }
-  }
-  if (tid == 0) s_pos = 0;
-  const int need = Bsel - block_sum_i<NW>(gt, redi);
-  const int ties = block_sum_i<NW>(eq, redi);
-  auto push = [&](unsigned kk, int flat) {
-    const int pos = atomicAdd(&s_pos, 1);
-    sbuf[pos] = ((unsigned long long)(~kk) << 32) | (unsigned)flat;
   };
-  const bool all_ties = (ties == need);  // the usual case (a single key equals K): no ranking needed
-  // (re-read from L2 in a rolled, coalesced loop: pushing from the register copy would unroll 64
-  // conditional atomics and spill)
-#pragma unroll 4
-  for (int i = tid; i < n; i += kSelThreads) {
-    const unsigned kk = f32_order_key(score[i]);
-    if (kk > K || (all_ties && kk == K)) push(kk, i);
+  unsigned d[R];  // first the order key (slots past n: 0, below every real key), then its distance from the largest
+  unsigned top = 0;
+  if constexpr (QUADS > 0) {
+#pragma unroll
+    for (int j = 0; j < QUADS; ++j) {
+      const int i = (j * kSelThreads + tid) * 4;
+      if (i + 4 <= n) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(score + i);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) d[4 * j + c] = select_key(v[c]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) d[4 * j + c] = i + c < n ? select_key(score[i + c]) : 0u;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < R; ++e) top = max(top, d[e]);
+  } else {
+    stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) { top = max(top, max(max(a, b), max(c, e))); });
   }
-  if (!all_ties) {
-    // Rare: more keys equal K than fit.  Lanes walk contiguous ranges so that an exclusive scan of
-    // their tie counts ranks the ties in flat-index order; the `need` first ones are taken.
-    const int lo = min(n, tid * per), hi = min(n, lo + per);
+  auto clear = [&]() {
+    *reinterpret_cast<u32x4*>(hist + 4 * tid) = u32x4{0u, 0u, 0u, 0u};
+  };
+  // sum of hist over the bins that come before this lane's four
+  auto scan = [&]() -> int {
     int mine = 0;
-    for (int i = lo; i < hi; ++i) mine += f32_order_key(score[i]) == K;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) mine += (int)hist[tid * BPT + i];
     int incl = mine;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
       const int t = __shfl_up(incl, o, 64);
-      if ((tid & 63) >= o) incl += t;
+      if (lane >= o) incl += t;
     }
-    if ((tid & 63) == 63) s_wave_ties[tid >> 6] = incl;
+    if (lane == 63) s_wave[wave] = incl;
+    __syncthreads();
+    int before = 0;
+    for (int w = 0; w < wave; ++w) before += s_wave[w];
+    return before + incl - mine;
+  };
+
+  clear();
+  if (tid == 0) {
+    s_pos = 0;
+    s_max = 0;
+    s_big = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
+  if (lane == 0) atomicMax(&s_max, top);
+  __syncthreads();
+  const unsigned kmax = s_max;  // slots past n end up at d == kmax, beyond every real key
+  if constexpr (QUADS > 0) {
+#pragma unroll
+    for (int e = 0; e < R; ++e) d[e] = kmax - d[e];
+  }
+  // f(four d, flat index of the first) over all candidates of this lane, in the same number of calls for every lane
+  auto each4 = [&](auto f) {
+    if constexpr (QUADS > 0) {
+#pragma unroll
+      for (int j = 0; j < QUADS; ++j) f(d[4 * j], d[4 * j + 1], d[4 * j + 2], d[4 * j + 3], (j * kSelThreads + tid) * 4);
+    } else {
+      stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int i) { f(kmax - a, kmax - b, kmax - c, kmax - e, i); });
+    }
+  };
+
+  // ---- threshold ---------------------------------------------------------------------------------------
+  unsigned D = 0xFFFFFFFFu;
+  int need = Bsel, ties = Bsel;  // of the candidates in the threshold's last bin: how many are taken, how many there are
+  if (n > Bsel) {
+    unsigned prefix = 0;
+    int above = 0, shift = 14, bits = 12;
+    bool first = true, wide = false;
+    while (true) {
+      if (first) {
+        each4([&](unsigned a, unsigned b, unsigned c, unsigned e, int) {
+          const unsigned t[4] = {a, b, c, e};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) atomicAdd(&hist[min(t[i] >> shift, (unsigned)(kSelBins - 1))], 1u);
+        });
+      } else {
+        each4([&](unsigned a, unsigned b, unsigned c, unsigned e, int) {
+          const unsigned t[4] = {a, b, c, e};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if ((t[i] >> (shift + bits)) == prefix && t[i] != kmax) atomicAdd(&hist[(t[i] >> shift) & ((1u << bits) - 1u)], 1u);
+        });
+      }
+      __syncthreads();
+      int start = above + scan();
+#pragma unroll
+      for (int i = 0; i < BPT; ++i) {
+        const int h = (int)hist[tid * BPT + i];
+        if (start < Bsel && start + h >= Bsel) {
+          s_bin = tid * BPT + i;
+          s_above = start;
+        }
+        start += h;
+      }
+      __syncthreads();
+      const unsigned b = (unsigned)s_bin;
+      const int at = s_above, h = (int)hist[b];
+      __syncthreads();
+      clear();
+      __syncthreads();
+      if (first && !wide && b == (unsigned)(kSelBins - 1)) {  // beyond 8 octaves: again, over all 32 bits
+        wide = true;
+        shift = 20;
+        continue;
+      }
+      first = false;
+      above = at;
+      prefix = (prefix << bits) | b;
+      need = Bsel - above;
+      ties = h;
+      D = shift ? ((prefix + 1u) << shift) - 1u : prefix;
+      if (ties == need || shift == 0) break;
+      bits = min(shift, 12);  // 14 -> 2 -> 0, or 20 -> 8 -> 0
+      shift -= bits;
+    }
+  }
+
+  // ---- winners: every d <= D where they are Bsel; else every d < D and of the d == D the `need` lowest flat indices
+  const bool all_ties = ties == need;
+  const unsigned take = all_ties ? D : D - 1u;  // (not all ties: some are better than D, or D = 0 and take wraps)
+  const bool none = !all_ties && D == 0;
+  each4([&](unsigned a, unsigned b, unsigned c, unsigned e, int flat) {
+    if (none || __builtin_amdgcn_ballot_w64(min(min(a, b), min(c, e)) <= take) == 0ull) return;
+    const unsigned t[4] = {a, b, c, e};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool hit = t[i] <= take && flat + i < n;
+      const unsigned long long who = __builtin_amdgcn_ballot_w64(hit);
+      if (who == 0ull) continue;
+      const int leader = __builtin_ctzll(who);
+      int pos = 0;
+      if (lane == leader) pos = atomicAdd(&s_pos, __builtin_popcountll(who));
+      pos = __builtin_amdgcn_readlane(pos, leader) + __builtin_popcountll(who & ((1ull << lane) - 1ull));
+      if (hit && pos < Bsel) sbuf[pos] = ((unsigned long long)t[i] << 32) | (unsigned)(flat + i);
+    }
+  });
+  if (!all_ties) {
+    // Rare: more candidates at D than fit.  Lanes walk contiguous ranges so that an exclusive scan of
+    // their tie counts ranks the ties in flat-index order; the `need` first ones are taken.
+    const int per = (n + kSelThreads - 1) / kSelThreads;
+    const int lo = min(n, tid * per), hi = min(n, lo + per);
+    int mine = 0;
+    for (int i = lo; i < hi; ++i) mine += kmax - select_key(score[i]) == D;
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
     int tie_rank = incl - mine;
-    for (int w = 0; w < (tid >> 6); ++w) tie_rank += s_wave_ties[w];
+    for (int w = 0; w < wave; ++w) tie_rank += s_wave[w];
     for (int i = lo; i < hi && tie_rank < need; ++i)
-      if (f32_order_key(score[i]) == K) {
-        push(K, i);
+      if (kmax - select_key(score[i]) == D) {
+        const int pos = atomicAdd(&s_pos, 1);
+        if (pos < Bsel) sbuf[pos] = ((unsigned long long)D << 32) | (unsigned)i;
         ++tie_rank;
       }
   }
   __syncthreads();
-  const int nsort = next_pow2(Bsel < 2 ? 2 : Bsel);
-  for (int i = Bsel + tid; i < nsort; i += kSelThreads) sbuf[i] = ~0ull;
-  block_bitonic_sort_u64<kSelThreads>(sbuf, nsort);
-  for (int i = tid; i < Bsel; i += kSelThreads) {
-    const unsigned flat = (unsigned)(sbuf[i] & 0xFFFFFFFFull);
-    out_row[i] = (int)(flat / (unsigned)k);
-    out_token[i] = topk_idx[flat];
-    out_score[i] = score[flat];
+
+  // ---- order: (score descending, flat index ascending) = ascending entries --------------------------------
+  auto emit = [&](int place, unsigned flat) {
+    out_row[place] = (int)(flat / (unsigned)k);
+    out_token[place] = topk_idx[flat];
+    out_score[place] = score[flat];
+  };
+  const unsigned range = min(D, kmax);
+  const int bshift = range < (unsigned)kSelBins ? 0 : 32 - 12 - __builtin_clz(range);  // range >> bshift < 4096
+  unsigned long long* placed = sbuf + next_pow2(Bsel < 2 ? 2 : Bsel);
+  constexpr int E = 8192 / kSelThreads;  // winners per lane at most
+  unsigned bucket[E], slot[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * kSelThreads + tid;
+    bucket[e] = slot[e] = 0;
+    if (i < Bsel) {
+      bucket[e] = min((unsigned)(sbuf[i] >> 32) >> bshift, (unsigned)(kSelBins - 1));
+      slot[e] = atomicAdd(&hist[bucket[e]], 1u);
+      if (slot[e] >= kBucketMax) s_big = 1;
+    }
+  }
+  __syncthreads();
+  if (s_big == 0) {
+    int start = scan();
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {  // each lane turns its own four counts into first place << 8 | count
+      const unsigned h = hist[tid * BPT + i];
+      hist[tid * BPT + i] = ((unsigned)start << 8) | h;
+      start += (int)h;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = e * kSelThreads + tid;
+      if (i < Bsel) placed[(hist[bucket[e]] >> 8) + slot[e]] = sbuf[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = e * kSelThreads + tid;
+      if (i < Bsel) {
+        const unsigned h = hist[bucket[e]], first = h >> 8, cnt = h & 255u;
+        const unsigned long long me = sbuf[i];
+        int place = (int)first;
+        for (unsigned j = 0; j < cnt; ++j) place += placed[first + j] < me ? 1 : 0;
+        emit(place, (unsigned)me);
+      }
+    }
+  } else {
+    const int nsort = next_pow2(Bsel < 2 ? 2 : Bsel);
+    for (int i = Bsel + tid; i < nsort; i += kSelThreads) sbuf[i] = ~0ull;
+    block_bitonic_sort_u64<kSelThreads>(sbuf, nsort);
+    for (int i = tid; i < Bsel; i += kSelThreads) emit(i, (unsigned)(sbuf[i] & 0xFFFFFFFFull));
   }
   if (tid == 0) n_out[0] = Bsel;
 }
@@ -600,17 +768,16 @@ extern "C" size_t sx_expand_topk_workspace(int32_t N, int32_t V, int32_t k, int3
 
 namespace {
 
-// B = 8192 needs the full 64 KB of dynamic LDS next to the static arrays; set once per device
+// B = 8192 needs 128 KB of dynamic LDS next to the static arrays; set once per device
 int configure_select_once() {
   static bool configured[64] = {};
   int dev = 0;
   SX_HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return SX_ERR_HIP;
   if (configured[dev]) return SX_OK;
-  SX_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&global_select_kernel<true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, 8192 * 8));
-  SX_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&global_select_kernel<false>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, 8192 * 8));
+  const void* forms[] = {reinterpret_cast<const void*>(&global_select_kernel<1>), reinterpret_cast<const void*>(&global_select_kernel<4>),
+                         reinterpret_cast<const void*>(&global_select_kernel<0>)};
+  for (const void* f : forms) SX_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 8192 * 8));
   configured[dev] = true;
   return SX_OK;
 }
@@ -626,18 +793,17 @@ int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, in
   sx_prof_end(st);
   if (rc != SX_OK) return rc;
   const int n = N * k;
-  const int per = (n + kSelThreads - 1) / kSelThreads;
   const int Bsel = B < n ? B : n;
   int nsort = 2;
   while (nsort < Bsel) nsort <<= 1;
-  const size_t shmem = (size_t)nsort * sizeof(unsigned long long);
+  const size_t shmem = 2 * (size_t)nsort * sizeof(unsigned long long);
   sx_prof_begin(SX_K_SELECT, st);
-  if (per <= 64)
-    global_select_kernel<true><<<1, kSelThreads, shmem, st>>>(score, idx, n, k, B, per, out_row, out_token,
-                                                               out_cum_logp, n_out);
-  else
-    global_select_kernel<false><<<1, kSelThreads, shmem, st>>>(score, idx, n, k, B, per, out_row, out_token,
-                                                                out_cum_logp, n_out);
+#define SX_SELECT(QUADS) \
+  global_select_kernel<QUADS><<<1, kSelThreads, shmem, st>>>(score, idx, n, k, B, out_row, out_token, out_cum_logp, n_out)
+  if (n <= 4 * kSelThreads) SX_SELECT(1);
+  else if (n <= 16 * kSelThreads) SX_SELECT(4);
+  else SX_SELECT(0);
+#undef SX_SELECT
   sx_prof_end(st);
   SX_LAUNCH_CHECK();
   return SX_OK;

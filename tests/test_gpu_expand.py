@@ -114,6 +114,31 @@ def test_global_select_edge_cases(sx):
     _check_global(_run(sx, one[0], one[1], 16, 8), ref, 8, 16)
 
 
+@pytest.mark.parametrize("N,k,B", [(1, 1, 1), (100, 32, 2048), (128, 32, 4096), (129, 32, 1), (500, 32, 8192), (512, 32, 700),
+                                   (513, 32, 8191), (33, 255, 1025)])
+@pytest.mark.parametrize("spread", ["wide", "narrow", "rounded", "dead"])
+def test_global_select_sizes_and_spreads(sx, N, k, B, spread):
+    """Candidate counts around what the select kernel holds per lane (4096 and 16384), every size of winner list, and
+    scores over one octave, over many, with long ties, and with dead rows (-inf) among the winners."""
+    logits, cum = wl.gen_expand_inputs(N, 400, seed=N + k)
+    if spread == "narrow":
+        cum = (-1000.0 + cum * 1e-3).astype(np.float32)
+    elif spread == "rounded":
+        logits, cum = np.round(logits), np.round(cum).astype(np.float32)
+    elif spread == "dead":
+        cum[N // 3:] = -np.inf
+    ld, cd = to_dev(logits), to_dev(cum)
+    lp, idx = sx.row_logsoftmax_topk(ld, k)
+    r, t, s, n = _run(sx, logits, cum, k, B)
+    m = min(B, N * k)
+    score = (torch.from_numpy(cum)[:, None] + lp.cpu()).numpy().reshape(-1)      # the fp32 values the kernel orders
+    order = np.lexsort((np.arange(N * k), -score))[:m]
+    assert int(n) == m
+    np.testing.assert_array_equal(r[:m], order // k)
+    np.testing.assert_array_equal(t[:m], idx.cpu().numpy().reshape(-1)[order])
+    np.testing.assert_array_equal(s[:m], score[order])
+
+
 def test_many_rows_memory_path(sx):
     """N*k above 512*128: the select kernel walks candidates from memory instead of registers."""
     logits, cum = wl.gen_expand_inputs(3000, 256, seed=9)
