@@ -1,6 +1,6 @@
 // The small memory-bound pieces of the decoder forward (Alg. 1, FORWARD): embedding gather,
-// RMSNorm, rotary embedding at position P + tree depth, SwiGLU (fp32 path only; the bf16 path
-// fuses it into the gate/up GEMM).
+// RMSNorm, rotary embedding at position P + tree depth, SwiGLU of the 4-bit path (the others fuse it
+// into the gate/up GEMM).
 #include "kernels.h"
 
 namespace {
@@ -110,15 +110,6 @@ __global__ void rope_split_kernel(const float* __restrict__ qkv, const float2* _
   }
 }
 
-__global__ void swiglu_f32_kernel(const float* __restrict__ g, const float* __restrict__ u, float* __restrict__ a,
-                                  size_t n) {
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const float x = g[i];
-    a[i] = x / (1.0f + expf(-x)) * u[i];
-  }
-}
-
 // act[i][f] = bf16(silu(gu[i][f]) * gu[i][F + f]): the SwiGLU of a gate|up product kept in fp32 (4-bit path)
 __global__ void swiglu_pair_bf16_kernel(const float* __restrict__ gu, int n, int F, unsigned short* __restrict__ act) {
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -212,12 +203,6 @@ int sx_launch_dequant_w4(const sx_w4_matrix* m, int N, int K, int group, void* W
   dequant_w4_kernel<<<(unsigned)((words + 255) / 256), 256, 0, s>>>(
       (const uint32_t*)m->qweight, (const unsigned short*)m->scales, (const unsigned char*)m->zeros, words, K / 8,
       __builtin_ctz((unsigned)group), K / group, (unsigned short*)W_bf16);
-  SX_LAUNCH_CHECK();
-  return SX_OK;
-}
-
-int sx_launch_swiglu_f32(const float* g, const float* u, float* a, size_t n, hipStream_t s) {
-  swiglu_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(g, u, a, n);
   SX_LAUNCH_CHECK();
   return SX_OK;
 }

@@ -27,12 +27,14 @@ int sx_launch_rmsnorm(const float* h, const void* gain, int dtype, int T, int d,
 // qkv fp32 [T][Nq+2Nkv] -> q (dtype) [T][Hq][Dh] rotated, k (dtype) [T][Hkv][Dh] rotated, v (dtype)
 int sx_launch_rope_split(const float* qkv, const float2* rope_cs, int T, int Hq, int Hkv, int Dh, int dtype,
                          void* q, void* k, void* v, hipStream_t st);
-int sx_launch_swiglu_f32(const float* g, const float* u, float* a, size_t n, hipStream_t st);
+
+enum { SX_GEMM_STORE = 0, SX_GEMM_RESIDUAL = 1, SX_GEMM_SWIGLU = 2, SX_GEMM_QKV_ROPE = 3 };
 
 // ---- fp32 reference-precision path (path_f32.hip) ---------------------------------------------------
-// Y[M][N] (+)= X[M][K] W[N][K]^T, all fp32, ldy = row stride of Y.
-int sx_launch_gemm_f32(const float* X, const float* W, float* Y, int M, int N, int K, int ldy, bool accumulate,
-                       hipStream_t st);
+// Y[M][n0+n1+n2] = X[M][K] [W0; W1; W2]^T (mode store; residual: added to Y), all fp32, ldy = row stride of Y;
+// mode SwiGLU: Y[M][n0] = silu(X W0^T) * (X W1^T), n1 == n0, n2 == 0.
+int sx_launch_gemm_f32(const float* X, const float* W0, const float* W1, const float* W2, int n0, int n1, int n2, float* Y,
+                       int M, int K, int ldy, int mode, hipStream_t st);
 // q and out hold the query nodes first .. T-1 (row = node - first); k_tree / v_tree hold all T nodes.
 int sx_launch_tree_attn_f32(const float* q, const float* k_tree, const float* v_tree, const float* k_prefix,
                             const float* v_prefix, const int32_t* par_s, const int32_t* depth, int T, int first, int P,
@@ -45,7 +47,6 @@ static inline bool sx_operand_fits_u32(long long rows, long long row_bytes) {
 }
 
 // ---- bf16 MFMA path -------------------------------------------------------------------------------
-enum { SX_GEMM_STORE = 0, SX_GEMM_RESIDUAL = 1, SX_GEMM_SWIGLU = 2, SX_GEMM_QKV_ROPE = 3 };
 // Y = X [W0;W1;W2]^T with n0/n1/n2 rows per segment (modes 0/1, Y fp32 [M][n0+n1+n2]), or
 // Y bf16 [M][n0] = silu(X W0^T) * (X W1^T) (mode 2, n1 == n0, n2 == 0).
 // Same contract for M <= 128 (narrow tiles; modes store, residual, SwiGLU); sx_launch_gemm_bf16 forwards to it.

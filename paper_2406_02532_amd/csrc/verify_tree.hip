@@ -12,7 +12,7 @@ struct Layout {
   int32_t *tok_s, *par_s, *depth, *klist, *kcnt;
   float2* rope_cs;
   unsigned long long* rowmask;
-  float *h, *qkv, *gate, *up, *gu;
+  float *h, *qkv, *gu;
   void *x, *q, *o, *act, *tk, *tv;
   void* split_ws;
   size_t split_bytes;
@@ -51,15 +51,12 @@ Layout carve(const sx_model_cfg& c, int P, int T, void* ws) {
     L.klist = cv.take<int32_t>(tiles * (size_t)T);
     L.kcnt = cv.take<int32_t>(tiles);
     L.rowmask = cv.take<unsigned long long>((size_t)T * ((T + 63) / 64));
-    L.gate = L.up = nullptr;
     // gate|up product in fp32 of a batch of at most 128 nodes: the 4-bit kernels leave the SwiGLU to a kernel of its own
     L.gu = cv.take<float>((size_t)(T < 128 ? T : 128) * 2 * c.d_ffn);
   } else {
     L.klist = L.kcnt = nullptr;
     L.rowmask = nullptr;
     L.gu = nullptr;
-    L.gate = cv.take<float>((size_t)T * c.d_ffn);
-    L.up = cv.take<float>((size_t)T * c.d_ffn);
   }
   L.bytes = cv.off;
   return L;
@@ -246,11 +243,8 @@ int sx_verify_tree_range_impl(const sx_weights* w, const void* prefix_k, const v
       SX_TIMED(SX_K_GEMM_QKV,
                sx_launch_gemm_bf16(L.x, lw.wq, lw.wk, lw.wv, Nq, Nkv, Nkv, L.qkv, n, d, SX_GEMM_STORE, split_ws, split_bytes, st));
     } else {
-      const int ld = Nq + 2 * Nkv;
-      const float* x = static_cast<const float*>(L.x);
-      SX_TRY(sx_launch_gemm_f32(x, (const float*)lw.wq, L.qkv, n, Nq, d, ld, false, st));
-      SX_TRY(sx_launch_gemm_f32(x, (const float*)lw.wk, L.qkv + Nq, n, Nkv, d, ld, false, st));
-      SX_TRY(sx_launch_gemm_f32(x, (const float*)lw.wv, L.qkv + Nq + Nkv, n, Nkv, d, ld, false, st));
+      SX_TRY(sx_launch_gemm_f32((const float*)L.x, (const float*)lw.wq, (const float*)lw.wk, (const float*)lw.wv, Nq, Nkv, Nkv,
+                                L.qkv, n, d, Nq + 2 * Nkv, SX_GEMM_STORE, st));
     }
     if (!fused_rope)
       SX_TIMED(SX_K_ROPE, sx_launch_rope_split(L.qkv, rope_cs, n, Hq, Hkv, Dh, c.dtype, L.q, tk, tv, st));
@@ -280,12 +274,13 @@ int sx_verify_tree_range_impl(const sx_weights* w, const void* prefix_k, const v
     } else {
       SX_TRY(sx_launch_tree_attn_f32((const float*)L.q, (const float*)tkb, (const float*)tvb, (const float*)pk,
                                      (const float*)pv, L.par_s, L.depth, T, first, P, Hq, Hkv, Dh, (float*)L.o, st));
-      SX_TRY(sx_launch_gemm_f32((const float*)L.o, (const float*)lw.wo, L.h, n, d, Nq, d, true, st));
+      SX_TRY(sx_launch_gemm_f32((const float*)L.o, (const float*)lw.wo, nullptr, nullptr, d, 0, 0, L.h, n, Nq, d,
+                                SX_GEMM_RESIDUAL, st));
       SX_TRY(sx_launch_rmsnorm(L.h, lw.ffn_norm, c.dtype, n, d, c.rms_eps, L.x, st));
-      SX_TRY(sx_launch_gemm_f32((const float*)L.x, (const float*)lw.w_gate, L.gate, n, F, d, F, false, st));
-      SX_TRY(sx_launch_gemm_f32((const float*)L.x, (const float*)lw.w_up, L.up, n, F, d, F, false, st));
-      SX_TRY(sx_launch_swiglu_f32(L.gate, L.up, (float*)L.act, (size_t)n * F, st));
-      SX_TRY(sx_launch_gemm_f32((const float*)L.act, (const float*)lw.w_down, L.h, n, d, F, d, true, st));
+      SX_TRY(sx_launch_gemm_f32((const float*)L.x, (const float*)lw.w_gate, (const float*)lw.w_up, nullptr, F, F, 0,
+                                (float*)L.act, n, d, F, SX_GEMM_SWIGLU, st));
+      SX_TRY(sx_launch_gemm_f32((const float*)L.act, (const float*)lw.w_down, nullptr, nullptr, d, 0, 0, L.h, n, F, d,
+                                SX_GEMM_RESIDUAL, st));
     }
   }
   SX_TIMED(SX_K_NORM, sx_launch_rmsnorm(L.h, w->final_norm, c.dtype, n, d, c.rms_eps, L.x, st));
@@ -293,7 +288,8 @@ int sx_verify_tree_range_impl(const sx_weights* w, const void* prefix_k, const v
     SX_TIMED(SX_K_GEMM_LMHEAD,
              sx_launch_gemm_bf16(L.x, w->lm_head, nullptr, nullptr, V, 0, 0, logits_out, n, d, SX_GEMM_STORE, split_ws, split_bytes, st));
   else
-    SX_TRY(sx_launch_gemm_f32((const float*)L.x, (const float*)w->lm_head, logits_out, n, V, d, V, false, st));
+    SX_TRY(sx_launch_gemm_f32((const float*)L.x, (const float*)w->lm_head, nullptr, nullptr, V, 0, 0, logits_out, n, d, V,
+                              SX_GEMM_STORE, st));
   return SX_OK;
 }
 

@@ -63,6 +63,27 @@ def test_c1_full_parity(sx, c1):
     assert np.abs(tv.cpu().double().numpy() - ref["tree_v"]).max() <= TOL_F32
 
 
+@pytest.mark.parametrize("d,Hq,Hkv,Dh,F,V,P,T", [
+    (30, 3, 1, 10, 37, 101, 5, 33),      # nothing a multiple of four: operands read element by element
+    (64, 2, 2, 66, 52, 515, 130, 17),    # head rows of odd alignment
+    (16, 4, 2, 256, 20, 70, 3, 1),       # the largest head, one node
+    (68, 2, 1, 128, 100, 3001, 9, 300),  # enough outputs for the 64 x 64 tiles, ragged in both directions
+])
+def test_fp32_odd_shapes(sx, d, Hq, Hkv, Dh, F, V, P, T):
+    cfg = wl.ModelCfg(1, d, Hq, Hkv, Dh, F, V, dtype="fp32")
+    w = wl.gen_weights(cfg, seed=d)
+    w["lm_head"] = w["lm_head"] * 4
+    pk, pv = wl.gen_prefix_kv(cfg, P, seed=d + 1)
+    tok, par = wl.gen_uniform_tree(T, V, seed=d + 2)
+    ref = oracle.verify_tree(cfg, weights_np(w), pk.double().numpy(), pv.double().numpy(), tok, par)
+    got, tk, tv = _gpu_verify(sx, cfg, w, pk, pv, tok, par, want_kv=True)
+    # fp32 against fp64: a relative error of a few 1e-7 per sum, eight sums deep
+    scale = np.abs(ref["logits"]).max()
+    assert np.abs(got - ref["logits"]).max() <= 1e-5 * max(scale, 1.0)
+    assert np.abs(tk.cpu().double().numpy() - ref["tree_k"]).max() <= 1e-5
+    assert np.abs(tv.cpu().double().numpy() - ref["tree_v"]).max() <= 1e-5
+
+
 def test_c1_chain_single_node_and_empty_prefix(sx, c1):
     cfg, w, wn, pk, pv = c1
     tok, par = wl.gen_chain_tree(33, cfg.vocab, seed=4)
