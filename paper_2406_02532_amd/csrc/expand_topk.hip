@@ -438,14 +438,97 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
 //               by a scan of the bucket counts and ranked inside their bucket by counting smaller entries.  Where one
 //               bucket holds more than kBucketMax (many equal scores) they go through a sorting network instead.
 // Before, the threshold was a search over 32 bits with a block-wide count each and the order a sorting network of 66
-// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 48 and 14 (of the 48 four passes over 256 KB by one compute unit are 33).
+// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 31 and 14.
 // QUADS > 0 (up to 16384 candidates): lane t holds the keys of the candidates 4 (j 1024 + t) .. + 3, j < QUADS, in
 // registers; 0: they are re-read, which beyond that costs less than the code it takes to hold them.
 constexpr int kSelThreads = 1024;
 constexpr int kSelBins = 4096;
 constexpr unsigned kBucketMax = 32;
+constexpr int kCodesMaxN = 65536, kCodesMaxB = 2048, kCodesCap = 3072;
 // order key of a candidate: never 0, which marks the slots past the end (only one NaN pattern would map there)
 __device__ __forceinline__ unsigned select_key(float v) { return max(f32_order_key(v), 1u); }
+
+// Exclusive sum over the lanes of `mine`, every lane of the workgroup calling.
+__device__ __forceinline__ int block_exclusive_scan(int mine, int* s_wave) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) s_wave[wave] = incl;
+  __syncthreads();
+  int before = 0;
+  for (int w = 0; w < wave; ++w) before += s_wave[w];
+  return before + incl - mine;
+}
+
+// The `keep` smallest of L <= 8192 distinct entries (distance from the best score << 32 | flat index), in order, to the
+// outputs; distances are at most `range`.  `placed` has room for L entries, or for the padding to a power of two of
+// sbuf's; hist is clear, *s_big zero.
+__device__ __forceinline__ void order_and_emit(unsigned long long* sbuf, unsigned long long* placed, int L, int keep,
+                                               unsigned range, unsigned* hist, int* s_wave, unsigned* s_big,
+                                               const float* __restrict__ score, const int* __restrict__ topk_idx, int k,
+                                               int* __restrict__ out_row, int* __restrict__ out_token,
+                                               float* __restrict__ out_score) {
+  constexpr int E = 8192 / kSelThreads, BPT = kSelBins / kSelThreads;
+  const int tid = threadIdx.x;
+  auto emit = [&](int place, unsigned flat) {
+    if (place >= keep) return;
+    out_row[place] = (int)(flat / (unsigned)k);
+    out_token[place] = topk_idx[flat];
+    out_score[place] = score[flat];
+  };
+  const int shift = range < (unsigned)kSelBins ? 0 : 32 - 12 - __builtin_clz(range);  // range >> shift < 4096
+  unsigned bucket[E], slot[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int i = e * kSelThreads + tid;
+    bucket[e] = slot[e] = 0;
+    if (i < L) {
+      bucket[e] = min((unsigned)(sbuf[i] >> 32) >> shift, (unsigned)(kSelBins - 1));
+      slot[e] = atomicAdd(&hist[bucket[e]], 1u);
+      if (slot[e] >= kBucketMax) *s_big = 1;
+    }
+  }
+  __syncthreads();
+  if (*s_big == 0) {
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) mine += (int)hist[tid * BPT + i];
+    int start = block_exclusive_scan(mine, s_wave);
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {  // each lane turns its own four counts into first place << 8 | count
+      const unsigned h = hist[tid * BPT + i];
+      hist[tid * BPT + i] = ((unsigned)start << 8) | h;
+      start += (int)h;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = e * kSelThreads + tid;
+      if (i < L) placed[(hist[bucket[e]] >> 8) + slot[e]] = sbuf[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int i = e * kSelThreads + tid;
+      if (i < L) {
+        const unsigned h = hist[bucket[e]], first = h >> 8, cnt = h & 255u;
+        const unsigned long long me = sbuf[i];
+        int place = (int)first;
+        for (unsigned j = 0; j < cnt; ++j) place += placed[first + j] < me ? 1 : 0;
+        emit(place, (unsigned)me);
+      }
+    }
+  } else {
+    const int nsort = next_pow2(L < 2 ? 2 : L);
+    for (int i = L + tid; i < nsort; i += kSelThreads) sbuf[i] = ~0ull;
+    block_bitonic_sort_u64<kSelThreads>(sbuf, nsort);
+    for (int i = tid; i < keep; i += kSelThreads) emit(i, (unsigned)(sbuf[i] & 0xFFFFFFFFull));
+  }
+}
 
 template <int QUADS>
 __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float* __restrict__ score,
@@ -457,11 +540,12 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   constexpr int NW = kSelThreads / 64;
   constexpr int BPT = kSelBins / kSelThreads;
   constexpr int R = QUADS > 0 ? QUADS * 4 : 1;
-  extern __shared__ unsigned long long sbuf[];  // winners, then room to place them: 2 x next_pow2(Bsel)
+  extern __shared__ __attribute__((aligned(16))) unsigned long long sbuf[];  // winners, then room to place them: 2 x next_pow2(Bsel)
   __shared__ __attribute__((aligned(16))) unsigned hist[kSelBins];
   __shared__ int s_wave[NW];
   __shared__ unsigned s_max, s_big;
   __shared__ int s_pos, s_bin, s_above;
+  __shared__ int s_sub[16];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int Bsel = min(B, n);
@@ -510,8 +594,6 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
     }
 #pragma unroll
     for (int e = 0; e < R; ++e) top = max(top, d[e]);
-  } else {
-    stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) { top = max(top, max(max(a, b), max(c, e))); });
   }
   auto clear = [&]() {
     *reinterpret_cast<u32x4*>(hist + 4 * tid) = u32x4{0u, 0u, 0u, 0u};
@@ -521,17 +603,7 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
     int mine = 0;
 #pragma unroll
     for (int i = 0; i < BPT; ++i) mine += (int)hist[tid * BPT + i];
-    int incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += t;
-    }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += s_wave[w];
-    return before + incl - mine;
+    return block_exclusive_scan(mine, s_wave);
   };
 
   clear();
@@ -539,8 +611,105 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
     s_pos = 0;
     s_max = 0;
     s_big = 0;
+    s_bin = 0;
+    s_above = n;
   }
+  if (tid < 16) s_sub[tid] = 0;
   __syncthreads();
+  if constexpr (QUADS == 0) {
+    // Up to 65536 candidates and kCodesMaxB winners, the paper-sized step: one pass over the scores.  The upper 16 bits of
+    // every key stay in LDS (128 KB); a histogram of the upper 12, counted on the way in, and one of the next 4, from LDS,
+    // leave a set that holds the winners and the few others of the last bin, and ordering the set cuts it.  (The four
+    // passes of the general form below, by one compute unit at some 20 bytes per cycle, are two thirds of its 48 us; this
+    // one takes 31.)  Only ties make the set too large for its list; then the general form runs.
+    if (n <= kCodesMaxN && Bsel <= kCodesMaxB && n > Bsel) {
+      unsigned* codes = reinterpret_cast<unsigned*>(sbuf);  // two per word
+      unsigned* flats = codes + kCodesMaxN / 2;             // [kCodesCap]
+      stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int i) {
+        codes[i / 2] = (a >> 16) | (b & 0xFFFF0000u);
+        codes[i / 2 + 1] = (c >> 16) | (e & 0xFFFF0000u);
+        const unsigned t[4] = {a >> 20, b >> 20, c >> 20, e >> 20};
+        if (t[0] == t[1] && t[1] == t[2] && t[2] == t[3]) {  // neighbours of a sorted row: mostly one bin
+          if (e != 0u) atomicAdd(&hist[t[0]], 4u);
+        } else {
+          if (a != 0u) atomicAdd(&hist[t[0]], 1u);
+          if (b != 0u) atomicAdd(&hist[t[1]], 1u);
+          if (c != 0u) atomicAdd(&hist[t[2]], 1u);
+          if (e != 0u) atomicAdd(&hist[t[3]], 1u);
+        }
+      });
+      __syncthreads();
+      int mine = 0;
+#pragma unroll
+      for (int i = 0; i < BPT; ++i) mine += (int)hist[kSelBins - 1 - (tid * BPT + i)];
+      int start = block_exclusive_scan(mine, s_wave);
+#pragma unroll
+      for (int i = 0; i < BPT; ++i) {
+        const int b = kSelBins - 1 - (tid * BPT + i), h = (int)hist[b];
+        if (start < Bsel && start + h >= Bsel) {
+          s_bin = b;
+          s_above = start;
+        }
+        start += h;
+      }
+      __syncthreads();
+      const unsigned bin = (unsigned)s_bin;
+      const int words = (n + 3) / 4 * 2;
+      for (int w = tid; w < words; w += kSelThreads) {
+        const unsigned v = codes[w];
+        if (((v >> 4) & 0xFFFu) == bin) atomicAdd(&s_sub[v & 15u], 1);
+        if ((v >> 20) == bin) atomicAdd(&s_sub[(v >> 16) & 15u], 1);
+      }
+      __syncthreads();
+      int L = s_above, sub = 15;
+      for (; sub >= 0; --sub) {
+        L += s_sub[sub];
+        if (L >= Bsel) break;
+      }
+      const unsigned least = (bin << 4) | (unsigned)max(sub, 0);  // the set: codes from here up (slots past n: code 0)
+      clear();
+      if (L <= kCodesCap && least > 0u) {
+        int cnt = 0;
+        for (int w = tid; w < words; w += kSelThreads) {
+          const unsigned v = codes[w];
+          cnt += ((v & 0xFFFFu) >= least ? 1 : 0) + ((v >> 16) >= least ? 1 : 0);
+        }
+        int at = block_exclusive_scan(cnt, s_wave);
+        for (int w = tid; w < words; w += kSelThreads) {
+          const unsigned v = codes[w];
+          if ((v & 0xFFFFu) >= least) flats[at++] = 2 * w;
+          if ((v >> 16) >= least) flats[at++] = 2 * w + 1;
+        }
+        __syncthreads();
+        constexpr int E = kCodesCap / kSelThreads;
+        unsigned flat[E], key[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int i = e * kSelThreads + tid;
+          flat[e] = i < L ? flats[i] : 0u;
+          key[e] = i < L ? select_key(score[flat[e]]) : 0u;
+          top = max(top, key[e]);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
+        if (lane == 0) atomicMax(&s_max, top);
+        __syncthreads();  // also: the codes have been read, the entries take their place
+        const unsigned best = s_max;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int i = e * kSelThreads + tid;
+          if (i < L) sbuf[i] = ((unsigned long long)(best - key[e]) << 32) | flat[e];
+        }
+        __syncthreads();
+        order_and_emit(sbuf, sbuf + 2 * kCodesMaxB, L, Bsel, best - (least << 16), hist, s_wave, &s_big, score, topk_idx, k,
+                       out_row, out_token, out_score);
+        if (tid == 0) n_out[0] = Bsel;
+        return;
+      }
+      __syncthreads();
+    }
+    stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) { top = max(top, max(max(a, b), max(c, e))); });
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
   if (lane == 0) atomicMax(&s_max, top);
@@ -642,16 +811,7 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
     const int lo = min(n, tid * per), hi = min(n, lo + per);
     int mine = 0;
     for (int i = lo; i < hi; ++i) mine += kmax - select_key(score[i]) == D;
-    int incl = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += t;
-    }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    int tie_rank = incl - mine;
-    for (int w = 0; w < wave; ++w) tie_rank += s_wave[w];
+    int tie_rank = block_exclusive_scan(mine, s_wave);
     for (int i = lo; i < hi && tie_rank < need; ++i)
       if (kmax - select_key(score[i]) == D) {
         const int pos = atomicAdd(&s_pos, 1);
@@ -661,60 +821,8 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   }
   __syncthreads();
 
-  // ---- order: (score descending, flat index ascending) = ascending entries --------------------------------
-  auto emit = [&](int place, unsigned flat) {
-    out_row[place] = (int)(flat / (unsigned)k);
-    out_token[place] = topk_idx[flat];
-    out_score[place] = score[flat];
-  };
-  const unsigned range = min(D, kmax);
-  const int bshift = range < (unsigned)kSelBins ? 0 : 32 - 12 - __builtin_clz(range);  // range >> bshift < 4096
-  unsigned long long* placed = sbuf + next_pow2(Bsel < 2 ? 2 : Bsel);
-  constexpr int E = 8192 / kSelThreads;  // winners per lane at most
-  unsigned bucket[E], slot[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int i = e * kSelThreads + tid;
-    bucket[e] = slot[e] = 0;
-    if (i < Bsel) {
-      bucket[e] = min((unsigned)(sbuf[i] >> 32) >> bshift, (unsigned)(kSelBins - 1));
-      slot[e] = atomicAdd(&hist[bucket[e]], 1u);
-      if (slot[e] >= kBucketMax) s_big = 1;
-    }
-  }
-  __syncthreads();
-  if (s_big == 0) {
-    int start = scan();
-#pragma unroll
-    for (int i = 0; i < BPT; ++i) {  // each lane turns its own four counts into first place << 8 | count
-      const unsigned h = hist[tid * BPT + i];
-      hist[tid * BPT + i] = ((unsigned)start << 8) | h;
-      start += (int)h;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = e * kSelThreads + tid;
-      if (i < Bsel) placed[(hist[bucket[e]] >> 8) + slot[e]] = sbuf[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = e * kSelThreads + tid;
-      if (i < Bsel) {
-        const unsigned h = hist[bucket[e]], first = h >> 8, cnt = h & 255u;
-        const unsigned long long me = sbuf[i];
-        int place = (int)first;
-        for (unsigned j = 0; j < cnt; ++j) place += placed[first + j] < me ? 1 : 0;
-        emit(place, (unsigned)me);
-      }
-    }
-  } else {
-    const int nsort = next_pow2(Bsel < 2 ? 2 : Bsel);
-    for (int i = Bsel + tid; i < nsort; i += kSelThreads) sbuf[i] = ~0ull;
-    block_bitonic_sort_u64<kSelThreads>(sbuf, nsort);
-    for (int i = tid; i < Bsel; i += kSelThreads) emit(i, (unsigned)(sbuf[i] & 0xFFFFFFFFull));
-  }
+  order_and_emit(sbuf, sbuf + next_pow2(Bsel < 2 ? 2 : Bsel), Bsel, Bsel, min(D, kmax), hist, s_wave, &s_big, score, topk_idx, k,
+                 out_row, out_token, out_score);
   if (tid == 0) n_out[0] = Bsel;
 }
 
@@ -768,7 +876,9 @@ extern "C" size_t sx_expand_topk_workspace(int32_t N, int32_t V, int32_t k, int3
 
 namespace {
 
-// B = 8192 needs 128 KB of dynamic LDS next to the static arrays; set once per device
+// dynamic LDS of the select kernel: winners and room to place them (B = 8192: 128 KB), or 128 KB of codes and their list;
+// more than a launch gets by default: allowed once per device
+constexpr size_t kSelectCodesLds = kCodesMaxN * 2 + kCodesCap * 4;
 int configure_select_once() {
   static bool configured[64] = {};
   int dev = 0;
@@ -777,7 +887,7 @@ int configure_select_once() {
   if (configured[dev]) return SX_OK;
   const void* forms[] = {reinterpret_cast<const void*>(&global_select_kernel<1>), reinterpret_cast<const void*>(&global_select_kernel<4>),
                          reinterpret_cast<const void*>(&global_select_kernel<0>)};
-  for (const void* f : forms) SX_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 8192 * 8));
+  for (const void* f : forms) SX_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectCodesLds));
   configured[dev] = true;
   return SX_OK;
 }
@@ -796,7 +906,8 @@ int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, in
   const int Bsel = B < n ? B : n;
   int nsort = 2;
   while (nsort < Bsel) nsort <<= 1;
-  const size_t shmem = 2 * (size_t)nsort * sizeof(unsigned long long);
+  size_t shmem = 2 * (size_t)nsort * sizeof(unsigned long long);
+  if (n > 16 * kSelThreads && n <= kCodesMaxN && Bsel <= kCodesMaxB) shmem = kSelectCodesLds;
   sx_prof_begin(SX_K_SELECT, st);
 #define SX_SELECT(QUADS) \
   global_select_kernel<QUADS><<<1, kSelThreads, shmem, st>>>(score, idx, n, k, B, out_row, out_token, out_cum_logp, n_out)

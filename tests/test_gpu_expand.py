@@ -114,7 +114,7 @@ def test_global_select_edge_cases(sx):
     _check_global(_run(sx, one[0], one[1], 16, 8), ref, 8, 16)
 
 
-@pytest.mark.parametrize("N,k,B", [(1, 1, 1), (100, 32, 2048), (128, 32, 4096), (129, 32, 1), (500, 32, 8192), (512, 32, 700),
+@pytest.mark.parametrize("N,k,B", [(1, 1, 1), (100, 32, 2048), (128, 32, 4096), (129, 32, 1), (500, 32, 8192), (512, 32, 700), (513, 32, 2048), (2048, 32, 2000),
                                    (513, 32, 8191), (33, 255, 1025)])
 @pytest.mark.parametrize("spread", ["wide", "narrow", "rounded", "dead"])
 def test_global_select_sizes_and_spreads(sx, N, k, B, spread):
