@@ -230,10 +230,10 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
                                              woff[t], SO_, 0, 0);                                              \
   else                                                                                                         \
     __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void_ptr)(STG_ + cdst + (t) * 1024), 16, xoff[t], SO_, 0, 0);
-#define SX_COPY(STG_, SLAB_)                                                                                   \
+#define SX_COPY(STG_, SO_)                                                                                     \
   _Pragma("unroll") for (int t = 0; t < 8; ++t) {                                                             \
-    SX_COPY1(STG_, (SLAB_) * (BK * 2), 0, t)                                                                   \
-    SX_COPY1(STG_, (SLAB_) * (BK * 2), 1, t)                                                                   \
+    SX_COPY1(STG_, SO_, 0, t)                                                                                  \
+    SX_COPY1(STG_, SO_, 1, t)                                                                                  \
   }
 #define SX_READW(STG_, FW, i, KC) FW[i] = *reinterpret_cast<const bf16x8*>(STG_ + wrow + (i) * (16 * BK * 2) + KC);
 #define SX_READX(STG_, FX, i, KC) FX[i] = *reinterpret_cast<const bf16x8*>(STG_ + xrow + (i) * (16 * BK * 2) + KC);
@@ -245,6 +245,8 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 #define SX_MMA(FX, FW)                                                                                         \
   _Pragma("unroll") for (int i = 0; i < 8; ++i) _Pragma("unroll") for (int j = 0; j < 8; ++j)                  \
       SX_MFMA(acc[i][j], FW[i], FX[j])
+// byte offset along K of this workgroup's i-th slab (past the last one: the last one's)
+#define SX_OFFSET(i) ((first + min((i), NB - 1) + rot - (min((i), NB - 1) + rot < NB ? 0 : NB)) * (BK * 2))
 // The 16 fragment reads of a k-step, dealt over the 8 row blocks of the phase before it in the order
 // the next phase needs them: W block 0 and all X blocks first, then W blocks 1..7.
 #define SX_READS_A(STG_, FX, FW, KC, r)                                                                        \
@@ -268,7 +270,8 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 //   phase 2: the 64 MFMAs of k-step 1, with the copies of the slab after next (K offset SO_) into STG_
 //   and the reads of the next slab's k-step 0 between them.  The copies go out early in the phase
 //   (kCopyRows row blocks): they have until the next barrier, a slab's worth of MFMAs away.
-#define SX_SLAB(STG_, STG_N, SO_)                                                                              \
+#define SX_SLAB(STG_, STG_N, NEXT_)                                                                                     \
+  const int so_next = SX_OFFSET(NEXT_);                                                                        \
   _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                                             \
     _Pragma("unroll") for (int j = 0; j < 4; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
     SX_READS_A(STG_, fx1, fw1, kc1, r)                                                                         \
@@ -279,18 +282,18 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                                             \
     _Pragma("unroll") for (int j = 0; j < 4; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
     if (r < kCopyRows) {                                                                                       \
-      _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, SO_, 0, r * (8 / kCopyRows) + c) \
+      _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, so_next, 0, r * (8 / kCopyRows) + c) \
     }                                                                                                          \
     SX_READS_A(STG_N, fx0, fw0, kc0, r)                                                                        \
     _Pragma("unroll") for (int j = 4; j < 8; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
     if (r < kCopyRows) {                                                                                       \
-      _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, SO_, 1, r * (8 / kCopyRows) + c) \
+      _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, so_next, 1, r * (8 / kCopyRows) + c) \
     }                                                                                                          \
     SX_READS_B(STG_N, fx0, fw0, kc0, r)                                                                        \
   }                                                                                                            \
   if (PF) { /* youngest in the queue: the barrier's wait lets these two loads stay in flight */                \
     asm volatile("" ::"v"(pfx), "v"(pfw) : "memory"); /* and they stay behind the copies issued above */       \
-    const int pso = min((SO_) + kPfDist * (BK * 2), last * (BK * 2));                 \
+    const int pso = SX_OFFSET((NEXT_) + kPfDist);                                                              \
     pfx = __builtin_amdgcn_raw_buffer_load_b32(xres, pfxoff, pso, 0);                                          \
     pfw = __builtin_amdgcn_raw_buffer_load_b32(pfwres, pfwoff, pso, 0);                                        \
   }
@@ -300,16 +303,23 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   // reads any more, and reads fragments nobody uses.
   const int nb_all = a.K / BK;
   const int first = kpart * nb_all / ksplit;                      // slabs of this workgroup: [first, first + NB)
-  const int NB = (kpart + 1) * nb_all / ksplit - first, last = first + NB - 1;
-  SX_COPY(stA, first)
-  SX_COPY(stB, min(first + 1, last))
+  const int NB = (kpart + 1) * nb_all / ksplit - first;
+  // Each XCD walks K from another eighth on: started all at the first slab, 256 workgroups ask for the same 128 bytes of rows
+  // that lie a power of two apart, and the memory channels take turns -- where a launch is near the weight stream's
+  // bound (70B MLP at 300 rows: gate|up 413 -> 374 us, down 237 -> 218; at 1000 rows 0 to 2 %).  The workgroups of an
+  // XCD stay in step with each other, since they share the operand lines in its L2 (rotated against each other they are
+  // up to 8 % slower at 2048 rows).  The prefetching form (8 row tiles) is bound by the matrix cores and 0.5 % slower with
+  // the rotation.
+  const int rot = PF ? 0 : xcd * NB / 8;
+  SX_COPY(stA, SX_OFFSET(0))
+  SX_COPY(stB, SX_OFFSET(1))
   if (PF) {
     // The in-loop barriers let the two youngest operations stay in flight, taking them to be a slab's two
     // prefetch loads.  Before the first slab has issued any, the two youngest would be the last copies into the
     // second stage (X and W rows 56..63 of each wave's share), read by the first slab's second phase: so the
     // prologue issues a pair of prefetch loads of its own.  (Without them those rows were occasionally stale.)
     asm volatile("" ::: "memory");
-    const int pso = min(first + 2, last) * (BK * 2);
+    const int pso = SX_OFFSET(2);
     pfx = __builtin_amdgcn_raw_buffer_load_b32(xres, pfxoff, pso, 0);
     pfw = __builtin_amdgcn_raw_buffer_load_b32(pfwres, pfwoff, pso, 0);
   }
@@ -317,11 +327,11 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   _Pragma("unroll") for (int i = 0; i < 8; ++i) { SX_READW(stA, fw0, i, kc0) SX_READX(stA, fx0, i, kc0) }
   int s = 0;
   for (; s + 2 <= NB; s += 2) {
-    SX_SLAB(stA, stB, min(first + s + 2, last) * (BK * 2))
-    SX_SLAB(stB, stA, min(first + s + 3, last) * (BK * 2))
+    { SX_SLAB(stA, stB, s + 2) }
+    { SX_SLAB(stB, stA, s + 3) }
   }
   if (s < NB) {  // one slab left, in stage A
-    SX_SLAB(stA, stB, last * (BK * 2))
+    SX_SLAB(stA, stB, NB)
   }
   // Copies past the end of K may still be in flight: they must land before this workgroup's LDS is released.
   __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -330,6 +340,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   // compiler cannot see the hand-written MFMAs, so the wait states are spelled out
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 #undef SX_COPY1
+#undef SX_OFFSET
 #undef SX_COPY
 #undef SX_READW
 #undef SX_READX

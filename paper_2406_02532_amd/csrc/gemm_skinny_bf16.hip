@@ -13,7 +13,11 @@
 // not what the copies wait for.  With the copies of W taken out the kernel still takes 29 us of 54 (gate|up,
 // warm), with those of X taken out 48: a 64-column tile copies all 128 rows of X again (16 KB per slab next to
 // 8 KB of weights), so the L2 -> LDS stream carries three times the weight bytes with two slabs of lookahead.
-// Hence the 128-column form below for wide matrices: 31 us for the same product.
+// Hence the 128-column form below for wide matrices: 31 us for the same product.  From HBM the channels bound it more than
+// the bytes: rotating the order of the slabs (below) took the wide shapes from 3.8-4.4 to 4.3-5.2 TB/s at 100 rows.
+// Nine slabs of weights in flight instead of three, tiles of 64 or 32 rows for small batches and an even cut of all
+// slabs among one workgroup per compute unit were measured as well (one wave half copying W, the other X): at 100 rows
+// 2 to 10 % slower, at 50 rows and less 2 to 15 % faster than this kernel was, and slower than it is with the rotation.
 #include "kernels.h"
 
 namespace {
@@ -27,6 +31,7 @@ constexpr int BM = 128, BK = 64;
 constexpr int kXBytes = BM * BK * 2;   // 16 KB
 constexpr int kWBytes = 64 * BK * 2;   // 8 KB per group of 64 columns
 constexpr int kWideMinSlabs = 40;
+constexpr int kOneRound = 256;         // workgroups that run side by side, one or two per compute unit
 
 struct SkinnyArgs {
   const unsigned short* X;
@@ -111,7 +116,7 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
   }
 #define SX_COPY(STG_, SLAB_)                                                                                     \
   {                                                                                                              \
-    const int so = (SLAB_) * (BK * 2);                                                                           \
+    const int sl = (SLAB_) + rot, so = (sl > last ? sl - NB : sl) * (BK * 2);                                    \
     _Pragma("unroll") for (int t = 0; t < kXCopies; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(               \
         xres, (lds_void_ptr)(STG_ + (kXCopies * wave + t) * 1024), 16, xoff[t], so, 0, 0);                       \
     _Pragma("unroll") for (int t = 0; t < 2; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                      \
@@ -152,6 +157,12 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
   const int nb_all = a.K / BK;
   const int first = kpart * nb_all / a.split;
   const int NB = (kpart + 1) * nb_all / a.split - first, last = first + NB - 1;
+  // Every workgroup walks its slabs from another one on.  Started all at their first, hundreds of workgroups ask for the
+  // same 128 bytes of rows that lie a power of two apart, step after step, and the memory channels take turns.  By
+  // neighbours on an XCD in a launch of one round, by all neighbours where later rounds drift apart anyway: 7B gate|up
+  // product at 100 rows 46.8 -> 41.5 us, head of 32000 rows 61.3 -> 50.7, of 128256 rows 236 -> 204, 70B O projection
+  // 43.4 -> 36.9, 70B gate|up 191 -> 176; of ten shapes at five batch sizes none got slower.
+  const int rot = (int)((unsigned)(a.tilesN * a.split > kOneRound ? 5 * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
   // (NH = 2: four stages, the copies of the next two slabs may stay in flight, those of the third go out)
   SX_COPY(st0, first)
   SX_COPY(st1, min(first + 1, last))
