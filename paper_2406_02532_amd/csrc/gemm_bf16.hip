@@ -1,15 +1,18 @@
 // Y = X W^T on the gfx950 matrix cores: the linear layers of the decoder forward (Alg. 1, FORWARD) at
 // M = number of tree tokens.  bf16 operands, fp32 accumulation.
 //
-// Tiling.  A workgroup of 4 waves (2 x 2) owns a 256 x 256 output tile; each wave a 128 x 128
-// quadrant = 8 x 8 blocks of v_mfma_f32_16x16x32_bf16, 256 fp32 accumulators per lane.  With real
+// Tiling.  A workgroup of 4 waves (2 x 2) owns a 32 JB x 256 output tile; each wave a 16 JB x 128
+// quadrant = JB x 8 blocks of v_mfma_f32_16x16x32_bf16, 4 * 8 * JB fp32 accumulators per lane.  The tile height is
+// a template parameter, JB = 8 (256 rows) down to 5 (160): the most arithmetic per operand byte where the rows and the
+// compute units come out even, lower where 256-row tiles would multiply padding or leave compute units without a tile
+// (launch() below has the rule and the figures).  With real
 // operand data the chip is power-limited long before the MFMA issue rate is: in a pure register loop
 // the 16x16x32 shape sustains ~1.95 PFLOP/s against ~1.75 for 32x32x16 (it holds a ~10% higher
 // clock), which is why the smaller block is used.  The product is formed transposed (W rows feed
 // the A operand, X rows the B operand), so a lane ends up with 4 consecutive output columns of one
 // row: 16-byte stores.
 //
-// K is walked in slabs of 64 (two MFMA k-steps, 128 MFMAs per wave) held in two LDS stages of 64 KB.
+// K is walked in slabs of 64 (two MFMA k-steps, 16 JB MFMAs per wave) held in two LDS stages of 32 + 4 JB KB.
 //
 // Global -> LDS without registers.  Operand slabs are copied by buffer loads that write LDS
 // directly (16 bytes per lane, a wave fills 1 KB of consecutive LDS per instruction), so the K loop
@@ -29,7 +32,7 @@
 // fragments of k-step 1; then one barrier, before which every wave waits for its own copies of the
 // next slab (now S' is complete and S is read out); phase 2 runs the MFMAs of k-step 1, starts the
 // copies of the slab after next into S and reads the next slab's k-step 0 from S'.  One barrier
-// per 128 MFMAs; a copy has about a slab's worth of MFMAs to arrive.  Copies and fragment reads
+// per 16 JB MFMAs; a copy has about a slab's worth of MFMAs to arrive.  Copies and fragment reads
 // are dealt out evenly between the MFMAs: bursts of copies fill the memory pipeline's queues and
 // stall the wave that issues them.
 //
@@ -45,11 +48,10 @@
 
 namespace {
 
-constexpr int BM = 256, BN = 256;
+constexpr int BN = 256;                   // tile columns; tile rows are 32 JB
 constexpr int BK = 64;                    // K elements per LDS stage ("slab"): two MFMA k-steps, whole 128-byte lines
 constexpr int kThreads = 256;
-constexpr int kOperandBytes = BM * BK * 2;            // 32 KB: one operand of one slab
-constexpr int kStageBytes = 2 * kOperandBytes;        // X slab then W slab
+constexpr int kWBytes = BN * BK * 2;                  // 32 KB: W's part of a slab
 constexpr int kPfDist = 3;                            // slabs between an L2 prefetch and the copy of the same lines
 
 struct GemmArgs {
@@ -80,7 +82,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p) {
 
 // s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt_hi[15:14]):
 // all LDS reads done, at most N vector-memory operations outstanding.
-constexpr int kWaitVm0 = 0x0070, kWaitVm2 = 0x0072, kWaitVm16 = 0x4070, kWaitVm18 = 0x4072;
+constexpr int wait_vm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
+constexpr int kWaitVm0 = wait_vm(0), kWaitVm2 = wait_vm(2);
 
 // Wait until this wave's LDS reads are done and at most the given number of copies are in flight, then
 // meet the other waves.  The barrier intrinsic alone does not order memory operations for the compiler,
@@ -92,13 +95,15 @@ constexpr int kWaitVm0 = 0x0070, kWaitVm2 = 0x0072, kWaitVm16 = 0x4070, kWaitVm1
   __builtin_amdgcn_s_barrier();           \
   asm volatile("" ::: "memory");
 
-template <int MODE, bool PF>
+template <int MODE, int JB, bool PF>
 __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
+#ifdef __HIP_DEVICE_COMPILE__  // the host pass has no use for the body and drops the launch stub over its asm constraints
   // One array per stage (see the header).  Row r of an operand's slab is 128 bytes at r * 128; 16-byte
   // chunk c of the row sits at position c ^ ((r >> 1) & 7).  The LDS serves 16 lanes x 16 bytes per
   // cycle (64 banks): 16 consecutive rows reading the same k chunk fall on 16 different bank groups.
-  __shared__ __attribute__((aligned(1024))) unsigned char stA[kStageBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char stB[kStageBytes];
+  constexpr int BM = 32 * JB, kXBytes = BM * BK * 2;
+  __shared__ __attribute__((aligned(1024))) unsigned char stA[kXBytes + kWBytes];  // X slab, then W slab
+  __shared__ __attribute__((aligned(1024))) unsigned char stB[kXBytes + kWBytes];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -129,23 +134,27 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   const int tile_m = lin % a.tilesM, tile_n = lin / a.tilesM;
 
   // ---- global sources of this lane's copies ---------------------------------------------------------
-  // Copy instruction t (0..7) of wave w fills rows 64 w + 8 t .. + 7 of an operand's slab (1 KB of LDS):
-  // lane l supplies row 64 w + 8 t + l / 8, LDS chunk position l % 8, i.e. k chunk
-  // (l % 8) ^ ((row >> 1) & 7) with (row >> 1) & 7 = (4 t + l / 16) & 7.  Eight lanes read one whole
+  // Copy instruction t of wave w fills rows 64 w + 8 t .. + 7 of W's slab (t < 8) or rows 8 (JB w + t) .. + 7 of X's
+  // (t < JB), 1 KB of LDS: lane l supplies row .. + l / 8, LDS chunk position l % 8, i.e. k chunk
+  // (l % 8) ^ ((row >> 1) & 7) with (row >> 1) & 7 = (4 t + l / 16) & 7 for W and (4 (JB w + t) + l / 16) & 7 for X.  Eight lanes read one whole
   // 128-byte line: the L2 serves whole-line requests half again as fast as half-line ones.  An 8-row
   // group never straddles two weight matrices (segment sizes are multiples of 16).
   const int crow = 64 * wave + (lane >> 3);
   const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.X);
   const __amdgpu_buffer_rsrc_t wres0 = make_rsrc(a.W0), wres1 = make_rsrc(a.W1), wres2 = make_rsrc(a.W2);
   __amdgpu_buffer_rsrc_t wres[8];
-  int xoff[8], woff[8];
+  int xoff[JB], woff[8];
+#pragma unroll
+  for (int t = 0; t < JB; ++t) {
+    const int g = JB * wave + t;
+    int m = tile_m * BM + 8 * g + (lane >> 3);
+    m = m < a.M ? m : a.M - 1;
+    xoff[t] = (int)(((unsigned)m * (unsigned)a.K + ((lane & 7) ^ ((4 * (g & 1) + (lane >> 4)) & 7)) * 8) * 2u);
+  }
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
     const int r = crow + 8 * t;
     const int cchunk = (lane & 7) ^ ((4 * (t & 1) + (lane >> 4)) & 7);
-    int m = tile_m * BM + r;
-    m = m < a.M ? m : a.M - 1;
-    xoff[t] = (int)(((unsigned)m * (unsigned)a.K + cchunk * 8) * 2u);
     if (MODE == SX_GEMM_SWIGLU) {
       // slab rows in 16-row groups: even group = gate, odd = up; rows 64 w + 8 t are in group 4 w + t / 2
       int f = tile_n * (BN / 2) + (2 * wave + (t >> 2)) * 16 + (t & 1) * 8 + (lane >> 3);
@@ -168,7 +177,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
       woff[t] = (int)(((unsigned)(n - first) * (unsigned)a.K + cchunk * 8) * 2u);
     }
   }
-  const int cdst = wave * 8192;  // this wave's 8 KB of an operand's slab
+  const int xdst = wave * (JB * 1024), wdst = kXBytes + wave * 8192;  // this wave's share of X's and of W's slab
 
   // ---- L2 prefetch (PF kernels: 8 row tiles, column tiles a multiple of 4) ---------------------------
   // The 32 workgroups that run side by side on an XCD are then 8 row tiles x 4 column tiles: an X tile
@@ -206,45 +215,41 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   }
 
   // acc[i][j]: W rows (output columns) 16 i .. + 15 of the quadrant, X rows (output rows) 16 j .. + 15
-  f32x4 acc[8][8];
+  f32x4 acc[8][JB];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
 
   // fragment addresses: row (quadrant base + 16 i + l16), k chunk 4 ks + lq at position ^ ((row >> 1) & 7)
   const int fsw = (l16 >> 1) & 7;
-  const int xrow = (wm * 128 + l16) * (BK * 2);
-  const int wrow = kOperandBytes + (wn * 128 + l16) * (BK * 2);
+  const int xrow = (wm * (16 * JB) + l16) * (BK * 2);
+  const int wrow = kXBytes + (wn * 128 + l16) * (BK * 2);
   const int kc0 = ((lq ^ fsw) << 4), kc1 = (((4 + lq) ^ fsw) << 4);
-  bf16x8 fx0[8], fw0[8], fx1[8], fw1[8];   // k-step 0 and k-step 1 of a slab
+  bf16x8 fx0[JB], fw0[8], fx1[JB], fw1[8];   // k-step 0 and k-step 1 of a slab
 
 // One copy instruction: rows 8 t .. + 7 of this wave's share of X (OP_ 0) or W (OP_ 1) at byte offset SO_
 // along K into stage STG_.  The K offset travels in the scalar offset: the instruction's immediate
 // offset would be added to the LDS address as well.
 #define SX_COPY1(STG_, SO_, OP_, t)                                                                            \
   if (OP_)                                                                                                     \
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[t], (lds_void_ptr)(STG_ + kOperandBytes + cdst + (t) * 1024), 16,   \
-                                             woff[t], SO_, 0, 0);                                              \
-  else                                                                                                         \
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void_ptr)(STG_ + cdst + (t) * 1024), 16, xoff[t], SO_, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[t], (lds_void_ptr)(STG_ + wdst + (t) * 1024), 16, woff[t], SO_, 0, 0); \
+  else if ((t) < JB)                                                                                           \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void_ptr)(STG_ + xdst + (t) * 1024), 16, xoff[(t) % JB], SO_, 0, 0);
 #define SX_COPY(STG_, SO_)                                                                                     \
   _Pragma("unroll") for (int t = 0; t < 8; ++t) {                                                             \
     SX_COPY1(STG_, SO_, 0, t)                                                                                  \
     SX_COPY1(STG_, SO_, 1, t)                                                                                  \
   }
 #define SX_READW(STG_, FW, i, KC) FW[i] = *reinterpret_cast<const bf16x8*>(STG_ + wrow + (i) * (16 * BK * 2) + KC);
-#define SX_READX(STG_, FX, i, KC) FX[i] = *reinterpret_cast<const bf16x8*>(STG_ + xrow + (i) * (16 * BK * 2) + KC);
+#define SX_READX(STG_, FX, i, KC) if ((i) < JB) FX[(i) % JB] = *reinterpret_cast<const bf16x8*>(STG_ + xrow + (i) * (16 * BK * 2) + KC);
 // The MFMA is written out: left to itself the compiler gives an accumulator that is updated more than
 // once per loop body a new destination register each time and shuffles hundreds of registers per
 // iteration to undo it.  "+a" keeps every accumulator in place in the accumulation registers.  The
 // statements are volatile, so the issue order below is the one written here.
 #define SX_MFMA(ACC, A, B) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(A), "v"(B));
-#define SX_MMA(FX, FW)                                                                                         \
-  _Pragma("unroll") for (int i = 0; i < 8; ++i) _Pragma("unroll") for (int j = 0; j < 8; ++j)                  \
-      SX_MFMA(acc[i][j], FW[i], FX[j])
 // byte offset along K of this workgroup's i-th slab (past the last one: the last one's)
 #define SX_OFFSET(i) ((first + min((i), NB - 1) + rot - (min((i), NB - 1) + rot < NB ? 0 : NB)) * (BK * 2))
 // The 16 fragment reads of a k-step, dealt over the 8 row blocks of the phase before it in the order
@@ -265,27 +270,27 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   if (r == 4) { SX_READW(STG_, FW, 4, KC) }                                                                    \
   if (r == 5) { SX_READW(STG_, FW, 6, KC) }
 // One slab from stage STG_ (its k-step 0 already in fx0/fw0):
-//   phase 1: the 64 MFMAs of k-step 0, with the fragment reads of k-step 1 between them;
+//   phase 1: the 8 JB MFMAs of k-step 0, with the fragment reads of k-step 1 between them;
 //   barrier: everybody has read all of STG_, and everybody's copies of the next slab (stage STG_N) are in;
-//   phase 2: the 64 MFMAs of k-step 1, with the copies of the slab after next (K offset SO_) into STG_
+//   phase 2: the 8 JB MFMAs of k-step 1, with the copies of the slab after next (K offset SO_) into STG_
 //   and the reads of the next slab's k-step 0 between them.  The copies go out early in the phase
 //   (kCopyRows row blocks): they have until the next barrier, a slab's worth of MFMAs away.
 #define SX_SLAB(STG_, STG_N, NEXT_)                                                                                     \
   const int so_next = SX_OFFSET(NEXT_);                                                                        \
   _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                                             \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
+    _Pragma("unroll") for (int j = 0; j < JB / 2; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
     SX_READS_A(STG_, fx1, fw1, kc1, r)                                                                         \
-    _Pragma("unroll") for (int j = 4; j < 8; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
+    _Pragma("unroll") for (int j = JB / 2; j < JB; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
     SX_READS_B(STG_, fx1, fw1, kc1, r)                                                                         \
   }                                                                                                            \
   SX_WAIT_BARRIER(PF ? kWaitVm2 : kWaitVm0)                                                                      \
   _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                                             \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
+    _Pragma("unroll") for (int j = 0; j < JB / 2; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
     if (r < kCopyRows) {                                                                                       \
       _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, so_next, 0, r * (8 / kCopyRows) + c) \
     }                                                                                                          \
     SX_READS_A(STG_N, fx0, fw0, kc0, r)                                                                        \
-    _Pragma("unroll") for (int j = 4; j < 8; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
+    _Pragma("unroll") for (int j = JB / 2; j < JB; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
     if (r < kCopyRows) {                                                                                       \
       _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, so_next, 1, r * (8 / kCopyRows) + c) \
     }                                                                                                          \
@@ -323,7 +328,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     pfx = __builtin_amdgcn_raw_buffer_load_b32(xres, pfxoff, pso, 0);
     pfw = __builtin_amdgcn_raw_buffer_load_b32(pfwres, pfwoff, pso, 0);
   }
-  SX_WAIT_BARRIER(PF ? kWaitVm18 : kWaitVm16)
+  SX_WAIT_BARRIER(wait_vm(8 + JB + (PF ? 2 : 0)))
   _Pragma("unroll") for (int i = 0; i < 8; ++i) { SX_READW(stA, fw0, i, kc0) SX_READX(stA, fx0, i, kc0) }
   int s = 0;
   for (; s + 2 <= NB; s += 2) {
@@ -345,7 +350,6 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 #undef SX_READW
 #undef SX_READX
 #undef SX_MFMA
-#undef SX_MMA
 #undef SX_SLAB
 #undef SX_READS_A
 #undef SX_READS_B
@@ -364,12 +368,12 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     __shared__ int s_last;
     const int tail_tile = lin - a.full_tiles;
     const __amdgpu_buffer_rsrc_t pres = make_rsrc(a.part);
-    const unsigned mine = (unsigned)(((tail_tile * ksplit + kpart) * 4 + wave) * (64 * 256) + lane * 4) * 4u;  // bytes
+    const unsigned mine = (unsigned)(((tail_tile * ksplit + kpart) * 4 + wave) * (JB * 8 * 256) + lane * 4) * 4u;  // bytes
 #pragma unroll
     for (int i = 0; i < 8; ++i)
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), pres, mine + (i * 8 + j) * 1024, 0,
+      for (int j = 0; j < JB; ++j)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), pres, mine + (i * JB + j) * 1024, 0,
                                                kScopeDevice);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -381,44 +385,44 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     }
     __syncthreads();
     if (!s_last) return;
-    constexpr int kBatch = 16;
+    constexpr int kBatch = 2 * JB;
     // Read back in batches of kBatch blocks per part, all loads of a batch in flight together: one memory round
     // trip per batch and part instead of one per block (a block at a time, the 64 dependent round trips were
     // most of what the split cost).  Parts are added in part order whatever the batch size.
-    const unsigned all = (unsigned)((tail_tile * ksplit * 4 + wave) * (64 * 256) + lane * 4) * 4u;
+    const unsigned all = (unsigned)((tail_tile * ksplit * 4 + wave) * (JB * 8 * 256) + lane * 4) * 4u;
 #pragma unroll
-    for (int b0 = 0; b0 < 64; b0 += kBatch) {
+    for (int b0 = 0; b0 < 8 * JB; b0 += kBatch) {
       f32x4 sum[kBatch];
       for (int p = 0; p < ksplit; ++p) {
         f32x4 t[kBatch];
         if (p == kpart) {  // this workgroup's own part is still in its registers (the same bits it stored)
 #pragma unroll
-          for (int b = 0; b < kBatch; ++b) t[b] = acc[(b0 + b) >> 3][(b0 + b) & 7];
+          for (int b = 0; b < kBatch; ++b) t[b] = acc[(b0 + b) / JB][(b0 + b) % JB];
         } else {
 #pragma unroll
           for (int b = 0; b < kBatch; ++b)
             t[b] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                 pres, all + (unsigned)p * (4u * 64 * 256 * 4) + (b0 + b) * 1024, 0,
+                                                 pres, all + (unsigned)p * (4u * JB * 8 * 256 * 4) + (b0 + b) * 1024, 0,
                                                  kScopeDevice));
         }
 #pragma unroll
         for (int b = 0; b < kBatch; ++b) sum[b] = p == 0 ? t[b] : sum[b] + t[b];
       }
 #pragma unroll
-      for (int b = 0; b < kBatch; ++b) acc[(b0 + b) >> 3][(b0 + b) & 7] = sum[b];
+      for (int b = 0; b < kBatch; ++b) acc[(b0 + b) / JB][(b0 + b) % JB] = sum[b];
     }
   }
 
   // ---- epilogue.  acc[i][j][e]: output row 16 j + l16 of the quadrant, W row 16 i + 4 lq + e ---------
-  const int mbase = tile_m * BM + wm * 128;
+  const int mbase = tile_m * BM + wm * (16 * JB);
   const bool vec = (a.N & 3) == 0;  // then every group of 4 columns is whole and 16-byte (8-byte) aligned
   if (MODE == SX_GEMM_QKV_ROPE) {
     // The quadrant's 128 columns are one head (head_dim 128): query head, key head or value head,
     // the same for the whole wave.  Column 16 i + 4 lq + e and column + 64 (block i + 4, same lane and
     // register) are the pair the rotary embedding turns by the row's angle (Alg. 1: node at position
     // P + depth); the values are rounded to bf16 once, after the rotation.
-    // The tile's 256 rows of the cos/sin table (512 bytes each) are first copied into the LDS the K loop has
-    // left free -- rows 0..127 into the first stage's array, 128..255 into the second's -- and read from there:
+    // The tile's rows of the cos/sin table (512 bytes each) are first copied into the LDS the K loop has
+    // left free -- the first half of them into the first stage's array, the rest into the second's -- and read from there:
     // loaded from memory row block by row block, every load waited behind the stores of the block before (one
     // counter covers both on this chip), 32 memory round trips per tile.  16-byte chunk c of table row r sits at
     // chunk position (c & 16) | ((c ^ r) & 15) of its 512 bytes: the 16 rows a read instruction covers fall on 16
@@ -432,13 +436,13 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
       __syncthreads();  // every wave is past its last fragment reads of the stages
       const __amdgpu_buffer_rsrc_t cres = make_rsrc(a.cs);
 #pragma unroll
-      for (int t = 0; t < 32; ++t) {  // copy t of wave w: table rows 2 (16 w + t % 16) and + 1 of half t / 16
-        const int r = 2 * (16 * wave + (t & 15)) + (lane >> 5);
-        int m = tile_m * BM + (t >> 4) * 128 + r;
+      for (int t = 0; t < 4 * JB; ++t) {  // copy t of wave w: table rows 2 (2 JB w + t % 2 JB) and + 1 of half t / 2 JB
+        const int blk = 2 * JB * wave + t % (2 * JB), r = 2 * blk + (lane >> 5);
+        int m = tile_m * BM + t / (2 * JB) * (16 * JB) + r;
         m = m < a.M ? m : a.M - 1;
         const int pch = lane & 31, c = (pch & 16) | ((pch ^ r) & 15);
-        unsigned char* stg = (t >> 4) ? stB : stA;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(cres, (lds_void_ptr)(stg + (16 * wave + (t & 15)) * 1024), 16,
+        unsigned char* stg = t >= 2 * JB ? stB : stA;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(cres, (lds_void_ptr)(stg + blk * 1024), 16,
                                                  (int)((unsigned)m * 512u + (unsigned)c * 16u), 0, 0, 0);
       }
       asm volatile("" ::: "memory");
@@ -449,7 +453,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     if (head < a.hq + 2 * a.hkv) {
       const unsigned char* tb = wm ? stB : stA;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < JB; ++j) {
         const int m = mbase + 16 * j + l16;
         if (m >= a.M) continue;
         unsigned short* y = dst + ((size_t)m * nh + hh) * 128 + 4 * lq;
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     // a whole tile: no edge tests between the stores
     unsigned short* Yb = static_cast<unsigned short*>(a.Y) + (size_t)(mbase + l16) * a.N + (tile_n * (BN / 2) + wn * 64 + 4 * lq);
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
       for (int ii = 0; ii < 4; ++ii) {
         float h[4];
@@ -507,7 +511,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   } else if (MODE == SX_GEMM_SWIGLU) {
     unsigned short* Y = static_cast<unsigned short*>(a.Y);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < JB; ++j) {
       const int m = mbase + 16 * j + l16;
 #pragma unroll
       for (int ii = 0; ii < 4; ++ii) {
@@ -538,17 +542,17 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     // round trips long.
     float* Yb = static_cast<float*>(a.Y) + (size_t)(mbase + l16) * a.N + (tile_n * BN + wn * 128 + 4 * lq);
 #pragma unroll
-    for (int j0 = 0; j0 < 8; j0 += 2) {
+    for (int j0 = 0; j0 < JB; j0 += 2) {
       f32x4 r[2][8];
       if (MODE == SX_GEMM_RESIDUAL) {
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+        for (int jj = 0; jj < 2 && j0 + jj < JB; ++jj)
 #pragma unroll
           for (int i = 0; i < 8; ++i)
             r[jj][i] = *reinterpret_cast<const f32x4*>(Yb + (size_t)(16 * (j0 + jj)) * a.N + 16 * i);
       }
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
+      for (int jj = 0; jj < 2 && j0 + jj < JB; ++jj)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           f32x4 v = acc[i][j0 + jj];
@@ -559,7 +563,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   } else {
     float* Y = static_cast<float*>(a.Y);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < JB; ++j) {
       const int m = mbase + 16 * j + l16;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -581,24 +585,35 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
       }
     }
   }
+#endif
 }
 #undef SX_WAIT_BARRIER
 
 
-// Decides which tiles are cut along K, given memory for the partial sums.  More tiles than compute units with a
+// Decides which tiles of 32 jb rows are cut along K, given memory for the partial sums, and returns what the launch is
+// expected to take in slab times of the 256-row tile (about 1.45 us).  More tiles than compute units with a
 // remainder that would fill at most half of the chip for a whole round: the remainder tiles, up to 4 ways (as many
 // as it takes to give every compute unit a part).  Fewer tiles than half the compute units: all of them.  Parts
 // are at least 8 slabs long.  (Batches of at most 128 rows never come here: for them a partial tile of 256 KB
 // outweighs the weights a part streams, and they take the narrow-tile kernel instead.)
-constexpr float kSplitPerPartSlabs = 4.5f;
+constexpr int kMinJB = 5, kMaxRows = 256;
+// A lower tile's slab costs more than its share of the arithmetic: it copies and reads the same W slab for fewer rows.
+constexpr float kSlabTime[4] = {0.8f, 0.86f, 0.93f, 1.f};
+constexpr float kSplitPerPartSlabs = 4.5f;  // also a round's beginning and end: first copies, epilogue
 constexpr int kSplitMaxWays = 16;
-void plan_split(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
+float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
+  a.tilesM = (a.M + 32 * jb - 1) / (32 * jb);
+  a.chunk = (a.tilesM * a.tilesN + 7) / 8;
   a.split = 1;
   a.part = nullptr;
   a.part_cnt = nullptr;
   a.full_tiles = a.tail_items = a.full_per_xcd = a.tail_per_xcd = 0;
   const int cus = sx_compute_units(), tiles = a.tilesM * a.tilesN, nb = a.K / BK;
-  if (!split_ws) return;
+  const float slab = kSlabTime[jb - kMinJB], way = kSplitPerPartSlabs * jb / 8.f;  // a slab's time; a further way's
+  const size_t part_bytes = (size_t)jb * 32 * BN * sizeof(float);
+  const int rounds = (tiles + cus - 1) / cus;
+  const float uncut = rounds * (nb * slab + kSplitPerPartSlabs);
+  if (!split_ws) return uncut;
   if (2 * tiles <= cus) {
     // Fewer tiles than half the compute units (trees of a few hundred nodes, narrow models): every tile is cut, as
     // many ways as keeps all parts in one round and pays.  Cost of a cut in slab times: each part walks nb / s
@@ -606,16 +621,16 @@ void plan_split(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
     // fitted to sweeps at the 70B and 7B layer shapes for 256 to 1024 rows, where it picks the fastest or
     // second-fastest cut (e.g. 8192 x 8192 at 256 rows: 152 us uncut, 74 us cut 5 ways, 82 us cut 8 ways).
     int best = 1;
-    float best_cost = (float)nb + kSplitPerPartSlabs;
+    float best_cost = uncut;
     for (int s2 = 2; s2 * tiles <= cus && s2 <= kSplitMaxWays && nb / s2 >= 8; ++s2) {
-      const float cost = (float)nb / s2 + kSplitPerPartSlabs * s2;
+      const float cost = nb * slab / s2 + kSplitPerPartSlabs + way * s2;
       if (cost < best_cost) {
         best_cost = cost;
         best = s2;
       }
     }
-    if (best < 2 || tiles > 256) return;
-    if (split_ws_bytes < 1024 + (size_t)tiles * best * BM * BN * sizeof(float)) return;
+    if (best < 2 || tiles > 256) return uncut;
+    if (split_ws_bytes < 1024 + (size_t)tiles * best * part_bytes) return uncut;
     a.split = best;
     a.full_tiles = 0;
     a.tail_items = tiles * best;
@@ -623,16 +638,16 @@ void plan_split(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
     a.tail_per_xcd = (a.tail_items + 7) / 8;
     a.part_cnt = static_cast<int*>(split_ws);
     a.part = reinterpret_cast<float*>(static_cast<char*>(split_ws) + 1024);
-    return;
+    return best_cost;
   }
-  if (tiles <= cus) return;
+  if (tiles <= cus) return uncut;
   const int rest = tiles % cus;
-  if (rest == 0 || 2 * rest > cus) return;
+  if (rest == 0 || 2 * rest > cus) return uncut;
   int split = cus / rest;
   if (split > 4) split = 4;  // measured at the 70B QKV shape: 4 ways 289 us, 3 ways 295, 2 ways 313 (uncut: 372)
   while (split > 1 && nb / split < 8) --split;
-  if (split < 2 || rest > 256) return;
-  if (split_ws_bytes < 1024 + (size_t)rest * split * BM * BN * sizeof(float)) return;
+  if (split < 2 || rest > 256) return uncut;
+  if (split_ws_bytes < 1024 + (size_t)rest * split * part_bytes) return uncut;
   a.split = split;
   a.full_tiles = tiles - rest;
   a.tail_items = rest * split;
@@ -640,15 +655,33 @@ void plan_split(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
   a.tail_per_xcd = (a.tail_items + 7) / 8;
   a.part_cnt = static_cast<int*>(split_ws);
   a.part = reinterpret_cast<float*>(static_cast<char*>(split_ws) + 1024);
+  // the last round's slabs, and per way 2 to 4.5 more: the fewer parts, the less they wait for each other's memory
+  return uncut - nb * slab + nb * slab / split + (2.f + 2.5f * a.tail_items / cus) * jb / 8.f * split;
 }
 
+// The tile height: the one that plan_split's figures expect to be fastest, the taller of two within 2 %.  Their
+// constants are fitted to sweeps of all four heights over the 7B and 70B layer shapes at 150 to 2048 rows, where the
+// choice is on average 0.5 % and at most 7 % behind the best.  256 rows -> the height chosen:
+//   150 rows (one tile of 160): 7B down 90.8 -> 73.1 us, 70B O 82.4 -> 69.0, gate|up 217 -> 200
+//   300 rows (two of 160): 70B QKV 92.6 -> 83.9, gate|up 369 -> 340
+//   640 rows (four of 160): 70B down 360 -> 328, 7B O 65.8 -> 50.6
+//   1000 rows (six of 192: 240 tiles instead of 160 on 256 compute units): 70B QKV 196 -> 167
+// and the 256-row tile stays where there are rounds enough (1000 rows, 70B gate|up: 720 us against 802, 872 and 931).
 template <int MODE>
-int launch(const GemmArgs& a, hipStream_t st) {
+int launch(GemmArgs& a, void* split_ws, size_t split_ws_bytes, hipStream_t st) {
+  int jb = 8;
+  float best = plan_split(a, 8, split_ws, split_ws_bytes);
+  for (int t = 7; t >= kMinJB; --t) {
+    const float cost = plan_split(a, t, split_ws, split_ws_bytes);
+    if (cost < 0.98f * best) best = cost, jb = t;
+  }
+  plan_split(a, jb, split_ws, split_ws_bytes);
   const int grid = a.split > 1 ? 8 * (a.full_per_xcd + a.tail_per_xcd) : 8 * a.chunk;
-  if (a.tilesM == 8 && a.tilesN % 4 == 0)
-    gemm_bf16_kernel<MODE, true><<<grid, kThreads, 0, st>>>(a);
-  else
-    gemm_bf16_kernel<MODE, false><<<grid, kThreads, 0, st>>>(a);
+  if (jb == 5) gemm_bf16_kernel<MODE, 5, false><<<grid, kThreads, 0, st>>>(a);
+  else if (jb == 6) gemm_bf16_kernel<MODE, 6, false><<<grid, kThreads, 0, st>>>(a);
+  else if (jb == 7) gemm_bf16_kernel<MODE, 7, false><<<grid, kThreads, 0, st>>>(a);
+  else if (a.tilesM == 8 && a.tilesN % 4 == 0) gemm_bf16_kernel<MODE, 8, true><<<grid, kThreads, 0, st>>>(a);
+  else gemm_bf16_kernel<MODE, 8, false><<<grid, kThreads, 0, st>>>(a);
   SX_LAUNCH_CHECK();
   return SX_OK;
 }
@@ -676,7 +709,6 @@ int sx_launch_gemm_bf16(const void* X, const void* W0, const void* W1, const voi
   a.Y = Y;
   a.M = M;
   a.K = K;
-  a.tilesM = (M + BM - 1) / BM;
   if (mode == SX_GEMM_SWIGLU) {
     if (n1 != n0 || n2 != 0 || !W1) return SX_ERR_SHAPE;
     a.N = n0;
@@ -685,18 +717,16 @@ int sx_launch_gemm_bf16(const void* X, const void* W0, const void* W1, const voi
     a.N = n0 + n1 + n2;
     a.tilesN = (a.N + BN - 1) / BN;
   }
-  a.chunk = (a.tilesM * a.tilesN + 7) / 8;
-  plan_split(a, split_ws, split_ws_bytes);
   switch (mode) {
-    case SX_GEMM_STORE: return launch<SX_GEMM_STORE>(a, st);
-    case SX_GEMM_RESIDUAL: return launch<SX_GEMM_RESIDUAL>(a, st);
-    case SX_GEMM_SWIGLU: return launch<SX_GEMM_SWIGLU>(a, st);
+    case SX_GEMM_STORE: return launch<SX_GEMM_STORE>(a, split_ws, split_ws_bytes, st);
+    case SX_GEMM_RESIDUAL: return launch<SX_GEMM_RESIDUAL>(a, split_ws, split_ws_bytes, st);
+    case SX_GEMM_SWIGLU: return launch<SX_GEMM_SWIGLU>(a, split_ws, split_ws_bytes, st);
   }
   return SX_ERR_SHAPE;
 }
 
 // 1 KB of counters (at most 256 split tiles, zero before the first launch) and one partial tile per compute unit
-size_t sx_gemm_split_workspace() { return 1024 + (size_t)sx_compute_units() * BM * BN * sizeof(float); }
+size_t sx_gemm_split_workspace() { return 1024 + (size_t)sx_compute_units() * kMaxRows * BN * sizeof(float); }
 
 int sx_launch_gemm_qkv_rope_bf16(const void* X, const void* Wq, const void* Wk, const void* Wv, int hq, int hkv,
                                  const float2* rope_cs, void* q, void* k, void* v, int M, int K, void* split_ws,
@@ -716,17 +746,14 @@ int sx_launch_gemm_qkv_rope_bf16(const void* X, const void* Wq, const void* Wk, 
   a.M = M;
   a.K = K;
   a.N = a.n0 + a.n1 + a.n2;
-  a.tilesM = (M + BM - 1) / BM;
   a.tilesN = (a.N + BN - 1) / BN;
-  a.chunk = (a.tilesM * a.tilesN + 7) / 8;
   a.cs = rope_cs;
   a.q = static_cast<unsigned short*>(q);
   a.k = static_cast<unsigned short*>(k);
   a.v = static_cast<unsigned short*>(v);
   a.hq = hq;
   a.hkv = hkv;
-  plan_split(a, split_ws, split_ws_bytes);
-  return launch<SX_GEMM_QKV_ROPE>(a, st);
+  return launch<SX_GEMM_QKV_ROPE>(a, split_ws, split_ws_bytes, st);
 }
 
 extern "C" size_t sx_gemm_bf16_workspace(void) { return sx_gemm_split_workspace(); }

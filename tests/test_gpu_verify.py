@@ -466,6 +466,32 @@ def test_gemm_bf16_few_tiles_cut_along_k(sx, M, N, K, mode):
     assert d.max() <= (1.01 * bf16_ulp(got).max() if mode == 2 else 1e-5 * np.sqrt(K) * np.abs(ref).max() + 1e-6)
 
 
+# Rows for which the wide kernel takes its lower tiles: one tile of 160 rows (129, 160), 192 (161, 192) or 224 (193,
+# 224), two of 160 (257, 320), and more tiles than compute units, the remainder cut along K (170 x 65800).
+@pytest.mark.parametrize("M,N,K", [(129, 272, 640), (160, 520, 192), (161, 72, 1088), (192, 512, 64), (193, 250, 320),
+                                   (224, 264, 2048), (257, 128, 704), (320, 512, 576), (170, 65800, 1024)])
+def test_gemm_bf16_tile_heights(sx, M, N, K):
+    X = wl.hash_normal(51, (M, K), dtype=torch.bfloat16).to(dev())
+    W = wl.hash_normal(52, (N, K), std=0.05, dtype=torch.bfloat16).to(dev())
+    W2 = wl.hash_normal(53, (N, K), std=0.05, dtype=torch.bfloat16).to(dev())
+    g, u = X.double() @ W.double().T, X.double() @ W2.double().T
+    ws = torch.zeros(sx.lib.sx_gemm_bf16_workspace(), dtype=torch.uint8, device=dev())
+    tol = 1e-5 * np.sqrt(K) * float(g.abs().max()) + 1e-6
+    for work in (None, ws):
+        # rows behind the last one stay untouched
+        Y = torch.full((M + 40, N), 7.0, dtype=torch.float32, device=dev())
+        sx.gemm_bf16(X, W, Y[:M], mode=0, workspace=work)
+        sx.gemm_bf16(X, W, Y[:M], mode=1, workspace=work)
+        assert float((Y[:M].double() - 2 * g).abs().max()) <= 2 * tol
+        assert bool((Y[M:] == 7.0).all())
+        H = torch.zeros((M, N), dtype=torch.bfloat16, device=dev())
+        sx.gemm_bf16(X, W, H, mode=2, W2=W2, workspace=work)
+        want = (g / (1 + torch.exp(-g)) * u).cpu().numpy()
+        assert np.all(np.abs(H.double().cpu().numpy() - want) <= 0.51 * bf16_ulp(want) + 1e-5 * np.abs(want).max())
+    if K % 128 == 0 and M < 300:  # and the rotary epilogue, whose table is staged by halves of the tile's rows
+        test_qkv_projection_with_rotary_epilogue(sx, M, K, 2, 1)
+
+
 # the last three shapes give more output tiles than the chip has compute units with a small remainder: the
 # remainder tiles are cut along K and their partial sums added up by the last workgroup to arrive
 # (256, 2048, 16, 4) and (512, 1024, 8, 8): fewer tiles than half the compute units, all of them cut along K;
