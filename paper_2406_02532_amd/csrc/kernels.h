@@ -87,18 +87,13 @@ int sx_launch_tree_attn_bf16(const void* q, const void* k_tree, const void* v_tr
 // memory for the partial results when few query rows make the launch share the key tiles among workgroups
 // (used only for Tq <= Tq_max; split_ws may be null: no sharing)
 size_t sx_tree_attn_split_workspace(int Tq_max, int Hq);
-// Query nodes per attention workgroup: 128 rows / G, fewer (down to one wave's 32 rows) when there are so few
-// query nodes that the grid would leave most of the chip idle -- the draft model's small batches.  The
-// workspace is sized for the smallest value.
-static inline int sx_attn_min_nodes_per_tile(int Hq, int Hkv) {
-  const int G = Hq / Hkv;
-  return G >= 32 ? 1 : 32 / G;
-}
+// Query nodes per attention workgroup: 128 rows / G, half of that when there are so few query nodes that the grid would
+// leave most of the chip idle (the draft model's small batches); its four waves then share the keys as well as the rows.
+// The workspace is sized for the smaller value.
+static inline int sx_attn_min_nodes_per_tile(int Hq, int Hkv) { return 64 / (Hq / Hkv); }
 static inline int sx_attn_nodes_per_tile(int Hq, int Hkv, int Tq) {
-  int npt = 128 / (Hq / Hkv);
-  const int lo = sx_attn_min_nodes_per_tile(Hq, Hkv);
-  while (npt > lo && ((Tq + npt - 1) / npt) * Hkv < 256) npt /= 2;
-  return npt;
+  const int npt = 128 / (Hq / Hkv);
+  return ((Tq + npt - 1) / npt) * Hkv < 256 ? npt / 2 : npt;
 }
 
 // ---- the forward itself (verify_tree.hip) -----------------------------------------------------------------

@@ -565,6 +565,16 @@ def test_tree_attention_bf16_best_first(sx, T, P, Hq, Hkv):
     _attn_case(sx, T, P, Hq, Hkv, (tok, par), seed=10 * T)
 
 
+# Both forms of the kernel at their edges: 64-row workgroups whose waves share the keys (one node; a tree whose upper key
+# half is empty; 64, 65 and 33 keys; 8 query heads per KV head with a last workgroup of one node) and, from a workgroup
+# per compute unit on, 128-row ones (96 and 128 heads).
+@pytest.mark.parametrize("T,P,Hq,Hkv", [(1, 0, 4, 4), (20, 0, 8, 8), (63, 1, 8, 8), (65, 33, 2, 1), (17, 500, 16, 2),
+                                        (9, 64, 8, 1), (257, 130, 96, 96), (129, 65, 128, 128)])
+def test_tree_attention_bf16_row_splits(sx, T, P, Hq, Hkv):
+    tok, par, _ = wl.gen_best_first_tree(T, 4, 1000, seed=T, max_depth=20)
+    _attn_case(sx, T, P, Hq, Hkv, (tok, par), seed=10 * T + 1)
+
+
 def test_tree_attention_bf16_chain_and_uniform(sx):
     _attn_case(sx, 300, 70, 8, 1, wl.gen_chain_tree(300, 100, seed=1), seed=7)      # depth 299: many tree tiles
     _attn_case(sx, 300, 70, 2, 2, wl.gen_uniform_tree(300, 100, seed=2), seed=8)
