@@ -9,12 +9,23 @@
 // fp32, rounded once) and feeds the matrix core.  Only X goes through LDS (copied by buffer loads that write
 // LDS), where the 128 rows are shared by the four waves.
 //
-// Tiling: a workgroup owns all M <= 128 rows x 128 columns; wave w the columns 32 w .. + 31 (2 blocks of 16 W
-// rows) x 8 blocks of 16 X rows: 16 MFMAs per k-step against 8 KB of X fragments.  K is walked in slabs of 128
-// (four k-steps).  The contraction index may be permuted as long as both operands agree: in k-step s of a slab a
-// lane of quarter lq takes the 16-byte chunk 4 lq + s of its row, so its four fragments of the slab are one
-// contiguous 16-byte load (64 contiguous bytes per W row and wave).
-// With at most a few dozen column tiles the K range is cut among workgroups (grid.y); partial sums meet in
+// Tiling: a workgroup owns all M <= 128 rows x 128 or 64 columns.  K is walked in slabs of 128 (four k-steps), and its
+// eight waves are four column groups (2 or 1 blocks of 16 W rows each, x 8 blocks of 16 X rows) times the two halves of
+// every slab's k-steps, whose sums meet in LDS at the end: two waves per SIMD without a second copy of X or a second
+// partial tile.  The contraction index may be permuted as long as both operands agree: in k-step s of a slab a
+// lane of quarter lq takes the 16-byte chunk 4 lq + s of its row, so its two fragments of the slab are one
+// contiguous 8-byte load (64 contiguous bytes per W row).
+// What bounds it: not HBM (23 MB in 31 us) but a compute unit's own slab, 1.35 us for 128 columns whether 32 or 172
+// workgroups run: X copied into LDS and read by every wave, the dequantisation, 64 MFMAs per SIMD.  So: X three slabs
+// ahead in four stages (a barrier waits only for its own slab's operations, by count); scales and zero points of up
+// to 48 groups fetched into LDS at a time, side by side, instead of two loads per lane, block and slab that each touch
+// 16 lines; the words of two slabs, which share their lines, fetched together.  Measured at 128 rows, before (4 waves, two
+// stages, loads of scales per slab) -> with eight waves and four stages -> now, 4096 x 4096: 28.4 -> 22.0 -> 19.0 us;
+// 4096 x 11008: 44.4 -> 34.7 -> 31.3; 12288 x 4096: 33.0 -> 42.1 -> 31.3; 22016 x 4096: 52.3 -> 64.4 -> 45.6; 10240 x
+// 8192: 49.8 -> 51.9 -> 40.2; 8192 x 28672: 95 -> 124 -> 89.  (The two k-steps software-pipelined by hand with the
+// MFMAs, reads and dequantisation dealt out evenly, and codes made floats by their exponent bits instead of
+// conversions, were measured: within 2 % either way.)
+// Where column tiles are fewer than compute units the K range is cut among workgroups (grid.y); partial sums meet in
 // memory and the last workgroup to arrive adds them in part order (deterministic, nobody waits).
 //
 // Up to three weight matrices may be stacked along N (the QKV projections, or gate and up) as long as each
@@ -24,8 +35,9 @@
 namespace {
 
 constexpr int BM = 128, BK = 128;   // columns per workgroup: 4 waves x WB blocks of 16 (template parameter)
-constexpr int kThreads = 256;
+constexpr int kThreads = 512;
 constexpr int kXBytes = BM * BK * 2;   // 32 KB: one slab of X
+constexpr int kParGroups = 48;         // groups whose scales and zero points are in LDS at a time
 
 struct W4Mat {
   const uint32_t* q;          // [n][K/8]
@@ -71,35 +83,39 @@ __device__ __forceinline__ bf16x8 dequant8(uint32_t q, float sc, float nzs) {
   return __builtin_bit_cast(bf16x8, o);
 }
 
-constexpr int kWaitVm0 = 0x0070;
-// all LDS reads of this wave done, all its vector-memory operations done, then meet the other waves
-#define SX_WAIT_BARRIER()                  \
+// all LDS reads of this wave done, at most N of its vector-memory operations outstanding, then meet the other waves
+constexpr int wait_vm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
+#define SX_WAIT_BARRIER(IMM)               \
   asm volatile("" ::: "memory");           \
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);    \
+  __builtin_amdgcn_s_waitcnt(IMM);         \
   __builtin_amdgcn_s_barrier();            \
   asm volatile("" ::: "memory");
 
 template <int MODE, int WB>
-__global__ __launch_bounds__(kThreads, 2) void gemm_w4_regs_kernel(W4RegArgs a) {
+__global__ __launch_bounds__(kThreads) void gemm_w4_regs_kernel(W4RegArgs a) {
   constexpr int BN = 64 * WB;             // columns of the workgroup
   constexpr int kPartFloats = BM * BN;    // partial sums of one K part of one tile
   // X slab: row r is 256 bytes at r * 256, its 16-byte chunk c at position c ^ (r & 15): the 16 rows a fragment
-  // read touches for one chunk index fall on 16 different bank groups.  Two stages.
+  // read touches for one chunk index fall on 16 different bank groups.  Four stages.
   __shared__ __attribute__((aligned(1024))) unsigned char sx0[kXBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char sx1[kXBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char sx2[kXBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char sx3[kXBytes];
+  __shared__ unsigned s_par[kParGroups * BN];  // [group][column]: the scale's bits, above the zero point
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, lq = lane >> 4;
+  const int wc = wave & 3, half = wave >> 2;  // columns; k-steps 2 half and 2 half + 1 of every slab
   const int tile_n = blockIdx.x, kpart = blockIdx.y;
 
-  // ---- X copies: instruction t (0..7) of wave w fills rows 32 w + 4 t .. + 3 (1 KB of LDS): lane l supplies row
+  // ---- X copies: instruction t (0..3) of wave w fills rows 16 w + 4 t .. + 3 (1 KB of LDS): lane l supplies row
   // + l / 16, position l % 16, i.e. chunk (l % 16) ^ (row & 15) of that row's 256 bytes of the slab
   const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.X);
-  int xoff[8];
+  int xoff[4];
 #pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int r = 32 * wave + 4 * t + (lane >> 4);
+  for (int t = 0; t < 4; ++t) {
+    const int r = 16 * wave + 4 * t + (lane >> 4);
     const int c = (lane & 15) ^ (r & 15);
     const int m = r < a.M ? r : a.M - 1;
     xoff[t] = (int)(((unsigned)m * (unsigned)a.K + c * 8) * 2u);
@@ -107,12 +123,12 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_w4_regs_kernel(W4RegArgs a) 
 #define SX_COPY(STG_, SLAB_)                                                                                     \
   {                                                                                                              \
     const int so = (SLAB_) * (BK * 2);                                                                           \
-    _Pragma("unroll") for (int t = 0; t < 8; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                      \
-        xres, (lds_void_ptr)(STG_ + wave * 8192 + t * 1024), 16, xoff[t], so, 0, 0);                             \
+    _Pragma("unroll") for (int t = 0; t < 4; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                      \
+        xres, (lds_void_ptr)(STG_ + wave * 4096 + t * 1024), 16, xoff[t], so, 0, 0);                             \
   }
 
   // ---- W: this wave's columns belong to one of the stacked matrices -------------------------------------------
-  const int c0 = tile_n * BN + 16 * WB * wave;  // first column of the wave (uniform)
+  const int c0 = tile_n * BN + 16 * WB * wc;  // first column of the wave (uniform)
   int first = 0, rows = a.n0, which = 0;
   if (c0 >= a.n0 + a.n1) {
     first = a.n0 + a.n1;
@@ -124,39 +140,48 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_w4_regs_kernel(W4RegArgs a) 
     which = 1;
   }
   const bool wave_has_cols = c0 < a.N;
-  const __amdgpu_buffer_rsrc_t qres = make_rsrc(a.m[which].q), sres = make_rsrc(a.m[which].s),
-                               zres = make_rsrc(a.m[which].z);
   const int ngroups = a.K >> a.group_log2;
-  int qoff[WB], goff[WB];
+  int qoff[WB];
 #pragma unroll
   for (int i = 0; i < WB; ++i) {
     int n = c0 - first + 16 * i + l16;          // row of the matrix; columns past the end re-read the last row
     n = n < rows ? n : rows - 1;
     n = n < 0 ? 0 : n;
-    qoff[i] = (int)(((unsigned)n * (unsigned)(a.K / 8) + 4u * lq) * 4u);   // + 64 bytes per slab
-    goff[i] = (int)((unsigned)n * (unsigned)ngroups);
+    qoff[i] = (int)(((unsigned)n * (unsigned)(a.K / 8) + 4u * lq + 2u * half) * 4u);   // + 64 bytes per slab
   }
-  // group of this lane's k range of a slab: k = 128 slab + 32 lq + 8 s + (0..7), the same for all four k-steps s
-  // whenever the group holds at least 32 values (groups are powers of two >= 64)
-  auto group_of = [&](int slab) { return (slab * BK + 32 * lq) >> a.group_log2; };
-
+  const __amdgpu_buffer_rsrc_t qres = make_rsrc(a.m[which].q);
   struct WRaw {
-    u32x4 q[WB];
-    float sc[WB], nzs[WB];
+    u32x2 q[2];
   };
-  auto load_w = [&](int slab) {
-    WRaw w;
-    const int g = group_of(slab);
-#pragma unroll
-    for (int i = 0; i < WB; ++i) {
-      w.q[i] = __builtin_amdgcn_raw_buffer_load_b128(qres, qoff[i], slab * 64, 0);
-      const float sc = bf16_bits_to_f32((unsigned short)__builtin_amdgcn_raw_buffer_load_b16(sres, (goff[i] + g) * 2, 0, 0));
-      const float z = (float)(unsigned char)__builtin_amdgcn_raw_buffer_load_b8(zres, goff[i] + g, 0, 0);
-      w.sc[i] = sc;
-      w.nzs[i] = -z * sc;
-    }
-    return w;
-  };
+  // the words of slabs A_ and B_, which share their 128-byte lines
+#define SX_LOAD_W2(WA_, WB_, A_, B_)                                                                             \
+  _Pragma("unroll") for (int i = 0; i < WB; ++i) {                                                               \
+    WA_.q[i] = __builtin_amdgcn_raw_buffer_load_b64(qres, qoff[i], (A_) * 64, 0);                                \
+    WB_.q[i] = __builtin_amdgcn_raw_buffer_load_b64(qres, qoff[i], (B_) * 64, 0);                                \
+  }
+  // Scales and zero points of the slabs [S0_, S1_) into LDS; par0 becomes the first of their groups.  A thread takes
+  // four (column, group) pairs at a time, the groups of a column side by side in memory.
+#define SX_FILL(S0_, S1_)                                                                                        \
+  {                                                                                                              \
+    par0 = ((S0_) * BK) >> a.group_log2;                                                                         \
+    const int ng = (((S1_) * BK - 1) >> a.group_log2) - par0 + 1, total = ng * BN;                               \
+    for (int b = 0; b < total; b += 4 * kThreads) {                                                              \
+      unsigned ps[4], pz[4];                                                                                     \
+      int at[4];                                                                                                 \
+      _Pragma("unroll") for (int u = 0; u < 4; ++u) {                                                            \
+        const int idx = min(b + u * kThreads + tid, total - 1);                                                  \
+        const int col = idx / ng, g = idx - col * ng;                                                            \
+        int n = min(tile_n * BN + col, a.N - 1);                                                                 \
+        const int wm = n >= a.n0 + a.n1 ? 2 : n >= a.n0 ? 1 : 0;                                                 \
+        n -= wm == 2 ? a.n0 + a.n1 : wm == 1 ? a.n0 : 0;                                                         \
+        const size_t e = (size_t)n * ngroups + par0 + g;                                                         \
+        ps[u] = (wm == 2 ? a.m[2].s : wm == 1 ? a.m[1].s : a.m[0].s)[e];                                         \
+        pz[u] = (wm == 2 ? a.m[2].z : wm == 1 ? a.m[1].z : a.m[0].z)[e];                                         \
+        at[u] = g * BN + col;                                                                                    \
+      }                                                                                                          \
+      _Pragma("unroll") for (int u = 0; u < 4; ++u) s_par[at[u]] = ps[u] << 16 | pz[u];                          \
+    }                                                                                                            \
+  }
 
   // acc[i][j]: W rows (output columns) c0 + 16 i .. + 15, X rows (output rows) 16 j .. + 15
   f32x4 acc[WB][8];
@@ -169,52 +194,113 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_w4_regs_kernel(W4RegArgs a) 
 
   // X fragment of block j in k-step s: row 16 j + l16, chunk 4 lq + s, at position chunk ^ (row & 15) = chunk ^ l16
   const int xrow = l16 * (BK * 2);
-#define SX_SLAB(XS_, W_)                                                                                         \
-  _Pragma("unroll") for (int s = 0; s < 4; ++s) {                                                                \
-    bf16x8 fw[WB], fx[8];                                                                                        \
-    _Pragma("unroll") for (int i = 0; i < WB; ++i) fw[i] = dequant8(W_.q[i][s], W_.sc[i], W_.nzs[i]);            \
-    const int xc = xrow + (((4 * lq + s) ^ l16) << 4);                                                           \
-    _Pragma("unroll") for (int j = 0; j < 8; ++j)                                                                \
-        fx[j] = *reinterpret_cast<const bf16x8*>(XS_ + j * (16 * BK * 2) + xc);                                  \
-    _Pragma("unroll") for (int i = 0; i < WB; ++i) _Pragma("unroll") for (int j = 0; j < 8; ++j)                 \
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);                   \
+#define SX_SLAB(XS_, W_, T_)                                                                                     \
+  {                                                                                                              \
+    /* group of this lane's k range, k = 128 slab + 32 lq + (0..31) (groups are powers of two >= 64) */          \
+    const int g = (((first_slab + (T_)) * BK + 32 * lq) >> a.group_log2) - par0;                                 \
+    float sc[WB], nzs[WB];                                                                                       \
+    _Pragma("unroll") for (int i = 0; i < WB; ++i) {                                                             \
+      const unsigned pr = s_par[g * BN + 16 * WB * wc + 16 * i + l16];                                           \
+      sc[i] = __uint_as_float(pr & 0xFFFF0000u);                                                                 \
+      nzs[i] = -(float)(pr & 0xFFu) * sc[i];                                                                     \
+    }                                                                                                            \
+    _Pragma("unroll") for (int s = 0; s < 2; ++s) {                                                              \
+      bf16x8 fw[WB], fx[8];                                                                                      \
+      const int xc = xrow + (((4 * lq + 2 * half + s) ^ l16) << 4);                                              \
+      _Pragma("unroll") for (int j = 0; j < 8; ++j)                                                              \
+          fx[j] = *reinterpret_cast<const bf16x8*>(XS_ + j * (16 * BK * 2) + xc);                                \
+      _Pragma("unroll") for (int i = 0; i < WB; ++i) fw[i] = dequant8(W_.q[i][s], sc[i], nzs[i]);                \
+      _Pragma("unroll") for (int i = 0; i < WB; ++i) _Pragma("unroll") for (int j = 0; j < 8; ++j)               \
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);                 \
+    }                                                                                                            \
   }
 
-  // Slabs [first_slab, first_slab + NB) of K; slab t sits in stage t % 2.  Per slab: wait for its X copies and W
-  // words and for everybody to be done with the other stage, start the copies of the next slab into that stage and
-  // the W loads of the next slab into registers, then multiply.  (Fetching two slabs ahead was measured in two forms
-  // -- a hand-counted wait that leaves the youngest loads in flight, which the compiler's own reordering of loads and
-  // copies defeats, and X through registers so that the compiler counts everything itself -- and gained nothing:
-  // the loop is not waiting for memory.)
+  // Slabs [first_slab, first_slab + NB) of K; slab t sits in stage t % 4 and its W words in register set t % 4.  Per
+  // slab: wait for its own copies and words (the two younger slabs' copies and the younger pair of words stay in
+  // flight) and for everybody to be done with the slab before it, start the copies of slab t + 3 into that stage,
+  // multiply; after every second slab fetch the words of slabs t + 3 and t + 4 together.  Past the end of K the last
+  // slab is fetched again.
+  constexpr int kFly = 8 + 2 * WB;  // two slabs' copies, one pair's words
+#define SX_SLAB_AT(i) (first_slab + min((i), NB - 1))
+#define SX_STEP(XS_, W_, XN_, T_)                                                                                \
+  SX_WAIT_BARRIER(wait_vm(kFly))                                                                                 \
+  SX_COPY(XN_, SX_SLAB_AT((T_) + 3))                                                                             \
+  asm volatile("" ::: "memory");                                                                                 \
+  SX_SLAB(XS_, W_, T_)
+#define SX_PAIR(WA_, WB_, T_)                                                                                    \
+  asm volatile("" ::: "memory");                                                                                 \
+  SX_LOAD_W2(WA_, WB_, SX_SLAB_AT(T_), SX_SLAB_AT((T_) + 1))                                                     \
+  asm volatile("" ::: "memory");
   const int nb_all = a.K / BK;
   const int first_slab = kpart * nb_all / a.split;
   const int NB = (kpart + 1) * nb_all / a.split - first_slab;
+  const int par_slabs = a.group_log2 > 6 ? kParGroups : kParGroups / 2;  // slabs whose groups fit s_par
+  int par0;
+  WRaw w0, w1, w2, w3;
   SX_COPY(sx0, first_slab)
-  WRaw w0 = load_w(first_slab);
-  for (int t = 0; t < NB; t += 2) {
-    {
-      SX_WAIT_BARRIER()
-      WRaw w1 = w0;
-      if (t + 1 < NB) {
-        SX_COPY(sx1, first_slab + t + 1)
-        w1 = load_w(first_slab + t + 1);
-      }
-      SX_SLAB(sx0, w0)
-      w0 = w1;
+  SX_PAIR(w0, w1, 0)
+  SX_COPY(sx1, SX_SLAB_AT(1))
+  SX_COPY(sx2, SX_SLAB_AT(2))
+  SX_PAIR(w2, w3, 2)
+  SX_FILL(first_slab, first_slab + min(NB, par_slabs))
+  int t = 0, refill = par_slabs;
+  for (; t + 4 <= NB; t += 4) {
+    if (t == refill) {  // everybody is done with the last groups' parameters; the next barrier shows the new ones
+      __syncthreads();
+      SX_FILL(first_slab + t, first_slab + min(NB, t + par_slabs))
+      refill += par_slabs;
     }
+    SX_STEP(sx0, w0, sx3, t)
+    SX_STEP(sx1, w1, sx0, t + 1)
+    SX_PAIR(w0, w1, t + 4)
+    SX_STEP(sx2, w2, sx1, t + 2)
+    SX_STEP(sx3, w3, sx2, t + 3)
+    SX_PAIR(w2, w3, t + 6)
+  }
+  // Up to three slabs are left, all on their way.  (They start no others: words nobody uses would be dropped by the
+  // compiler, and the counts of operations in flight would not hold.)
+  if (t < NB) {
+    if (t == refill) {
+      __syncthreads();
+      SX_FILL(first_slab + t, first_slab + NB)
+    }
+    SX_WAIT_BARRIER(wait_vm(kFly))
+    SX_SLAB(sx0, w0, t)
     if (t + 1 < NB) {
-      SX_WAIT_BARRIER()
-      WRaw w1 = w0;
-      if (t + 2 < NB) {
-        SX_COPY(sx0, first_slab + t + 2)
-        w1 = load_w(first_slab + t + 2);
-      }
-      SX_SLAB(sx1, w0)
-      w0 = w1;
+      SX_WAIT_BARRIER(wait_vm(4 + 2 * WB))
+      SX_SLAB(sx1, w1, t + 1)
+    }
+    if (t + 2 < NB) {
+      SX_WAIT_BARRIER(wait_vm(0))
+      SX_SLAB(sx2, w2, t + 2)
     }
   }
+  SX_WAIT_BARRIER(wait_vm(0))  // every copy is in and every stage is read: the LDS is free
+#undef SX_STEP
+#undef SX_PAIR
+#undef SX_SLAB_AT
 #undef SX_SLAB
+#undef SX_FILL
+#undef SX_LOAD_W2
 #undef SX_COPY
+
+  // ---- the two halves of the k-steps: the upper half's waves leave their sums in LDS, the lower half's add them ----
+  {
+    unsigned char* ob = (WB == 2 && (wc & 2) ? sx1 : sx0) + (WB == 2 ? wc & 1 : wc) * (8192 * WB) + lane * 16;
+    if (half == 1) {
+#pragma unroll
+      for (int i = 0; i < WB; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) *reinterpret_cast<f32x4*>(ob + (i * 8 + j) * 1024) = acc[i][j];
+    }
+    __syncthreads();
+    if (half == 0) {
+#pragma unroll
+      for (int i = 0; i < WB; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] += *reinterpret_cast<const f32x4*>(ob + (i * 8 + j) * 1024);
+    }
+  }
 
   // ---- K split: partial sums meet in memory, the last workgroup to arrive adds them in part order -------------
   // (device-scope stores and loads, stores complete before the counter's device-scope atomic is issued)
@@ -223,15 +309,17 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_w4_regs_kernel(W4RegArgs a) 
     __shared__ int s_last;
     const __amdgpu_buffer_rsrc_t pres = make_rsrc(a.part);
     const unsigned mine =
-        (unsigned)((tile_n * a.split + kpart) * kPartFloats + wave * (8 * WB * 256) + lane * 4) * 4u;  // bytes
+        (unsigned)((tile_n * a.split + kpart) * kPartFloats + wc * (8 * WB * 256) + lane * 4) * 4u;  // bytes
+    if (half == 0) {
 #pragma unroll
-    for (int i = 0; i < WB; ++i)
+      for (int i = 0; i < WB; ++i)
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), pres, mine + (i * 8 + j) * 1024, 0,
-                                               kScopeDevice);
+        for (int j = 0; j < 8; ++j)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), pres, mine + (i * 8 + j) * 1024, 0,
+                                                 kScopeDevice);
+    }
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
     __syncthreads();
     if (tid == 0) {
       const int before = atomicAdd(a.part_cnt + tile_n, 1);
@@ -239,31 +327,33 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_w4_regs_kernel(W4RegArgs a) 
       if (s_last) a.part_cnt[tile_n] = 0;  // ready for the next launch
     }
     __syncthreads();
-    if (!s_last) return;
-    // batches of 16 blocks per part, all loads of a batch in flight together (one memory round trip per batch
-    // and part, not one per block); parts are added in part order
-    const unsigned all = (unsigned)(tile_n * a.split * kPartFloats + wave * (8 * WB * 256) + lane * 4) * 4u;
+    if (!s_last || half == 1) return;
+    // batches of 8 blocks per part, all loads of a batch in flight together (one memory round trip per batch
+    // and part, not one per block); parts are added in part order, this workgroup's own out of its registers
+    const unsigned all = (unsigned)(tile_n * a.split * kPartFloats + wc * (8 * WB * 256) + lane * 4) * 4u;
 #pragma unroll
-    for (int b0 = 0; b0 < 8 * WB; b0 += 16) {
-      f32x4 sum[16];
+    for (int i = 0; i < WB; ++i) {
+      f32x4 sum[8];
+      for (int p = 0; p < a.split; ++p) {
+        f32x4 part[8];
+        if (p == kpart) {
 #pragma unroll
-      for (int b = 0; b < 16; ++b)
-        sum[b] = __builtin_bit_cast(
-            f32x4, __builtin_amdgcn_raw_buffer_load_b128(pres, all + (b0 + b) * 1024, 0, kScopeDevice));
-      for (int p = 1; p < a.split; ++p) {
-        f32x4 t[16];
+          for (int j = 0; j < 8; ++j) part[j] = acc[i][j];
+        } else {
 #pragma unroll
-        for (int b = 0; b < 16; ++b)
-          t[b] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                               pres, all + (unsigned)p * (kPartFloats * 4u) + (b0 + b) * 1024, 0,
-                                               kScopeDevice));
+          for (int j = 0; j < 8; ++j)
+            part[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                    pres, all + (unsigned)p * (kPartFloats * 4u) + (i * 8 + j) * 1024, 0,
+                                                    kScopeDevice));
+        }
 #pragma unroll
-        for (int b = 0; b < 16; ++b) sum[b] += t[b];
+        for (int j = 0; j < 8; ++j) sum[j] = p == 0 ? part[j] : sum[j] + part[j];
       }
 #pragma unroll
-      for (int b = 0; b < 16; ++b) acc[(b0 + b) >> 3][(b0 + b) & 7] = sum[b];
+      for (int j = 0; j < 8; ++j) acc[i][j] = sum[j];
     }
   }
+  if (half == 1) return;
 
   // ---- epilogue.  acc[i][j][e]: output row 16 j + l16, column c0 + 16 i + 4 lq + e --------------------------------
   if (!wave_has_cols) return;
@@ -329,31 +419,38 @@ int sx_launch_gemm_w4_regs(const void* X, const sx_w4_matrix* mats, const int* n
   a.M = M;
   a.N = N;
   a.K = K;
-  // Columns per workgroup: 128 (two blocks of 16 per wave).  256 was measured too (32 MFMAs per k-step against the
-  // same 8 KB of X fragments): slower at every 7B and 70B layer shape but one, where it ties -- half the tiles,
-  // K cut into twice the parts, twice the partial sums per part.
-  constexpr int WB = 2;
-  const int BN = 64 * WB;
-  const int tilesN = (N + BN - 1) / BN;
-  a.split = 1;
+  // Columns per workgroup and K cut, by expected slab times of the 128-column form (1.35 us): a 64-column slab costs
+  // 0.63, and every part's partial tile, written and read back by the last arriver, 1.25 per 64 columns.  One workgroup
+  // fits a compute unit; parts of at least 4 slabs.  (4096 x 4096: 64 columns cut 4 ways 19.0 us, uncut 29.7, 128
+  // columns cut 4 ways 24.8; 8192 x 28672: 128 columns cut 4 ways 89, 64 cut 2 ways 102.)
+  const int cus = sx_compute_units(), nb = K / BK;
   a.part = nullptr;
   a.part_cnt = nullptr;
-  // two workgroups fit a compute unit; cut K until the launch has about that many, parts of at least 4 slabs
-  const int min_slabs = 4;
-  const int slots = 2 * sx_compute_units(), nb = K / BK;
-  if (split_ws && tilesN <= 256) {
-    int split = slots / tilesN;
-    if (split > 16) split = 16;
-    while (split > 1 && nb / split < min_slabs) --split;
-    if (split > 1 && split_ws_bytes >= 1024 + (size_t)tilesN * split * BM * BN * sizeof(float)) {
-      a.split = split;
-      a.part_cnt = static_cast<int*>(split_ws);
-      a.part = reinterpret_cast<float*>(static_cast<char*>(split_ws) + 1024);
+  int wb = 2;
+  float best = 1e30f;
+  for (int w = 1; w <= 2; ++w) {
+    const int tiles = (N + 64 * w - 1) / (64 * w);
+    for (int sp = 1; sp <= 16; ++sp) {
+      if (sp > 1 && (!split_ws || tiles > 256 || tiles * sp > cus || nb / sp < 4 ||
+                     split_ws_bytes < 1024 + (size_t)tiles * sp * BM * 64 * w * sizeof(float)))
+        break;
+      const float cost = (float)((tiles * sp + cus - 1) / cus) * ((nb + sp - 1) / sp) * (w == 1 ? 0.63f : 1.f) +
+                         (sp > 1 ? 1.25f * w * sp : 0.f);
+      if (cost < best) best = cost, wb = w, a.split = sp;
     }
   }
-  const dim3 grid(tilesN, a.split);
-  if (mode == SX_GEMM_STORE) gemm_w4_regs_kernel<SX_GEMM_STORE, WB><<<grid, kThreads, 0, st>>>(a);
-  else gemm_w4_regs_kernel<SX_GEMM_RESIDUAL, WB><<<grid, kThreads, 0, st>>>(a);
+  const dim3 grid((N + 64 * wb - 1) / (64 * wb), a.split);
+  if (a.split > 1) {
+    a.part_cnt = static_cast<int*>(split_ws);
+    a.part = reinterpret_cast<float*>(static_cast<char*>(split_ws) + 1024);
+  }
+  if (mode == SX_GEMM_STORE) {
+    if (wb == 1) gemm_w4_regs_kernel<SX_GEMM_STORE, 1><<<grid, kThreads, 0, st>>>(a);
+    else gemm_w4_regs_kernel<SX_GEMM_STORE, 2><<<grid, kThreads, 0, st>>>(a);
+  } else {
+    if (wb == 1) gemm_w4_regs_kernel<SX_GEMM_RESIDUAL, 1><<<grid, kThreads, 0, st>>>(a);
+    else gemm_w4_regs_kernel<SX_GEMM_RESIDUAL, 2><<<grid, kThreads, 0, st>>>(a);
+  }
   SX_LAUNCH_CHECK();
   return SX_OK;
 }

@@ -410,6 +410,18 @@ def test_gemm_w4a16(sx, M, N, K, group, split):
     assert np.abs(Y.cpu().double().numpy() - 2 * ref).max() <= 2 * tol
 
 
+# The register form's slab pipeline and its parameters in LDS: 1, 2, 3, 4 and 5 slabs of K; more groups than LDS holds at a
+# time (55 slabs of 64-value groups, 112 of 128-value ones, refilled after 24 and 48), groups of several slabs whose
+# parts begin inside one, a K cut (3072 x 4096: 64-column tiles, 12416 x 2048: 128-column ones), columns past the end.
+@pytest.mark.parametrize("M,N,K,group,split", [(128, 64, 128, 128, False), (5, 130, 256, 64, False), (100, 72, 384, 128, True),
+                                               (128, 40, 512, 512, True), (17, 136, 640, 64, True),
+                                               (33, 200, 7040, 64, False), (64, 130, 14336, 128, False),
+                                               (100, 90, 8192, 1024, True), (77, 3072, 4096, 512, True),
+                                               (128, 12416, 2048, 128, True)])
+def test_gemm_w4a16_slabs_and_groups(sx, M, N, K, group, split):
+    test_gemm_w4a16(sx, M, N, K, group, split)
+
+
 @pytest.mark.parametrize("M,F,K", [(256, 128, 64), (300, 200, 256), (100, 11008, 128), (128, 96, 4096), (7, 40, 64),
                                    (77, 9000, 128)])
 def test_gemm_bf16_swiglu(sx, M, F, K):
