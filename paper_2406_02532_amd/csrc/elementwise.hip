@@ -29,6 +29,35 @@ __global__ void embed_kernel(const W* __restrict__ embed, const int* __restrict_
   for (int c = threadIdx.x; c < d; c += blockDim.x) h[dst + c] = ld<W>(embed, src + c);
 }
 
+// Same, eight columns per lane: d a multiple of 8 and 16-byte aligned rows.  A row was sixteen dependent trips through a
+// lane before (128 rows of 4096: 9.9 -> 5.0 us, of which an empty launch is 4.6; 2048 rows of 8192: 33.8 -> 21.5).
+template <typename W>
+__global__ __launch_bounds__(256) void embed_vec_kernel(const W* __restrict__ embed, const int* __restrict__ tok, int d,
+                                                        size_t chunks, float* __restrict__ h) {
+  const size_t c = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (c >= chunks) return;
+  const unsigned per = (unsigned)d >> 3;
+  const size_t row = c / per, col = (c % per) * 8;
+  const W* src = embed + (size_t)tok[row] * d + col;
+  f32x4 lo, hi;
+  if constexpr (sizeof(W) == 4) {
+    lo = reinterpret_cast<const f32x4*>(src)[0];
+    hi = reinterpret_cast<const f32x4*>(src)[1];
+  } else {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(src);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      lo[2 * e] = __uint_as_float(v[e] << 16);
+      lo[2 * e + 1] = __uint_as_float(v[e] & 0xFFFF0000u);
+      hi[2 * e] = __uint_as_float(v[e + 2] << 16);
+      hi[2 * e + 1] = __uint_as_float(v[e + 2] & 0xFFFF0000u);
+    }
+  }
+  f32x4* dst = reinterpret_cast<f32x4*>(h + c * 8);
+  dst[0] = lo;
+  dst[1] = hi;
+}
+
 // One workgroup (256 lanes) per row: x = h * rsqrt(mean(h^2) + eps) * g.
 template <typename W>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ h, const W* __restrict__ g, int d,
@@ -148,7 +177,13 @@ __global__ void zero_i32_kernel(int32_t* p, int n) {
 }  // namespace
 
 int sx_launch_embed(const void* embed, int dtype, const int32_t* tok_s, int T, int d, float* h, hipStream_t s) {
-  if (dtype == SX_F32)
+  // eight columns per lane where every row starts on 16 bytes: all models but those of odd width or an offset table
+  if (d % 8 == 0 && ((reinterpret_cast<uintptr_t>(embed) | reinterpret_cast<uintptr_t>(h)) & 15) == 0) {
+    const size_t chunks = (size_t)T * (d / 8);
+    const unsigned blocks = (unsigned)((chunks + 255) / 256);
+    if (dtype == SX_F32) embed_vec_kernel<float><<<blocks, 256, 0, s>>>((const float*)embed, tok_s, d, chunks, h);
+    else embed_vec_kernel<unsigned short><<<blocks, 256, 0, s>>>((const unsigned short*)embed, tok_s, d, chunks, h);
+  } else if (dtype == SX_F32)
     embed_kernel<float><<<T, 256, 0, s>>>((const float*)embed, tok_s, d, h);
   else
     embed_kernel<unsigned short><<<T, 256, 0, s>>>((const unsigned short*)embed, tok_s, d, h);
