@@ -176,7 +176,8 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_f32_kernel(
 #pragma unroll
     for (int e = 0; e < W; ++e) qv[i][e] = c + e < Dh ? qp[c + e] : 0.f;
   }
-  // this lane's elements of a row (of zero weight past Dh: q, or the output element, is not there)
+  // this lane's elements of a row; past Dh it re-reads the row's last ones, which nobody may multiply by a zero: an
+  // infinity there is another lane's
   auto row = [&](const float* prefix, const float* tree, int j, vec (&r)[NI]) {
     const float* p = j < P ? prefix + ((size_t)j * Hkv + kv) * Dh : tree + ((size_t)anc[j - P] * Hkv + kv) * Dh;
 #pragma unroll
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_f32_kernel(
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int e = 0; e < W; ++e) s += qv[i][e] * r[u][i][e];
+        for (int e = 0; e < W; ++e) s += (i * 16 + l16) * W < Dh ? qv[i][e] * r[u][i][e] : 0.f;
 #pragma unroll
       for (int o = 1; o < 16; o <<= 1) s += __shfl_xor(s, o, 64);
       s *= scale;
@@ -229,11 +230,11 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_f32_kernel(
     for (int u = 0; u < U; ++u) {
       const int j = min(j0 + u * NG, nk - 1);
       row(v_prefix, v_tree, j, r[u]);
-      p[u] = j0 + u * NG < nk ? sc[j] : 0.f;
+      p[u] = sc[j];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (p[u] != 0.f) {  // (a weight of zero must not meet an infinity)
+      if (j0 + u * NG < nk) {  // (past the end the last key is read again)
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll

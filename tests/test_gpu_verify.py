@@ -84,6 +84,34 @@ def test_fp32_odd_shapes(sx, d, Hq, Hkv, Dh, F, V, P, T):
     assert np.abs(tv.cpu().double().numpy() - ref["tree_v"]).max() <= 1e-5
 
 
+@pytest.mark.parametrize("Dh", [10, 64, 66, 128, 192, 256])
+def test_fp32_attention_with_infinite_keys_and_values(sx, Dh):
+    """An infinite element of a key, the row's last one among them, takes the key's score to +-inf: the key drops out at
+    -inf, as one whose score is very low does, and nothing is left at +inf.  An infinite value is met by every node, also
+    under a weight that rounds to zero: the plain sum over all keys has a NaN there."""
+    P = 37
+    cfg = wl.ModelCfg(1, 64, 1, 1, Dh, 52, 70, dtype="fp32")
+    w = wl.gen_weights(cfg, seed=Dh)
+    pk, pv = wl.gen_prefix_kv(cfg, P, seed=Dh + 1)
+    tok, par = wl.gen_chain_tree(1, 70, seed=1)
+
+    def logits(key_elem, at, value_elem=None):
+        k, v = pk.clone(), pv.clone()
+        k[0, 20, 0, at] = key_elem
+        if value_elem is not None:
+            v[0, 20, 0, 0] = value_elem
+        return _gpu_verify(sx, cfg, w, k, v, tok, par)[0]
+
+    for at in (0, Dh - 1):
+        got = {sign: logits(sign * np.inf, at) for sign in (1.0, -1.0)}
+        sign = 1.0 if np.isfinite(got[1.0]).all() else -1.0   # the sign with which the one query head pushes the key out
+        low = logits(sign * 1e30, at)
+        np.testing.assert_array_equal(got[sign], low)         # the key has weight 0 either way
+        assert np.isnan(got[-sign]).all()
+        assert np.abs(low - logits(-sign * 1e30, at)).max() > 0
+        assert np.isnan(logits(sign * 1e30, at, np.inf)).all()
+
+
 def test_c1_chain_single_node_and_empty_prefix(sx, c1):
     cfg, w, wn, pk, pv = c1
     tok, par = wl.gen_chain_tree(33, cfg.vocab, seed=4)
