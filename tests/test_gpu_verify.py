@@ -68,6 +68,9 @@ def test_c1_full_parity(sx, c1):
     (64, 2, 2, 66, 52, 515, 130, 17),    # head rows of odd alignment
     (16, 4, 2, 256, 20, 70, 3, 1),       # the largest head, one node
     (68, 2, 1, 128, 100, 3001, 9, 300),  # enough outputs for the 64 x 64 tiles, ragged in both directions
+    # head widths on both sides of what one more load per lane covers, in single elements and in fours
+    (20, 2, 2, 2, 24, 50, 19, 20), (32, 2, 1, 16, 40, 50, 19, 20), (36, 2, 1, 18, 40, 50, 19, 20), (60, 2, 1, 62, 40, 50, 19, 20),
+    (32, 2, 1, 126, 40, 50, 19, 20), (32, 2, 1, 130, 40, 50, 19, 20), (32, 1, 1, 68, 40, 50, 19, 20), (32, 1, 1, 132, 40, 50, 19, 20),
 ])
 def test_fp32_odd_shapes(sx, d, Hq, Hkv, Dh, F, V, P, T):
     cfg = wl.ModelCfg(1, d, Hq, Hkv, Dh, F, V, dtype="fp32")
