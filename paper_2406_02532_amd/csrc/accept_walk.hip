@@ -323,7 +323,10 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         if (hit && slot < kListCap) list[slot] = ((u64)(unsigned)id << 32) | payload;
       };
       const float x_cut = x_below(0.4f * (1.0f - top_p) / (float)V);
-      const float c2 = inv_t * 1.4426950408889634f, mc2 = -M * c2;
+      // e of the small ones: from v - M, which is exact or nearly so (with v c2 - M c2 the rounding of the product, a row's
+      // offset over t times 2^-24, would be an error of every term)
+      const float c2 = inv_t * 1.4426950408889634f;
+      auto small_e = [&](float v) { return __builtin_amdgcn_exp2f((v - M) * c2); };
       // e below 2^-46 counts nothing, as in fix44: with peaked rows that skips most exponentials
       const float x_zero = fminf(x_cut, x_below(1.4210854715202004e-14f));
       float lowf = 0.f;
@@ -333,13 +336,13 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         const float v[4] = {v0, v1, v2, v3};
         if (__builtin_amdgcn_ballot_w64(m4 >= x_cut) == 0) {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) lowf += __builtin_amdgcn_exp2f(fmaf(v[c], c2, mc2));  // exp2(-inf) = 0 past the end
+          for (int c = 0; c < 4; ++c) lowf += small_e(v[c]);  // exp2(-inf) = 0 past the end
           return;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           const bool hit = v[c] >= x_cut;
-          if (!hit) lowf += __builtin_amdgcn_exp2f(fmaf(v[c], c2, mc2));
+          if (!hit) lowf += small_e(v[c]);
           append(hit && id + c < V, id + c, __float_as_uint(v[c]));
         }
       });

@@ -131,6 +131,41 @@ def test_walk_with_any_number_of_candidates(sx, V, top_p, tied):
     assert checked >= 12
 
 
+@pytest.mark.parametrize("M,t,V,above", [(-100.0, 1e-3, 32000, False), (37.0, 2e-4, 32000, True), (100.0, 1e-3, 50001, True)])
+def test_walk_on_rows_with_an_offset(sx, M, t, V, above):
+    """A row far from zero and sharpened by a low temperature, whose many small probabilities (a tenth of the mass, each
+    too small for the nucleus) decide whether the nucleus is one token or two: their sum must come from the differences
+    to the maximum.  (From logits and maximum scaled apart its relative error is |M| / t * 1e-7, ten times the margin.)"""
+    f = np.float32
+    r = np.random.default_rng(0)
+    e = lambda x: np.exp((np.float64(x) - np.float64(f(M))) / np.float64(f(t)))  # noqa: E731
+    grid = [f(M)]
+    while e(grid[-1]) > 2e-5:
+        grid.append(np.nextafter(grid[-1], f(-np.inf)))
+    weights = np.array([e(x) for x in grid])
+    lg = np.full((1, V), f(M - t * 12.8), f)
+    ids = r.permutation(V)
+    lg[0, ids[0]] = M                                    # weight 1; top_p 0.5 asks whether the others weigh more than 1
+    left = 1.0 - e(lg[0, ids[1]]) * (V - 61) + (3e-4 if above else -3e-4)
+    k = 1
+    while k < 61 and left > 2e-5:
+        j = int(np.argmax(weights <= min(left, 0.3 - 0.01 * min(k, 20))))   # no two alike
+        lg[0, ids[k]] = grid[j]
+        left -= weights[j]
+        k += 1
+    tok, par = np.array([3], np.int32), np.array([-1], np.int32)
+    ld, td, pd = to_dev(lg), to_dev(tok), to_dev(par)
+    checked = 0
+    for seed in range(40):
+        ref = oracle.accept_walk(lg, tok, par, t, 0.5, seed=seed, pos0=2)
+        m = ref["margins"][0]
+        assert 2e-5 < m["m_p"] < 2e-4
+        if m["m_u"] > MARGIN:
+            assert _walk(sx, ld, td, pd, t, 0.5, seed, 2)[1] == ref["tokens"], seed
+            checked += 1
+    assert checked >= 30
+
+
 def test_duplicate_siblings_and_single_node(sx):
     tok = np.array([5, 3, 3, 9], np.int32)
     par = np.array([-1, 0, 0, 1], np.int32)
