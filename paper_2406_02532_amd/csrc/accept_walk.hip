@@ -10,15 +10,17 @@
 //      rows a few out of V;
 //   3. at most 64 of them are finished by one wave in registers: the nucleus threshold, the largest bit pattern K with
 //      sum{e >= K} >= top_p * Z, ties, nucleus mass, and the draw, the largest id Y with  sum{nucleus, id < Y} <= u * mass
-//      (inverse CDF in id order).  Longer lists are cut by histograms over the bits of e, lists that do not fit
-//      (flat rows, top_p = 1) by the same histograms over the whole row, re-read from L2.
+//      (inverse CDF in id order).  Longer lists are cut by histograms over the bits of e.  Where the list overflows (flat
+//      rows, top_p = 1) e of every element is computed once and kept -- over the row in LDS, or in the scratch row -- for
+//      the same histograms over the row, and the draw takes a wave's 256 consecutive ids per sum.
 // All sums but that of the small elements are integers: e in units of 2^-44 (at most 2^17 elements of at most 1, so 61
 // bits; what an element loses to truncation is below 2^-44, 7e-9 of Z in all, an order below what fp32 partial sums
 // lose).  Integer sums do not depend on the order in which LDS atomics arrive, so a given input always gives the same path.
 // The form before this one searched threshold and draw bit by bit, 48 block-wide sums per step of about 1 us each (at
-// V > 32768 each a pass over 512 KB in L2).  Three walks of 7 to 14 steps at V = 32000: 564 us each on average, now 62
-// (8 us a step: 2.4 the row, 2.4 the two passes, 1.2 the candidates, 0.9 the child); of 10 to 14 steps at V = 128256
-// with draft probabilities: 6950 us, now 192.
+// V > 32768 each a pass over 512 KB in L2).  Per step, that form -> this one: peaked rows of 32000 60 -> 6.3 us (2.4 the
+// row, 1.2 the candidates, 0.9 the child); rows of 32000 independent N(0, 1) logits at top_p = 0.9 60 -> 42, at top_p = 1
+// 60 -> 24 (with e computed again in each of seven sweeps and every element through LDS atomics: 70 and 79); of 128256:
+// peaked 805 -> 14, N(0, 1) 813 -> 127 and 784 -> 80.
 //
 // With draft probabilities (SI = true) the same kernel runs the comparison system of Sect. 4.1 instead:
 // a drafted child with token x is accepted with probability P_target(x) / P_draft(x), capped at one.  The
@@ -85,16 +87,42 @@ __device__ __forceinline__ u64 lane_u64(u64 v, int j) {
 SX_WAVE_REDUCE(wave_max_u32, max, 0u)
 SX_WAVE_REDUCE(wave_min_u32, min, 0xFFFFFFFFu)
 #undef SX_WAVE_REDUCE
+__device__ __forceinline__ float wave_max_f32(float v) {
+#define SX_STEP(CTRL, ROWS) \
+  v = fmaxf(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp((int)0xFF800000, (int)__float_as_uint(v), CTRL, ROWS, 0xf, false)));
+  SX_STEP(0x111, 0xf)
+  SX_STEP(0x112, 0xf)
+  SX_STEP(0x114, 0xf)
+  SX_STEP(0x118, 0xf)
+  SX_STEP(0x142, 0xa)
+  SX_STEP(0x143, 0xc)
+#undef SX_STEP
+  return __uint_as_float(lane_u32(__float_as_uint(v), 63));
+}
+// sum over the lanes up to and with this one, the same way
+__device__ __forceinline__ u64 wave_scan_u64(u64 v) {
+#define SX_STEP(CTRL, ROWS)                                                                                              \
+  v += ((u64)(unsigned)__builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, ROWS, 0xf, false) << 32) |                   \
+       (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+  SX_STEP(0x111, 0xf)
+  SX_STEP(0x112, 0xf)
+  SX_STEP(0x114, 0xf)
+  SX_STEP(0x118, 0xf)
+  SX_STEP(0x142, 0xa)
+  SX_STEP(0x143, 0xc)
+#undef SX_STEP
+  return v;
+}
 
-// INLDS: the row fits the LDS (V <= 32768) and is copied there by loads that write LDS; otherwise every pass reads it
-// from memory, after the first one from L2.  (Held in registers the row cost more than it saved: 32 unrolled copies of
-// every pass's body outgrew the instruction cache, and the rest of the kernel spilled.)  SI: acceptance by the ratio of
-// target and draft probability.
 template <int N>
 struct Const {
   static constexpr int value = N;
 };
 
+// INLDS: the row fits the LDS (V <= 32768) and is copied there by loads that write LDS; otherwise every pass reads it
+// from memory, after the first one from L2.  (Held in registers the row cost more than it saved: 32 unrolled copies of
+// every pass's body outgrew the instruction cache, and the rest of the kernel spilled.)  SI: acceptance by the ratio of
+// target and draft probability.
 template <int NT, bool INLDS, bool SI>
 __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict__ logits,
                                                          const float* __restrict__ draft_probs,
@@ -283,7 +311,12 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
       s_token = 0;
       s_child = 0x7FFFFFFF;
     }
-    const float M = block_max<NW>(tm, redf);
+    tm = wave_max_f32(tm);
+    if (lane == 0) redf[wave] = tm;
+    __syncthreads();
+    float M = redf[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, redf[w]);
     int token;
     int nl = -1;          // SI: entries of the nucleus list; -1: the distribution is in ebuf
     if (temperature == 0.f) {
@@ -312,23 +345,27 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         const float l = logf(e);
         return M + temperature * (l - 1e-4f * (1.0f - l)) - 1e-6f * fabsf(M);
       };
-      // appends (id, payload) of the lanes that hit; entries past the end of the list are counted only
+      // appends (id, payload) of the lanes that hit; entries past the end of the list are counted only, and a wave that has
+      // found it full stops counting
+      bool full = false;
       auto append = [&](bool hit, int id, unsigned payload) {
         const u64 who = __builtin_amdgcn_ballot_w64(hit);
-        if (who == 0) return;
+        if (who == 0 || full) return;
         const int leader = __builtin_ctzll(who);
         int slot = 0;
         if (lane == leader) slot = atomicAdd(&s_n, __builtin_popcountll(who));
-        slot = __builtin_amdgcn_readlane(slot, leader) + __builtin_popcountll(who & ((1ull << lane) - 1ull));
+        slot = __builtin_amdgcn_readlane(slot, leader);
+        full = slot >= kListCap;
+        slot += __builtin_popcountll(who & ((1ull << lane) - 1ull));
         if (hit && slot < kListCap) list[slot] = ((u64)(unsigned)id << 32) | payload;
       };
-      const float x_cut = x_below(0.4f * (1.0f - top_p) / (float)V);
+      // e below 2^-46 counts nothing, as in fix44: with peaked rows that skips most exponentials
+      const float x_zero = x_below(1.4210854715202004e-14f);
+      const float x_cut = fmaxf(x_zero, x_below(0.4f * (1.0f - top_p) / (float)V));
       // e of the small ones: from v - M, which is exact or nearly so (with v c2 - M c2 the rounding of the product, a row's
       // offset over t times 2^-24, would be an error of every term)
       const float c2 = inv_t * 1.4426950408889634f;
       auto small_e = [&](float v) { return __builtin_amdgcn_exp2f((v - M) * c2); };
-      // e below 2^-46 counts nothing, as in fix44: with peaked rows that skips most exponentials
-      const float x_zero = fminf(x_cut, x_below(1.4210854715202004e-14f));
       float lowf = 0.f;
       sweep([&](float v0, float v1, float v2, float v3, int id) {
         const float m4 = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
@@ -346,8 +383,9 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
           append(hit && id + c < V, id + c, __float_as_uint(v[c]));
         }
       });
-      const u64 low = wave_sum_u64(fix44(__float_as_uint(lowf)));
-      if (lane == 0 && low) atomicAdd(&s_low, low);
+      // (at top_p = 1 the threshold is the sum of the candidates: the rest, below 2^-46 each, is not to raise it)
+      const u64 low = top_p < 1.0f ? wave_scan_u64(fix44(__float_as_uint(lowf))) : 0;
+      if (lane == 63 && low) atomicAdd(&s_low, low);
       __syncthreads();
       const u64 u24 = mix24(seed, pos);
       int nc = s_n;
@@ -359,6 +397,95 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
       auto threshold = [&](u64 Z) -> u64 {
         const u64 t = (u64)ceil((double)top_p * (double)Z);
         return t > Z ? Z : (t < 1 ? 1 : t);
+      };
+      auto in_nucleus = [&](unsigned b, unsigned id) { return b > K || (b == K && id < Ytie); };
+      auto weight_of = [&](unsigned b, int id) { return in_nucleus(b, (unsigned)id) ? fix44(b) : 0; };
+      auto is_tie = [&](unsigned b, int) { return (u64)(b == K ? 1 : 0); };
+      // the flat row's e, four at a time: what a lane wrote in one sweep it reads in the next
+      float* const es = INLDS ? row : ebuf;
+      auto row_bits = [&](float v0, float v1, float v2, float v3) -> u32x4 {
+        const float v[4] = {v0, v1, v2, v3};
+        u32x4 b = {0u, 0u, 0u, 0u};
+        if (__builtin_amdgcn_ballot_w64(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)) >= x_cut) == 0) return b;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          b[c] = v[c] >= x_cut ? e_bits(v[c]) : 0u;
+          if (b[c] > 0x3F800000u) b[c] = 0u;  // a NaN
+        }
+        return b;
+      };
+      auto keep_e = [&](int id, u32x4 b) {
+        if (id < V) *reinterpret_cast<u32x4*>(es + id) = b;  // (either array ends on 16 bytes)
+      };
+      auto sweep_e = [&](auto f) {
+        for (int id = tid * 4; id < V; id += 4 * NT) f(*reinterpret_cast<const u32x4*>(es + id), id);
+      };
+      // as first_beyond, over the row: a wave's 64 quads are 256 consecutive ids, whose sum needs no atomics
+      auto first_beyond_e = [&](auto weight, u64 target) -> int {
+        __syncthreads();
+        clear_hist();
+        sweep_e([&](u32x4 b, int id) {
+          const u64 f = (weight(b[0], id) + weight(b[1], id + 1)) + (weight(b[2], id + 2) + weight(b[3], id + 3));
+          const u64 incl = wave_scan_u64(f);
+          if (lane == 63 || id + 4 >= V) hist[id >> 8] = incl;  // (the last lane that has a quad)
+        });
+        __syncthreads();
+        u64 sum;
+        const u64 start = scan(false, sum);
+        find(false, start, target + 1);
+        if (wave == 0) {
+          const int id = s_bin * 256 + lane * 4;
+          u32x4 b = {0u, 0u, 0u, 0u};
+          if (id < V) b = *reinterpret_cast<const u32x4*>(es + id);
+          u64 f[4], all = 0;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) all += f[c] = weight(b[c], id + c);
+          u64 before = s_above + wave_scan_u64(all) - all;
+          unsigned hit = 0x7FFFFFFFu;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            before += f[c];
+            if (before > target) hit = min(hit, (unsigned)(id + c));
+          }
+          hit = wave_min_u32(hit);
+          if (lane == 0) s_token = hit < (unsigned)V ? (int)hit : min(s_bin * 256, V - 1);
+        }
+        __syncthreads();
+        return s_token;
+      };
+      // K from its top bits (`prefix`, the sum `above` that bin): the lower ones by two more histograms; then the nucleus mass
+      // and how many of the elements equal to K are in it
+      bool ties_left = false;  // not all of them
+      u64 ties_taken = 0;
+      auto refine = [&](auto each, unsigned prefix, u64 above) {
+        for (int shift = 10; shift >= 0; shift -= 10) {
+          __syncthreads();
+          clear_hist();
+          each([&](unsigned b, int) {
+            if (b <= 0x3F800000u && (b >> (shift + 10)) == prefix) {
+              const u64 f = fix44(b);
+              if (f) atomicAdd(&hist[(b >> shift) & (kBins - 1)], f);
+            }
+          });
+          __syncthreads();
+          u64 t2;
+          const u64 st = above + scan(true, t2);
+          find(true, st, thr);
+          prefix = (prefix << 10) | (unsigned)s_bin;
+          above = s_above;
+        }
+        K = prefix;
+        const u64 fk = fix44(K);
+        const u64 tie_sum = hist[K & (kBins - 1)];  // the last histogram's bin holds the elements equal to K alone
+        mass = above;
+        if (fk > 0) {
+          const u64 n_tie = tie_sum / fk;
+          u64 m = thr > above ? (thr - above + fk - 1) / fk : 1;
+          m = m < 1 ? 1 : (m > n_tie ? n_tie : m);
+          mass = above + m * fk;
+          ties_left = m < n_tie;
+          ties_taken = m;
+        }
       };
       // at most 64 candidates in `list` (payload: bits of e), one per lane of one wave; `thr` known (have_thr) or made
       // from their sum and the small elements'
@@ -413,34 +540,46 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
           if (lane == 0) s_token = t < (unsigned)V ? (int)t : 0;
         }
       };
-      bool done = false;
+      bool done = false, in_list = true;  // finished by one wave; the nucleus is among the entries of the list
       if (nc <= 64) {
         if (wave == 0) {
           if (lane < nc) list[lane] = (list[lane] & 0xFFFFFFFF00000000ull) | e_bits(__uint_as_float((unsigned)list[lane]));
           few(nc, false);
         }
         done = true;
+      } else if (overflow && top_p >= 1.0f) {
+        // ---- a flat row of which every element is in the nucleus ---------------------------------------------
+        u64 part = 0;
+        sweep([&](float v0, float v1, float v2, float v3, int id) {
+          const u32x4 b = row_bits(v0, v1, v2, v3);
+          keep_e(id, b);
+          part += (fix44(b[0]) + fix44(b[1])) + (fix44(b[2]) + fix44(b[3]));
+        });
+        part = wave_scan_u64(part);
+        if (lane == 63) atomicAdd(&s_low, part);
+        __syncthreads();
+        mass = s_low;
+        Ytie = 0;
+        in_list = false;
       } else {
         // ---- more: bin of the threshold by a histogram over the top bits of e (8 bins per octave) ---------------
-        auto each_x = [&](auto f) {
-          if (!overflow) {
-            for (int i = tid; i < nc; i += NT) f(__uint_as_float((unsigned)list[i]), (int)(list[i] >> 32));
-          } else {
-            sweep([&](float v0, float v1, float v2, float v3, int id) {
-              if (id < V) f(v0, id);
-              if (id + 1 < V) f(v1, id + 1);
-              if (id + 2 < V) f(v2, id + 2);
-              if (id + 3 < V) f(v3, id + 3);
-            });
-          }
-        };
-        each_x([&](float v, int) {
-          if (v >= x_cut) {
-            const unsigned b = e_bits(v);
+        if (!overflow) {
+          for (int i = tid; i < nc; i += NT) {
+            const unsigned b = e_bits(__uint_as_float((unsigned)list[i]));
             const u64 f = fix44(b);
             if (f) atomicAdd(&hist[min(b >> 20, (unsigned)(kBins - 1))], f);
           }
-        });
+        } else {
+          sweep([&](float v0, float v1, float v2, float v3, int id) {
+            const u32x4 b = row_bits(v0, v1, v2, v3);
+            keep_e(id, b);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const u64 f = fix44(b[c]);
+              if (f) atomicAdd(&hist[b[c] >> 20], f);
+            }
+          });
+        }
         __syncthreads();
         u64 total;
         const u64 start = scan(true, total);
@@ -448,7 +587,8 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         find(true, start, thr);
         const unsigned floor_bits = (unsigned)s_bin << 20;
         u64 above = s_above;
-        // ---- the elements of that bin and above ---------------------------------------------------------------
+        // ---- the elements of that bin and above as a list, if they fit ------------------------------------------
+        full = false;
         if (!overflow) {  // in place: every lane takes its entries before anyone writes
           u64 mine[kListCap / NT];
 #pragma unroll
@@ -465,72 +605,50 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
           __syncthreads();
           if (tid == 0) s_n = 0;
           __syncthreads();
-          const float x_floor = floor_bits ? x_below(__uint_as_float(floor_bits)) : NEG_INF;
-          sweep([&](float v0, float v1, float v2, float v3, int id) {
-            const float v[4] = {v0, v1, v2, v3};
+          sweep_e([&](u32x4 b, int id) {
+            if (__builtin_amdgcn_ballot_w64(max(max(b[0], b[1]), max(b[2], b[3])) >= floor_bits) == 0) return;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              const bool maybe = id + c < V && v[c] >= x_floor;
-              if (__builtin_amdgcn_ballot_w64(maybe) == 0) continue;
-              const unsigned b = e_bits(v[c]);
-              append(maybe && b >= floor_bits && b <= 0x3F800000u, id + c, b);
-            }
+            for (int c = 0; c < 4; ++c) append(b[c] >= floor_bits && id + c < V, id + c, b[c]);
           });
         }
         __syncthreads();
         nc = s_n;
+        in_list = nc <= kListCap;
         if (nc <= 64) {
           if (wave == 0) few(nc, true);
           done = true;
-        } else {
-          // ---- still many: the lower bits of the threshold by two more histograms, the draw by blocks of ids -----
-          auto each = [&](auto f) {
-            if (nc <= kListCap) {
+        } else {  // still many: the lower bits of the threshold by two more histograms, the draw by blocks of ids
+          if (in_list) {
+            auto each = [&](auto f) {
               for (int i = tid; i < nc; i += NT) f((unsigned)list[i], (int)(list[i] >> 32));
-            } else {
-              sweep([&](float v0, float v1, float v2, float v3, int id) {
-                if (id < V) f(e_bits(v0), id);
-                if (id + 1 < V) f(e_bits(v1), id + 1);
-                if (id + 2 < V) f(e_bits(v2), id + 2);
-                if (id + 3 < V) f(e_bits(v3), id + 3);
-              });
-            }
-          };
-          unsigned prefix = floor_bits >> 20;
-          for (int shift = 10; shift >= 0; shift -= 10) {
-            __syncthreads();
-            clear_hist();
-            each([&](unsigned b, int) {
-              if (b <= 0x3F800000u && (b >> (shift + 10)) == prefix) {
-                const u64 f = fix44(b);
-                if (f) atomicAdd(&hist[(b >> shift) & (kBins - 1)], f);
-              }
-            });
-            __syncthreads();
-            u64 t2;
-            const u64 st = above + scan(true, t2);
-            find(true, st, thr);
-            prefix = (prefix << 10) | (unsigned)s_bin;
-            above = s_above;
+            };
+            refine(each, floor_bits >> 20, above);
+            if (ties_left) Ytie = (unsigned)first_beyond(each, is_tie, ties_taken);
+            if constexpr (!SI) token = first_beyond(each, weight_of, scaled(mass, u24));
+          } else {
+            refine([&](auto f) { sweep_e([&](u32x4 b, int id) {
+#pragma unroll
+                                   for (int c = 0; c < 4; ++c) f(b[c], id + c);
+                                 }); },
+                   floor_bits >> 20, above);
+            if (ties_left) Ytie = (unsigned)first_beyond_e(is_tie, ties_taken);
           }
-          K = prefix;
-          const u64 fk = fix44(K);
-          const u64 tie_sum = hist[K & (kBins - 1)];  // the last histogram's bin holds the elements equal to K alone
-          mass = above;
-          if (fk > 0) {
-            const u64 n_tie = tie_sum / fk;
-            u64 m = thr > above ? (thr - above + fk - 1) / fk : 1;
-            m = m < 1 ? 1 : (m > n_tie ? n_tie : m);
-            mass = above + m * fk;
-            if (m < n_tie)
-              Ytie = (unsigned)first_beyond(each, [&](unsigned b, int) { return (u64)(b == K ? 1 : 0); }, m);
-          }
-          if constexpr (!SI)
-            token = first_beyond(each,
-                                 [&](unsigned b, int id) {
-                                   return b <= 0x3F800000u && (b > K || (b == K && (unsigned)id < Ytie)) ? fix44(b) : 0;
-                                 },
-                                 scaled(mass, u24));
+        }
+      }
+      if (!in_list) {
+        if constexpr (!SI) {
+          token = first_beyond_e(weight_of, scaled(mass, u24));
+        } else {  // the nucleus as a list, if it is short enough for one
+          __syncthreads();
+          if (tid == 0) s_n = 0;
+          __syncthreads();
+          full = false;
+          sweep_e([&](u32x4 b, int id) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) append(in_nucleus(b[c], (unsigned)(id + c)), id + c, b[c]);
+          });
+          __syncthreads();
+          nc = s_n;
         }
       }
       if (done) {
@@ -539,7 +657,6 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         else token = s_token;
       }
       if (SI && !done) {  // p = the nucleus, normalised
-        auto member = [&](unsigned b, unsigned id) { return b > K || (b == K && id < Ytie); };
         const float inv_mass = (float)(17592186044416.0 / (double)mass);  // 2^44 / mass
         __syncthreads();
         if (nc <= kListCap) {
@@ -547,7 +664,7 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
           const int np2 = next_pow2(nc < 2 ? 2 : nc);
           int mine = 0;
           for (int i = tid; i < np2; i += NT) {
-            const bool in = i < nc && member((unsigned)list[i], (unsigned)(list[i] >> 32));
+            const bool in = i < nc && in_nucleus((unsigned)list[i], (unsigned)(list[i] >> 32));
             if (!in) list[i] = ~0ull;
             mine += in ? 1 : 0;
           }
@@ -556,8 +673,8 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
           for (int i = tid; i < nl; i += NT) plist[i] = __uint_as_float((unsigned)list[i]) * inv_mass;
         } else {
           for (int id = tid; id < V; id += NT) {
-            const unsigned b = e_bits(x[id]);
-            ebuf[id] = member(b, (unsigned)id) ? __uint_as_float(b) * inv_mass : 0.f;
+            const float e = es[id];
+            ebuf[id] = in_nucleus(__float_as_uint(e), (unsigned)id) ? e * inv_mass : 0.f;
           }
         }
         __syncthreads();

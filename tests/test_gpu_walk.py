@@ -131,6 +131,44 @@ def test_walk_with_any_number_of_candidates(sx, V, top_p, tied):
     assert checked >= 12
 
 
+@pytest.mark.parametrize("V", [1000, 4095, 32000, 32768, 40001, 131072])
+@pytest.mark.parametrize("top_p", [0.7, 1.0])
+def test_walk_on_masked_rows(sx, V, top_p):
+    """Rows of which all but c tokens are masked out (-inf): only those can be drawn, by both walks, with c on both sides
+    of what the kernel finishes in one wave, in its list and over the whole row; ids at both ends of the row and of the
+    256-id blocks of its sums.  A row with nothing left gives token 0."""
+    r = np.random.default_rng(V)
+    tok, par = np.array([3], np.int32), np.array([-1], np.int32)
+    td, pd = to_dev(tok), to_dev(par)
+    qd = to_dev(np.full((1, V), 1.0 / V, np.float32))
+    checked = 0
+    for c in (1, 2, 70, 1024, 1025, 2000, V):
+        if c > V:
+            continue
+        lg = np.full((1, V), -np.inf, np.float32)
+        ends = np.array([0, V - 1, 255, 256, V - 2, V // 256 * 256 - 1])[:c]
+        ids = np.concatenate([ends, r.permutation(np.setdiff1d(np.arange(V), ends))[:c - len(ends)]])
+        lg[0, ids] = r.normal(0.0, 2.0, size=len(ids)).astype(np.float32) + 20.0
+        ld = to_dev(lg)
+        for seed in range(8):
+            ref = oracle.accept_walk(lg, tok, par, 0.9, top_p, seed=seed, pos0=9)
+            m = ref["margins"][0]
+            # the exponentials are good to 1e-6 and independent: sums over the row to a few 1e-8 of the mass
+            if min(m["m_p"], m["m_u"]) > 2e-7:
+                assert _walk(sx, ld, td, pd, 0.9, top_p, seed, 9)[1] == ref["tokens"], (c, seed)
+                checked += 1
+            ref = oracle.specinfer_walk(lg, np.full((1, V), 1.0 / V), tok, par, 0.9, top_p, seed=seed, pos0=9)
+            if ref["margins"][0]["m_u"] > 2e-7 and m["m_p"] > 2e-7:
+                _, toks, n, _ = sx.accept_walk(ld, td, pd, 0.9, top_p, seed, 9, draft_probs=qd)
+                torch.cuda.synchronize()
+                assert int(n.item()) == 1 and int(toks[0].item()) == ref["tokens"][0], (c, seed)
+                checked += 1
+    assert checked >= 60
+    ld = to_dev(np.full((1, V), -np.inf, np.float32))
+    assert _walk(sx, ld, td, pd, 0.9, top_p, 1, 9)[1] == [0]
+    assert _walk(sx, ld, td, pd, 0.0, top_p, 1, 9)[1] == [0]
+
+
 @pytest.mark.parametrize("M,t,V,above", [(-100.0, 1e-3, 32000, False), (37.0, 2e-4, 32000, True), (100.0, 1e-3, 50001, True)])
 def test_walk_on_rows_with_an_offset(sx, M, t, V, above):
     """A row far from zero and sharpened by a low temperature, whose many small probabilities (a tenth of the mass, each
