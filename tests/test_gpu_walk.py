@@ -310,6 +310,33 @@ def test_ratio_acceptance_matches_oracle(sx, V, T, kids, t, top_p):
     assert checked >= 12 and accepted >= 4        # the walks do go down the tree: target and draft agree roughly
 
 
+@pytest.mark.parametrize("V", [1000, 32000, 50000])
+@pytest.mark.parametrize("c", [65, 300, 1000])
+def test_ratio_acceptance_over_lists_of_any_length(sx, V, c):
+    """Targets with c possible tokens (the others masked out), more than one wave holds and fewer than the list's end, and
+    children that are mostly rejected: the distribution goes through several rejections before it is drawn from."""
+    T = 24
+    tok, par, target, dq = _sampled_tree(T, V, 6, seed=V + c)
+    r = np.random.default_rng(c)
+    for i in range(T):
+        keep = np.concatenate([np.argsort(-dq[i])[:6], r.choice(V, size=c, replace=False)])[:c]
+        row = np.full(V, -np.inf, np.float32)
+        row[keep] = r.normal(0.0, 2.0, size=len(keep))
+        target[i] = row
+    ld, qd, td, pd = to_dev(target), to_dev(dq), to_dev(tok), to_dev(par)
+    checked = 0
+    for seed in range(16):
+        ref = oracle.specinfer_walk(target, dq, tok, par, 0.7, 1.0, seed=seed, pos0=31)
+        if not _si_safe(ref):
+            continue
+        path, toks, n, _ = sx.accept_walk(ld, td, pd, 0.7, 1.0, seed, 31, draft_probs=qd)
+        torch.cuda.synchronize()
+        n = int(n.item())
+        assert path[:n].cpu().tolist() == ref["path"] and toks[:n].cpu().tolist() == ref["tokens"], (seed, ref)
+        checked += 1
+    assert checked >= 8
+
+
 def test_ratio_acceptance_emits_the_target_distribution(sx):
     """chi-square on the device: k children drawn from q by numpy; the first emitted token must follow p."""
     p = np.array([0.02, 0.4, 0.08, 0.25, 0.05, 0.2])
