@@ -431,20 +431,24 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
 // One workgroup of 1024 lanes picks the Bsel best of n candidates and orders them.  What bounds it is a chain of block-wide
 // steps on one compute unit, so there are few of them:
 //   threshold   with d = (largest order key) - (order key), the smallest D with #(d <= D) >= Bsel, by histograms of d in
-//               LDS: 4096 bins of 2^14 keys (1024 per octave of the scores, 8 octaves below the best; bins of an eighth of
+//               LDS: 4096 bins of 2^14 keys (512 per octave of the scores, 8 octaves below the best; bins of an eighth of
 //               an octave made a row's candidates meet in one bin, and their atomics queue), then bins of 4, then single
 //               keys, as far as needed.  Scores further apart (-inf among the winners) take bins over all 32 bits;
 //   order       the winners fall into 4096 buckets of equal key range (two per bucket at most on average), are placed
 //               by a scan of the bucket counts and ranked inside their bucket by counting smaller entries.  Where one
 //               bucket holds more than kBucketMax (many equal scores) they go through a sorting network instead.
 // Before, the threshold was a search over 32 bits with a block-wide count each and the order a sorting network of 66
-// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 31 and 14.
+// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 31 and 14.  Where scores
+// tie, adds to one LDS address and ranking by serial reads had made that slower than the search (65536 equal scores: 194 us
+// in all, the whole step of 2048 x 1000; 374 with them): equal scores need no threshold, the second histogram has copies
+// where many scores share a bin, and ties are ranked 4096 at a time until enough are found: 115.
 // QUADS > 0 (up to 16384 candidates): lane t holds the keys of the candidates 4 (j 1024 + t) .. + 3, j < QUADS, in
 // registers; 0: they are re-read, which beyond that costs less than the code it takes to hold them.
 constexpr int kSelThreads = 1024;
 constexpr int kSelBins = 4096;
 constexpr unsigned kBucketMax = 32;
 constexpr int kCodesMaxN = 65536, kCodesMaxB = 2048, kCodesCap = 3072;
+constexpr int kSubQueue = 32768;  // adds to 16 counters that cost less than clearing and summing copies of them
 // order key of a candidate: never 0, which marks the slots past the end (only one NaN pattern would map there)
 __device__ __forceinline__ unsigned select_key(float v) { return max(f32_order_key(v), 1u); }
 
@@ -543,8 +547,8 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   extern __shared__ __attribute__((aligned(16))) unsigned long long sbuf[];  // winners, then room to place them: 2 x next_pow2(Bsel)
   __shared__ __attribute__((aligned(16))) unsigned hist[kSelBins];
   __shared__ int s_wave[NW];
-  __shared__ unsigned s_max, s_big;
-  __shared__ int s_pos, s_bin, s_above;
+  __shared__ unsigned s_max, s_min, s_big;
+  __shared__ int s_pos, s_bin, s_above, s_in;
   __shared__ int s_sub[16];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -610,6 +614,7 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   if (tid == 0) {
     s_pos = 0;
     s_max = 0;
+    s_min = 0xFFFFFFFFu;
     s_big = 0;
     s_bin = 0;
     s_above = n;
@@ -649,16 +654,36 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
         if (start < Bsel && start + h >= Bsel) {
           s_bin = b;
           s_above = start;
+          s_in = h;
         }
         start += h;
       }
       __syncthreads();
       const unsigned bin = (unsigned)s_bin;
       const int words = (n + 3) / 4 * 2;
-      for (int w = tid; w < words; w += kSelThreads) {
-        const unsigned v = codes[w];
-        if (((v >> 4) & 0xFFFu) == bin) atomicAdd(&s_sub[v & 15u], 1);
-        if ((v >> 20) == bin) atomicAdd(&s_sub[(v >> 16) & 15u], 1);
+      if (__builtin_expect(s_in > kSubQueue, 0)) {
+        // scores close together: 256 copies of the 16 counts, a lane's own copy shared with none of its wave
+        __syncthreads();
+        clear();
+        __syncthreads();
+#pragma unroll 1
+        for (int w = tid; w < words; w += kSelThreads) {
+          const unsigned v = codes[w];
+          if (((v >> 4) & 0xFFFu) == bin) atomicAdd(&hist[(v & 15u) * 256 + (tid & 255)], 1u);
+          if ((v >> 20) == bin) atomicAdd(&hist[((v >> 16) & 15u) * 256 + (tid & 255)], 1u);
+        }
+        __syncthreads();
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c += (int)hist[wave * 256 + i * 64 + lane];
+        c = wave_sum_i(c);
+        if (lane == 0) s_sub[wave] = c;
+      } else {
+        for (int w = tid; w < words; w += kSelThreads) {
+          const unsigned v = codes[w];
+          if (((v >> 4) & 0xFFFu) == bin) atomicAdd(&s_sub[v & 15u], 1);
+          if ((v >> 20) == bin) atomicAdd(&s_sub[(v >> 16) & 15u], 1);
+        }
       }
       __syncthreads();
       int L = s_above, sub = 15;
@@ -708,7 +733,14 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
       }
       __syncthreads();
     }
-    stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) { top = max(top, max(max(a, b), max(c, e))); });
+    unsigned low = 0xFFFFFFFFu;  // one less than the smallest key (a slot past n: the largest number)
+    stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) {
+      top = max(top, max(max(a, b), max(c, e)));
+      low = min(low, min(min(a - 1u, b - 1u), min(c - 1u, e - 1u)));
+    });
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) low = min(low, (unsigned)__shfl_xor((int)low, o, 64));
+    if (lane == 0) atomicMin(&s_min, low);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
@@ -732,7 +764,10 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   // ---- threshold ---------------------------------------------------------------------------------------
   unsigned D = 0xFFFFFFFFu;
   int need = Bsel, ties = Bsel;  // of the candidates in the threshold's last bin: how many are taken, how many there are
-  if (n > Bsel) {
+  if (QUADS == 0 && n > Bsel && s_min + 1u == kmax) {  // all scores equal: the first ones are taken
+    D = 0;
+    ties = n;
+  } else if (n > Bsel) {
     unsigned prefix = 0;
     int above = 0, shift = 14, bits = 12;
     bool first = true, wide = false;
@@ -789,8 +824,8 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   const bool all_ties = ties == need;
   const unsigned take = all_ties ? D : D - 1u;  // (not all ties: some are better than D, or D = 0 and take wraps)
   const bool none = !all_ties && D == 0;
-  each4([&](unsigned a, unsigned b, unsigned c, unsigned e, int flat) {
-    if (none || __builtin_amdgcn_ballot_w64(min(min(a, b), min(c, e)) <= take) == 0ull) return;
+  if (!none) each4([&](unsigned a, unsigned b, unsigned c, unsigned e, int flat) {
+    if (__builtin_amdgcn_ballot_w64(min(min(a, b), min(c, e)) <= take) == 0ull) return;
     const unsigned t[4] = {a, b, c, e};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -804,20 +839,29 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
       if (hit && pos < Bsel) sbuf[pos] = ((unsigned long long)t[i] << 32) | (unsigned)(flat + i);
     }
   });
-  if (!all_ties) {
-    // Rare: more candidates at D than fit.  Lanes walk contiguous ranges so that an exclusive scan of
-    // their tie counts ranks the ties in flat-index order; the `need` first ones are taken.
-    const int per = (n + kSelThreads - 1) / kSelThreads;
-    const int lo = min(n, tid * per), hi = min(n, lo + per);
-    int mine = 0;
-    for (int i = lo; i < hi; ++i) mine += kmax - select_key(score[i]) == D;
-    int tie_rank = block_exclusive_scan(mine, s_wave);
-    for (int i = lo; i < hi && tie_rank < need; ++i)
-      if (kmax - select_key(score[i]) == D) {
-        const int pos = atomicAdd(&s_pos, 1);
-        if (pos < Bsel) sbuf[pos] = ((unsigned long long)D << 32) | (unsigned)i;
-        ++tie_rank;
-      }
+  if (__builtin_expect(!all_ties, 0)) {
+    // More candidates at D than fit: the `need` lowest flat indices, 4096 candidates at a time, a scan over the lanes' quads
+    // giving each its rank, until enough are found.
+    int found = 0;
+#pragma unroll 1
+    for (int i0 = 0; i0 < n && found < need; i0 += 4 * kSelThreads) {
+      const int i = i0 + 4 * tid;
+      unsigned tie = 0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (i + c < n && kmax - select_key(score[i + c]) == D) tie |= 1u << c;
+      int rank = found + block_exclusive_scan(__builtin_popcount(tie), s_wave);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (tie >> c & 1) {
+          if (rank < need) sbuf[Bsel - need + rank] = ((unsigned long long)D << 32) | (unsigned)(i + c);
+          ++rank;
+        }
+      if (tid == kSelThreads - 1) s_above = rank;
+      __syncthreads();
+      found = s_above;
+      __syncthreads();
+    }
   }
   __syncthreads();
 

@@ -125,11 +125,13 @@ def test_global_select_edge_cases(sx):
 
 
 @pytest.mark.parametrize("N,k,B", [(1, 1, 1), (100, 32, 2048), (128, 32, 4096), (129, 32, 1), (500, 32, 8192), (512, 32, 700), (513, 32, 2048), (2048, 32, 2000),
-                                   (513, 32, 8191), (33, 255, 1025)])
-@pytest.mark.parametrize("spread", ["wide", "narrow", "rounded", "dead"])
+                                   (513, 32, 8191), (33, 255, 1025), (2048, 32, 2048), (2047, 32, 2047), (2049, 32, 64),
+                                   (600, 100, 4096)])
+@pytest.mark.parametrize("spread", ["wide", "narrow", "rounded", "dead", "equal", "late"])
 def test_global_select_sizes_and_spreads(sx, N, k, B, spread):
-    """Candidate counts around what the select kernel holds per lane (4096 and 16384), every size of winner list, and
-    scores over one octave, over many, with long ties, and with dead rows (-inf) among the winners."""
+    """Candidate counts around what the select kernel holds per lane (4096 and 16384) and as codes (65536), every size of
+    winner list, and scores over one octave, over many, with long ties, with dead rows (-inf) among the winners, all
+    equal, and with ties that start behind the first 4096 candidates."""
     logits, cum = wl.gen_expand_inputs(N, 400, seed=N + k)
     if spread == "narrow":
         cum = (-1000.0 + cum * 1e-3).astype(np.float32)
@@ -137,6 +139,12 @@ def test_global_select_sizes_and_spreads(sx, N, k, B, spread):
         logits, cum = np.round(logits), np.round(cum).astype(np.float32)
     elif spread == "dead":
         cum[N // 3:] = -np.inf
+    elif spread == "equal":
+        logits, cum = np.zeros_like(logits), np.zeros_like(cum)
+    elif spread == "late":
+        logits, cum = np.zeros_like(logits), np.full_like(cum, -3.0)
+        cum[:N // 2] = -4.0 - np.arange(N // 2, dtype=np.float32) / N
+        cum[0] = -2.0
     ld, cd = to_dev(logits), to_dev(cum)
     lp, idx = sx.row_logsoftmax_topk(ld, k)
     r, t, s, n = _run(sx, logits, cum, k, B)
