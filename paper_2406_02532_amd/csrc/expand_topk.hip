@@ -890,8 +890,9 @@ int row_topk_dispatch(const float* logits, const float* cum, int N, int V, int k
   else {  // the row no longer fits the registers of a workgroup that leaves room for a second one
     const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
     // No more rows than compute units: a row has one to itself, and what it can keep in flight is the bound (64 bytes per
-    // lane), so twice the lanes: 100 rows of 128256 36 -> 28.7 us.
-    if (N <= sx_compute_units()) {
+    // lane), so twice the lanes: 100 rows of 128256 36 -> 28.7 us.  Not for k > 64, where every lane ranks its maximum
+    // among those of all lanes, which then takes longer than the row (k = 200: 57.7 us with 512 lanes, 68 with 1024).
+    if (N <= sx_compute_units() && k <= 64) {
       if (vec) row_topk_stream_kernel<1024, true><<<N, 1024, 0, st>>>(logits, cum, V, k, lp, idx, score);
       else row_topk_stream_kernel<1024, false><<<N, 1024, 0, st>>>(logits, cum, V, k, lp, idx, score);
     } else if (vec) row_topk_stream_kernel<512, true><<<N, 512, 0, st>>>(logits, cum, V, k, lp, idx, score);

@@ -84,10 +84,10 @@ def test_row_topk_shapes(sx, V, k):
     _check_rows(sx, logits, k)
 
 
-# Vocabularies too large for registers: a row to a workgroup of 1024 lanes up to a row per compute unit, of 512 above.
-# Odd widths (no 16-byte rows), one entry past a pass of all lanes, more than 64 wanted.
-@pytest.mark.parametrize("N,V,k", [(1, 32769, 5), (2, 65540, 256), (3, 49153, 64), (256, 33000, 65), (257, 33001, 32),
-                                   (300, 33000, 100)])
+# Vocabularies too large for registers: a row to a workgroup of 1024 lanes up to a row per compute unit and 64 wanted, of
+# 512 otherwise.  Odd widths (no 16-byte rows), one entry past a pass of all lanes, both sides of each line.
+@pytest.mark.parametrize("N,V,k", [(1, 32769, 5), (2, 65540, 256), (3, 49153, 64), (3, 49153, 65), (256, 33000, 65), (256, 33000, 64),
+                                   (257, 33001, 32), (300, 33000, 100)])
 def test_row_topk_streamed_rows(sx, N, V, k):
     logits, _ = wl.gen_expand_inputs(N, V, seed=V + k)
     logits[0, 100:160] = logits[0].max()              # ties at the top
