@@ -114,13 +114,16 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
       woff[t] = (int)(((unsigned)(n - first) * (unsigned)a.K + cchunk * 8) * 2u);
     }
   }
-#define SX_COPY(STG_, SLAB_)                                                                                     \
+// copies the next slab into stage STG_ and steps on, from the last slab to the first one (past the end of the walk too:
+// a slab nobody reads any more)
+#define SX_COPY(STG_)                                                                                            \
   {                                                                                                              \
-    const int sl = (SLAB_) + rot, so = (sl > last ? sl - NB : sl) * (BK * 2);                                    \
     _Pragma("unroll") for (int t = 0; t < kXCopies; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(               \
         xres, (lds_void_ptr)(STG_ + (kXCopies * wave + t) * 1024), 16, xoff[t], so, 0, 0);                       \
     _Pragma("unroll") for (int t = 0; t < 2; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                      \
         wres[t], (lds_void_ptr)(STG_ + kXBytes + wave * 2048 + t * 1024), 16, woff[t], so, 0, 0);                \
+    so += BK * 2;                                                                                                \
+    so = so == so_end ? so_begin : so;                                                                           \
   }
 
   // acc[i][j]: W rows (output columns) 64 wh + 32 wn + 16 i .. + 15, X rows (output rows) 64 wm + 16 j .. + 15
@@ -138,9 +141,9 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
 
 // "+v": the accumulators stay where they are (see the wide kernel); statements are volatile, order as written
 #define SX_MFMA(ACC, A, B) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(ACC) : "v"(A), "v"(B));
-#define SX_SLAB(STG_, STG_F, SLAB_F)                                                                             \
+#define SX_SLAB(STG_, STG_F)                                                                                     \
   SX_WAIT_BARRIER(NH == 1 ? kWaitVm6 : kWaitVm8)                                                                 \
-  SX_COPY(STG_F, SLAB_F)                                                                                         \
+  SX_COPY(STG_F)                                                                                                 \
   _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                                             \
     bf16x8 fx[4], fw[2];                                                                                         \
     _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                                \
@@ -156,39 +159,42 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
   // is done with the previous slab), start the copies of the slab after next into the stage just freed.
   const int nb_all = a.K / BK;
   const int first = kpart * nb_all / a.split;
-  const int NB = (kpart + 1) * nb_all / a.split - first, last = first + NB - 1;
+  const int NB = (kpart + 1) * nb_all / a.split - first;
   // Every workgroup walks its slabs from another one on.  Started all at their first, hundreds of workgroups ask for the
   // same 128 bytes of rows that lie a power of two apart, step after step, and the memory channels take turns.  By
   // neighbours on an XCD in a launch of one round, by all neighbours where later rounds drift apart anyway: 7B gate|up
   // product at 100 rows 46.8 -> 41.5 us, head of 32000 rows 61.3 -> 50.7, of 128256 rows 236 -> 204, 70B O projection
-  // 43.4 -> 36.9, 70B gate|up 191 -> 176; of ten shapes at five batch sizes none got slower.
+  // 43.4 -> 36.9, 70B gate|up 191 -> 176.  With weights that a cache still holds, up to 3 % slower; the offset is stepped
+  // from slab to slab, since computing it anew cost every slab another 40 cycles (301 x 8192, uncut: 37.9 -> 40.1 us).
   const int rot = (int)((unsigned)(a.tilesN * a.split > kOneRound ? 5 * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
+  const int so_begin = first * (BK * 2), so_end = so_begin + NB * (BK * 2);
+  int so = so_begin + rot * (BK * 2);  // of the next slab to copy
   // (NH = 2: four stages, the copies of the next two slabs may stay in flight, those of the third go out)
-  SX_COPY(st0, first)
-  SX_COPY(st1, min(first + 1, last))
+  SX_COPY(st0)
+  SX_COPY(st1)
   int s = 0;
   if (NH == 1) {
     for (; s + 3 <= NB; s += 3) {
-      SX_SLAB(st0, st2, min(first + s + 2, last))
-      SX_SLAB(st1, st0, min(first + s + 3, last))
-      SX_SLAB(st2, st1, min(first + s + 4, last))
+      SX_SLAB(st0, st2)
+      SX_SLAB(st1, st0)
+      SX_SLAB(st2, st1)
     }
     if (s < NB) {
-      SX_SLAB(st0, st2, last)
-      if (s + 1 < NB) { SX_SLAB(st1, st0, last) }
+      SX_SLAB(st0, st2)
+      if (s + 1 < NB) { SX_SLAB(st1, st0) }
     }
   } else {
-    SX_COPY(st2, min(first + 2, last))
+    SX_COPY(st2)
     for (; s + 4 <= NB; s += 4) {
-      SX_SLAB(st0, st3, min(first + s + 3, last))
-      SX_SLAB(st1, st0, min(first + s + 4, last))
-      SX_SLAB(st2, st1, min(first + s + 5, last))
-      SX_SLAB(st3, st2, min(first + s + 6, last))
+      SX_SLAB(st0, st3)
+      SX_SLAB(st1, st0)
+      SX_SLAB(st2, st1)
+      SX_SLAB(st3, st2)
     }
     if (s < NB) {
-      SX_SLAB(st0, st3, last)
-      if (s + 1 < NB) { SX_SLAB(st1, st0, last) }
-      if (s + 2 < NB) { SX_SLAB(st2, st1, last) }
+      SX_SLAB(st0, st3)
+      if (s + 1 < NB) { SX_SLAB(st1, st0) }
+      if (s + 2 < NB) { SX_SLAB(st2, st1) }
     }
   }
   __builtin_amdgcn_s_waitcnt(kWaitVm0);  // copies past the end of K must land before the LDS is released
