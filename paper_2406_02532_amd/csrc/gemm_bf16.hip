@@ -63,6 +63,7 @@ struct GemmArgs {
   void* Y;
   int M, N, K;  // N = logical output columns
   int tilesM, tilesN, chunk;
+  int rotate;  // the XCDs walk K from different eighths on
   // SX_GEMM_QKV_ROPE only: rotary table [M][64] (cos, sin), outputs bf16 [M][hq][128], [M][hkv][128] x 2
   const float2* cs;
   unsigned short *q, *k, *v;
@@ -309,13 +310,11 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   const int nb_all = a.K / BK;
   const int first = kpart * nb_all / ksplit;                      // slabs of this workgroup: [first, first + NB)
   const int NB = (kpart + 1) * nb_all / ksplit - first;
-  // Each XCD walks K from another eighth on: started all at the first slab, 256 workgroups ask for the same 128 bytes of rows
-  // that lie a power of two apart, and the memory channels take turns -- where a launch is near the weight stream's
-  // bound (70B MLP at 300 rows: gate|up 413 -> 374 us, down 237 -> 218; at 1000 rows 0 to 2 %).  The workgroups of an
+  // Each XCD walks K from another eighth on (pick_plan() has the rule): started all at the first slab, 256 workgroups ask for
+  // the same 128 bytes of rows that lie a power of two apart, and the memory channels take turns.  The workgroups of an
   // XCD stay in step with each other, since they share the operand lines in its L2 (rotated against each other they are
-  // up to 8 % slower at 2048 rows).  The prefetching form (8 row tiles) is bound by the matrix cores and 0.5 % slower with
-  // the rotation.
-  const int rot = PF ? 0 : xcd * NB / 8;
+  // up to 8 % slower at 2048 rows).
+  const int rot = PF || !a.rotate ? 0 : xcd * NB / 8;
   SX_COPY(stA, SX_OFFSET(0))
   SX_COPY(stB, SX_OFFSET(1))
   if (PF) {
@@ -598,7 +597,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 // outweighs the weights a part streams, and they take the narrow-tile kernel instead.)
 constexpr int kMinJB = 5, kMaxRows = 256;
 // A lower tile's slab costs more than its share of the arithmetic: it copies and reads the same W slab for fewer rows.
-constexpr float kSlabTime[4] = {0.8f, 0.86f, 0.93f, 1.f};
+constexpr float kSlabTime[4] = {0.86f, 0.96f, 0.95f, 1.f};
 constexpr float kSplitPerPartSlabs = 4.5f;  // also a round's beginning and end: first copies, epilogue
 constexpr int kSplitMaxWays = 16;
 float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
@@ -659,28 +658,52 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
   return uncut - nb * slab + nb * slab / split + (2.f + 2.5f * a.tail_items / cus) * jb / 8.f * split;
 }
 
-// The tile height: the one that plan_split's figures expect to be fastest, the taller of two within 2 %.  Their
-// constants are fitted to sweeps of all four heights over the 7B and 70B layer shapes at 150 to 2048 rows, where the
-// choice is on average 0.5 % and at most 7 % behind the best.  256 rows -> the height chosen:
-//   150 rows (one tile of 160): 7B down 90.8 -> 73.1 us, 70B O 82.4 -> 69.0, gate|up 217 -> 200
-//   300 rows (two of 160): 70B QKV 92.6 -> 83.9, gate|up 369 -> 340
-//   640 rows (four of 160): 70B down 360 -> 328, 7B O 65.8 -> 50.6
-//   1000 rows (six of 192: 240 tiles instead of 160 on 256 compute units): 70B QKV 196 -> 167
-// and the 256-row tile stays where there are rounds enough (1000 rows, 70B gate|up: 720 us against 802, 872 and 931).
-template <int MODE>
-int launch(GemmArgs& a, void* split_ws, size_t split_ws_bytes, hipStream_t st) {
-  int jb = 8;
-  float best = plan_split(a, 8, split_ws, split_ws_bytes);
+// What a launch looks like: tile height 32 jb, the prefetching form or not, and a's split and rotation.
+//
+// The height: the one that plan_split's figures expect to be fastest, if it beats 256 rows by 4 %.  The figures are fitted to
+// sweeps of all four heights over the layer shapes of widths 2048 to 8192 at 129 to 4096 rows, 680 cases with weights from
+// memory (a cache that still holds the weights, as in a loop over one product, makes lower tiles look up to 15 % better than
+// they are in a model) and again with weights at hand.  Against 256 rows throughout, the choice is 7 % faster on average
+// from memory, at best 27 %, at worst 2 % slower, and within 1 % of the best height on average.
+// Three things the figures do not know keep 256 rows:
+//   the prefetching form (8 row tiles, whole groups of 4 column tiles) streams the weights better than they say (13B down at
+//   2048 rows: 259 us, the lower tiles 285 to 348, predicted 10 % faster);
+//   as many row tiles of a lower height as of 256 rows only drop padding, which costs little once the chip is full: repeated
+//   rows draw little power, and power is what bounds it then (224 rows for 256 at 800 to 1344 rows: up to 12 % slower);
+//   as many rounds, two or more, of more row tiles gain nothing either (70B QKV at 1600 rows: 329 us, 160-row tiles 347).
+//
+// The rotation: worth 2 to 3 %, at best 15 %, for one or two row tiles, where a launch is bound by the weight stream, about 1 %
+// up to 8 row tiles of whole K; beyond that, and where the parts of a cut K start apart by themselves, it costs up to 1 %.
+struct Plan {
+  int jb;
+  bool prefetch;
+};
+Plan pick_plan(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
+  const int cus = sx_compute_units();
+  Plan p = {8, false};
+  const float tall = plan_split(a, 8, split_ws, split_ws_bytes);
+  const int rows8 = a.tilesM, rounds8 = (a.tilesM * a.tilesN + cus - 1) / cus;
+  const bool can_prefetch = a.tilesM == 8 && a.tilesN % 4 == 0;
+  float best = 0.96f * (can_prefetch ? 0.87f : 1.f) * tall;
   for (int t = 7; t >= kMinJB; --t) {
     const float cost = plan_split(a, t, split_ws, split_ws_bytes);
-    if (cost < 0.98f * best) best = cost, jb = t;
+    if (a.tilesM == rows8 ? a.tilesM > (t == 7 ? 2 : 3) : rounds8 >= 2 && (a.tilesM * a.tilesN + cus - 1) / cus == rounds8) continue;
+    if (cost < best) best = cost, p.jb = t;
   }
-  plan_split(a, jb, split_ws, split_ws_bytes);
+  plan_split(a, p.jb, split_ws, split_ws_bytes);
+  p.prefetch = p.jb == 8 && can_prefetch;
+  a.rotate = a.tilesM <= (a.split > 1 ? 2 : 8);
+  return p;
+}
+
+template <int MODE>
+int launch(GemmArgs& a, void* split_ws, size_t split_ws_bytes, hipStream_t st) {
+  const Plan p = pick_plan(a, split_ws, split_ws_bytes);
   const int grid = a.split > 1 ? 8 * (a.full_per_xcd + a.tail_per_xcd) : 8 * a.chunk;
-  if (jb == 5) gemm_bf16_kernel<MODE, 5, false><<<grid, kThreads, 0, st>>>(a);
-  else if (jb == 6) gemm_bf16_kernel<MODE, 6, false><<<grid, kThreads, 0, st>>>(a);
-  else if (jb == 7) gemm_bf16_kernel<MODE, 7, false><<<grid, kThreads, 0, st>>>(a);
-  else if (a.tilesM == 8 && a.tilesN % 4 == 0) gemm_bf16_kernel<MODE, 8, true><<<grid, kThreads, 0, st>>>(a);
+  if (p.jb == 5) gemm_bf16_kernel<MODE, 5, false><<<grid, kThreads, 0, st>>>(a);
+  else if (p.jb == 6) gemm_bf16_kernel<MODE, 6, false><<<grid, kThreads, 0, st>>>(a);
+  else if (p.jb == 7) gemm_bf16_kernel<MODE, 7, false><<<grid, kThreads, 0, st>>>(a);
+  else if (p.prefetch) gemm_bf16_kernel<MODE, 8, true><<<grid, kThreads, 0, st>>>(a);
   else gemm_bf16_kernel<MODE, 8, false><<<grid, kThreads, 0, st>>>(a);
   SX_LAUNCH_CHECK();
   return SX_OK;
@@ -757,6 +780,23 @@ int sx_launch_gemm_qkv_rope_bf16(const void* X, const void* Wq, const void* Wk, 
 }
 
 extern "C" size_t sx_gemm_bf16_workspace(void) { return sx_gemm_split_workspace(); }
+
+extern "C" int sx_gemm_bf16_wide_plan(int32_t M, int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t* tile_rows,
+                                      int32_t* k_parts, int32_t* cut_tiles, int32_t* prefetch) {
+  if (!tile_rows || !k_parts || !cut_tiles || !prefetch) return SX_ERR_NULL;
+  if (mode < 0 || mode > 2 || M < 1 || N < 1 || K < BK || K % BK != 0) return SX_ERR_SHAPE;
+  GemmArgs a;
+  a.M = M;
+  a.K = K;
+  a.tilesN = mode == SX_GEMM_SWIGLU ? (N + BN / 2 - 1) / (BN / 2) : (N + BN - 1) / BN;
+  int32_t somewhere = 0;  // (only whether there is memory is asked)
+  const Plan p = pick_plan(a, workspace_bytes ? &somewhere : nullptr, workspace_bytes);
+  *tile_rows = 32 * p.jb;
+  *k_parts = a.split;
+  *cut_tiles = a.split > 1 ? a.tilesM * a.tilesN - a.full_tiles : 0;
+  *prefetch = p.prefetch;
+  return SX_OK;
+}
 
 extern "C" int sx_gemm_bf16_ws(const void* X, const void* W, const void* W2, void* Y, int32_t M, int32_t N, int32_t K,
                                int32_t mode, void* workspace, size_t workspace_bytes, void* stream) {

@@ -70,3 +70,21 @@ def test_host_side_errors_return_codes(sx):
     assert L.sx_gemm_bf16_ws(one, one, None, one, 8, 8, 100, 0, one, 1 << 20, None) == -2               # K % 64 != 0
     assert L.sx_verify_tree(None, None, None, 0, one, one, 4, one, None, None, one, 1 << 20, None) == -1
     assert L.sx_row_logsoftmax_topk(one, 4, 100, 300, one, one, None) == -2
+
+
+def test_wide_gemm_plan(sx):
+    """Which tile height the wide GEMM takes: a lower one where it was faster with weights from memory, 256 rows where the
+    lower one only looked so (measured, us, 256 rows | the height the bare cost figures prefer)."""
+    ws = sx.lib.sx_gemm_bf16_workspace()
+    plan = lambda M, N, K, mode=0: sx.gemm_bf16_wide_plan(M, N, K, mode, ws)[0]  # noqa: E731
+    assert plan(150, 8192, 8192) == 160 and plan(300, 28672, 8192, 2) == 160
+    assert plan(192, 8192, 28672) == 192 and plan(224, 8192, 28672) == 224
+    assert sx.gemm_bf16_wide_plan(2048, 5120, 13824, 1, ws) == (256, 1, 0, True)      # 259 | 306
+    assert sx.gemm_bf16_wide_plan(2048, 5120, 5120, 1, ws) == (256, 1, 0, True)       # 114 | 128
+    assert plan(1300, 5120, 13824) == 256                                             # 187 | 202
+    assert plan(1100, 32000, 8192) == 256                                             # 512 | 529
+    assert sx.gemm_bf16_wide_plan(1600, 10240, 8192, 0, 0)[0] == 256                  # 329 | 347
+    out = (C.c_int32 * 4)()
+    assert sx.lib.sx_gemm_bf16_wide_plan(300, 512, 100, 0, 0, out, out, out, out) == -2
+    assert sx.lib.sx_gemm_bf16_wide_plan(300, 512, 128, 3, 0, out, out, out, out) == -2
+    assert sx.lib.sx_gemm_bf16_wide_plan(300, 512, 128, 0, 0, out, None, out, out) == -1

@@ -509,42 +509,71 @@ def test_gemm_bf16_few_tiles_cut_along_k(sx, M, N, K, mode):
     assert d.max() <= (1.01 * bf16_ulp(got).max() if mode == 2 else 1e-5 * np.sqrt(K) * np.abs(ref).max() + 1e-6)
 
 
-# Rows for which the wide kernel takes its lower tiles: one tile of 160 rows (129, 160), 192 (161, 192) or 224 (193,
-# 224), two of 160 (257, 320), and more tiles than compute units, the remainder cut along K (170 x 65800).
-@pytest.mark.parametrize("M,N,K", [(129, 272, 640), (160, 520, 192), (161, 72, 1088), (192, 512, 64), (193, 250, 320),
-                                   (224, 264, 2048), (257, 128, 704), (320, 512, 576), (170, 65800, 1024)])
-def test_gemm_bf16_tile_heights(sx, M, N, K):
-    X = wl.hash_normal(51, (M, K), dtype=torch.bfloat16).to(dev())
-    W = wl.hash_normal(52, (N, K), std=0.05, dtype=torch.bfloat16).to(dev())
-    W2 = wl.hash_normal(53, (N, K), std=0.05, dtype=torch.bfloat16).to(dev())
-    g, u = X.double() @ W.double().T, X.double() @ W2.double().T
+def _wide_plan(sx, M, N, K, mode=0):
+    """(tile rows, which tiles are cut along K, prefetching form) with the workspace the forward has"""
+    rows, parts, cut, prefetch = sx.gemm_bf16_wide_plan(M, N, K, mode, sx.lib.sx_gemm_bf16_workspace())
+    tiles = -(-M // rows) * -(-N // (128 if mode == 2 else 256))
+    return rows, "none" if parts == 1 else "all" if cut == tiles else "tail", prefetch
+
+
+# Every tile height of the wide kernel with no tile cut along K, all of them and those of the last round, and the
+# prefetching form (8 row tiles), at ragged rows and columns; the plan is asserted, so that a change of the rule cannot
+# leave a form without a test.  (No shape of the sweeps behind the rule takes 192 rows uncut.)
+@pytest.mark.parametrize("mode,M,N,K,rows,cut,prefetch", [
+    (0, 131, 72, 192, 160, "none", False), (0, 129, 72, 1088, 160, "all", False), (0, 150, 65800, 1088, 160, "tail", False),
+    (0, 185, 16392, 2048, 192, "all", False), (0, 192, 65800, 1088, 192, "tail", False),
+    (0, 185, 40000, 2048, 224, "none", False), (0, 200, 16392, 2048, 224, "all", False), (0, 193, 65800, 1088, 224, "tail", False),
+    (0, 129, 72, 64, 256, "none", False), (0, 225, 16392, 2048, 256, "all", False), (0, 900, 16392, 1088, 256, "tail", False),
+    (0, 2047, 1000, 64, 256, "none", True), (0, 2001, 3000, 2048, 256, "all", True), (0, 2001, 10240, 1088, 256, "tail", True),
+    (2, 131, 72, 192, 160, "none", False), (2, 160, 72, 1088, 160, "all", False), (2, 300, 16392, 1088, 160, "tail", False),
+    (2, 185, 8200, 2048, 192, "all", False), (2, 370, 16392, 1088, 192, "tail", False),
+    (2, 161, 16392, 2048, 224, "none", False), (2, 223, 8200, 2048, 224, "all", False), (2, 440, 16392, 1088, 224, "tail", False),
+    (2, 129, 72, 64, 256, "none", False), (2, 225, 8200, 2048, 256, "all", False), (2, 900, 8200, 1088, 256, "tail", False),
+    (2, 2047, 512, 64, 256, "none", True), (2, 2001, 1000, 4096, 256, "all", True), (2, 2001, 5120, 1088, 256, "tail", True),
+    # what the suite has run all along, whatever the height
+    (0, 160, 520, 192, None, None, None), (0, 161, 72, 1088, None, None, None), (0, 192, 512, 64, None, None, None),
+    (0, 193, 250, 320, None, None, None), (0, 224, 264, 2048, None, None, None), (0, 257, 128, 704, None, None, None),
+    (0, 320, 512, 576, None, None, None), (0, 170, 65800, 1024, None, None, None), (2, 224, 264, 2048, None, None, None),
+])
+def test_gemm_bf16_tile_heights(sx, mode, M, N, K, rows, cut, prefetch):
+    if rows is not None:
+        assert _wide_plan(sx, M, N, K, mode) == (rows, cut, prefetch)
+    X = wl.hash_normal(51, (M, K), dtype=torch.bfloat16, device=dev())
+    W = wl.hash_normal(52, (N, K), std=0.05, dtype=torch.bfloat16, device=dev())
+    g = X.double() @ W.double().T
     ws = torch.zeros(sx.lib.sx_gemm_bf16_workspace(), dtype=torch.uint8, device=dev())
     tol = 1e-5 * np.sqrt(K) * float(g.abs().max()) + 1e-6
     for work in (None, ws):
         # rows behind the last one stay untouched
-        Y = torch.full((M + 40, N), 7.0, dtype=torch.float32, device=dev())
-        sx.gemm_bf16(X, W, Y[:M], mode=0, workspace=work)
-        sx.gemm_bf16(X, W, Y[:M], mode=1, workspace=work)
-        assert float((Y[:M].double() - 2 * g).abs().max()) <= 2 * tol
+        if mode == 0:
+            Y = torch.full((M + 40, N), 7.0, dtype=torch.float32, device=dev())
+            sx.gemm_bf16(X, W, Y[:M], mode=0, workspace=work)
+            sx.gemm_bf16(X, W, Y[:M], mode=1, workspace=work)
+            assert float((Y[:M].double() - 2 * g).abs().max()) <= 2 * tol
+        else:
+            W2 = wl.hash_normal(53, (N, K), std=0.05, dtype=torch.bfloat16, device=dev())
+            Y = torch.full((M + 40, N), 7.0, dtype=torch.bfloat16, device=dev())
+            sx.gemm_bf16(X, W, Y[:M], mode=2, W2=W2, workspace=work)
+            want = (g / (1 + torch.exp(-g)) * (X.double() @ W2.double().T)).cpu().numpy()
+            assert np.all(np.abs(Y[:M].double().cpu().numpy() - want) <= 0.51 * bf16_ulp(want) + 1e-5 * np.abs(want).max())
         assert bool((Y[M:] == 7.0).all())
-        H = torch.zeros((M, N), dtype=torch.bfloat16, device=dev())
-        sx.gemm_bf16(X, W, H, mode=2, W2=W2, workspace=work)
-        want = (g / (1 + torch.exp(-g)) * u).cpu().numpy()
-        assert np.all(np.abs(H.double().cpu().numpy() - want) <= 0.51 * bf16_ulp(want) + 1e-5 * np.abs(want).max())
-    if K % 128 == 0 and M < 300:  # and the rotary epilogue, whose table is staged by halves of the tile's rows
-        test_qkv_projection_with_rotary_epilogue(sx, M, K, 2, 1)
+    assert int(ws[:1024].max()) == 0
 
 
-# the last three shapes give more output tiles than the chip has compute units with a small remainder: the
-# remainder tiles are cut along K and their partial sums added up by the last workgroup to arrive
-# (256, 2048, 16, 4) and (512, 1024, 8, 8): fewer tiles than half the compute units, all of them cut along K;
-# (77, 8192, 64, 8): few rows, three stacked matrices through the 128-column form of the narrow kernel, K cut in 3
-@pytest.mark.parametrize("T,d,Hq,Hkv", [(256, 256, 2, 2), (300, 512, 4, 1), (77, 1024, 8, 2),
-                                        (2048, 2048, 64, 8), (2048, 2048, 64, 1), (2304, 1024, 64, 8),
-                                        (256, 2048, 16, 4), (512, 1024, 8, 8), (77, 8192, 64, 8)])
-def test_qkv_projection_with_rotary_epilogue(sx, T, d, Hq, Hkv):
+# The projection with its rotary epilogue, whose table is staged by halves of the tile's rows, at every tile height:
+# (150, 192, 2, 1) 160 rows uncut, (129, 1088, 2, 1) and the next three 160, 192, 224 and 256 rows with K cut among two or
+# three workgroups; (2048, 2048, 64, 8), (2048, 2048, 64, 1) and (2304, 1024, 64, 8) the tiles of the last round cut, the
+# first by the prefetching form; (77, 8192, 64, 8): few rows, K cut in 6.
+@pytest.mark.parametrize("T,d,Hq,Hkv,rows,cut,prefetch", [
+    (256, 256, 2, 2, 160, "none", False), (300, 512, 4, 1, 160, "none", False), (77, 1024, 8, 2, 160, "all", False),
+    (2048, 2048, 64, 8, 256, "tail", True), (2048, 2048, 64, 1, 256, "tail", False), (2304, 1024, 64, 8, 256, "tail", False),
+    (256, 2048, 16, 4, 160, "all", False), (512, 1024, 8, 8, 160, "all", False), (77, 8192, 64, 8, 160, "all", False),
+    (150, 192, 2, 1, 160, "none", False), (129, 1088, 2, 1, 160, "all", False), (161, 2048, 112, 16, 192, "all", False),
+    (193, 2048, 112, 16, 224, "all", False), (225, 2048, 112, 16, 256, "all", False)])
+def test_qkv_projection_with_rotary_epilogue(sx, T, d, Hq, Hkv, rows, cut, prefetch):
     """The QKV GEMM that rotates and splits into heads in its epilogue, against the oracle's rope applied to
     fp64 projections (rows beyond a tile, GQA, head columns that cross tile boundaries)."""
+    assert _wide_plan(sx, T, (Hq + 2 * Hkv) * 128, d) == (rows, cut, prefetch)
     X = wl.hash_normal(11, (T, d), dtype=torch.bfloat16)
     Wq = wl.hash_normal(12, (Hq * 128, d), std=0.05, dtype=torch.bfloat16)
     Wk = wl.hash_normal(13, (Hkv * 128, d), std=0.05, dtype=torch.bfloat16)
@@ -567,6 +596,7 @@ def test_qkv_projection_repeats_bit_for_bit_in_fresh_workspaces(sx):
     partial sums through memory: four calls, each in a workspace of its own holding whatever was there before, give
     the same bits."""
     T, d, Hq, Hkv = 2048, 2048, 64, 8
+    assert sx.gemm_bf16_wide_plan(T, (Hq + 2 * Hkv) * 128, d, 0, sx.lib.sx_gemm_bf16_workspace()) == (256, 4, 64, True)
     X = wl.hash_normal(11, (T, d), dtype=torch.bfloat16).to(dev())
     Wq = wl.hash_normal(12, (Hq * 128, d), std=0.05, dtype=torch.bfloat16).to(dev())
     Wk = wl.hash_normal(13, (Hkv * 128, d), std=0.05, dtype=torch.bfloat16).to(dev())
