@@ -298,7 +298,8 @@ def test_c1_tree_verified_in_batches_of_nodes_matches_oracle(sx, c1):
         np.testing.assert_allclose(tree_v[:, :T].cpu().double().numpy(), ref["tree_v"], atol=1e-4)
 
 
-def test_bf16_tree_verified_in_batches_matches_one_pass(sx):
+@pytest.mark.parametrize("P", [600, 330])   # ten key tiles of prefix, which batches of few nodes share among several
+def test_bf16_tree_verified_in_batches_matches_one_pass(sx, P):  # workgroups, and six, too few to be worth sharing
     """Same on the MFMA path (4 narrow bf16 layers, GQA): batches of nodes against the one-pass result.  The
     batches change which keys share an attention tile and, at 128 rows or fewer, which GEMM kernel runs (narrow
     tiles, K cut in parts), hence the order of fp32 sums: bf16 roundings flip here and there, so the two results
@@ -306,7 +307,6 @@ def test_bf16_tree_verified_in_batches_matches_one_pass(sx):
     flip-noise floor is 2.4e-2), with 99% of the logits within half of it."""
     cfg = wl.ModelCfg(4, 1024, 8, 2, 128, 2752, 4000, dtype="bf16")
     w = wl.gen_weights(cfg, seed=41)
-    P = 600           # ten key tiles of prefix: batches of few nodes share them among several workgroups
     pk, pv = wl.gen_prefix_kv(cfg, P, seed=42)
     tok, par, _ = wl.gen_best_first_tree(150, 6, cfg.vocab, seed=43)
     T = len(tok)
