@@ -31,7 +31,6 @@ constexpr int BM = 128, BK = 64;
 constexpr int kXBytes = BM * BK * 2;   // 16 KB
 constexpr int kWBytes = 64 * BK * 2;   // 8 KB per group of 64 columns
 constexpr int kWideMinSlabs = 40;
-constexpr int kOneRound = 256;         // workgroups that run side by side, one or two per compute unit
 
 struct SkinnyArgs {
   const unsigned short* X;
@@ -42,6 +41,7 @@ struct SkinnyArgs {
   void* Y;
   int M, N, K;
   int tilesN, split;
+  int rounds;  // of workgroups, one per compute unit
   float* part;
   int* part_cnt;
 };
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
   // product at 100 rows 46.8 -> 41.5 us, head of 32000 rows 61.3 -> 50.7, of 128256 rows 236 -> 204, 70B O projection
   // 43.4 -> 36.9, 70B gate|up 191 -> 176.  With weights that a cache still holds, up to 3 % slower; the offset is stepped
   // from slab to slab, since computing it anew cost every slab another 40 cycles (301 x 8192, uncut: 37.9 -> 40.1 us).
-  const int rot = (int)((unsigned)(a.tilesN * a.split > kOneRound ? 5 * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
+  const int rot = (int)((a.rounds > 1 ? 5u * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
   const int so_begin = first * (BK * 2), so_end = so_begin + NB * (BK * 2);
   int so = so_begin + rot * (BK * 2);  // of the next slab to copy
   // (NH = 2: four stages, the copies of the next two slabs may stay in flight, those of the third go out)
@@ -389,6 +389,7 @@ int sx_launch_gemm_skinny_bf16(const void* X, const void* W0, const void* W1, co
     a.part = reinterpret_cast<float*>(static_cast<char*>(split_ws) + 1024);
   }
   const int grid = a.tilesN * a.split;
+  a.rounds = (grid + slots - 1) / slots;
 #define SX_GO(MODE_)                                                                    \
   if (nh == 2) gemm_skinny_bf16_kernel<MODE_, 2><<<grid, 512, 0, st>>>(a);              \
   else gemm_skinny_bf16_kernel<MODE_, 1><<<grid, 256, 0, st>>>(a);

@@ -93,7 +93,7 @@ size_t sx_tree_attn_split_workspace(int Tq_max, int Hq);
 static inline int sx_attn_min_nodes_per_tile(int Hq, int Hkv) { return 64 / (Hq / Hkv); }
 static inline int sx_attn_nodes_per_tile(int Hq, int Hkv, int Tq) {
   const int npt = 128 / (Hq / Hkv);
-  return ((Tq + npt - 1) / npt) * Hkv < 256 ? npt / 2 : npt;
+  return ((Tq + npt - 1) / npt) * Hkv < sx_compute_units() ? npt / 2 : npt;
 }
 
 // ---- the forward itself (verify_tree.hip) -----------------------------------------------------------------

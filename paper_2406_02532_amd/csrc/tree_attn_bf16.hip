@@ -439,12 +439,14 @@ int sx_launch_tree_attn_bf16(const void* q, const void* k_tree, const void* v_tr
   dim3 grid((Tq + a.npt - 1) / a.npt, Hkv);
   // few query rows (a batch of the draft model): the grid leaves most of the chip idle while each workgroup
   // walks all key tiles one after the other; give shares of the key tiles to up to 8 workgroups instead.  One workgroup
-  // per compute unit: with two, each one's tiles halve but the partial results double (22.0 + 9.4 us for 19.7 + 5.3)
+  // per compute unit: with two, each one's tiles halve but the partial results double (22.0 + 9.4 us for 19.7 + 5.3).  With
+  // more workgroups than half the compute units nothing is shared (80 / 10 heads, 128 nodes: 160 workgroups, 13.8, 23.7 and
+  // 65.8 us at 300, 1024 and 4096 keys; 20.1, 43.6 and 143.9 with 32-row workgroups in up to three shares)
   a.splits = 1;
   a.part_o = a.part_m = a.part_l = nullptr;
-  const int wgs = (int)(grid.x * grid.y), npre = (P + KTILE - 1) / KTILE;
-  if (split_ws && wgs < 256 && npre >= 4) {
-    int s = 256 / wgs;
+  const int wgs = (int)(grid.x * grid.y), npre = (P + KTILE - 1) / KTILE, cus = sx_compute_units();
+  if (split_ws && wgs < cus && npre >= 4) {
+    int s = cus / wgs;
     if (s > 8) s = 8;
     if (s > npre / 2) s = npre / 2;
     // putting the results together is a launch of its own, about six key tiles' time (0.9 us each): 128 nodes, 64 / 32 heads,
