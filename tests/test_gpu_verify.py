@@ -441,7 +441,8 @@ def test_gemm_w4a16(sx, M, N, K, group, split):
     assert np.abs(Y.cpu().double().numpy() - 2 * ref).max() <= 2 * tol
 
 
-# The register form's slab pipeline and its parameters in LDS: 1, 2, 3, 4 and 5 slabs of K; more groups than LDS holds at a
+# One slab of K, which goes through LDS; the register form's slab pipeline and its parameters in LDS: 2, 3, 4 and 5 slabs
+# of K (one: in the tests of whole models); more groups than LDS holds at a
 # time (55 slabs of 64-value groups, 112 of 128-value ones, refilled after 24 and 48), groups of several slabs whose
 # parts begin inside one, a K cut (3072 x 4096: 64-column tiles, 12416 x 2048: 128-column ones), columns past the end.
 @pytest.mark.parametrize("M,N,K,group,split", [(128, 64, 128, 128, False), (5, 130, 256, 64, False), (100, 72, 384, 128, True),

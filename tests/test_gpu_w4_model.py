@@ -70,14 +70,17 @@ def _bf16_twin(gpu, ref):
                 lm_head=gpu["lm_head"].to(dev()), layers=layers)
 
 
-@pytest.mark.parametrize("T", [100, 200])
-def test_forward_with_4bit_layers_matches_oracle(sx, T):
-    """T = 100: at most 128 query nodes, the linear layers read the 4-bit weights directly (dequantised in registers).
-    T = 200: each layer is expanded to bf16 into the scratch and the wide kernels run on the copy -- which must give
-    bit for bit what the plain bf16 model with those weights gives."""
-    cfg = wl.ModelCfg(3, 1024, 8, 2, 128, 2816, 4000, dtype="bf16")
+@pytest.mark.parametrize("T,shape", [(100, (3, 1024, 8, 2, 128, 2816, 4000)), (200, (3, 1024, 8, 2, 128, 2816, 4000)),
+                                     (60, (2, 128, 1, 1, 128, 128, 500)), (128, (1, 256, 2, 1, 128, 384, 500))])
+def test_forward_with_4bit_layers_matches_oracle(sx, T, shape):
+    """At most 128 query nodes: the linear layers read the 4-bit weights directly (dequantised in registers), over one,
+    two, three or more slabs of K.  T = 200: each layer is expanded to bf16 into the scratch and the wide kernels run on
+    the copy -- which must give bit for bit what the plain bf16 model with those weights gives."""
+    cfg = wl.ModelCfg(*shape, dtype="bf16")
     P = 150
     gpu, ref_w = _w4_model(cfg, seed=91)
+    if cfg.d_model < 1024:      # logits of the same size from narrow models
+        gpu["lm_head"] = ref_w["lm_head"] = (gpu["lm_head"].float() * 2.5).to(torch.bfloat16)
     pk, pv = wl.gen_prefix_kv(cfg, P, seed=92)
     tok, par, _ = wl.gen_best_first_tree(T, 8, cfg.vocab, seed=93)
     ref = oracle.verify_tree(cfg, ref_w, pk, pv, tok, par, act_round="bf16")["logits"]
