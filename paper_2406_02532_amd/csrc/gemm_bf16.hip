@@ -5,7 +5,7 @@
 // quadrant = JB x 8 blocks of v_mfma_f32_16x16x32_bf16, 4 * 8 * JB fp32 accumulators per lane.  The tile height is
 // a template parameter, JB = 8 (256 rows) down to 5 (160): the most arithmetic per operand byte where the rows and the
 // compute units come out even, lower where 256-row tiles would multiply padding or leave compute units without a tile
-// (launch() below has the rule and the figures).  With real
+// (pick_plan() below has the rule and the figures).  With real
 // operand data the chip is power-limited long before the MFMA issue rate is: in a pure register loop
 // the 16x16x32 shape sustains ~1.95 PFLOP/s against ~1.75 for 32x32x16 (it holds a ~10% higher
 // clock), which is why the smaller block is used.  The product is formed transposed (W rows feed

@@ -7,7 +7,7 @@
 // its own fragments straight from global memory (16 bytes = four fragments per load), dequantises them in
 // registers (w = bf16(scale * (code - zero)): one byte-to-float conversion and one fma per weight, exact in
 // fp32, rounded once) and feeds the matrix core.  Only X goes through LDS (copied by buffer loads that write
-// LDS), where the 128 rows are shared by the four waves.
+// LDS), where the 128 rows are shared by the eight waves.
 //
 // Tiling: a workgroup owns all M <= 128 rows x 128 or 64 columns.  K is walked in slabs of 128 (four k-steps), and its
 // eight waves are four column groups (2 or 1 blocks of 16 W rows each, x 8 blocks of 16 X rows) times the two halves of
@@ -29,12 +29,12 @@
 // memory and the last workgroup to arrive adds them in part order (deterministic, nobody waits).
 //
 // Up to three weight matrices may be stacked along N (the QKV projections, or gate and up) as long as each
-// holds a multiple of 64 rows: a wave's 64 columns then belong to one matrix.
+// holds a multiple of 64 rows: a wave's 16 or 32 columns then belong to one matrix.
 #include "kernels.h"
 
 namespace {
 
-constexpr int BM = 128, BK = 128;   // columns per workgroup: 4 waves x WB blocks of 16 (template parameter)
+constexpr int BM = 128, BK = 128;   // rows, K of a slab; columns: 4 groups x WB blocks of 16 (template parameter)
 constexpr int kThreads = 512;
 constexpr int kXBytes = BM * BK * 2;   // 32 KB: one slab of X
 constexpr int kParGroups = 48;         // groups whose scales and zero points are in LDS at a time
