@@ -597,7 +597,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 // outweighs the weights a part streams, and they take the narrow-tile kernel instead.)
 constexpr int kMinJB = 5, kMaxRows = 256;
 // A lower tile's slab costs more than its share of the arithmetic: it copies and reads the same W slab for fewer rows.
-constexpr float kSlabTime[4] = {0.86f, 0.96f, 0.95f, 1.f};
+constexpr float kSlabTime[4] = {0.83f, 0.91f, 0.92f, 1.f};
 constexpr float kSplitPerPartSlabs = 4.5f;  // also a round's beginning and end: first copies, epilogue
 constexpr int kSplitMaxWays = 16;
 float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
@@ -660,17 +660,19 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
 
 // What a launch looks like: tile height 32 jb, the prefetching form or not, and a's split and rotation.
 //
-// The height: the one that plan_split's figures expect to be fastest, if it beats 256 rows by 4 %.  The figures are fitted to
-// sweeps of all four heights over the layer shapes of widths 2048 to 8192 at 129 to 4096 rows, 680 cases with weights from
-// memory (a cache that still holds the weights, as in a loop over one product, makes lower tiles look up to 15 % better than
-// they are in a model) and again with weights at hand.  Against 256 rows throughout, the choice is 7 % faster on average
-// from memory, at best 27 %, at worst 2 % slower, and within 1 % of the best height on average.
-// Three things the figures do not know keep 256 rows:
-//   the prefetching form (8 row tiles, whole groups of 4 column tiles) streams the weights better than they say (13B down at
-//   2048 rows: 259 us, the lower tiles 285 to 348, predicted 10 % faster);
+// The height: the one that plan_split's figures expect to be fastest.  The figures are fitted to sweeps of all four heights
+// over the layer shapes of widths 2048 to 8192 at 129 to 4096 rows, 680 cases with weights from memory (a cache that still
+// holds the weights, as in a loop over one product, makes lower tiles look up to 15 % better than they are in a model) and
+// again with weights at hand.  Against 256 rows throughout, the choice is 7.4 % faster on average from memory, more than 2 %
+// slower in 16 of the cases (8 % at worst), and within 1 % of the best height on average; of 140 forwards
+// through a layer of the 1B to 70B shapes none is slower.
+// Two things the figures do not know speak for 256 rows:
+//   the prefetching form (8 row tiles, whole groups of 4 column tiles), unless every tile is cut, streams the weights better
+//   than they say (13B down at 2048 rows: 259 us, the lower tiles 285 to 348, predicted 10 % faster): a fifth;
 //   as many row tiles of a lower height as of 256 rows only drop padding, which costs little once the chip is full: repeated
-//   rows draw little power, and power is what bounds it then (224 rows for 256 at 800 to 1344 rows: up to 12 % slower);
-//   as many rounds, two or more, of more row tiles gain nothing either (70B QKV at 1600 rows: 329 us, 160-row tiles 347).
+//   rows draw little power, and power is what bounds it then (224 rows for 256 at 1100 rows, 7B QKV 105.3 against 101.5 us,
+//   gate|up 194 against 186): not from five row tiles on.  (At four, 800 rows, a layer of the 7B shape takes 700 us with
+//   224 rows and 724 with 256; the 70B shape 1835 and 1903.)
 //
 // The rotation: worth 2 to 3 %, at best 15 %, for one or two row tiles, where a launch is bound by the weight stream, about 1 %
 // up to 8 row tiles of whole K; beyond that, and where the parts of a cut K start apart by themselves, it costs up to 1 %.
@@ -679,15 +681,14 @@ struct Plan {
   bool prefetch;
 };
 Plan pick_plan(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
-  const int cus = sx_compute_units();
   Plan p = {8, false};
   const float tall = plan_split(a, 8, split_ws, split_ws_bytes);
-  const int rows8 = a.tilesM, rounds8 = (a.tilesM * a.tilesN + cus - 1) / cus;
+  const int rows8 = a.tilesM;
   const bool can_prefetch = a.tilesM == 8 && a.tilesN % 4 == 0;
-  float best = 0.96f * (can_prefetch ? 0.87f : 1.f) * tall;
+  float best = 0.99f * (can_prefetch && !(a.split > 1 && a.full_tiles == 0) ? 0.8f : 1.f) * tall;
   for (int t = 7; t >= kMinJB; --t) {
     const float cost = plan_split(a, t, split_ws, split_ws_bytes);
-    if (a.tilesM == rows8 ? a.tilesM > (t == 7 ? 2 : 3) : rounds8 >= 2 && (a.tilesM * a.tilesN + cus - 1) / cus == rounds8) continue;
+    if (a.tilesM == rows8 && rows8 > 4) continue;
     if (cost < best) best = cost, p.jb = t;
   }
   plan_split(a, p.jb, split_ws, split_ws_bytes);

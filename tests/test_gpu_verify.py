@@ -519,18 +519,21 @@ def _wide_plan(sx, M, N, K, mode=0):
 
 # Every tile height of the wide kernel with no tile cut along K, all of them and those of the last round, and the
 # prefetching form (8 row tiles), at ragged rows and columns; the plan is asserted, so that a change of the rule cannot
-# leave a form without a test.  (No shape of the sweeps behind the rule takes 192 rows uncut.)
+# leave a form without a test.
 @pytest.mark.parametrize("mode,M,N,K,rows,cut,prefetch", [
     (0, 131, 72, 192, 160, "none", False), (0, 129, 72, 1088, 160, "all", False), (0, 150, 65800, 1088, 160, "tail", False),
     (0, 185, 16392, 2048, 192, "all", False), (0, 192, 65800, 1088, 192, "tail", False),
-    (0, 185, 40000, 2048, 224, "none", False), (0, 200, 16392, 2048, 224, "all", False), (0, 193, 65800, 1088, 224, "tail", False),
-    (0, 129, 72, 64, 256, "none", False), (0, 225, 16392, 2048, 256, "all", False), (0, 900, 16392, 1088, 256, "tail", False),
-    (0, 2047, 1000, 64, 256, "none", True), (0, 2001, 3000, 2048, 256, "all", True), (0, 2001, 10240, 1088, 256, "tail", True),
+    (0, 185, 32776, 192, 192, "none", False), (0, 223, 32776, 192, 224, "none", False),
+    (0, 200, 16392, 2048, 224, "all", False), (0, 193, 65800, 1088, 224, "tail", False),
+    (0, 225, 32776, 64, 256, "none", False), (0, 225, 16392, 2048, 256, "all", False), (0, 500, 32776, 1088, 256, "tail", False),
+    (0, 2047, 1000, 64, 256, "none", True), (0, 2001, 3000, 2048, 224, "all", False), (0, 2001, 4000, 2048, 256, "all", True),
+    (0, 2001, 10240, 1088, 256, "tail", True),
     (2, 131, 72, 192, 160, "none", False), (2, 160, 72, 1088, 160, "all", False), (2, 300, 16392, 1088, 160, "tail", False),
     (2, 185, 8200, 2048, 192, "all", False), (2, 370, 16392, 1088, 192, "tail", False),
-    (2, 161, 16392, 2048, 224, "none", False), (2, 223, 8200, 2048, 224, "all", False), (2, 440, 16392, 1088, 224, "tail", False),
-    (2, 129, 72, 64, 256, "none", False), (2, 225, 8200, 2048, 256, "all", False), (2, 900, 8200, 1088, 256, "tail", False),
-    (2, 2047, 512, 64, 256, "none", True), (2, 2001, 1000, 4096, 256, "all", True), (2, 2001, 5120, 1088, 256, "tail", True),
+    (2, 185, 16392, 192, 192, "none", False), (2, 223, 16392, 192, 224, "none", False),
+    (2, 223, 8200, 2048, 224, "all", False), (2, 440, 16392, 1088, 224, "tail", False),
+    (2, 225, 16392, 64, 256, "none", False), (2, 225, 8200, 2048, 256, "all", False), (2, 500, 16392, 1088, 256, "tail", False),
+    (2, 2047, 512, 64, 256, "none", True), (2, 2001, 2040, 2048, 256, "all", True), (2, 2001, 5120, 1088, 256, "tail", True),
     # what the suite has run all along, whatever the height
     (0, 160, 520, 192, None, None, None), (0, 161, 72, 1088, None, None, None), (0, 192, 512, 64, None, None, None),
     (0, 193, 250, 320, None, None, None), (0, 224, 264, 2048, None, None, None), (0, 257, 128, 704, None, None, None),
@@ -562,12 +565,12 @@ def test_gemm_bf16_tile_heights(sx, mode, M, N, K, rows, cut, prefetch):
 
 
 # The projection with its rotary epilogue, whose table is staged by halves of the tile's rows, at every tile height:
-# (150, 192, 2, 1) 160 rows uncut, (129, 1088, 2, 1) and the next three 160, 192, 224 and 256 rows with K cut among two or
-# three workgroups; (2048, 2048, 64, 8), (2048, 2048, 64, 1) and (2304, 1024, 64, 8) the tiles of the last round cut, the
-# first by the prefetching form; (77, 8192, 64, 8): few rows, K cut in 6.
+# (150, 192, 2, 1) 160 and (2304, 1024, 64, 8) 192 rows uncut, (129, 1088, 2, 1) and the next three 160, 192, 224 and 256
+# rows with K cut among two or three workgroups; (2048, 2048, 64, 8) and (2048, 2048, 64, 1) the tiles of the last round
+# cut, the first by the prefetching form; (77, 8192, 64, 8): few rows, K cut in 6.
 @pytest.mark.parametrize("T,d,Hq,Hkv,rows,cut,prefetch", [
     (256, 256, 2, 2, 160, "none", False), (300, 512, 4, 1, 160, "none", False), (77, 1024, 8, 2, 160, "all", False),
-    (2048, 2048, 64, 8, 256, "tail", True), (2048, 2048, 64, 1, 256, "tail", False), (2304, 1024, 64, 8, 256, "tail", False),
+    (2048, 2048, 64, 8, 256, "tail", True), (2048, 2048, 64, 1, 256, "tail", False), (2304, 1024, 64, 8, 192, "none", False),
     (256, 2048, 16, 4, 160, "all", False), (512, 1024, 8, 8, 160, "all", False), (77, 8192, 64, 8, 160, "all", False),
     (150, 192, 2, 1, 160, "none", False), (129, 1088, 2, 1, 160, "all", False), (161, 2048, 112, 16, 192, "all", False),
     (193, 2048, 112, 16, 224, "all", False), (225, 2048, 112, 16, 256, "all", False)])
