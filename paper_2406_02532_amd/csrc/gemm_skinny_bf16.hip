@@ -114,16 +114,16 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
       woff[t] = (int)(((unsigned)(n - first) * (unsigned)a.K + cchunk * 8) * 2u);
     }
   }
-// copies the next slab into stage STG_ and steps on, from the last slab to the first one (past the end of the walk too:
-// a slab nobody reads any more)
+// copies the next slab into stage STG_ and steps on, from the last slab of K to the first; past the end of the walk its last
+// slab again, which nobody reads any more
 #define SX_COPY(STG_)                                                                                            \
   {                                                                                                              \
     _Pragma("unroll") for (int t = 0; t < kXCopies; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(               \
         xres, (lds_void_ptr)(STG_ + (kXCopies * wave + t) * 1024), 16, xoff[t], so, 0, 0);                       \
     _Pragma("unroll") for (int t = 0; t < 2; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                      \
         wres[t], (lds_void_ptr)(STG_ + kXBytes + wave * 2048 + t * 1024), 16, woff[t], so, 0, 0);                \
-    so += BK * 2;                                                                                                \
-    so = so == so_end ? so_begin : so;                                                                           \
+    const int next = so + BK * 2 == so_end ? so_begin : so + BK * 2;                                             \
+    so = next == so_start ? so : next;                                                                           \
   }
 
   // acc[i][j]: W rows (output columns) 64 wh + 32 wn + 16 i .. + 15, X rows (output rows) 64 wm + 16 j .. + 15
@@ -168,7 +168,8 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
   // from slab to slab, since computing it anew cost every slab another 40 cycles (301 x 8192, uncut: 37.9 -> 40.1 us).
   const int rot = (int)((a.rounds > 1 ? 5u * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
   const int so_begin = first * (BK * 2), so_end = so_begin + NB * (BK * 2);
-  int so = so_begin + rot * (BK * 2);  // of the next slab to copy
+  const int so_start = so_begin + rot * (BK * 2);
+  int so = so_start;  // of the next slab to copy
   // (NH = 2: four stages, the copies of the next two slabs may stay in flight, those of the third go out)
   SX_COPY(st0)
   SX_COPY(st1)
