@@ -674,8 +674,10 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
 //   gate|up 194 against 186): not from five row tiles on.  (At four, 800 rows, a layer of the 7B shape takes 700 us with
 //   224 rows and 724 with 256; the 70B shape 1835 and 1903.)
 //
-// The rotation: worth 2 to 3 %, at best 15 %, for one or two row tiles, where a launch is bound by the weight stream, about 1 %
-// up to 8 row tiles of whole K; beyond that, and where the parts of a cut K start apart by themselves, it costs up to 1 %.
+// The rotation: worth 2 to 3 %, at best 15 %, for one or two row tiles, where a launch is bound by the weight stream, 1 % and
+// at best 6 up to 8 row tiles (70B O at 1000 rows, two parts of K: 142.7 -> 138.2 us).  Beyond that, and under a last round
+// that is cut from four row tiles on, it gives and takes up to 3 %; parts of less than 20 slabs start apart by themselves
+// and lose up to 5 % (7B O at 320 rows, four parts of 16).
 struct Plan {
   int jb;
   bool prefetch;
@@ -693,7 +695,7 @@ Plan pick_plan(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
   }
   plan_split(a, p.jb, split_ws, split_ws_bytes);
   p.prefetch = p.jb == 8 && can_prefetch;
-  a.rotate = a.tilesM <= (a.split > 1 ? 2 : 8);
+  a.rotate = a.tilesM <= (a.split > 1 && a.full_tiles > 0 ? 3 : 8) && a.K / BK / a.split >= 20;
   return p;
 }
 
