@@ -438,7 +438,8 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
 //               by a scan of the bucket counts and ranked inside their bucket by counting smaller entries.  Where one
 //               bucket holds more than kBucketMax (many equal scores) they go through a sorting network instead.
 // Before, the threshold was a search over 32 bits with a block-wide count each and the order a sorting network of 66
-// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 31 and 14.  Where scores
+// stages with a barrier each: 104 us for the 2048 best of 65536 and 74 us for those of 3200; now 31 and 14.  (In a draft
+// loop, 2048 of 4096 cumulative scores that lie close together: 11 to 53, 25 on average -- buckets overflow.)  Where scores
 // tie, adds to one LDS address and ranking by serial reads had made that slower than the search (65536 equal scores: 194 us
 // in all, the whole step of 2048 x 1000; 374 with them): equal scores need no threshold, the second histogram has copies
 // where many scores share a bin, and ties are ranked 4096 at a time until enough are found: 115.
