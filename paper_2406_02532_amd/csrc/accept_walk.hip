@@ -1112,6 +1112,8 @@ size_t scratch_bytes(int32_t V) { return sx_align_up((size_t)V * 4, 256); }
 
 extern "C" size_t sx_accept_walk_workspace(int32_t T, int32_t V) {
   if (V < 1) return 0;
+  // (one workgroup walks a larger tree, but a buffer sized for it is to serve the smaller ones too)
+  if (T > kStageNodes) T = kStageNodes;
   // many workgroups: the records, and a scratch row for every other workgroup
   const size_t many = walk_by_many(T, V)
                           ? sx_align_up((size_t)T * 8, 256) + (size_t)((T < kNodes ? T : kNodes) - 1) * scratch_bytes(V)
