@@ -733,7 +733,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   extern __shared__ __attribute__((aligned(16))) u64 keys[];  // [kPlaceCap] the set: ~order key << 32 | flat index
   __shared__ __attribute__((aligned(16))) unsigned hist[kSelBins];
   __shared__ int s_wave[kSelThreads / 64];
-  __shared__ int s_cnt, s_own, s_bin, s_above, s_in;
+  __shared__ int s_cnt, s_bad, s_own, s_bin, s_above, s_in;
   u64* const own = keys + kPlaceCap;  // [kSelBins]: this workgroup's entries, by a hash of the flat index
   const int tid = threadIdx.x, lane = tid & 63;
   const int Bsel = min(B, n);
@@ -741,7 +741,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   auto claim = [&](u64 e) {
     if (((unsigned)e * 2654435761u >> 16 & (gridDim.x - 1u)) == blockIdx.x) own[atomicAdd(&s_own, 1)] = e;
   };
-  int W = n;  // size of the set
+  int W = n, bad = 0;  // size of the set, entries that are none
   if (tid == 0) s_own = 0;
   __syncthreads();
   if (!count) {
@@ -797,14 +797,19 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
           start += c;
         }
       }
-      if (tid == 0) s_cnt = 0;
+      if (tid == 0) s_cnt = s_bad = 0;
       __syncthreads();
       thr |= (unsigned)s_bin << shift;
       above = s_above;
       if ((float)s_in * per_sample <= 0.8f * kPlaceCap) break;  // (the same answer in every lane: s_in is read between barriers)
       __syncthreads();
     }
-    const float least = f32_from_order_key(thr);  // (the key is monotonic, and -0 counts as +0 in both)
+    // The set is all keys from thr up, gathered by comparing floats: not less than `least`, its score (the key is monotonic,
+    // and -0 counts as +0 in both).  That takes every NaN too, of which those with the sign (keys below -inf's) do not belong
+    // to the set and are sorted out where the few hits are stored.  Below the key of -inf and above that of +inf there are
+    // only NaN, which `least` cannot be; where the threshold is -inf, candidates of that score are too many for the set.
+    thr = min(max(thr, f32_order_key(-__builtin_huge_valf()) + 1u), f32_order_key(__builtin_huge_valf()));
+    const float least = f32_from_order_key(thr);
     // ---- the set, unless the samples say that it would be too large ---------------------------------------------------
     if ((float)s_in * per_sample <= 1.1f * kPlaceCap) {
       __syncthreads();  // the bins have been read
@@ -818,16 +823,16 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
           const int i = i0 + (u * kSelThreads + tid) * 4;
           if (i + 4 <= n) {
             v[u] = *reinterpret_cast<const f32x4*>(score + i);
-          } else {  // (no score: below every threshold, as no comparison with a NaN holds)
+          } else {  // (no score: below every threshold)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[u][c] = i + c < n ? score[i + c] : __builtin_nanf("");
+            for (int c = 0; c < 4; ++c) v[u][c] = i + c < n ? score[i + c] : -__builtin_huge_valf();
           }
         }
         int hits = 0;
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) hits += v[u][c] >= least ? 1 : 0;
+          for (int c = 0; c < 4; ++c) hits += v[u][c] < least ? 0 : 1;
         int incl = hits;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -841,18 +846,21 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int c = 0; c < 4; ++c)
-            if (v[u][c] >= least) {
-              const u64 e = entry(select_key(v[u][c]), i0 + (u * kSelThreads + tid) * 4 + c);
+            if (!(v[u][c] < least)) {
+              const unsigned key = select_key(v[u][c]);
+              const u64 e = key >= thr ? entry(key, i0 + (u * kSelThreads + tid) * 4 + c) : ~0ull;
               if (at < kPlaceCap) keys[at] = e;
               ++at;
-              claim(e);
+              if (key >= thr) claim(e);
+              else atomicAdd(&s_bad, 1);
             }
       }
       __syncthreads();
       W = s_cnt;
+      bad = s_bad;
     }
   }
-  if (W < Bsel || W > kPlaceCap) {  // (W < Bsel: the samples were off by four deviations)
+  if (W - bad < Bsel || W > kPlaceCap) {  // (too few: the samples were off by four deviations, or -inf is among the picks)
     __syncthreads();
     if (blockIdx.x == 0) select_by_one(score, topk_idx, n, k, B, out_row, out_token, out_score, n_out, keys, hist, s_wave);
     return;

@@ -232,3 +232,28 @@ def test_selection_among_few_candidates(sx, N, k, ties):
         np.testing.assert_array_equal(row, want // k)
         np.testing.assert_array_equal(tok, idx.cpu().numpy().reshape(-1)[want])
         np.testing.assert_array_equal(score, flat[want])
+
+
+@pytest.mark.parametrize("N,k", [(64, 4), (300, 4), (512, 16), (513, 16), (2048, 32), (5000, 128)])
+@pytest.mark.parametrize("B", [3, 200])
+def test_nan_scores_have_one_place_at_every_size(sx, N, k, B):
+    """A score that is NaN is ordered by its bit pattern, before every number without the sign and behind -inf with it,
+    whichever way the picks are selected (few candidates, all in the set, a sampled set, one workgroup), and the order of the
+    others does not change."""
+    V = 300
+    r = np.random.default_rng(N + B)
+    logits = r.standard_normal((N, V)).astype(np.float32)
+    cum = -r.exponential(2.0, N).astype(np.float32)
+    first, last = N // 3, N // 2
+    cum[first] = np.nan
+    cum[last:last + 2] = np.array([0xFFC00000], np.uint32).view(np.float32)[0]
+    lp, idx = sx.row_logsoftmax_topk(to_dev(logits), k)
+    flat = lp.cpu().numpy() + np.where(np.isnan(cum), 0.0, cum).astype(np.float32)[:, None]
+    flat[first], flat[last:last + 2] = np.inf, -np.inf
+    order = np.argsort(-flat.reshape(-1), kind="stable")
+    row, tok, score, n = _run(sx, logits, cum, k, B)
+    want = order[:min(B, N * k)]
+    assert n == len(want)
+    np.testing.assert_array_equal(row, want // k)
+    np.testing.assert_array_equal(tok, idx.cpu().numpy().reshape(-1)[want])
+    assert np.isnan(score[row == first]).all() and not np.isnan(score[(row != first) & (row != last) & (row != last + 1)]).any()
