@@ -443,8 +443,9 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelBins = 4096;
 constexpr unsigned kBucketMax = 32;
 constexpr int kPlaceCap = 8192;     // candidates whose places are counted: beyond that, counting takes longer than histograms
-constexpr int kSelBlocks = 256;     // workgroups at most; a workgroup's share of all flat indices is at most kSelBins (its list)
+constexpr int kSelBlocks = 256;     // workgroups at most
 constexpr int kSamples = 4096;
+constexpr unsigned kShareHash = 2654435761u;  // bits 16 and up of flat index * this: whose entry it is
 // order key of a candidate: never 0, which marks the slots past the end (only one NaN pattern would map there)
 __device__ __forceinline__ unsigned select_key(float v) { return max(f32_order_key(v), 1u); }
 
@@ -721,7 +722,7 @@ __device__ __forceinline__ void select_by_one(const float* __restrict__ score, c
 // In many workgroups: each of them gathers, in LDS, a set of at most kPlaceCap candidates that holds the Bsel best -- all of
 // them, or those from a threshold up that the order keys of 4096 candidates, one out of each 4096th of the list, set a few
 // deviations beyond Bsel -- and its waves count, for their share of the set, the better ones: a ballot and a bit count per 64
-// entries.  All workgroups gather the same set (read 64 times, by 64 compute units at once, 256 KB of scores take them 4 us)
+// entries.  All workgroups gather the same set (read 128 times, by 128 compute units at once, 256 KB of scores take them 4 us)
 // and write disjoint places, so nobody waits for anybody, and the order in which LDS atomics fill a set does not show.  65536
 // candidates, 2048 picks: 22.6 us, by histograms in one workgroup 31 (and where the scores lie close together 30 instead of
 // 150); 3200 candidates 9.5 against 14.2.  From 6144 picks on, where counting would take longer, one workgroup does it.
@@ -734,12 +735,16 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   __shared__ __attribute__((aligned(16))) unsigned hist[kSelBins];
   __shared__ int s_wave[kSelThreads / 64];
   __shared__ int s_cnt, s_bad, s_own, s_bin, s_above, s_in;
-  u64* const own = keys + kPlaceCap;  // [kSelBins]: this workgroup's entries, by a hash of the flat index
+  // [kSelBins]: this workgroup's entries, by a hash of the flat index.  select_blocks() keeps a workgroup's share of all flat
+  // indices below that; a set that is given up for its size may have more hits, of which none is looked at.
+  u64* const own = keys + kPlaceCap;
   const int tid = threadIdx.x, lane = tid & 63;
   const int Bsel = min(B, n);
   auto entry = [](unsigned key, int flat) { return ((u64)~key << 32) | (unsigned)flat; };
   auto claim = [&](u64 e) {
-    if (((unsigned)e * 2654435761u >> 16 & (gridDim.x - 1u)) == blockIdx.x) own[atomicAdd(&s_own, 1)] = e;
+    if (((unsigned)e * kShareHash >> 16 & (gridDim.x - 1u)) != blockIdx.x) return;
+    const int at = atomicAdd(&s_own, 1);
+    if (at < kSelBins) own[at] = e;
   };
   int W = n, bad = 0;  // size of the set, entries that are none
   if (tid == 0) s_own = 0;
@@ -1004,7 +1009,8 @@ namespace {
 
 // dynamic LDS of the select kernel: the set, or by histograms winners and room to place them (B = 8192); more than a launch
 // gets by default: allowed once per device
-constexpr size_t kSelectLds = 131072;  // >= (kPlaceCap + kSelBins) * 8
+constexpr size_t kSelectLds = 131072;
+static_assert(kSelectLds >= (kPlaceCap + kSelBins) * 8, "the set and the list of a workgroup");
 int configure_select_once() {
   static bool configured[64] = {};
   int dev = 0;
@@ -1018,6 +1024,14 @@ int configure_select_once() {
 
 // both kernels of the expansion step on `st`; score / lp / idx hold N*k entries each (every one of them is
 // written by the first kernel before the second reads it: nothing has to be cleared)
+// Workgroups of the selection of Bsel out of n > kSmallSelect candidates: some 20 to 60 entries of the set for each; one
+// alone, by histograms, where the set would be too large.  The set is not known here, but a workgroup's share of all flat
+// indices is: n / blocks and, counted out up to the largest n, 8 more at most -- 2060 of the kSelBins that its list holds.
+int select_blocks(int n, int Bsel) {
+  if (n > kPlaceCap && (Bsel > kPlaceCap * 3 / 4 || n > kSelBlocks * kSelBins / 2)) return 1;
+  return n <= 2048 ? 64 : n <= 4096 ? 128 : n <= kPlaceCap || n > 128 * kSelBins / 2 ? kSelBlocks : 128;
+}
+
 int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, int k, int B, int* out_row,
                     int* out_token, float* out_cum_logp, int* n_out, float* score, float* lp, int* idx,
                     hipStream_t st) {
@@ -1031,10 +1045,8 @@ int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, in
   if (n <= kSmallSelect) {
     small_select_kernel<<<1, kSelThreads, 0, st>>>(score, idx, n, k, B, out_row, out_token, out_cum_logp, n_out);
   } else {
-    // some 20 to 60 entries per workgroup; one alone, by histograms, where the set would be too large
-    const int Bsel = B < n ? B : n;
-    const bool count = n <= kPlaceCap || (Bsel <= kPlaceCap * 3 / 4 && n <= kSelBlocks * kSelBins / 2);
-    const int blocks = !count ? 1 : n <= 2048 ? 64 : n > kPlaceCap || n <= 4096 ? 128 : 256;
+    const int blocks = select_blocks(n, B < n ? B : n);
+    const bool count = blocks > 1;
     select_kernel<<<blocks, kSelThreads, kSelectLds, st>>>(score, idx, n, k, B, count, out_row, out_token, out_cum_logp, n_out);
   }
   sx_prof_end(st);

@@ -257,3 +257,31 @@ def test_nan_scores_have_one_place_at_every_size(sx, N, k, B):
     np.testing.assert_array_equal(row, want // k)
     np.testing.assert_array_equal(tok, idx.cpu().numpy().reshape(-1)[want])
     assert np.isnan(score[row == first]).all() and not np.isnan(score[(row != first) & (row != last) & (row != last + 1)]).any()
+
+
+def test_share_of_a_selecting_workgroup_fits_its_list():
+    """Flat indices are dealt to the selecting workgroups by a hash; whatever the scores, none gets more than its list holds."""
+    bits = (np.arange(1 << 19, dtype=np.uint64) * 2654435761 & 0xFFFFFFFF) >> 16
+    for blocks, upto in ((64, 2048), (128, 4096), (256, 8192), (128, 1 << 18), (256, 1 << 19)):
+        assert np.bincount((bits[:upto] & (blocks - 1)).astype(np.int64)).max() <= min(4096, upto // blocks + 16)
+
+
+@pytest.mark.parametrize("n", [8193, 262144, 262145, 524288, 524289])
+@pytest.mark.parametrize("B", [1, 2048, 6144])
+@pytest.mark.parametrize("misled", [False, True])
+def test_selection_by_samples_up_to_its_limit(sx, n, B, misled):
+    """Sampled sets of one candidate per row, to the last size that takes one and past it.  misled: the samples are all low and
+    hide that nearly every candidate is above the threshold they set; the set is given up, and the picks are the same."""
+    r = np.random.default_rng(n + B)
+    cum = r.standard_normal(n).astype(np.float32)
+    if misled:
+        i = np.arange(4096, dtype=np.uint64)
+        lo, hi = i * n // 4096, (i + 1) * n // 4096
+        cum[lo + (i * 2654435761 % (1 << 32) >> 8) % (hi - lo)] -= 60.0
+    logits = np.zeros((n, 2), np.float32)
+    row, tok, score, got = _run(sx, logits, cum, 1, B)
+    flat = sx.row_logsoftmax_topk(to_dev(logits[:1]), 1)[0].cpu().numpy()[0, 0] + cum
+    want = np.argsort(-flat, kind="stable")[:B]
+    assert got == B and not tok.any()
+    np.testing.assert_array_equal(row, want)
+    np.testing.assert_array_equal(score, flat[want])
