@@ -444,7 +444,7 @@ constexpr int kSelBins = 4096;
 constexpr unsigned kBucketMax = 32;
 constexpr int kPlaceCap = 8192;     // candidates whose places are counted: beyond that, counting takes longer than histograms
 constexpr int kSelBlocks = 256;     // workgroups at most
-constexpr int kSamples = 4096;
+constexpr int kSamplesPerLane = 6;  // at most
 constexpr unsigned kShareHash = 2654435761u;  // bits 16 and up of flat index * this: whose entry it is
 // order key of a candidate: never 0, which marks the slots past the end (only one NaN pattern would map there)
 __device__ __forceinline__ unsigned select_key(float v) { return max(f32_order_key(v), 1u); }
@@ -531,12 +531,15 @@ __device__ __forceinline__ void order_and_emit(unsigned long long* sbuf, unsigne
   }
 }
 
-// sbuf: winners, then room to place them: 2 x next_pow2(Bsel).
+// sbuf: winners, then room to place them: 2 x next_pow2(Bsel).  QUADS > 0 (n <= 4096 QUADS): lane t holds the keys of the
+// candidates 4 (j 1024 + t) .. + 3, j < QUADS, in registers; 0: every pass re-reads them, which beyond 16384 candidates costs
+// less than the code it takes to hold them (8192 of 16200: 33 us with four, 37 re-read).
+template <int QUADS>
 __device__ __forceinline__ void select_by_one(const float* __restrict__ score, const int* __restrict__ topk_idx, int n, int k,
                                               int B, int* __restrict__ out_row, int* __restrict__ out_token,
                                               float* __restrict__ out_score, int* __restrict__ n_out,
                                               unsigned long long* sbuf, unsigned* hist, int* s_wave) {
-  constexpr int BPT = kSelBins / kSelThreads;
+  constexpr int BPT = kSelBins / kSelThreads, R = QUADS > 0 ? QUADS * 4 : 1;
   __shared__ unsigned s_max, s_min, s_big;
   __shared__ int s_pos, s_bin, s_above;
 
@@ -570,6 +573,22 @@ __device__ __forceinline__ void select_by_one(const float* __restrict__ score, c
       }
     }
   };
+  unsigned d[R];  // first the order key (slots past n: 0, below every real key), then its distance from the largest
+  if constexpr (QUADS > 0) {
+    f32x4 v[QUADS];
+#pragma unroll
+    for (int j = 0; j < QUADS; ++j) {
+      const int i = (j * kSelThreads + tid) * 4;
+      if (i + 4 <= n) {
+        v[j] = *reinterpret_cast<const f32x4*>(score + i);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[j][c] = i + c < n ? score[i + c] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < R; ++e) d[e] = ((e / 4) * kSelThreads + tid) * 4 + e % 4 < n ? select_key(v[e / 4][e % 4]) : 0u;
+  }
   unsigned top = 0;
   auto clear = [&]() {
     *reinterpret_cast<u32x4*>(hist + 4 * tid) = u32x4{0u, 0u, 0u, 0u};
@@ -593,27 +612,48 @@ __device__ __forceinline__ void select_by_one(const float* __restrict__ score, c
   }
   __syncthreads();
   unsigned low = 0xFFFFFFFFu;  // one less than the smallest key (a slot past n: the largest number)
-  stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) {
-    top = max(top, max(max(a, b), max(c, e)));
-    low = min(low, min(min(a - 1u, b - 1u), min(c - 1u, e - 1u)));
-  });
+  if constexpr (QUADS > 0) {
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) low = min(low, (unsigned)__shfl_xor((int)low, o, 64));
-  if (lane == 0) atomicMin(&s_min, low);
+    for (int e = 0; e < R; ++e) top = max(top, d[e]);
+  } else {
+    stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int) {
+      top = max(top, max(max(a, b), max(c, e)));
+      low = min(low, min(min(a - 1u, b - 1u), min(c - 1u, e - 1u)));
+    });
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) low = min(low, (unsigned)__shfl_xor((int)low, o, 64));
+    if (lane == 0) atomicMin(&s_min, low);
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) top = max(top, (unsigned)__shfl_xor((int)top, o, 64));
   if (lane == 0) atomicMax(&s_max, top);
   __syncthreads();
   const unsigned kmax = s_max;  // slots past n end up at d == kmax, beyond every real key
   // f(four d, flat index of the first) over all candidates of this lane, in the same number of calls for every lane
+  if constexpr (QUADS > 0) {
+    unsigned differ = 0;
+#pragma unroll
+    for (int e = 0; e < R; ++e) {
+      d[e] = kmax - d[e];
+      differ |= ((e / 4) * kSelThreads + tid) * 4 + e % 4 < n ? d[e] : 0u;
+    }
+    if (differ) s_min = 0;
+    __syncthreads();
+  }
+  const bool equal = QUADS > 0 ? s_min != 0 : s_min + 1u == kmax;
   auto each4 = [&](auto f) {
+    if constexpr (QUADS > 0) {
+#pragma unroll
+      for (int j = 0; j < QUADS; ++j) f(d[4 * j], d[4 * j + 1], d[4 * j + 2], d[4 * j + 3], (j * kSelThreads + tid) * 4);
+      return;
+    }
     stream([&](unsigned a, unsigned b, unsigned c, unsigned e, int i) { f(kmax - a, kmax - b, kmax - c, kmax - e, i); });
   };
 
   // ---- threshold ---------------------------------------------------------------------------------------
   unsigned D = 0xFFFFFFFFu;
   int need = Bsel, ties = Bsel;  // of the candidates in the threshold's last bin: how many are taken, how many there are
-  if (n > Bsel && s_min + 1u == kmax) {  // all scores equal: the first ones are taken
+  if (n > Bsel && equal) {  // all scores equal: the first ones are taken
     D = 0;
     ties = n;
   } else if (n > Bsel) {
@@ -720,12 +760,16 @@ __device__ __forceinline__ void select_by_one(const float* __restrict__ score, c
 }
 
 // In many workgroups: each of them gathers, in LDS, a set of at most kPlaceCap candidates that holds the Bsel best -- all of
-// them, or those from a threshold up that the order keys of 4096 candidates, one out of each 4096th of the list, set a few
-// deviations beyond Bsel -- and its waves count, for their share of the set, the better ones: a ballot and a bit count per 64
-// entries.  All workgroups gather the same set (read 128 times, by 128 compute units at once, 256 KB of scores take them 4 us)
-// and write disjoint places, so nobody waits for anybody, and the order in which LDS atomics fill a set does not show.  65536
-// candidates, 2048 picks: 22.6 us, by histograms in one workgroup 31 (and where the scores lie close together 30 instead of
-// 150); 3200 candidates 9.5 against 14.2.  From 6144 picks on, where counting would take longer, one workgroup does it.
+// them, or those from a threshold up that the order keys of one candidate out of every few set a few deviations beyond Bsel --
+// and its waves count, for their share of the set, the better ones: a ballot and a bit count per 64 entries.  Candidates that
+// tie at the threshold (equal scores; the -inf of dead rows) are not gathered: they fill the places that the set leaves, in
+// index order.  All workgroups gather the same set (read 256 times, by 256 compute units at once, 256 KB of scores take them
+// 4 us) and write disjoint places, so nobody waits for anybody, and the order in which LDS atomics fill a set does not show.
+// 65536 candidates, 2048 picks: 19 us, by histograms in one workgroup 31; where the scores lie close together 24 and 175; with
+// -inf among the picks 22 and 286; all equal 17 and 60.  3200 candidates, 100 picks: 6.3 and 7.8; 8192 candidates, 64
+// picks 4.3 (all of them counted: 11.3) and 10.3.  From 6144 picks on, where counting would take longer, one
+// workgroup does it: 8192 of 16000 33 us.
+template <int QUADS>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ score, const int* __restrict__ topk_idx,
                                                              int n, int k, int B, bool count, int* __restrict__ out_row,
                                                              int* __restrict__ out_token, float* __restrict__ out_score,
@@ -735,8 +779,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   __shared__ __attribute__((aligned(16))) unsigned hist[kSelBins];
   __shared__ int s_wave[kSelThreads / 64];
   __shared__ int s_cnt, s_bad, s_own, s_bin, s_above, s_in;
-  // [kSelBins]: this workgroup's entries, by a hash of the flat index.  select_blocks() keeps a workgroup's share of all flat
-  // indices below that; a set that is given up for its size may have more hits, of which none is looked at.
+  __shared__ unsigned s_tied, s_first, s_mixed;
+  // [kSelBins]: this workgroup's entries, by a hash of the flat index (select_blocks() keeps a workgroup's share of all flat
+  // indices below that)
   u64* const own = keys + kPlaceCap;
   const int tid = threadIdx.x, lane = tid & 63;
   const int Bsel = min(B, n);
@@ -744,44 +789,74 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   auto claim = [&](u64 e) {
     if (((unsigned)e * kShareHash >> 16 & (gridDim.x - 1u)) != blockIdx.x) return;
     const int at = atomicAdd(&s_own, 1);
-    if (at < kSelBins) own[at] = e;
+    if (at < kSelBins) own[at] = e;  // always
   };
   int W = n, bad = 0;  // size of the set, entries that are none
-  if (tid == 0) s_own = 0;
+  unsigned tied = 0;   // key of the score that fills the places which the set leaves
+  if (tid == 0) s_own = s_cnt = s_bad = s_mixed = 0;
+  *reinterpret_cast<u32x4*>(hist + 4 * tid) = u32x4{0u, 0u, 0u, 0u};  // the places so far of `own`
   __syncthreads();
+  auto pad = [&](int i) {  // the set ends with entries worse than any, in whole steps of the count
+    for (; i < (W + 4095 & ~4095); i += kSelThreads) keys[i] = ~0ull;
+  };
   if (!count) {
     W = -1;
-  } else if (n <= kPlaceCap) {
+  } else if (n <= kPlaceCap / 2 || (n <= kPlaceCap && 4 * Bsel > n)) {
     for (int i = tid; i < n; i += kSelThreads) {
       const u64 e = entry(select_key(score[i]), i);
       keys[i] = e;
       claim(e);
     }
+    pad(n + tid);
+    __syncthreads();
   } else {
     // ---- the threshold: the want-th best of the samples, from the upper 14 bits of their keys (32 bins per octave of the
     // scores), and from the next 14 where that bin holds too much ------------------------------------------------------
-    constexpr int E = kSamples / kSelThreads, kBins = 16384, BPT = kBins / kSelThreads;
+    constexpr int E = kSamplesPerLane, kBins = 16384, BPT = kBins / kSelThreads;
+    // A sample per lane takes 0.6 us; fewer of them make a larger set, to be on the safe side, or a set that is missed.  16384
+    // candidates, 256 picks: 10.4 us with one, 11.9 with four; 65536, 2048 picks: 24.3 with one, 19.5 with three, 20.1 with
+    // four, 21.3 with six; 524288, 2048 picks: 59.1, 59.0 and 66.6 with three, six and sixteen, but 6000 picks leave a deviation
+    // to either side with three.  (Fewer samples than candidates: every range below has one.)
+    const int per_lane = n <= 24576 ? 1 : n <= 131072 ? 3 : E, samples = per_lane * kSelThreads;
     unsigned* const bins = reinterpret_cast<unsigned*>(keys);
     unsigned sample[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
+      sample[e] = 0;
+      if (e >= per_lane) continue;
       const unsigned i = e * kSelThreads + tid;
-      const unsigned lo = (unsigned)((u64)i * (unsigned)n / kSamples), hi = (unsigned)((u64)(i + 1) * (unsigned)n / kSamples);
-      sample[e] = select_key(score[lo + (i * 2654435761u >> 8) % (hi - lo)]);  // (rows are sorted: not always the same rank)
+      const unsigned lo = (unsigned)((u64)i * (unsigned)n / samples), hi = (unsigned)((u64)(i + 1) * (unsigned)n / samples);
+      sample[e] = select_key(score[lo + (i * kShareHash >> 8) % (hi - lo)]);  // (rows are sorted: not always the same rank)
     }
-    const float mean = (float)Bsel * (float)kSamples / (float)n, per_sample = (float)n / kSamples;
-    const int want = min((int)(mean + 4.0f * sqrtf(mean) + 8.0f), kSamples);
+    // four deviations beyond Bsel, or midway to what the set holds
+    const float per_sample = (float)n / samples, mean = (float)Bsel / per_sample;
+    const int want = min((int)min(mean + 4.0f * sqrtf(mean) + 8.0f, 0.5f * (mean + kPlaceCap / per_sample)), samples);
     unsigned thr = 0;
     int above = 0;
+    if (tid == 0) s_first = sample[0];
 #pragma unroll 1
     for (int shift = 18; shift >= 4; shift -= 14) {
 #pragma unroll
       for (int i = 0; i < BPT / 4; ++i) *reinterpret_cast<u32x4*>(bins + 4 * (i * kSelThreads + tid)) = u32x4{0u, 0u, 0u, 0u};
       __syncthreads();
+      bool mixed = false;
+#pragma unroll
+      for (int e = 0; e < E; ++e) mixed |= e < per_lane && sample[e] != s_first;
+      if (mixed) s_mixed = 1;
 #pragma unroll
       for (int e = 0; e < E; ++e)
-        if (shift == 18 || (sample[e] ^ thr) >> 18 == 0) atomicAdd(&bins[(sample[e] >> shift) & (kBins - 1)], 1u);
+        if (e < per_lane && (shift == 18 || (sample[e] ^ thr) >> 18 == 0)) {
+          // (many equal scores: one add for the lanes that are here; 64 to one address are 64 adds, one after the other)
+          const unsigned bin = (sample[e] >> shift) & (kBins - 1), one = (unsigned)__builtin_amdgcn_readfirstlane((int)bin);
+          const u64 same = __builtin_amdgcn_ballot_w64(bin == one);
+          if (bin != one) atomicAdd(&bins[bin], 1u);
+          else if (lane == __builtin_ctzll(same)) atomicAdd(&bins[bin], (unsigned)__builtin_popcountll(same));
+        }
       __syncthreads();
+      if (s_mixed == 0) {  // all samples equal
+        tied = s_first;
+        break;
+      }
       u32x4 h[BPT / 4];  // this lane's bins, the highest first
       int mine = 0;
 #pragma unroll
@@ -802,25 +877,41 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
           start += c;
         }
       }
-      if (tid == 0) s_cnt = s_bad = 0;
       __syncthreads();
       thr |= (unsigned)s_bin << shift;
       above = s_above;
-      if ((float)s_in * per_sample <= 0.8f * kPlaceCap) break;  // (the same answer in every lane: s_in is read between barriers)
+      if ((float)s_in * per_sample <= 0.8f * kPlaceCap && s_in <= 2 * want) break;  // (the same answer in every lane: s_in is read between barriers)
       __syncthreads();
     }
+    // Where the threshold is -inf, or one score is so frequent that the bin is too large all the same, the set is what is
+    // above that score, and its first candidates in index order fill the places that the set leaves.
+    constexpr float kInf = __builtin_huge_valf();
+    if (!tied && thr <= f32_order_key(-kInf)) {
+      tied = f32_order_key(-kInf);
+    } else if (!tied && (float)s_in * per_sample > 0.95f * kPlaceCap) {
+      if (tid == 0) s_tied = 0;
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < E; ++e) tied = e < per_lane && (sample[e] ^ thr) >> 4 == 0 ? max(tied, sample[e]) : tied;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) tied = max(tied, (unsigned)__shfl_xor((int)tied, o, 64));
+      if (lane == 0) atomicMax(&s_tied, tied);
+      __syncthreads();
+      tied = s_tied;
+    }
+    if (tied) thr = tied + 1u;
     // The set is all keys from thr up, gathered by comparing floats: not less than `least`, its score (the key is monotonic,
     // and -0 counts as +0 in both).  That takes every NaN too, of which those with the sign (keys below -inf's) do not belong
-    // to the set and are sorted out where the few hits are stored.  Below the key of -inf and above that of +inf there are
-    // only NaN, which `least` cannot be; where the threshold is -inf, candidates of that score are too many for the set.
-    thr = min(max(thr, f32_order_key(-__builtin_huge_valf()) + 1u), f32_order_key(__builtin_huge_valf()));
+    // to the set and are sorted out where the few hits are stored.  `least` itself cannot be a NaN: not below the key of
+    // -inf + 1, and where it is above that of +inf (many equal NaN) the set is given up.
     const float least = f32_from_order_key(thr);
-    // ---- the set, unless the samples say that it would be too large ---------------------------------------------------
-    if ((float)s_in * per_sample <= 1.1f * kPlaceCap) {
+    // ---- the set ---------------------------------------------------------------------------------------------------------
+    W = -1;
+    if (least <= kInf) {
       __syncthreads();  // the bins have been read
-      // 64 scores a lane, all on their way together; a lane's hits go behind those of the lanes before it, and a wave asks for
+      // 64 scores a lane (16 where that is all), all on their way together; a lane's hits go behind those of the lanes before it, and a wave asks for
       // room once (a ballot and an atomic per element held the waves up for 20 us: every fourth has a hit)
-      constexpr int U = 16;
+      constexpr int U = QUADS > 0 ? QUADS : 16;
       for (int i0 = 0; i0 < n; i0 += U * 4 * kSelThreads) {
         f32x4 v[U];
 #pragma unroll
@@ -851,70 +942,105 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
         for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int c = 0; c < 4; ++c)
-            if (!(v[u][c] < least)) {
-              const unsigned key = select_key(v[u][c]);
-              const u64 e = key >= thr ? entry(key, i0 + (u * kSelThreads + tid) * 4 + c) : ~0ull;
-              if (at < kPlaceCap) keys[at] = e;
+            if (!(v[u][c] < least)) {  // (as little as possible here: 64 copies of it)
+              if (at < kPlaceCap) keys[at] = (u64)__float_as_uint(v[u][c]) << 32 | (unsigned)(i0 + (u * kSelThreads + tid) * 4 + c);
               ++at;
-              if (key >= thr) claim(e);
-              else atomicAdd(&s_bad, 1);
             }
       }
       __syncthreads();
       W = s_cnt;
+      for (int i = tid; i < min(W, kPlaceCap); i += kSelThreads) {
+        const unsigned key = select_key(__uint_as_float((unsigned)(keys[i] >> 32)));
+        const u64 e = key >= thr ? entry(key, (int)(unsigned)keys[i]) : ~0ull;
+        keys[i] = e;
+        if (key >= thr) claim(e);
+        else atomicAdd(&s_bad, 1);
+      }
+      if (W <= kPlaceCap) pad(W + tid);
+      __syncthreads();
       bad = s_bad;
     }
   }
-  if (W - bad < Bsel || W > kPlaceCap) {  // (too few: the samples were off by four deviations, or -inf is among the picks)
-    __syncthreads();
-    if (blockIdx.x == 0) select_by_one(score, topk_idx, n, k, B, out_row, out_token, out_score, n_out, keys, hist, s_wave);
-    return;
-  }
-  // ---- places: a wave holds 1/16 of the set, four entries a lane at a time, and counts for every entry of the workgroup's
-  // list (entry e in lane e % 64) how many of them are better ---------------------------------------------------------------
-  for (int i = W + tid; i < (W + 4095 & ~4095); i += kSelThreads) keys[i] = ~0ull;
-  __syncthreads();
-  const int m = s_own;
-  for (int e = tid; e < m; e += kSelThreads) hist[e] = 0;  // the places so far
-  __syncthreads();
-  for (int j0 = 0; j0 < W; j0 += 4 * kSelThreads) {
-    u32x2 other[4];
+  const int rest = max(Bsel - (W - bad), 0);
+  bool alone = W < 0 || (rest > 0 && !tied) || W > kPlaceCap;  // (too few: the samples were off by four deviations)
+  if (!alone) {
+    // ---- places: a wave holds 1/16 of the set, four entries a lane at a time, and counts for every entry of the workgroup's
+    // list (entry e in lane e % 64) how many of them are better ---------------------------------------------------------------
+    const int m = s_own;
+    for (int j0 = 0; j0 < W; j0 += 4 * kSelThreads) {
+      u32x2 other[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) other[r] = *reinterpret_cast<const u32x2*>(keys + j0 + r * kSelThreads + tid);
-    for (int e0 = 0; e0 < m; e0 += 64) {
-      const u64 mine = own[min(e0 + lane, m - 1)];
-      int place = 0;
-      for (int e = 0; e < min(64, m - e0); ++e) {
-        const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(mine >> 32), e);
-        int c = 0;
-        u64 equal = 0;
+      for (int r = 0; r < 4; ++r) other[r] = *reinterpret_cast<const u32x2*>(keys + j0 + r * kSelThreads + tid);
+      for (int e0 = 0; e0 < m; e0 += 64) {
+        const u64 mine = own[min(e0 + lane, m - 1)];
+        int place = 0;
+        for (int e = 0; e < min(64, m - e0); ++e) {
+          const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(mine >> 32), e);
+          int c = 0;
+          u64 equal = 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(other[r][1] < hi));
-          equal |= __builtin_amdgcn_ballot_w64(other[r][1] == hi);
+          for (int r = 0; r < 4; ++r) {
+            c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(other[r][1] < hi));
+            equal |= __builtin_amdgcn_ballot_w64(other[r][1] == hi);
+          }
+          if (equal) {
+            const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)mine, e);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(other[r][1] == hi && other[r][0] < lo));
+          }
+          place = lane == e ? c : place;
         }
-        if (equal) {
-          const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)mine, e);
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(other[r][1] == hi && other[r][0] < lo));
-        }
-        place = lane == e ? c : place;
+        if (e0 + lane < m && place) atomicAdd(&hist[e0 + lane], (unsigned)place);
       }
-      if (e0 + lane < m && place) atomicAdd(&hist[e0 + lane], (unsigned)place);
     }
+    __syncthreads();
+    for (int e = tid; e < m; e += kSelThreads) {
+      const int p = (int)hist[e];
+      if (p < Bsel) {
+        const unsigned flat = (unsigned)own[e];
+        out_row[p] = (int)(flat / (unsigned)k);
+        out_token[p] = topk_idx[flat];
+        out_score[p] = score[flat];
+      }
+    }
+    if (blockIdx.x != gridDim.x - 1) return;
+    // ---- the last workgroup: the first `rest` candidates of key `tied`, 16384 candidates at a time ---------------------------
+    int found = 0;
+    for (int i0 = 0; i0 < n && found < rest; i0 += 16 * kSelThreads) {
+      const int i = i0 + 16 * tid;
+      f32x4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (i + 4 * u + 4 <= n) {
+          v[u] = *reinterpret_cast<const f32x4*>(score + i + 4 * u);
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[u][c] = i + 4 * u + c < n ? score[i + 4 * u + c] : 0.f;
+        }
+      }
+      unsigned tie = 0;
+#pragma unroll
+      for (int c = 0; c < 16; ++c)
+        if (i + c < n && select_key(v[c / 4][c % 4]) == tied) tie |= 1u << c;
+      int rank = found + block_exclusive_scan(__builtin_popcount(tie), s_wave);
+      if (tid == kSelThreads - 1) s_cnt = rank + __builtin_popcount(tie);
+      for (; tie && rank < rest; tie &= tie - 1, ++rank) {
+        const int flat = i + __builtin_ctz(tie), p = Bsel - rest + rank;
+        out_row[p] = flat / k;
+        out_token[p] = topk_idx[flat];
+        out_score[p] = score[flat];
+      }
+      __syncthreads();
+      found = s_cnt;
+      __syncthreads();
+    }
+    alone = found < rest;  // NaN with the sign are among the picks (the others' places are the same)
   }
+  if (blockIdx.x != gridDim.x - 1) return;
   __syncthreads();
-  for (int e = tid; e < m; e += kSelThreads) {
-    const int p = (int)hist[e];
-    if (p < Bsel) {
-      const unsigned flat = (unsigned)own[e];
-      out_row[p] = (int)(flat / (unsigned)k);
-      out_token[p] = topk_idx[flat];
-      out_score[p] = score[flat];
-    }
-  }
-  if (blockIdx.x == 0 && tid == 0) n_out[0] = Bsel;
+  if (alone) select_by_one<QUADS>(score, topk_idx, n, k, B, out_row, out_token, out_score, n_out, keys, hist, s_wave);
+  else if (tid == 0) n_out[0] = Bsel;
 }
 
 // The same for few candidates in one workgroup (64 candidates: 2.4 us, 6.3 by histograms).  Counting one key per lane grows
@@ -1017,7 +1143,8 @@ int configure_select_once() {
   SX_HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= 64) return SX_ERR_HIP;
   if (configured[dev]) return SX_OK;
-  SX_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectLds));
+  const void* forms[] = {reinterpret_cast<const void*>(&select_kernel<0>), reinterpret_cast<const void*>(&select_kernel<4>)};
+  for (const void* f : forms) SX_HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectLds));
   configured[dev] = true;
   return SX_OK;
 }
@@ -1029,7 +1156,7 @@ int configure_select_once() {
 // indices is: n / blocks and, counted out up to the largest n, 8 more at most -- 2060 of the kSelBins that its list holds.
 int select_blocks(int n, int Bsel) {
   if (n > kPlaceCap && (Bsel > kPlaceCap * 3 / 4 || n > kSelBlocks * kSelBins / 2)) return 1;
-  return n <= 2048 ? 64 : n <= 4096 ? 128 : n <= kPlaceCap || n > 128 * kSelBins / 2 ? kSelBlocks : 128;
+  return n <= 2048 ? 64 : kSelBlocks;
 }
 
 int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, int k, int B, int* out_row,
@@ -1047,7 +1174,8 @@ int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, in
   } else {
     const int blocks = select_blocks(n, B < n ? B : n);
     const bool count = blocks > 1;
-    select_kernel<<<blocks, kSelThreads, kSelectLds, st>>>(score, idx, n, k, B, count, out_row, out_token, out_cum_logp, n_out);
+    const auto form = n <= 4 * 4 * kSelThreads ? select_kernel<4> : select_kernel<0>;
+    form<<<blocks, kSelThreads, kSelectLds, st>>>(score, idx, n, k, B, count, out_row, out_token, out_cum_logp, n_out);
   }
   sx_prof_end(st);
   SX_LAUNCH_CHECK();

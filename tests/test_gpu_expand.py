@@ -266,8 +266,7 @@ def test_share_of_a_selecting_workgroup_fits_its_list():
         assert np.bincount((bits[:upto] & (blocks - 1)).astype(np.int64)).max() <= min(4096, upto // blocks + 16)
 
 
-@pytest.mark.parametrize("n", [8193, 262144, 262145, 524288, 524289])
-@pytest.mark.parametrize("B", [1, 2048, 6144])
+@pytest.mark.parametrize("n,B", [(8193, 2048), (262144, 6144), (262145, 1), (524288, 6144), (524289, 2048)])
 @pytest.mark.parametrize("misled", [False, True])
 def test_selection_by_samples_up_to_its_limit(sx, n, B, misled):
     """Sampled sets of one candidate per row, to the last size that takes one and past it.  misled: the samples are all low and
@@ -282,6 +281,41 @@ def test_selection_by_samples_up_to_its_limit(sx, n, B, misled):
     row, tok, score, got = _run(sx, logits, cum, 1, B)
     flat = sx.row_logsoftmax_topk(to_dev(logits[:1]), 1)[0].cpu().numpy()[0, 0] + cum
     want = np.argsort(-flat, kind="stable")[:B]
+    assert got == B and not tok.any()
+    np.testing.assert_array_equal(row, want)
+    np.testing.assert_array_equal(score, flat[want])
+
+
+@pytest.mark.parametrize("n,B", [(4097, 40), (8193, 8192), (16384, 6144), (16385, 40), (24577, 6144), (131073, 2000)])
+@pytest.mark.parametrize("kind", ["equal", "few above", "dead", "dead and signed nan", "two values", "close"])
+def test_ties_at_the_threshold_fill_the_picks_in_index_order(sx, n, B, kind):
+    """More candidates of one score, -inf among them, than there are places: those above it first, then the lowest indices,
+    wherever they lie and whichever form selects."""
+    r = np.random.default_rng(n + B)
+    cum = np.full(n, -3.5, np.float32)
+    if kind == "few above":
+        at = r.choice(n, B // 3, replace=False)
+        cum[at] = -3.5 + r.integers(1, 50, B // 3).astype(np.float32) / 16
+    elif kind.startswith("dead"):
+        cum[:] = -np.inf
+        live = r.choice(n, B // 2, replace=False)
+        cum[live] = r.standard_normal(B // 2).astype(np.float32)
+        if kind != "dead":  # so many that the -inf do not fill the picks
+            rest = np.setdiff1d(np.arange(n), live)
+            cum[rest[:len(rest) - B // 4]] = np.array([0xFFC00000], np.uint32).view(np.float32)[0]
+    elif kind == "two values":
+        cum[r.random(n) < 0.5] = 0.0
+        cum[r.random(n) < 0.1] = -0.0
+    elif kind == "close":
+        cum += 1e-6 * r.integers(0, 4, n).astype(np.float32)
+    logits = np.zeros((n, 2), np.float32)
+    row, tok, score, got = _run(sx, logits, cum, 1, B)
+    flat = sx.row_logsoftmax_topk(to_dev(logits[:1]), 1)[0].cpu().numpy()[0, 0] + cum
+    signed = np.isnan(flat)  # behind -inf
+    want = np.argsort(np.where(signed, np.inf, -flat) + 0.0, kind="stable")
+    if signed.any():
+        want = np.concatenate([want[~signed[want]], np.flatnonzero(signed)])
+    want = want[:B]
     assert got == B and not tok.any()
     np.testing.assert_array_equal(row, want)
     np.testing.assert_array_equal(score, flat[want])
