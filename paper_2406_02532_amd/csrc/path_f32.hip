@@ -207,12 +207,14 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
-// exp(x), x <= 0 or NaN, to about an ulp: the rounding of x log2(e) comes back as a factor.  (A tenth of the code of expf.)
+// exp(x), x <= 0 or NaN, to 2 ulp: 2^h of the hardware, h the rounding of x log2(e); what h has lost, to the product and to
+// the constant (whose second part it takes: without it 5 ulp at -20 and 20 at -85), comes back as a factor.  (A tenth of the
+// code of expf.)
 __device__ __forceinline__ float exp_neg(float x) {
-  constexpr float l2e = 1.4426950408889634f, ln2 = 0.6931471805599453f;
+  constexpr float l2e = 1.4426950408889634f, l2e_low = (float)(1.4426950408889634 - (double)l2e), ln2 = 0.6931471805599453f;
   x = x < -200.f ? -200.f : x;
   const float h = x * l2e, e = __builtin_amdgcn_exp2f(h);
-  return __builtin_fmaf(e, __builtin_fmaf(x, l2e, -h) * ln2, e);
+  return __builtin_fmaf(e, __builtin_fmaf(x, l2e_low, __builtin_fmaf(x, l2e, -h)) * ln2, e);
 }
 
 template <int W, int NI>  // element (i, e) of a lane: (i * 16 + lane % 16) * W + e, i < NI
