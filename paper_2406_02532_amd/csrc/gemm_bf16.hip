@@ -349,7 +349,10 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   // XCD stay in step with each other, since they share the operand lines in its L2 (rotated against each other they are
   // up to 8 % slower at 2048 rows).
   const int rot = SHARE || !a.rotate ? 0 : xcd * NB / 8;
+  // (The waits count operations, so the slabs' copies have to go out in this order; they write arrays of their own, and
+  // nothing else keeps the compiler from mixing them.)
   SX_COPY(stA, SX_OFFSET(0))
+  asm volatile("" ::: "memory");
   SX_COPY(stB, SX_OFFSET(1))
   if (SHARE) {
     // The in-loop barriers let the two youngest operations stay in flight, taking them to be a slab's two
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     pfx = __builtin_amdgcn_raw_buffer_load_b32(xres, pfxoff, pso, 0);
     pfw = __builtin_amdgcn_raw_buffer_load_b32(pfwres, pfwoff, pso, 0);
   }
-  if (NS == 3) { SX_COPY(stC, SX_OFFSET(2)) }
+  if (NS == 3) { asm volatile("" ::: "memory"); SX_COPY(stC, SX_OFFSET(2)) }
   if (TOUCH) { asm volatile("" ::: "memory"); SX_TOUCH(2 + kAhead) asm volatile("" ::: "memory"); }
   SX_WAIT_BARRIER(wait_vm((NS - 1) * kCopies + (SHARE ? 2 : TOUCH ? 1 : 0)))
   _Pragma("unroll") for (int i = 0; i < 8; ++i) { SX_READW(stA, fw0, i, kc0) SX_READX(stA, fx0, i, kc0) }

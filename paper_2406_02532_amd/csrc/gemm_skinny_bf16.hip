@@ -181,8 +181,11 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
   const int so_start = so_begin + rot * (BK * 2);
   int so = so_start;  // of the next slab to copy
   // (NH = 2: four stages, the copies of the next two slabs may stay in flight, those of the third go out)
+  // (the waits count copies, which must go out slab by slab: nothing else orders writes to different arrays)
   SX_COPY(st0)
+  asm volatile("" ::: "memory");
   SX_COPY(st1)
+  asm volatile("" ::: "memory");
   int s = 0;
   if (NH == 1) {
     for (; s + 3 <= NB; s += 3) {

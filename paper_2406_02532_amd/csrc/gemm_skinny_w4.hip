@@ -164,6 +164,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_skinny_w4_kernel(W4Args a) {
   const int NB = (kpart + 1) * nb_all / a.split - first, last = first + NB - 1;
   Packed pw0 = load_w(first);
   SX_COPY(sx0, first)
+  asm volatile("" ::: "memory");  // (the waits count copies: in this order)
   SX_COPY(sx1, min(first + 1, last))
   SX_DEQUANT(sw0, pw0)
   pw0 = load_w(min(first + 1, last));

@@ -244,6 +244,7 @@ __global__ __launch_bounds__(kThreads) void gemm_w4_regs_kernel(W4RegArgs a) {
   SX_COPY(sx0, first_slab)
   SX_PAIR(w0, w1, 0)
   SX_COPY(sx1, SX_SLAB_AT(1))
+  asm volatile("" ::: "memory");  // (the waits count operations: in this order)
   SX_COPY(sx2, SX_SLAB_AT(2))
   SX_PAIR(w2, w3, 2)
   SX_FILL(first_slab, first_slab + min(NB, par_slabs))
