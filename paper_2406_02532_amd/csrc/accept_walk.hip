@@ -42,27 +42,48 @@ constexpr int kListCap = 1024;   // elements kept in LDS
 constexpr int kStageNodes = 4096;  // the parents of trees up to this size are read once, into LDS
 
 // The walk by many workgroups.  What a step draws depends on its node alone (the uniforms are keyed by position, that is
-// by depth), so the steps need not wait for each other: a first launch takes the step at each of the first kNodes nodes of
-// the tree at once, one workgroup per node, and records token and child; a second one follows the records to the first
-// node without one, takes the steps at it and at the nodes below it, and follows those; from where that ends, if it does
-// not end the walk, its first workgroup goes on alone.  Draft trees come in the order of a best-first search, so the path
-// is mostly among the first nodes, and the subtree below a node late in the order is small: over simulated trees of 64 to
-// 2048 nodes and walks of 7 to 20 steps, 64 nodes a launch leave the last workgroup no step (32: 0.3 of one, 16: 1.2).
-// More than 64 make the rows wait for each other in memory: 2048 nodes, V = 128256 50.5 us with 64, 61.8 with 256.
-// Measured against the walk by one workgroup (us, means of four walks of 3 to 19 steps): V = 32000, 64 nodes 47 -> 14, 2048
-// nodes 87 -> 29; V = 128256, 384 nodes 148 -> 33, by ratio 201 -> 46; rows of which every token counts (t = 1, top_p = 1)
-// V = 32000 125 -> 39.  A walk that ends at its first node pays for the second launch: N(0, 1) rows 43 -> 47 at V = 32000,
-// 133 -> 145 at 128256.
+// by depth), so the steps need not wait for each other: one launch, in which workgroup i takes the step at node i, i < kNodes,
+// at once, and records token and child.  The first one (the walker) goes on from node 0 along the records; where they end it
+// takes the step itself, and the others, who have followed them to the same node, the steps at the nodes below, in index
+// order; and so on.  Nobody waits but for a bounded time: the walker can take every step itself, and the others leave when the
+// walk has ended or does not come on.  Draft trees come in the order of a best-first search, so the path is mostly among the
+// first nodes, and the subtree below a node late in the order is small.  More than 64 workgroups make the rows wait for each
+// other in memory: 2048 nodes, V = 128256 50.5 us with 64, 61.8 with 256.
+// us, means over walks of 3 to 19 steps: by one workgroup | in two launches, the second at the nodes below the first record
+// missing after the first | in one.  V = 32000: 64 nodes 54 | 14.0 | 13.3, 2048 nodes 95 | 30.7 | 24.6; V = 128256: 384 nodes
+// 188 | 34.6 | 35.7, by ratio 232 | 45.8 | 45.5, 2048 nodes by ratio 295 | 71.6 | 50.8.  Flat rows, where the walk ends at its
+// first node: V = 32000 43.4 | 46.8 | 46.1, t = 1, top_p = 1 25.3 | 28.5 | 26.6; V = 128256 133 | 144 | 134.6.  (What is left
+// of that is code: the walker without the others takes as long.)
 constexpr int kNodes = 64;
-constexpr int kSmallVocab = 4096;  // up to here four waves walk alone: a step takes them 1 us, less than a launch
-constexpr int kSpecDepth = 32;   // nodes further below the walk's position are not taken ahead of it
-constexpr int kLooks = 8;        // times (of 1 to 2 us) that the last workgroup looks for a step in progress
-// a node's record: the child (or none) + 1 << 32 | token << 3 | flags
-constexpr u64 kRecValid = 1, kRecError = 2, kRecPending = 4;
-constexpr unsigned kRecToken = 0x3FFFF;
-// A row whose Z is certainly above this (the elements of an overflowing list come to it alone) is so flat that the walk
-// hardly goes on behind it.  Such rows, the slow ones, are not taken ahead: taken, they cost a walk that ends at its first
-// node 12 us of 133 at V = 128256, in memory traffic.
+constexpr int kSmallVocab = 4096;  // up to here four waves walk alone: a step takes them 1 us
+constexpr int kSpecDepth = 32;   // nodes further below node 0, or the walker's, are not taken ahead of the walk
+// Words of the workspace.  [0]: the board, where the walker posts its own steps; [i]: the record of node i; [kNodes + i - 1]: of
+// the node that workgroup i has taken since.  Fields: state, token (board: depth of the child), child or none + 1, node, tag.
+// The tag makes words of this launch known from what was in the workspace before: the walker begins by reading them all and
+// posts a tag that none of them has.  Who publishes uses the tag on the board; a tag from before the walker's post is on no
+// word that the walker would believe, since the one it posts differs from it.
+constexpr unsigned kDone = 0, kDoneError = 1, kPending = 2, kDeclined = 3;  // records
+constexpr unsigned kBegun = 0, kWalking = 1, kEnded = 2;                    // the board
+constexpr int kWords = 2 * kNodes;
+constexpr unsigned kTokenMax = 0x3FFFF;
+__device__ __forceinline__ unsigned long long pack_word(unsigned tag, int node, int child, unsigned token, unsigned state) {
+  return (unsigned long long)tag << 48 | (unsigned long long)node << 33 | (unsigned long long)(child + 1) << 20 | token << 2 | state;
+}
+// the same value in every lane, told to the compiler: what depends on it stays in scalar registers and branches.  (A walk's node
+// as a vector register, from the records in LDS, cost a flat step 2.5 us in longer code.)
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ unsigned long long uniform(unsigned long long v) {
+  return (unsigned long long)(unsigned)uniform((int)(v >> 32)) << 32 | (unsigned)uniform((int)v);
+}
+struct Word {
+  unsigned tag, state, token;
+  int node, child;
+  __device__ __forceinline__ explicit Word(unsigned long long w)
+      : tag((unsigned)(w >> 48)), state((unsigned)w & 3u), token((unsigned)(w >> 2) & kTokenMax), node((int)(w >> 33) & 0xFFF),
+        child((int)((unsigned)(w >> 20) & 0x1FFFu) - 1) {}
+};
+// A row of more candidates than the list holds and Z above this is so flat that the walk hardly goes on behind it.  Such
+// rows, the slow ones, are not taken ahead.
 constexpr float kFlat = 8.0f;
 
 __device__ __forceinline__ u64 mix24(u64 seed, long long position) {  // the uniform of a position, in units of 2^-24
@@ -148,40 +169,48 @@ struct Const {
 // from memory, after the first one from L2.  (Held in registers the row cost more than it saved: 32 unrolled copies of
 // every pass's body outgrew the instruction cache, and the rest of the kernel spilled.)  SI: acceptance by the ratio of
 // target and draft probability.
-// MANY: the walk by many workgroups, `second` saying which of the two launches this is (one instance for both: as an
-// instance of its own the first one had its variables in scratch memory, 63 us instead of 43 for a flat row).
-template <int NT, bool INLDS, bool SI, bool MANY>
-__global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict__ logits,
-                                                         const float* __restrict__ draft_probs,
-                                                         const int* __restrict__ tokens,
-                                                         const int* __restrict__ parent, int T, int V,
-                                                         float temperature, float top_p, u64 seed,
-                                                         int pos0, int* __restrict__ path_out,
-                                                         int* __restrict__ tokens_out, int* __restrict__ n_out,
-                                                         float* __restrict__ scratch, u64* __restrict__ rec,
-                                                         bool second, int* __restrict__ status) {
+// MANY: the walk by many workgroups.
+// AHEAD: the workgroup is one of the others, not the walker.
+template <int NT, bool SI>
+struct Shared {
+  u64 hist[kBins];
+  u64 list[kListCap];  // id << 32 | bits of e
+  u64 wsum[NT / 64], low, above;
+  float plist[SI ? kListCap : 1], redf[16], px;
+  int redi[16], n, nl, bin, token, child, err, pick, hops;
+  unsigned tag;
+  short par[kStageNodes];
+};
+template <int NT, bool INLDS, bool SI, bool MANY, bool AHEAD>
+__device__ __forceinline__ void walk_steps(const float* __restrict__ logits, const float* __restrict__ draft_probs,
+                                           const int* __restrict__ tokens, const int* __restrict__ parent, int T, int V,
+                                           float temperature, float top_p, u64 seed, int pos0, int* __restrict__ path_out,
+                                           int* __restrict__ tokens_out, int* __restrict__ n_out, float* __restrict__ scratch,
+                                           u64* __restrict__ rec, int* __restrict__ status, Shared<NT, SI>& sh,
+                                           float* const row) {
   constexpr int NW = NT / 64;
   constexpr int BPT = kBins / NT;  // bins per lane in a scan
-  __shared__ u64 hist[kBins];
-  __shared__ u64 list[kListCap];   // id << 32 | bits of e
-  __shared__ float plist[SI ? kListCap : 1];
-  __shared__ short s_par[kStageNodes];
-  extern __shared__ __attribute__((aligned(1024))) float row[];  // INLDS: V rounded up to 4 NT
-  __shared__ float redf[16];
-  __shared__ int redi[16];
-  __shared__ u64 s_wsum[NW];
-  __shared__ u64 s_low, s_above;
-  __shared__ int s_n, s_nl, s_bin, s_token, s_child, s_err, s_pick, s_hops;
-  __shared__ float s_px;
+  constexpr bool ahead = AHEAD;
+  u64(&hist)[kBins] = sh.hist;
+  u64(&list)[kListCap] = sh.list;
+  auto& plist = sh.plist;
+  auto& redf = sh.redf;
+  auto& redi = sh.redi;
+  auto& s_par = sh.par;
+  auto& s_wsum = sh.wsum;
+  u64 &s_low = sh.low, &s_above = sh.above;
+  int &s_n = sh.n, &s_nl = sh.nl, &s_bin = sh.bin, &s_token = sh.token, &s_child = sh.child, &s_err = sh.err, &s_pick = sh.pick,
+      &s_hops = sh.hops;
+  unsigned& s_tag = sh.tag;
+  float& s_px = sh.px;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float NEG_INF = -__builtin_huge_valf();
 
-  const bool walker = !MANY || (second && blockIdx.x == 0);  // writes the results
-  // the scratch row: of the first workgroup at `scratch`, of the others behind the records (all pieces on 256 bytes)
-  float* const ebuf = MANY && blockIdx.x > 0 ? reinterpret_cast<float*>(rec) + ((T * 2 + 63) & ~63) +
-                                                   (size_t)(blockIdx.x - 1) * (size_t)((V + 63) & ~63)
-                                             : scratch;
-  const bool ahead = MANY && blockIdx.x > 0;  // takes a step that the walk may not come to
+  const int who = AHEAD ? (int)(blockIdx.x - (blockIdx.x >> 3)) : 0;
+  const int words = min(T, kWords);
+  // the scratch row: of the walker at `scratch`, of the others behind the words (all pieces on 256 bytes)
+  float* const ebuf =
+      ahead ? reinterpret_cast<float*>(rec) + ((words * 2 + 63) & ~63) + (size_t)(who - 1) * (size_t)((V + 63) & ~63) : scratch;
   const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
   auto copy_row = [&](const float* x) {  // copies past the end of the row write zeros
     const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, V * 4, 0x00020000);
@@ -196,21 +225,17 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
                                                    (b0 + wave * 256 + c * 64 + lane) * 4, 0, 0, 0);
     }
   };
-  if (MANY && second && (rec[0] & kRecValid) && (rec[0] >> 32) == 0) return;  // the walk ended at node 0: written already
-  int cur = 0, depth = 0, n = 0;
+  auto word = [&](int i) { return __hip_atomic_load(rec + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto post = [&](int i, u64 w) { __hip_atomic_store(rec + i, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  int cur = who, depth = 0, n = 0;
   bool copied = false;  // the row of `cur` is on its way already
-  if (MANY && !second) {
-    cur = blockIdx.x;
-    if constexpr (INLDS) {
-      copy_row(logits + (size_t)cur * (size_t)V);
-      copied = true;
-    }
-    for (int j = gridDim.x + cur * NT + tid; j < T; j += gridDim.x * NT) rec[j] = 0;
+  if (MANY && INLDS) {
+    copy_row(logits + (size_t)cur * (size_t)V);
+    copied = true;
   }
   if (tid == 0) {
-    if (!MANY || (!second && cur == 0)) status[0] = (parent[0] != -1) ? SX_ERR_TREE : SX_OK;  // node 0 must be the root
+    if (!ahead) status[0] = (parent[0] != -1) ? SX_ERR_TREE : SX_OK;  // node 0 must be the root
     s_err = 0;
-    s_pick = -1;
   }
   const bool staged = MANY || T <= kStageNodes;
   if (staged)
@@ -293,144 +318,163 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
     return min(block * 128 + s_bin, V - 1);
   };
 
-  // ---- many workgroups: which node is this workgroup's ----------------------------------------------------------------
-  u64* const srec = reinterpret_cast<u64*>(row);  // second launch: the records, where the row comes later
-  auto publish = [&](u64 r) {
-    if (tid == 0) __hip_atomic_store(rec + cur, r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  // the walk as far as the records go (every lane follows it): the first node without one, or -1 where the walk has ended
-  auto follow = [&]() {
-    while (cur >= 0) {
-      const u64 r = srec[cur];
-      if (!(r & kRecValid)) break;
-      if (walker && tid == 0) {
-        path_out[n] = cur;
-        tokens_out[n] = (int)(r >> 3) & (int)kRecToken;
-        if (r & kRecError) s_err = 1;
+  // ---- many workgroups ------------------------------------------------------------------------------------------------
+  // One wave, all words in two registers of it: along the records from node `at`, its depth beside it, to the first node that
+  // has none (-1: the walk ends); true if the step there is in progress.  found(node, record) for every record passed.
+  auto chase = [&](u64 w0, u64 w1, unsigned tag, int& at, int& dep, auto found) -> bool {
+    while (at >= 0) {
+      u64 w;
+      if (at < kNodes) {
+        w = lane_u64(w0, at);
+      } else {
+        const u64 who_has = __builtin_amdgcn_ballot_w64(kNodes + lane < words && Word(w1).tag == tag && Word(w1).node == at);
+        if (who_has == 0) return false;
+        w = lane_u64(w1, __builtin_ctzll(who_has));
       }
-      ++n;
-      ++depth;
-      const int next = (int)(r >> 32) - 1;
-      cur = next > cur ? next : -1;
+      const Word r(w);
+      if (r.tag != tag || r.node != at) return true;  // (of the first kNodes: not there yet)
+      if (r.state > kDoneError) return r.state == kPending;
+      found(at, r);
+      ++dep;
+      at = r.child > at ? r.child : -1;
     }
+    return false;
   };
-  if (MANY && !second) {
+  // One of the others: its step's result, and the next node if it finds where the walker is; false: nothing more to do.
+  // They look for that (some 1.3 us a time) about as long as a peaked row's step takes: flat rows take several times as long,
+  // a walk that has come to one is nearly over, and they have left before it ends.
+  const int polls = who <= T - kNodes ? 12 + V / 4096 : 0;
+  int slot = who, seen = 0;
+  unsigned slot_tag = 0;  // of the words that led to the step's node; in the first step what is on the board near its end
+  auto publish_and_next = [&](int child, int tok, unsigned state) -> bool {
+    __syncthreads();
+    if (wave == 0) {
+      if ((unsigned)tok > kTokenMax) state = kDeclined;  // (a row of NaN: left to the walker)
+      if (state == kDone && s_err) state = kDoneError;
+      auto record = [&](unsigned with) {
+        if (lane == 0) post(slot, pack_word(with, cur, child, (unsigned)tok & kTokenMax, state));
+      };
+      record(slot_tag);
+      int at = -1, dep = 0;
+      unsigned tag = slot_tag;
+      for (int p = 0; p <= polls; ++p) {
+        const u64 w0 = word(min(lane, words - 1)), w1 = word(min(kNodes + lane, words - 1));
+        const Word b(lane_u64(w0, 0));
+        if (p == 0 && slot == who && b.tag != tag) record(b.tag);
+        at = -1;
+        if (b.state == kEnded || p == polls) break;
+        if (b.state == kWalking) {
+          at = b.child < T ? b.child : -1;
+          dep = (int)b.token;
+          tag = b.tag;
+          const bool wait = chase(w0, w1, tag, at, dep, [](int, const Word&) {});
+          if (at < 0 || (!wait && at > seen)) break;
+        }
+        __builtin_amdgcn_s_sleep(4);
+      }
+      if (lane == 0) {
+        s_err = 0;
+        s_pick = at;
+        s_hops = dep;
+        s_tag = tag;
+      }
+    }
+    __syncthreads();
+    seen = uniform(s_pick);
+    if (seen < 0) return false;
+    const int seen_depth = uniform(s_hops);
+    slot_tag = (unsigned)uniform((int)s_tag);
+    // the who-th of the nodes below `seen`, in index order, the first kNodes left out
+    constexpr int E = kStageNodes / NT;
+    const int per = (T + NT - 1) / NT;
+    int p[E], hops[E], hits = 0;
+    bool on[E], hit[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      p[i] = tid * per + i;
+      hops[i] = 0;
+      hit[i] = false;
+      on[i] = i < per && p[i] > seen && p[i] >= kNodes && p[i] < T;
+    }
+    for (int h = 0; h < kSpecDepth; ++h) {
+      bool any = false;
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        if (!on[i]) continue;
+        const int q = s_par[p[i]];
+        ++hops[i];
+        hit[i] = q == seen;
+        on[i] = q > seen && q < p[i];
+        p[i] = q;
+        any |= on[i];
+      }
+      if (__builtin_amdgcn_ballot_w64(any) == 0) break;
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) hits += hit[i];
+    int incl = hits;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += t;
+    }
+    if (lane == 63) redi[wave] = incl;
+    __syncthreads();
+    if (tid == 0) s_pick = -1;
+    __syncthreads();
+    int rank = incl - hits;
+    for (int w = 0; w < wave; ++w) rank += redi[w];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      if (hit[i] && rank == who - 1) {
+        s_pick = tid * per + i;
+        s_hops = hops[i];
+      }
+      rank += hit[i];
+    }
+    __syncthreads();
+    if (uniform(s_pick) < 0) return false;
+    cur = uniform(s_pick);
+    depth = seen_depth + uniform(s_hops);
+    slot = kNodes + who - 1;
+    if (tid == 0) post(slot, pack_word(slot_tag, cur, -1, 0, kPending));
+    return true;
+  };
+  auto walk_ended = [&]() -> bool {
+    if (tid == 0) s_pick = Word(word(0)).state == kEnded ? 1 : 0;
+    __syncthreads();
+    const bool e = uniform(s_pick) != 0;
+    __syncthreads();
+    return e;
+  };
+  // the result of a step: child or -1, token, and for the others the state of the record
+  int r_child = -1, r_token = 0;
+  unsigned r_state = kDone;
+  bool declined = false;  // there is none: the node is not taken
+  u64 begun = __builtin_amdgcn_s_memtime();
+  if (ahead) {
     __syncthreads();
     int j = cur, hops = 0;  // nodes deeper than kSpecDepth, and those that do not hang from node 0, are left alone
     while (j > 0 && hops < kSpecDepth) {
-      const int p = s_par[j];
+      const int p = uniform(s_par[j]);
       if (p < 0 || p >= j) break;
       j = p;
       ++hops;
     }
-    if (j != 0) {
-      publish(0);
-      return;
-    }
     depth = hops;
-  }
-  if (MANY && second) {
-    for (int j = tid; j < T; j += NT) srec[j] = rec[j];
-    __syncthreads();
-    follow();
-    if (cur >= 0 && blockIdx.x > 0) {  // the blockIdx.x-th of the nodes below `cur`, in index order
-      constexpr int E = kStageNodes / NT;
-      const int per = (T + NT - 1) / NT;
-      int p[E], hops[E], hits = 0;
-      bool on[E], hit[E];
-#pragma unroll
-      for (int i = 0; i < E; ++i) {
-        p[i] = tid * per + i;
-        hops[i] = 0;
-        hit[i] = false;
-        on[i] = i < per && p[i] > cur && p[i] < T && !(srec[min(p[i], T - 1)] & kRecValid);
-      }
-      for (int h = 0; h < kSpecDepth; ++h) {
-        bool any = false;
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-          if (!on[i]) continue;
-          const int q = s_par[p[i]];
-          ++hops[i];
-          hit[i] = q == cur;
-          on[i] = q > cur && q < p[i];
-          p[i] = q;
-          any |= on[i];
-        }
-        if (__builtin_amdgcn_ballot_w64(any) == 0) break;
-      }
-#pragma unroll
-      for (int i = 0; i < E; ++i) hits += hit[i];
-      int incl = hits;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-      }
-      if (lane == 63) redi[wave] = incl;
-      __syncthreads();
-      int rank = incl - hits;
-      for (int w = 0; w < wave; ++w) rank += redi[w];
-#pragma unroll
-      for (int i = 0; i < E; ++i) {
-        if (hit[i] && rank == (int)blockIdx.x - 1) {
-          s_pick = tid * per + i;
-          s_hops = hops[i];
-        }
-        rank += hit[i];
-      }
-      __syncthreads();
-      if (s_pick < 0) return;
-      cur = s_pick;
-      depth += s_hops;
-      publish(kRecPending);
-    } else if (cur < 0 && blockIdx.x > 0) {
-      return;
+    if (j != 0) {
+      __builtin_amdgcn_s_waitcnt(0x0070);  // the row's copy: this workgroup may end
+      copied = false;
+      declined = true;
+      r_state = kDeclined;
     }
   }
 
   __syncthreads();
-  for (int step = n; step < T && cur >= 0; ++step) {
+  bool first = true;
+  // The step at `cur`.  False (the others only): the walk has ended meanwhile.
+  auto take_step = [&]() -> bool {
     const float* x = logits + (size_t)cur * (size_t)V;
-    // the step's result: the token, and the child it leads to or -1; true if this workgroup has another step to do
-    auto advance = [&](int child, int tok) -> bool {
-      if constexpr (MANY) {
-        if (!walker) {
-          __syncthreads();
-          if (tid == 0 && cur == 0 && child < 0) {  // the whole walk (only node 0's own workgroup can be here with cur == 0)
-            path_out[0] = 0;
-            tokens_out[0] = tok;
-            n_out[0] = 1;
-            if (s_err) status[0] = SX_ERR_TREE;
-          }
-          // (a token past every vocabulary, of a row of NaN: left to the last workgroup)
-          publish((unsigned)tok > kRecToken ? 0
-                                            : kRecValid | (s_err ? kRecError : 0) | (u64)tok << 3 | (u64)(unsigned)(child + 1) << 32);
-          return false;
-        }
-      }
-      if (tid == 0) {
-        path_out[n] = cur;
-        tokens_out[n] = tok;
-      }
-      __syncthreads();  // everybody has read child and token before the next step clears them
-      ++n;
-      ++depth;
-      cur = child;
-      if constexpr (MANY) {
-        // what the other workgroups have found meanwhile.  A node one of them is at is waited for, but not for long: this
-        // workgroup can always take the step itself
-        for (int look = 0; look < kLooks && cur >= 0; ++look) {
-          for (int j = tid; j < T; j += NT) srec[j] = __hip_atomic_load(rec + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __syncthreads();
-          follow();
-          const bool wait = cur >= 0 && (srec[max(cur, 0)] & kRecPending);
-          __syncthreads();
-          if (!wait) break;
-        }
-      }
-      return cur >= 0;
-    };
     // f(four consecutive elements, id of the first) over the row, in the same number of rounds for every lane; past the
     // end x reads as -inf.  A lane always takes the same quads, so in LDS it reads what its own wave has copied.
     auto edge = [&](float v, int id) { return id < V ? v : NEG_INF; };
@@ -485,6 +529,13 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
       asm volatile("" ::: "memory");
     }
     const long long pos = (long long)pos0 + depth + 1;
+    // the first step's last wave of the walker: what the words were, asked for behind the row
+    const bool tags = MANY && !ahead && first && wave == NW - 1;
+    u64 old0 = 0, old1 = 0;
+    if (tags) {
+      old0 = word(min(lane, words - 1));
+      old1 = word(min(kNodes + lane, words - 1));
+    }
     // ---- row maximum (and the greedy answer) ------------------------------------------------------
     float tm = NEG_INF;
     sweep_by(Const<8>{}, [&](float v0, float v1, float v2, float v3, int) { tm = fmaxf(tm, fmaxf(fmaxf(v0, v1), fmaxf(v2, v3))); });
@@ -500,6 +551,16 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
     }
     tm = wave_max_f32(tm);
     if (lane == 0) redf[wave] = tm;
+    if (tags) {  // a tag that no word has: 128 words, 65536 tags
+      const unsigned t0 = Word(old0).tag, t1 = Word(old1).tag;
+      unsigned tag = lane_u32(t0, 0);
+      do tag = (tag + 1) & 0xFFFFu;
+      while (__builtin_amdgcn_ballot_w64(t0 == tag || t1 == tag));
+      if (lane == 0) {
+        post(0, pack_word(tag, 0, -1, 0, kBegun));
+        s_tag = tag;
+      }
+    }
     __syncthreads();
     float M = redf[0];
 #pragma unroll
@@ -576,13 +637,22 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
       __syncthreads();
       const u64 u24 = mix24(seed, pos);
       int nc = s_n;
+      if (ahead && first && tid == 0) slot_tag = Word(word(0)).tag;
       const bool overflow = nc > kListCap;
       if (ahead && overflow) {
+        if (walk_ended()) return false;  // the slow steps end with the walk
+        // Z from a quad per lane, those of the peak left out
+        const float* at = (INLDS ? row : x) + (V >> 2) / NT * 4 * tid;
         float z = 0.f;
-        for (int i = tid; i < kListCap; i += NT) z += __uint_as_float(e_bits(__uint_as_float((unsigned)list[i])));
-        if (block_sum<NW>(z, redf) > kFlat) {
-          publish(0);
-          return;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float e = __uint_as_float(e_bits(at[c]));
+          z += e < 0.0625f ? e : 0.f;
+        }
+        if (block_sum<NW>(z, redf) * (float)V > kFlat * (float)(4 * NT)) {
+          r_child = -1;
+          r_state = kDeclined;
+          return true;
         }
       }
       u64 thr = 0;
@@ -964,12 +1034,14 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
           }
         }
         __syncthreads();
-        const int next = s_child;
-        if (!advance(next, next >= 0 ? tokens[next] : s_token)) break;
-        continue;
+        r_child = s_child;
+        r_token = r_child >= 0 ? tokens[r_child] : s_token;
+        return true;
       }
       int after = cur, trial = 0, accepted = -1;
+      bool ended = false;
       while (true) {
+        if (ahead && trial > 0 && (ended = walk_ended())) break;
         int c = 0x7FFFFFFF;
         for (int j = after + 1 + tid; j < T; j += NT)
           if (par_of(j) == cur) c = min(c, j);
@@ -1016,9 +1088,11 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
         }
         __syncthreads();
       }
+      if (ended) return false;
       if (accepted >= 0) {
-        if (!advance(accepted, tokens[accepted])) break;
-        continue;
+        r_child = accepted;
+        r_token = tokens[accepted];
+        return true;
       }
       // ---- every child rejected: draw from what p has become, then stop ----------------------------------
       // (p is at most 1 up to the rounding of its normalisation; a value above 1 counts as 1)
@@ -1039,8 +1113,9 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
       if (lane == 0 && part) atomicAdd(&s_low, part);
       __syncthreads();
       token = first_beyond(each, weight, scaled(s_low, trial24(seed, pos, trial)));
-      advance(-1, token);
-      break;
+      r_child = -1;
+      r_token = token;
+      return true;
     }
     // ---- cache lookup: lowest-index child of cur carrying the sampled token -------------------------
     int child = 0x7FFFFFFF;
@@ -1048,13 +1123,92 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
       if (par_of(j) == cur && tokens[j] == token) child = min(child, j);
     if (child != 0x7FFFFFFF) atomicMin(&s_child, child);
     __syncthreads();
-    child = s_child;
-    if (!advance(child == 0x7FFFFFFF ? -1 : child, token)) break;
+    r_child = s_child == 0x7FFFFFFF ? -1 : s_child;
+    r_token = token;
+    return true;
+  };
+  while (true) {
+    if (!declined && !take_step()) break;
+    first = declined = false;
+    // the step's result, and where to go from there
+    if (ahead) {
+      if (!publish_and_next(r_child, r_token, r_state)) break;
+      r_state = kDone;
+      continue;
+    }
+    if (tid == 0) {
+      path_out[n] = cur;
+      tokens_out[n] = r_token;
+    }
+    __syncthreads();  // everybody has read child and token before the next step clears them
+    ++n;
+    ++depth;
+    const int stepped = cur;
+    cur = uniform(r_child);
+    if constexpr (MANY) {
+      // What the others have found.  A node one of them is at is waited for as long as the walker's own last step took, and
+      // some 4 us for their way there: they have begun earlier, if they have begun.
+      if (__builtin_expect(cur >= 0, 0)) {  // (out of the way of the steps: with it inside, a flat one is 1 us longer)
+        if (wave == 0) {
+          const unsigned tag = (unsigned)uniform((int)s_tag);
+          if (lane == 0) post(0, pack_word(tag, stepped, cur, (unsigned)depth, kWalking));
+          const u64 now = __builtin_amdgcn_s_memtime(), until = now + (now - begun) + 8192;
+          int at = cur, dep = depth;
+          while (true) {
+            const u64 w0 = word(min(lane, words - 1)), w1 = word(min(kNodes + lane, words - 1));
+            const bool wait = chase(w0, w1, tag, at, dep, [&](int node, const Word& r) {
+              if (lane != 0) return;
+              path_out[n + dep - depth] = node;
+              tokens_out[n + dep - depth] = (int)r.token;
+              if (r.state == kDoneError) s_err = 1;
+            });
+            if (!wait || __builtin_amdgcn_s_memtime() >= until) break;
+          }
+          if (lane == 0) {
+            s_pick = at;
+            s_hops = dep;
+          }
+        }
+        __syncthreads();
+        cur = uniform(s_pick);
+        n += uniform(s_hops) - depth;
+        depth = uniform(s_hops);
+        __syncthreads();
+        begun = __builtin_amdgcn_s_memtime();
+      }
+    }
+    if (cur < 0) break;
   }
-  if (walker && tid == 0) {
+  if (!ahead && tid == 0) {
     n_out[0] = n;
     if (s_err) status[0] = SX_ERR_TREE;
+    if (MANY) post(0, pack_word(s_tag, 0, -1, 0, kEnded));
   }
+}
+
+template <int NT, bool INLDS, bool SI, bool MANY>
+__global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict__ logits,
+                                                         const float* __restrict__ draft_probs,
+                                                         const int* __restrict__ tokens,
+                                                         const int* __restrict__ parent, int T, int V,
+                                                         float temperature, float top_p, u64 seed,
+                                                         int pos0, int* __restrict__ path_out,
+                                                         int* __restrict__ tokens_out, int* __restrict__ n_out,
+                                                         float* __restrict__ scratch, u64* __restrict__ rec,
+                                                         int* __restrict__ status) {
+  __shared__ Shared<NT, SI> sh;
+  extern __shared__ __attribute__((aligned(1024))) float row[];  // INLDS: V rounded up to 4 NT
+  if (!MANY || blockIdx.x == 0) {
+    walk_steps<NT, INLDS, SI, MANY, false>(logits, draft_probs, tokens, parent, T, V, temperature, top_p, seed, pos0, path_out,
+                                           tokens_out, n_out, scratch, rec, status, sh, row);
+    return;
+  }
+  // Workgroups go round the eight XCDs; those that would share the walker's, and its L2, stay away.  (A flat row of 128256
+  // is read again and again from there: 145 us for the step with seven others' rows beside it, 134 alone.)
+  if constexpr (MANY)
+    if (blockIdx.x & 7)
+      walk_steps<NT, INLDS, SI, MANY, true>(logits, draft_probs, tokens, parent, T, V, temperature, top_p, seed, pos0, path_out,
+                                            tokens_out, n_out, scratch, rec, status, sh, row);
 }
 
 }  // namespace
@@ -1070,15 +1224,13 @@ struct WalkArgs {
   int pos0;
   int *path_out, *tokens_out, *n_out;
   float* ebuf;
-  u64* rec;         // null: one workgroup
-  int first_nodes;  // workgroups of the first launch
+  u64* rec;  // null: one workgroup
   int* status;
 };
 
 template <int NT, bool INLDS, bool SI, bool MANY>
-int launch_walk(const WalkArgs& a, int blocks, bool second, hipStream_t st) {
-  // (the second launch keeps 8 bytes per node where the row comes: NT = 1024 rounds rows of more than 4096 up to 32 KB or more)
-  const size_t row_bytes = INLDS ? sx_align_up((size_t)a.V * 4, (size_t)NT * 16) : MANY ? sx_align_up((size_t)a.T * 8, 16) : 0;
+int launch_walk(const WalkArgs& a, hipStream_t st) {
+  const size_t row_bytes = INLDS ? sx_align_up((size_t)a.V * 4, (size_t)NT * 16) : 0;
   if (INLDS) {  // above the default limit of dynamic LDS: allowed once per device
     static bool configured[64] = {};
     int dev = 0;
@@ -1090,17 +1242,20 @@ int launch_walk(const WalkArgs& a, int blocks, bool second, hipStream_t st) {
       configured[dev] = true;
     }
   }
+  int blocks = 1;
+  if (MANY) {  // a walker and up to 63 others, who number without the multiples of 8
+    const int others = (a.T < kNodes ? a.T : kNodes) - 1;
+    blocks += others + (others - 1) / 7;
+  }
   accept_walk_kernel<NT, INLDS, SI, MANY><<<blocks, NT, row_bytes, st>>>(
       a.logits, a.draft_probs, a.tokens, a.parent, a.T, a.V, a.temperature, a.top_p, a.seed, a.pos0, a.path_out, a.tokens_out,
-      a.n_out, a.ebuf, a.rec, second, a.status);
+      a.n_out, a.ebuf, a.rec, a.status);
   SX_LAUNCH_CHECK();
   return SX_OK;
 }
 template <bool INLDS, bool SI>
 int launch_walks(const WalkArgs& a, hipStream_t st) {
-  if (!a.rec) return launch_walk<1024, INLDS, SI, false>(a, 1, false, st);
-  SX_TRY((launch_walk<1024, INLDS, SI, true>(a, a.first_nodes, false, st)));
-  return launch_walk<1024, INLDS, SI, true>(a, a.T > a.first_nodes ? a.first_nodes : 1, true, st);
+  return a.rec ? launch_walk<1024, INLDS, SI, true>(a, st) : launch_walk<1024, INLDS, SI, false>(a, st);
 }
 
 // many workgroups where the steps saved are worth a launch (2 nodes: V = 5000 9.7 us by one workgroup, 12.9 by many, V =
@@ -1114,9 +1269,9 @@ extern "C" size_t sx_accept_walk_workspace(int32_t T, int32_t V) {
   if (V < 1) return 0;
   // (one workgroup walks a larger tree, but a buffer sized for it is to serve the smaller ones too)
   if (T > kStageNodes) T = kStageNodes;
-  // many workgroups: the records, and a scratch row for every other workgroup
+  // many workgroups: the words, and a scratch row for every other workgroup
   const size_t many = walk_by_many(T, V)
-                          ? sx_align_up((size_t)T * 8, 256) + (size_t)((T < kNodes ? T : kNodes) - 1) * scratch_bytes(V)
+                          ? sx_align_up((size_t)(T < kWords ? T : kWords) * 8, 256) + (size_t)((T < kNodes ? T : kNodes) - 1) * scratch_bytes(V)
                           : 0;
   return sx_accept_walk_min_workspace(V) + many;
 }
@@ -1135,18 +1290,16 @@ extern "C" int sx_accept_walk(const float* logits, const float* draft_probs, con
   float* ebuf = reinterpret_cast<float*>(static_cast<char*>(workspace) + SX_WS_HEADER);
   // (a workspace of the size that one workgroup needs is one workgroup's)
   u64* rec = nullptr;
-  int first_nodes = 1;
   if (walk_by_many(T, V) && workspace_bytes >= sx_accept_walk_workspace(T, V)) {
     rec = reinterpret_cast<u64*>(static_cast<char*>(workspace) + sx_accept_walk_min_workspace(V));
-    first_nodes = T < kNodes ? T : kNodes;
   }
   const WalkArgs a = {logits, draft_probs, tree_tokens, parent_idx, T, V, temperature, top_p, (u64)seed, pos0, path_out,
-                      tokens_out, n_out, ebuf, rec, first_nodes, status};
+                      tokens_out, n_out, ebuf, rec, status};
   sx_prof_begin(SX_K_WALK, st);
   int rc;
   // the row in LDS while it fits; small rows with fewer waves to meet at the barriers
   if (V <= kSmallVocab)
-    rc = draft_probs ? launch_walk<256, true, true, false>(a, 1, false, st) : launch_walk<256, true, false, false>(a, 1, false, st);
+    rc = draft_probs ? launch_walk<256, true, true, false>(a, st) : launch_walk<256, true, false, false>(a, st);
   else if (V <= 32768)
     rc = draft_probs ? launch_walks<true, true>(a, st) : launch_walks<true, false>(a, st);
   else

@@ -318,6 +318,43 @@ def test_walk_by_many_workgroups_is_the_walk_by_one(sx, V, T, tree, ratio, t, to
                 assert sx.lib.sx_check_status(ws.data_ptr(), None) == want
 
 
+@pytest.mark.parametrize("V,T", [(5001, 64), (5001, 700), (40000, 100)])
+def test_walk_believes_nothing_that_was_in_the_workspace(sx, V, T):
+    """The workgroups of a walk meet in words of the workspace, which nobody clears: what an earlier walk over other logits has
+    left there, or anything else -- here records of every node with a wrong token and end, under a board that has begun, walked
+    to a node or ended, and under all tags that this walk may choose -- changes no result, call after call."""
+    tok, par, _ = wl.gen_best_first_tree(T, 8, V, seed=V + T, max_depth=24)
+    td, pd = to_dev(np.array(tok, np.int32)), to_dev(np.array(par, np.int32))
+    many, one = sx.lib.sx_accept_walk_workspace(T, V), sx.lib.sx_accept_walk_workspace(1, V)
+    g = torch.Generator(device=dev()).manual_seed(T)
+    logits = []
+    for likely in range(3):
+        x = torch.randn((T, V), generator=g, device=dev()) - 12.0
+        kids = {}
+        for i in range(1, T):
+            kids.setdefault(int(par[i]), []).append(i)
+        for p, c in kids.items():
+            x[p, int(tok[c[likely % len(c)]])] = 9.0
+        logits.append(x)
+    words = min(T, 128)
+    node = np.concatenate([np.arange(min(T, 64)), np.arange(64, words)]).astype(np.uint64)
+    ws = torch.zeros(many, dtype=torch.uint8, device=dev())
+    ws1 = torch.zeros(one, dtype=torch.uint8, device=dev())
+    for r in range(30):
+        if r >= 6:
+            tags = np.full(words, 7 * r) if r % 2 else 500 + np.arange(words)
+            fake = tags.astype(np.uint64) << np.uint64(48) | node << np.uint64(33) | np.uint64(77 << 2)
+            child = [0, 6, 4096, 8191][r // 4 % 4] << 20  # none, a node, the last one there can be, one past every tree
+            board = [0, 1 | child, 2, 1 | child | 5 << 2][r % 4] | int(tags[0]) << 48
+            fake[0] = board
+            ws[one:one + 8 * words] = torch.from_numpy(fake.view(np.uint8)).to(dev())
+        x = logits[r % 3]
+        path, toks, n, _ = sx.accept_walk(x, td, pd, 0.6, 0.9, r, 3, workspace=ws)
+        p1, t1, n1, _ = sx.accept_walk(x, td, pd, 0.6, 0.9, r, 3, workspace=ws1)
+        n, n1 = int(n.item()), int(n1.item())
+        assert n == n1 and path[:n].tolist() == p1[:n].tolist() and toks[:n].tolist() == t1[:n].tolist(), r
+
+
 # ------------------------------------------------------------------------------------------------
 # acceptance by the ratio of target and draft probability (Sect. 4.1, "Comparison to speculative
 # decoding"): sx_accept_walk with draft_probs against oracle.specinfer_walk
