@@ -696,9 +696,10 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
 
 // What a launch looks like: tile height 32 jb, the prefetching form or not, and a's split and rotation.
 //
-// The height: the one that plan_split's figures expect to be fastest, 256, 224, 160 or 128 rows.  Over the 400 products of
-// the fit the choice is within 0.8 % of the best launch on average, 12 % at worst.  (192 rows, two stages, were the best of
-// three of the 400, by 3 % at most.)
+// The height: the one that plan_split's figures expect to be fastest.  Over the 400 products of the fit the choice among 256,
+// 224, 160 and 128 rows is within 0.8 % of the best launch on average, 12 % at worst.  192 rows, two stages, were the best of
+// three of the 400, by 3 % at most, but are where the others come out uneven: 12288 columns, K = 4096 at 850 rows 90 us, 256
+// rows 96 and 224 rows 97; 32000 columns at 330 rows 104, 224 rows 103, 160 rows 122.
 // Two things the figures do not know speak for 256 rows:
 //   the prefetching form (8 row tiles, whole groups of 4 column tiles), unless every tile is cut, streams the weights better
 //   than they say: a tenth;
@@ -709,7 +710,10 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
 // The prefetch at 128 and 160 rows: from three row tiles on, where they share the touched lines, and only where they are all
 // but full: 4 % on average, up to 18 (70B down, 640 rows in five tiles, 397 -> 336 us).  A row tile that is mostly padding
 // copies less, runs ahead of the others and is their prefetch by itself; touching costs up to 8 % there, and up to 30 % where
-// one row tile streams the weights for itself (70B gate|up at 150 rows).
+// one row tile streams the weights for itself (70B gate|up at 150 rows).  Nor where rounds of uncut tiles follow each other with
+// the last one nine tenths full but not whole: 32000 columns, K = 4096, at 600 rows (1.95 rounds) 142 us and 161 with it, at
+// 740 (2.93) 190 and 199, at 1280 (3.91) 293 and 318; all ten products measured there are slower with it, those of whole
+// rounds (70B O at 2048 rows, 2.0) up to 11 % faster.
 //
 // The rotation: at 128 and 160 rows always (150 rows, 70B gate|up 214 -> 173 us, never more than 2 % slower).  At 224 and 256:
 // 2 to 3 %, at best 15 %, for one or two row tiles, where a launch is bound by the weight stream, 1 % and
@@ -733,7 +737,9 @@ Plan pick_plan(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
   }
   plan_split(a, p.jb, split_ws, split_ws_bytes);
   if (stages(p.jb) == 3) {
-    p.prefetch = a.tilesM >= 3 && a.M * 25ll >= 23ll * 32 * p.jb * a.tilesM;
+    const int cus = sx_compute_units(), tiles = a.tilesM * a.tilesN;
+    const bool nearly_whole = a.split == 1 && tiles > cus && tiles % cus * 10 >= 9 * cus;
+    p.prefetch = a.tilesM >= 3 && a.M * 25ll >= 23ll * 32 * p.jb * a.tilesM && !nearly_whole;
     a.rotate = 1;
   } else {
     p.prefetch = p.jb == 8 && can_prefetch;
