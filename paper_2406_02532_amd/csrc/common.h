@@ -96,6 +96,13 @@ __device__ __forceinline__ float f32_from_order_key(uint32_t k) {
   return __uint_as_float(b);
 }
 
+// The rotary embedding's turn of a pair.  The roundings are spelled out: left to contract as it likes, the compiler takes the
+// sums one way in one kernel and the other way in the next, and a product of the same values is rounded to another bf16.
+__device__ __forceinline__ void rope_turn(float x0, float x1, float c, float s, float& lo, float& hi) {
+  lo = __builtin_fmaf(x0, c, -(x1 * s));
+  hi = __builtin_fmaf(x1, c, x0 * s);
+}
+
 // ---- wave reductions (64 lanes) ---------------------------------------------------------
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

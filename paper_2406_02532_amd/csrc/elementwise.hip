@@ -120,7 +120,8 @@ __global__ void rope_split_kernel(const float* __restrict__ qkv, const float2* _
   const float a = src[j], b = src[j + half];
   if (hd < Hq + Hkv) {
     const float2 t = cs[(size_t)i * half + j];
-    const float ra = a * t.x - b * t.y, rb = a * t.y + b * t.x;
+    float ra, rb;
+    rope_turn(a, b, t.x, t.y, ra, rb);
     if (hd < Hq) {
       const size_t o = ((size_t)i * Hq + hd) * Dh;
       st<W>(q, o + j, ra);

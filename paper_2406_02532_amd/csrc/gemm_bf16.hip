@@ -532,8 +532,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float x0 = acc[i][j][e], x1 = acc[i + 4][j][e];
-              lo[e] = x0 * cs_[e] - x1 * sn_[e];
-              hi[e] = x0 * sn_[e] + x1 * cs_[e];
+              rope_turn(x0, x1, cs_[e], sn_[e], lo[e], hi[e]);
             }
             u32x2 o;
             o[0] = pack_bf16x2(lo[0], lo[1]);

@@ -314,8 +314,8 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
       for (int e = 0; e < 4; ++e) {
         const float x0 = acc[0][j][e], x1 = acc[1][j][e];
         const float c = t[j][e >> 1][2 * (e & 1)], s = t[j][e >> 1][2 * (e & 1) + 1];
-        lo[e] = is_v ? x0 : x0 * c - x1 * s;
-        hi[e] = is_v ? x1 : x0 * s + x1 * c;
+        rope_turn(x0, x1, c, s, lo[e], hi[e]);
+        if (is_v) lo[e] = x0, hi[e] = x1;
       }
       unsigned short* y = Y + (size_t)m * nheads * 128;
       u32x2 o;

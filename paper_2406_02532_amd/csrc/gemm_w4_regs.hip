@@ -434,8 +434,8 @@ __global__ __launch_bounds__(kThreads) void gemm_w4_regs_kernel(W4RegArgs a) {
         for (int e = 0; e < 4; ++e) {
           const float x0 = lo[j][e], x1 = hi[j][e];
           const float c = t[j][e >> 1][2 * (e & 1)], s = t[j][e >> 1][2 * (e & 1) + 1];
-          x[e] = is_v ? x0 : x0 * c - x1 * s;
-          y[e] = is_v ? x1 : x0 * s + x1 * c;
+          rope_turn(x0, x1, c, s, x[e], y[e]);
+          if (is_v) x[e] = x0, y[e] = x1;
         }
         unsigned short* to = Y + (size_t)m * nheads * 128;
         u32x2 o;
