@@ -324,7 +324,7 @@ int sx_row_logsoftmax_topk(const float *logits, int32_t N, int32_t V, int32_t k,
 int sx_gemm_bf16(const void *X, const void *W, const void *W2, void *Y, int32_t M, int32_t N,
                  int32_t K, int32_t mode, void *stream);
 /* The same product with memory for partial sums, as the forward calls it: where the output tiles
- * (256 columns and 160 to 256 rows) are fewer than half the compute units, or their last round would fill at most half of them, those tiles
+ * (256 columns and 128 to 256 rows) are fewer than half the compute units, or their last round would fill at most half of them, those tiles
  * are cut along K among several workgroups; the parts are added in a fixed order, so results repeat bit for
  * bit.  workspace: NULL (then exactly sx_gemm_bf16), or device memory of sx_gemm_bf16_workspace() bytes,
  * 256-byte aligned (SX_ERR_WORKSPACE otherwise), whose first 1024 bytes are zero before the first call (every call
@@ -337,6 +337,10 @@ int sx_gemm_bf16_ws(const void *X, const void *W, const void *W2, void *Y, int32
  * form that prefetches operand lines runs.  Up to 128 rows: how it would, where it takes 256-column tiles at all.  Launches nothing; for tests and profiling. */
 int sx_gemm_bf16_wide_plan(int32_t M, int32_t N, int32_t K, int32_t mode, size_t workspace_bytes,
                            int32_t *tile_rows, int32_t *k_parts, int32_t *cut_tiles, int32_t *prefetch);
+/* The same for the narrow tiles that most products of at most 128 rows and every QKV projection of that size take: columns
+ * of a tile (64 or 128; rows of the gate and the up matrix both count) and parts that K is cut in. */
+int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t *tile_columns,
+                             int32_t *k_parts);
 
 /* QKV projection of the decoder layer (Alg. 1, FORWARD) with the rotary embedding applied in the
  * GEMM's epilogue, head_dim 128: q_out device bf16 [T][n_q_heads][128], k_out and v_out device

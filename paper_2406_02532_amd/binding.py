@@ -11,7 +11,7 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libspecexec
 EXPORTS = ["sx_verify_tree_workspace", "sx_verify_tree_w4_workspace", "sx_verify_tree", "sx_verify_tree_cached", "sx_verify_tree_range", "sx_commit_kv",
            "sx_specexec_round_workspace", "sx_specexec_round", "sx_draft_tree_workspace", "sx_draft_tree", "sx_accept_walk_workspace", "sx_accept_walk",
            "sx_expand_topk_workspace", "sx_expand_topk", "sx_expand_topk_static", "sx_check_status", "sx_status_string", "sx_version",
-           "sx_row_logsoftmax_topk", "sx_gemm_bf16", "sx_gemm_bf16_workspace", "sx_gemm_bf16_ws", "sx_gemm_bf16_wide_plan", "sx_gemm_w4a16_workspace", "sx_gemm_w4a16_bf16", "sx_qkv_rope_workspace", "sx_qkv_rope_bf16", "sx_tree_attention_workspace", "sx_tree_attention_bf16",
+           "sx_row_logsoftmax_topk", "sx_gemm_bf16", "sx_gemm_bf16_workspace", "sx_gemm_bf16_ws", "sx_gemm_bf16_wide_plan", "sx_gemm_bf16_narrow_plan", "sx_gemm_w4a16_workspace", "sx_gemm_w4a16_bf16", "sx_qkv_rope_workspace", "sx_qkv_rope_bf16", "sx_tree_attention_workspace", "sx_tree_attention_bf16",
            "sx_profile_enable", "sx_profile_select", "sx_profile_disable", "sx_profile_read"]
 
 SX_F32, SX_BF16 = 0, 1
@@ -103,6 +103,8 @@ def _load():
     L.sx_gemm_bf16_ws.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, vp, sz, vp]
     L.sx_gemm_bf16_wide_plan.restype = C.c_int
     L.sx_gemm_bf16_wide_plan.argtypes = [i32, i32, i32, i32, sz, vp, vp, vp, vp]
+    L.sx_gemm_bf16_narrow_plan.restype = C.c_int
+    L.sx_gemm_bf16_narrow_plan.argtypes = [i32, i32, i32, sz, vp, vp]
     L.sx_gemm_w4a16_workspace.restype = sz
     L.sx_gemm_w4a16_workspace.argtypes = []
     L.sx_gemm_w4a16_bf16.restype = C.c_int
@@ -388,6 +390,13 @@ def gemm_bf16_wide_plan(M: int, N: int, K: int, mode: int = 0, workspace_bytes: 
     at = [C.byref(out, 4 * i) for i in range(4)]
     _check(lib.sx_gemm_bf16_wide_plan(M, N, K, mode, workspace_bytes, *at), "sx_gemm_bf16_wide_plan")
     return out[0], out[1], out[2], bool(out[3])
+
+
+def gemm_bf16_narrow_plan(N: int, K: int, mode: int = 0, workspace_bytes: int = 0):
+    """sx_gemm_bf16_narrow_plan: (columns of a tile, parts of K) of the narrow GEMM at this shape."""
+    out = (C.c_int32 * 2)()
+    _check(lib.sx_gemm_bf16_narrow_plan(N, K, mode, workspace_bytes, C.byref(out, 0), C.byref(out, 4)), "sx_gemm_bf16_narrow_plan")
+    return out[0], out[1]
 
 
 def gemm_w4a16_bf16(X, qweight, scales, zeros, Y, group: int, mode: int = 0, workspace=None, stream=None):

@@ -489,3 +489,16 @@ int sx_launch_gemm_skinny_qkv_rope_bf16(const void* X, const void* Wq, const voi
   plan_skinny(a, a.N, split_ws, split_ws_bytes);
   return launch<SX_GEMM_QKV_ROPE>(a, st);
 }
+
+extern "C" int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t* tile_columns,
+                                        int32_t* k_parts) {
+  if (!tile_columns || !k_parts) return SX_ERR_NULL;
+  if (mode < 0 || mode > 2 || N < 1 || K < BK || K % BK != 0) return SX_ERR_SHAPE;
+  SkinnyArgs a = {};
+  a.K = K;
+  int32_t somewhere = 0;  // (only whether there is memory is asked)
+  plan_skinny(a, mode == SX_GEMM_SWIGLU ? 2 * N : N, workspace_bytes ? &somewhere : nullptr, workspace_bytes);
+  *tile_columns = 64 * a.nh;
+  *k_parts = a.split;
+  return SX_OK;
+}
