@@ -140,17 +140,6 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return s;
 }
 template <int NW>
-__device__ __forceinline__ float block_max(float v, float* red) {
-  v = wave_max(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float s = red[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) s = fmaxf(s, red[w]);
-  return s;
-}
-template <int NW>
 __device__ __forceinline__ int block_sum_i(int v, int* red) {
   v = wave_sum_i(v);
   __syncthreads();

@@ -23,11 +23,6 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kCandCap = 1024;  // LDS slots for row candidates before the exact fallback is taken
 
-template <int THREADS>
-__device__ __forceinline__ int block_count(bool pred, int* red) {
-  return block_sum_i<THREADS / 64>(pred ? 1 : 0, red);
-}
-
 // Exact selection for rows the cheap bound cannot handle.  Bitwise search for the k-th largest
 // order key, then for the index below which ties are taken, each probe being one pass over the
 // row (served by L2: the row was just read).  Leaves exactly k entries in cand[], returns k.
