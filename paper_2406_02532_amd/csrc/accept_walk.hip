@@ -69,8 +69,7 @@ constexpr unsigned kTokenMax = 0x3FFFF;
 __device__ __forceinline__ unsigned long long pack_word(unsigned tag, int node, int child, unsigned token, unsigned state) {
   return (unsigned long long)tag << 48 | (unsigned long long)node << 33 | (unsigned long long)(child + 1) << 20 | token << 2 | state;
 }
-// the same value in every lane, told to the compiler: what depends on it stays in scalar registers and branches.  (A walk's node
-// as a vector register, from the records in LDS, cost a flat step 2.5 us in longer code.)
+// the same value in every lane, told to the compiler: what depends on it stays in scalar registers and branches
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ unsigned long long uniform(unsigned long long v) {
   return (unsigned long long)(unsigned)uniform((int)(v >> 32)) << 32 | (unsigned)uniform((int)v);
@@ -1148,7 +1147,7 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
     if constexpr (MANY) {
       // What the others have found.  A node one of them is at is waited for as long as the walker's own last step took, and
       // some 4 us for their way there: they have begun earlier, if they have begun.
-      if (__builtin_expect(cur >= 0, 0)) {  // (out of the way of the steps: with it inside, a flat one is 1 us longer)
+      if (__builtin_expect(cur >= 0, 0)) {  // (out of the way of the steps: with it inside, a flat one is 0.2 to 0.8 us longer)
         if (wave == 0) {
           const unsigned tag = (unsigned)uniform((int)s_tag);
           if (lane == 0) post(0, pack_word(tag, stepped, cur, (unsigned)depth, kWalking));
@@ -1204,7 +1203,8 @@ __global__ __launch_bounds__(NT) void accept_walk_kernel(const float* __restrict
     return;
   }
   // Workgroups go round the eight XCDs; those that would share the walker's, and its L2, stay away.  (A flat row of 128256
-  // is read again and again from there: 145 us for the step with seven others' rows beside it, 134 alone.)
+  // is read again and again from there: 139.7 us for the step with seven others' rows beside it, 135.2 without; a peaked walk
+  // over 64 such nodes 23.3 and 24.3.)
   if constexpr (MANY)
     if (blockIdx.x & 7)
       walk_steps<NT, INLDS, SI, MANY, true>(logits, draft_probs, tokens, parent, T, V, temperature, top_p, seed, pos0, path_out,
@@ -1258,8 +1258,10 @@ int launch_walks(const WalkArgs& a, hipStream_t st) {
   return a.rec ? launch_walk<1024, INLDS, SI, true>(a, st) : launch_walk<1024, INLDS, SI, false>(a, st);
 }
 
-// many workgroups where the steps saved are worth a launch (2 nodes: V = 5000 9.7 us by one workgroup, 12.9 by many, V =
-// 50000 18.1 and 13.2) and the parents fit the LDS
+// Many workgroups where the parents fit the LDS and the steps saved outweigh what their code costs a flat row that ends the
+// walk at once, 2.5 us up to V = 32768 and 1 above (us, peaked walk to the last node, by one workgroup -> by many | flat):
+// 4 nodes, V = 5000 17.8 -> 9.3 | 21.0 -> 23.7, V = 32000 26.5 -> 11.6 | 42.9 -> 45.2; 2 nodes, V = 5000 10.0 -> 9.5 |
+// 21.0 -> 23.9, V = 32000 14.3 -> 10.5 | 42.9 -> 45.3, V = 33000 by ratio 17.2 -> 11.7 | 84.8 -> 86.0.
 bool walk_by_many(int32_t T, int32_t V) { return V > kSmallVocab && T <= kStageNodes && (T > 3 || (T > 1 && V > 32768)); }
 size_t scratch_bytes(int32_t V) { return sx_align_up((size_t)V * 4, 256); }
 

@@ -190,8 +190,8 @@ def test_speculative_generation_end_to_end_equals_sequential_sampling(sx, draft_
 
 
 def test_draft_tree_bf16_model_close_to_oracle(sx):
-    """The MFMA path of the draft loop (narrow-tile GEMMs with K cut in parts, 32-row attention tiles, rotation in a
-    kernel of its own, growing tree K/V in bf16) against the oracle evaluating the same bf16 model.  Two bf16
+    """The MFMA path of the draft loop (narrow-tile GEMMs with K cut in parts, small attention tiles, rotation in the
+    QKV product's epilogue, growing tree K/V in bf16) against the oracle evaluating the same bf16 model.  Two bf16
     evaluations differ by rounding flips (a few 1e-3 in log-probability), which can swap candidates whose scores
     nearly tie; so: scores of the nodes both trees contain agree to 0.05, and at least 90% of the nodes coincide."""
     cfg = wl.ModelCfg(2, 512, 4, 2, 128, 1408, 2000, dtype="bf16")
