@@ -53,7 +53,8 @@ constexpr int kStageNodes = 4096;  // the parents of trees up to this size are r
 // missing after the first | in one.  V = 32000: 64 nodes 54 | 14.0 | 13.3, 2048 nodes 95 | 30.7 | 24.6; V = 128256: 384 nodes
 // 188 | 34.6 | 35.7, by ratio 232 | 45.8 | 45.5, 2048 nodes by ratio 295 | 71.6 | 50.8.  Flat rows, where the walk ends at its
 // first node: V = 32000 43.4 | 46.8 | 46.1, t = 1, top_p = 1 25.3 | 28.5 | 26.6; V = 128256 133 | 144 | 134.6.  (What is left
-// of that is code: the walker without the others takes as long.)
+// of that is code: the walker without the others takes as long.)  Rows not quite as flat, which the others take: N(0, 1.8)
+// logits, t = 0.6 35 or 44, by seed | 49 | 47.5 or 52.
 constexpr int kNodes = 64;
 constexpr int kSmallVocab = 4096;  // up to here four waves walk alone: a step takes them 1 us
 constexpr int kSpecDepth = 32;   // nodes further below node 0, or the walker's, are not taken ahead of the walk
@@ -446,6 +447,14 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
     __syncthreads();
     return e;
   };
+  // The same at the end of each sweep of a slow step: one lane asks, and behind the barrier that is there anyway everybody
+  // knows.  (V = 32000, N(0, 1.8) logits at t = 0.6: the walk ends at node 0 after 37 or 46 us, half of the others are at steps
+  // of up to 50.  The call takes 47.5 or 52, and 52 in either case when they only ask once.  Asked in every round of a sweep,
+  // with the rest of it skipped, the others get slower: 44.5 or 53.5.)
+  auto ask = [&]() {
+    if (ahead && tid == 0) s_pick = Word(word(0)).state == kEnded ? 1 : 0;
+  };
+  auto told = [&]() -> bool { return ahead && uniform(s_pick) != 0; };
   // the result of a step: child or -1, token, and for the others the state of the record
   int r_child = -1, r_token = 0;
   unsigned r_state = kDone;
@@ -636,10 +645,13 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
       __syncthreads();
       const u64 u24 = mix24(seed, pos);
       int nc = s_n;
-      if (ahead && first && tid == 0) slot_tag = Word(word(0)).tag;
       const bool overflow = nc > kListCap;
+      if (ahead && (first || overflow) && tid == 0) {
+        const Word b(word(0));
+        if (first) slot_tag = b.tag;
+        s_pick = b.state == kEnded ? 1 : 0;
+      }
       if (ahead && overflow) {
-        if (walk_ended()) return false;  // the slow steps end with the walk
         // Z from a quad per lane, those of the peak left out
         const float* at = (INLDS ? row : x) + (V >> 2) / NT * 4 * tid;
         float z = 0.f;
@@ -648,7 +660,9 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
           const float e = __uint_as_float(e_bits(at[c]));
           z += e < 0.0625f ? e : 0.f;
         }
-        if (block_sum<NW>(z, redf) * (float)V > kFlat * (float)(4 * NT)) {
+        const bool flat = block_sum<NW>(z, redf) * (float)V > kFlat * (float)(4 * NT);
+        if (told()) return false;  // the slow steps end with the walk
+        if (flat) {
           r_child = -1;
           r_state = kDeclined;
           return true;
@@ -684,7 +698,8 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
       auto sweep_e = [&](auto f) {
         for (int id = tid * 4; id < V; id += 4 * NT) f(*reinterpret_cast<const u32x4*>(es + id), id);
       };
-      // as first_beyond, over the row: a wave's 64 quads are 256 consecutive ids, whose sum needs no atomics
+      // as first_beyond, over the row: a wave's 64 quads are 256 consecutive ids, whose sum needs no atomics.  (The others: -1,
+      // the walk has ended meanwhile.)
       auto first_beyond_e = [&](auto weight, u64 target) -> int {
         __syncthreads();
         clear_hist();
@@ -693,7 +708,9 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
           const u64 incl = wave_scan_u64(f);
           if (lane == 63 || id + 4 >= V) hist[id >> 8] = incl;  // (the last lane that has a quad)
         });
+        ask();
         __syncthreads();
+        if (told()) return -1;
         u64 sum;
         const u64 start = scan(false, sum);
         find(false, start, target + 1);
@@ -721,7 +738,7 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
       // and how many of the elements equal to K are in it
       bool ties_left = false;  // not all of them
       u64 ties_taken = 0;
-      auto refine = [&](auto each, unsigned prefix, u64 above) {
+      auto refine = [&](auto each, unsigned prefix, u64 above) -> bool {  // false: the walk has ended meanwhile
         for (int shift = 10; shift >= 0; shift -= 10) {
           __syncthreads();
           clear_hist();
@@ -731,7 +748,9 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
               if (f) atomicAdd(&hist[(b >> shift) & (kBins - 1)], f);
             }
           });
+          ask();
           __syncthreads();
+          if (told()) return false;
           u64 t2;
           const u64 st = above + scan(true, t2);
           find(true, st, thr);
@@ -750,6 +769,7 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
           ties_left = m < n_tie;
           ties_taken = m;
         }
+        return true;
       };
       // at most 64 candidates in `list` (payload: bits of e), one per lane of one wave; `thr` known (have_thr) or made
       // from their sum and the small elements'
@@ -821,7 +841,9 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
         });
         part = wave_scan_u64(part);
         if (lane == 63) atomicAdd(&s_low, part);
+        ask();
         __syncthreads();
+        if (told()) return false;
         mass = s_low;
         Ytie = 0;
         in_list = false;
@@ -843,8 +865,10 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
               if (f) atomicAdd(&hist[b[c] >> 20], f);
             }
           });
+          ask();
         }
         __syncthreads();
+        if (overflow && told()) return false;
         u64 total;
         const u64 start = scan(true, total);
         thr = threshold(total + s_low);
@@ -874,8 +898,10 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
 #pragma unroll
             for (int c = 0; c < 4; ++c) append(b[c] >= floor_bits && id + c < V, id + c, b[c]);
           });
+          ask();
         }
         __syncthreads();
+        if (overflow && told()) return false;
         nc = s_n;
         in_list = nc <= kListCap;
         if (nc <= 64) {
@@ -886,22 +912,28 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
             auto each = [&](auto f) {
               for (int i = tid; i < nc; i += NT) f((unsigned)list[i], (int)(list[i] >> 32));
             };
-            refine(each, floor_bits >> 20, above);
+            if (!refine(each, floor_bits >> 20, above)) return false;
             if (ties_left) Ytie = (unsigned)first_beyond(each, is_tie, ties_taken);
             if constexpr (!SI) token = first_beyond(each, weight_of, scaled(mass, u24));
           } else {
-            refine([&](auto f) { sweep_e([&](u32x4 b, int id) {
+            if (!refine([&](auto f) { sweep_e([&](u32x4 b, int id) {
 #pragma unroll
-                                   for (int c = 0; c < 4; ++c) f(b[c], id + c);
-                                 }); },
-                   floor_bits >> 20, above);
-            if (ties_left) Ytie = (unsigned)first_beyond_e(is_tie, ties_taken);
+                                        for (int c = 0; c < 4; ++c) f(b[c], id + c);
+                                      }); },
+                        floor_bits >> 20, above))
+              return false;
+            if (ties_left) {
+              const int y = first_beyond_e(is_tie, ties_taken);
+              if (ahead && y < 0) return false;
+              Ytie = (unsigned)y;
+            }
           }
         }
       }
       if (!in_list) {
         if constexpr (!SI) {
           token = first_beyond_e(weight_of, scaled(mass, u24));
+          if (ahead && token < 0) return false;
         } else {  // the nucleus as a list, if it is short enough for one
           __syncthreads();
           if (tid == 0) s_n = 0;
@@ -911,7 +943,9 @@ __device__ __forceinline__ void walk_steps(const float* __restrict__ logits, con
 #pragma unroll
             for (int c = 0; c < 4; ++c) append(in_nucleus(b[c], (unsigned)(id + c)), id + c, b[c]);
           });
+          ask();
           __syncthreads();
+          if (told()) return false;
           nc = s_n;
         }
       }
