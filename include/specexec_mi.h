@@ -338,7 +338,8 @@ int sx_gemm_bf16_ws(const void *X, const void *W, const void *W2, void *Y, int32
 int sx_gemm_bf16_wide_plan(int32_t M, int32_t N, int32_t K, int32_t mode, size_t workspace_bytes,
                            int32_t *tile_rows, int32_t *k_parts, int32_t *cut_tiles, int32_t *prefetch);
 /* The same for the narrow tiles that most products of at most 128 rows and every QKV projection of that size take: columns
- * of a tile (64 or 128; rows of the gate and the up matrix both count) and parts that K is cut in. */
+ * of a tile (64 or 128, mode 2 and the QKV projection also 96; rows of the gate and the up matrix both count) and parts that
+ * K is cut in, for 128 rows (fewer may take another width or fewer parts). */
 int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t *tile_columns,
                              int32_t *k_parts);
 

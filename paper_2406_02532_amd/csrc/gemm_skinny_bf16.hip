@@ -1,52 +1,45 @@
 // Y = X W^T for few rows (M <= 128): the linear layers of the draft model's forward over one batch of tree
 // nodes (Alg. 2, forward(batch, theta_draft)).  At this M the product is bound by streaming the weights once
-// from HBM, so the tile is narrow in N (128 x 64 per workgroup: many workgroups, each a different slice of W)
+// from HBM, so the tile is narrow in N (all rows x 64, 96 or 128 columns: many workgroups, each a different slice of W)
 // and, where even that leaves compute units idle, K is cut as well and the partial sums are added up by the
 // last workgroup to arrive, in a fixed order.  Same building blocks as the wide kernel: operands go global ->
-// LDS by buffer loads that write LDS (whole 128-byte lines, chunk swizzle applied on the global side), three
-// stages of K = 64, one barrier per stage, v_mfma_f32_16x16x32_bf16 with the product formed transposed so that
+// LDS by buffer loads that write LDS (whole 128-byte lines, chunk swizzle applied on the global side), slabs of K = 64
+// in as many stages as fit, one barrier per slab, v_mfma_f32_16x16x32_bf16 with the product formed transposed so that
 // a lane holds 4 consecutive output columns.
 //
-// What bounds it (7B shapes, 128 rows): 2.0-2.4 TB/s of weights from HBM, 3-6 TB/s out of the Infinity Cache.
-// A plain load kernel walking the same 64 rows x 128 bytes per step streams the same matrix from HBM at 5 TB/s,
-// and a fifth wave touching the weight lines 3 to 12 slabs ahead of the copies made every shape slower: HBM is
-// not what the copies wait for.  With the copies of W taken out the kernel still takes 29 us of 54 (gate|up,
-// warm), with those of X taken out 48: a 64-column tile copies all 128 rows of X again (16 KB per slab next to
-// 8 KB of weights), so the L2 -> LDS stream carries three times the weight bytes with two slabs of lookahead.
-// Hence the 128-column form below for wide matrices: 31 us for the same product.  From HBM the channels bound it more than
-// the bytes: rotating the order of the slabs (below) took the wide shapes from 3.8-4.4 to 4.3-5.2 TB/s at 100 rows.
-// Nine slabs of weights in flight instead of three, tiles of 64 or 32 rows for small batches and an even cut of all
-// slabs among one workgroup per compute unit were measured as well (one wave half copying W, the other X): at 100 rows
-// 2 to 10 % slower, at 50 rows and less 2 to 15 % faster than this kernel was, and slower than it is with the rotation.
+// What bounds it: HBM up to some 32 rows (5.5 to 6.6 TB/s of weights where the chip is full); beyond that the copies into LDS
+// as a whole, weights and X together, at 10 to 11 TB/s: every column tile copies all of X again, at 100 rows and 128 columns
+// as many bytes as of W.  Hence:
+//   the tile has as many blocks of 16 rows as M asks for (1, 2, 4, 5, 7 or 8), whose room goes to further stages;
+//   96 columns where 128 leave a third of the chip idle (gate|up of 2 x 11008: 172 tiles or 230);
+//   of 96 columns on, W goes past the caches' other contents (nontemporal), which leaves X there.  With 64 columns, cut, that
+//   was 2 to 7 % slower.
+// Weights from memory, us, the kernel before (128 rows of X always, 64 or 128 columns, three or four stages) -> now, at 16,
+// 64, 100 and 128 rows: 7B O 13.4 -> 10.5, 14.0 -> 12.5, 14.7 -> 14.2, 15.1 -> 15.2; down 24.7 -> 18.9, 25.6 -> 22.4, 26.8 ->
+// 26.6, 29.0 -> 29.1; gate|up 36.2 -> 30.5, 39.0 -> 33.5, 42.1 -> 37.3, 45.4 -> 40.7; head of 32000 46.6 -> 44.2, 47.7 -> 44.4,
+// 49.3 -> 46.9, 52.6 -> 51.4; 70B O 32.4 -> 26.3, 34.0 -> 28.5, 35.4 -> 34.0, 37.1 -> 38.2; down 89.4 -> 73.5, 94.0 -> 80.9, 99.7
+// -> 89.4, 104.7 -> 98.1.  Twelve shapes at 12 row counts: 0.85 of the time; 64 columns at 128 rows up to 3 % slower.
+// Measured and not kept: W straight into registers in the layout of the MFMA operand (a load then touches 16 rows, 64 bytes
+// each, and the address unit bounds it: head at 100 rows 59 us); 32 columns (7B O at 16 rows 9.2, no better from 64 rows on); a
+// walk that starts at the same slab everywhere (see the rotation below).
 #include "kernels.h"
 
 namespace {
 
-// A workgroup is NH groups of 4 waves; group h owns output columns 64 h .. 64 h + 63 of a 128 x 64 NH tile and all
-// groups share the tile's X slab.  NH = 1: three stages of 24 KB, two workgroups per compute unit.  NH = 2: four
-// stages of 32 KB, one workgroup of 8 waves: X is copied once for 128 columns instead of twice and the copies run
-// three slabs ahead instead of two -- for wide matrices (many column tiles); narrow ones keep NH = 1, which gives
-// twice as many workgroups to cut K among.
-constexpr int BM = 128, BK = 64;
-constexpr int kXBytes = BM * BK * 2;   // 16 KB
-constexpr int kWBytes = 64 * BK * 2;   // 8 KB per group of 64 columns
-constexpr int kWideMinSlabs = 40;
+constexpr int BK = 64;  // K of a slab
 
 struct SkinnyArgs {
   const unsigned short* X;
-  const unsigned short* W0;
-  const unsigned short* W1;
-  const unsigned short* W2;
-  int n0, n1, n2;
+  const void* W[3];  // bf16 [n][K]
+  int n0, n1, n2;    // rows of the stacked matrices
   void* Y;
-  int M, N, K;
-  int tilesN, split, nh;
-  int rounds;  // of workgroups, one per compute unit
+  int M, N, K;       // N: columns of Y (SwiGLU: of one matrix)
+  int tiles, split;
+  int rounds;        // of workgroups, one per compute unit
   float* part;
   int* part_cnt;
-  const float2* cs;                // QKV: rows of 64 (cos, sin)
+  const float2* cs;  // QKV: rows of 64 (cos, sin)
   unsigned short *q, *k, *v;
-  int hq, hkv;
 };
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
@@ -55,269 +48,319 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000);
 }
 
-constexpr int kWaitVm0 = 0x0070, kWaitVm6 = 0x0076, kWaitVm8 = 0x0078;
-#define SX_WAIT_BARRIER(IMM)              \
-  asm volatile("" ::: "memory");          \
-  __builtin_amdgcn_s_waitcnt(IMM);        \
-  __builtin_amdgcn_s_barrier();           \
-  asm volatile("" ::: "memory");
+// all LDS reads of this wave done, at most N of its vector-memory operations outstanding
+constexpr int wait_vm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 
-template <int MODE, int NH>
-__global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(SkinnyArgs a) {
-  constexpr int BN = 64 * NH;
-  constexpr int kStageBytes = kXBytes + NH * kWBytes;
-  constexpr int kPartFloats = BM * BN;   // partial sums of one K part of one tile
-  constexpr int kXCopies = 4 / NH;       // copy instructions (1 KB each) per wave and slab: X, then 2 for W
+// Copy instructions (1 KB each) of a slab: RB blocks of 16 rows of X, then BN rows of W; the same number to every wave, and a KB
+// of its own in the stage for those that are over.
+constexpr int copies(int rb, int bn) { return rb * 2 + bn / 8; }
+constexpr int stage_kb(int rb, int bn, int waves) { return copies(rb, bn) + (copies(rb, bn) % waves != 0); }
+// stages of a tile: as many as fit the 160 KB of LDS, up to 8
+constexpr int stages(int rb, int bn, int waves) {
+  const int s = (160 * 1024 - 1024) / (stage_kb(rb, bn, waves) * 1024);
+  return s < 8 ? s : 8;
+}
+
+// CG column groups of WB blocks of 16 columns, times RG groups of rows: a wave each; RB blocks of 16 rows.
+template <int MODE, int CG, int RG, int WB, int RB>
+__global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyArgs a) {
+  constexpr int NW = CG * RG;
+  constexpr int S = stages(RB, 16 * CG * WB, NW);
+  constexpr int NCB = CG * WB, BN = 16 * NCB;   // columns of the workgroup, in blocks and singly
+  constexpr int RW = (RB + RG - 1) / RG;        // row blocks per wave
+  constexpr int BLOCKS = RB * NCB;              // 16 x 16 blocks of the tile
+  constexpr int kPartFloats = BLOCKS * 256;     // partial sums of one K part of one tile
+  // CP copy instructions to every wave; what is over reads nothing.  (Behind a branch by wave, the compiler would wait for more
+  // of them than needed before each LDS read.)
+  constexpr int COPIES = copies(RB, BN), CP = (COPIES + NW - 1) / NW;
+  constexpr int kXBytes = RB * 2048, kStage = stage_kb(RB, BN, NW) * 1024;
+  constexpr bool kStream = BN >= 96;            // W past the caches' other contents, where an instruction is all W
+  constexpr int kNt = 2;
+  constexpr bool kPairs = MODE == SX_GEMM_SWIGLU || MODE == SX_GEMM_QKV_ROPE;
+  static_assert(CP <= 8 && S >= 3, "");
   // one array per stage: X rows then W rows, 128 bytes each, 16-byte chunk c of row r at position c ^ ((r >> 1) & 7)
-  __shared__ __attribute__((aligned(1024))) unsigned char st0[kStageBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char st1[kStageBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char st2[kStageBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char st3[NH == 2 ? kStageBytes : 1024];
+  __shared__ __attribute__((aligned(1024))) unsigned char st0[kStage];
+  __shared__ __attribute__((aligned(1024))) unsigned char st1[kStage];
+  __shared__ __attribute__((aligned(1024))) unsigned char st2[kStage];
+  __shared__ __attribute__((aligned(S > 3 ? 1024 : 16))) unsigned char st3[S > 3 ? kStage : 16];
+  __shared__ __attribute__((aligned(S > 4 ? 1024 : 16))) unsigned char st4[S > 4 ? kStage : 16];
+  __shared__ __attribute__((aligned(S > 5 ? 1024 : 16))) unsigned char st5[S > 5 ? kStage : 16];
+  __shared__ __attribute__((aligned(S > 6 ? 1024 : 16))) unsigned char st6[S > 6 ? kStage : 16];
+  __shared__ __attribute__((aligned(S > 7 ? 1024 : 16))) unsigned char st7[S > 7 ? kStage : 16];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wh = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
   const int l16 = lane & 15, lq = lane >> 4;
+  const int wc = wave % CG, wr = wave / CG;
   const int tile_n = blockIdx.x / a.split, kpart = blockIdx.x % a.split;
+  // Where columns go in pairs (gate and up, the two halves of a head), the tile's blocks of 16 alternate between the first
+  // and the second of them.
+  auto stacked_row = [&](int col) {  // column of the tile -> row of the stacked matrices
+    const int p = tile_n * (BN / 2) + (col >> 5) * 16 + (col & 15), second = (col >> 4) & 1;
+    return MODE == SX_GEMM_SWIGLU    ? min(p, a.n0 - 1) + (second ? a.n0 : 0)
+           : MODE == SX_GEMM_QKV_ROPE ? min((p >> 6) * 128 + second * 64 + (p & 63), a.N - 1)
+                                      : min(tile_n * BN + col, a.N - 1);
+  };
 
-  // ---- copies: instruction t of wave w fills X rows 8 (kXCopies w + t) .. + 7 or W rows 16 w + 8 t .. + 7 (t < 2)
+  // ---- copies: instruction c fills rows 8 c .. 8 c + 7 of the stage; wave w issues w, w + NW, ...
   const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.X);
-  const __amdgpu_buffer_rsrc_t wres0 = make_rsrc(a.W0), wres1 = make_rsrc(a.W1), wres2 = make_rsrc(a.W2);
-  __amdgpu_buffer_rsrc_t wres[2];
-  int xoff[4], woff[2];
+  __amdgpu_buffer_rsrc_t res[8];
+  int off[8];  // [CP] (of sizes that the template does not give the host pass drops the kernel)
 #pragma unroll
-  for (int t = 0; t < kXCopies; ++t) {
-    const int cchunk = (lane & 7) ^ ((4 * (t & 1) + (lane >> 4)) & 7);
-    int m = 8 * (kXCopies * wave + t) + (lane >> 3);
-    m = m < a.M ? m : a.M - 1;
-    xoff[t] = (int)(((unsigned)m * (unsigned)a.K + cchunk * 8) * 2u);
-  }
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int cchunk = (lane & 7) ^ ((4 * (t & 1) + (lane >> 4)) & 7);
-    if (MODE == SX_GEMM_SWIGLU) {
-      // slab rows in 16-row groups, even = gate, odd = up: wave w copies group w
-      int f = tile_n * (BN / 2) + (wave >> 1) * 16 + 8 * t + (lane >> 3);
-      f = f < a.N ? f : a.N - 1;
-      wres[t] = (wave & 1) ? wres1 : wres0;
-      woff[t] = (int)(((unsigned)f * (unsigned)a.K + cchunk * 8) * 2u);
-    } else if (MODE == SX_GEMM_QKV_ROPE) {
-      // the same groups: even = 16 columns of the lower half of a head, odd = their partners in the upper one
-      const int p0 = tile_n * (BN / 2) + (wave >> 1) * 16, head = p0 >> 6;
-      const int first = head >= a.hq + a.hkv ? a.hq + a.hkv : head >= a.hq ? a.hq : 0;
-      const int n = (head - first) * 128 + (wave & 1) * 64 + (p0 & 63) + 8 * t + (lane >> 3);
-      wres[t] = head >= a.hq + a.hkv ? wres2 : head >= a.hq ? wres1 : wres0;
-      woff[t] = (int)(((unsigned)n * (unsigned)a.K + cchunk * 8) * 2u);
+  for (int t = 0; t < CP; ++t) {
+    const int c = wave + t * NW, r = 8 * (c < RB * 2 ? c : c - RB * 2) + (lane >> 3);
+    const int chunk = (lane & 7) ^ ((r >> 1) & 7);
+    if (c < RB * 2) {
+      res[t] = xres;
+      off[t] = (int)(((unsigned)min(r, a.M - 1) * (unsigned)a.K + chunk * 8) * 2u);
+    } else if (c < COPIES) {
+      const int b0 = stacked_row((c - RB * 2) * 8);  // (eight rows belong to one of the stacked matrices)
+      const int which = b0 >= a.n0 + a.n1 ? 2 : b0 >= a.n0 ? 1 : 0;
+      const int n = stacked_row(r) - (which == 2 ? a.n0 + a.n1 : which == 1 ? a.n0 : 0);
+      res[t] = make_rsrc(which == 2 ? a.W[2] : which == 1 ? a.W[1] : a.W[0]);
+      off[t] = (int)(((unsigned)n * (unsigned)a.K + chunk * 8) * 2u);
     } else {
-      const int r0 = tile_n * BN + 16 * wave + 8 * t;
-      const int g0 = min(r0, a.N - 1);  // first row of the 8-row group decides the matrix
-      int n = min(r0 + (lane >> 3), a.N - 1);
-      int first = 0;
-      wres[t] = wres0;
-      if (g0 >= a.n0 + a.n1) {
-        wres[t] = wres2;
-        first = a.n0 + a.n1;
-      } else if (g0 >= a.n0) {
-        wres[t] = wres1;
-        first = a.n0;
-      }
-      woff[t] = (int)(((unsigned)(n - first) * (unsigned)a.K + cchunk * 8) * 2u);
+      res[t] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(a.X), 0, 0, 0x00020000);
+      off[t] = 0;
     }
   }
-// copies the next slab into stage STG_ and steps on, from the last slab of K to the first; past the end of the walk its last
-// slab again, which nobody reads any more
-#define SX_COPY(STG_)                                                                                            \
-  {                                                                                                              \
-    _Pragma("unroll") for (int t = 0; t < kXCopies; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(               \
-        xres, (lds_void_ptr)(STG_ + (kXCopies * wave + t) * 1024), 16, xoff[t], so, 0, 0);                       \
-    _Pragma("unroll") for (int t = 0; t < 2; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                      \
-        wres[t], (lds_void_ptr)(STG_ + kXBytes + wave * 2048 + t * 1024), 16, woff[t], so, 0, 0);                \
-    const int next = so + BK * 2 == so_end ? so_begin : so + BK * 2;                                             \
-    so = next == so_start ? so : next;                                                                           \
-  }
-
-  // acc[i][j]: W rows (output columns) 64 wh + 32 wn + 16 i .. + 15, X rows (output rows) 64 wm + 16 j .. + 15
-  f32x4 acc[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
-  const int fsw = (l16 >> 1) & 7;
-  const int xrow = (wm * 64 + l16) * (BK * 2);
-  const int wrow = kXBytes + (wh * 64 + wn * 32 + l16) * (BK * 2);
-  const int kc[2] = {(lq ^ fsw) << 4, ((4 + lq) ^ fsw) << 4};
-
-// "+v": the accumulators stay where they are (see the wide kernel); statements are volatile, order as written
-#define SX_MFMA(ACC, A, B) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(ACC) : "v"(A), "v"(B));
-#define SX_SLAB(STG_, STG_F)                                                                                     \
-  SX_WAIT_BARRIER(NH == 1 ? kWaitVm6 : kWaitVm8)                                                                 \
-  SX_COPY(STG_F)                                                                                                 \
-  _Pragma("unroll") for (int ks = 0; ks < 2; ++ks) {                                                             \
-    bf16x8 fx[4], fw[2];                                                                                         \
-    _Pragma("unroll") for (int i = 0; i < 2; ++i)                                                                \
-        fw[i] = *reinterpret_cast<const bf16x8*>(STG_ + wrow + i * (16 * BK * 2) + kc[ks]);                      \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                                \
-        fx[j] = *reinterpret_cast<const bf16x8*>(STG_ + xrow + j * (16 * BK * 2) + kc[ks]);                      \
-    _Pragma("unroll") for (int i = 0; i < 2; ++i) _Pragma("unroll") for (int j = 0; j < 4; ++j)                  \
-        SX_MFMA(acc[i][j], fw[i], fx[j])                                                                         \
-  }
-
-  // slabs [first, first + NB) of K; slab s sits in stage (s - first) % 3.  Iteration: wait for this wave's
-  // copies of the current slab (those of the next may stay in flight), barrier (everybody's are in, everybody
-  // is done with the previous slab), start the copies of the slab after next into the stage just freed.
+  // Slabs [first, first + NB) of K from slab first + rot on and round; past the end of the walk its last slab again, which
+  // nobody reads any more.
   const int nb_all = a.K / BK;
   const int first = kpart * nb_all / a.split;
   const int NB = (kpart + 1) * nb_all / a.split - first;
   // Every workgroup walks its slabs from another one on.  Started all at their first, hundreds of workgroups ask for the
   // same 128 bytes of rows that lie a power of two apart, step after step, and the memory channels take turns.  By
-  // neighbours on an XCD in a launch of one round, by all neighbours where later rounds drift apart anyway: 7B gate|up
-  // product at 100 rows 46.8 -> 41.5 us, head of 32000 rows 61.3 -> 50.7, of 128256 rows 236 -> 204, 70B O projection
-  // 43.4 -> 36.9, 70B gate|up 191 -> 176.  With weights that a cache still holds, up to 3 % slower; the offset is stepped
-  // from slab to slab, since computing it anew cost every slab another 40 cycles (301 x 8192, uncut: 37.9 -> 40.1 us).
+  // neighbours on an XCD in a launch of one round, by all neighbours where later rounds drift apart anyway: in this kernel's
+  // predecessor 7B gate|up at 100 rows 46.8 -> 41.5 us, head of 32000 rows 61.3 -> 50.7, of 128256 rows 236 -> 204.
   const int rot = (int)((a.rounds > 1 ? 5u * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
   const int so_begin = first * (BK * 2), so_end = so_begin + NB * (BK * 2);
   const int so_start = so_begin + rot * (BK * 2);
   int so = so_start;  // of the next slab to copy
-  // (NH = 2: four stages, the copies of the next two slabs may stay in flight, those of the third go out)
-  // (the waits count copies, which must go out slab by slab: nothing else orders writes to different arrays)
+#define SX_COPY(STG_)                                                                                            \
+  {                                                                                                              \
+    _Pragma("unroll") for (int t = 0; t < CP; ++t) {                                                             \
+      const lds_void_ptr to = (lds_void_ptr)(STG_ + min(wave + t * NW, COPIES) * 1024);                          \
+      if (kStream && t * NW >= RB * 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(res[t], to, 16, off[t], so, 0, kNt); \
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(res[t], to, 16, off[t], so, 0, 0);                           \
+    }                                                                                                            \
+    const int next = so + BK * 2 == so_end ? so_begin : so + BK * 2;                                             \
+    so = next == so_start ? so : next;                                                                           \
+    asm volatile("" ::: "memory"); /* (the waits count copies, which must go out slab by slab) */                \
+  }
+// this wave's copies but those of the N_ youngest slabs are in; then everybody's
+#define SX_WAIT(N_)                                                                                              \
+  asm volatile("" ::: "memory");                                                                                 \
+  __builtin_amdgcn_s_waitcnt(wait_vm((N_) * CP));                                                                \
+  __builtin_amdgcn_s_barrier();                                                                                  \
+  asm volatile("" ::: "memory");
+
+  // acc[i][j]: W rows (output columns) 16 (WB wc + i) .. + 15 of the tile, X rows (output rows) 16 (RW wr + j) .. + 15
+  f32x4 acc[WB][RW];
+#pragma unroll
+  for (int i = 0; i < WB; ++i)
+#pragma unroll
+    for (int j = 0; j < RW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fsw = (l16 >> 1) & 7;
+  const int wrow = kXBytes + (WB * wc * 16 + l16) * 128;
+#define SX_SLAB(STG_)                                                                                            \
+  _Pragma("unroll") for (int s = 0; s < 2; ++s) {                                                                \
+    bf16x8 fw[WB], fx[RW];                                                                                       \
+    const int kc = ((4 * s + lq) ^ fsw) << 4;                                                                    \
+    _Pragma("unroll") for (int i = 0; i < WB; ++i)                                                               \
+        fw[i] = *reinterpret_cast<const bf16x8*>(STG_ + wrow + i * 2048 + kc);                                   \
+    _Pragma("unroll") for (int j = 0; j < RW; ++j)                                                               \
+        fx[j] = *reinterpret_cast<const bf16x8*>(STG_ + (min(RW * wr + j, RB - 1) * 16 + l16) * 128 + kc);       \
+    _Pragma("unroll") for (int i = 0; i < WB; ++i) _Pragma("unroll") for (int j = 0; j < RW; ++j)                \
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);                   \
+  }
+
+  // Slab t of the walk sits in stage t % S.  Per slab: wait for its copies (those of the next S - 2 stay in flight) and for
+  // everybody to be done with the slab before it, start the copies of slab t + S - 1 into that stage, multiply.
   SX_COPY(st0)
-  asm volatile("" ::: "memory");
   SX_COPY(st1)
-  asm volatile("" ::: "memory");
+  if constexpr (S > 3) SX_COPY(st2)
+  if constexpr (S > 4) SX_COPY(st3)
+  if constexpr (S > 5) SX_COPY(st4)
+  if constexpr (S > 6) SX_COPY(st5)
+  if constexpr (S > 7) SX_COPY(st6)
+#define SX_STEP(STG_, PREV_)             \
+  {                                      \
+    SX_WAIT(S - 2)                       \
+    SX_COPY(PREV_)                       \
+    SX_SLAB(STG_)                        \
+  }
+#define SX_STEP0()                                   \
+  if constexpr (S == 3) SX_STEP(st0, st2)            \
+  if constexpr (S == 4) SX_STEP(st0, st3)            \
+  if constexpr (S == 5) SX_STEP(st0, st4)            \
+  if constexpr (S == 6) SX_STEP(st0, st5)            \
+  if constexpr (S == 7) SX_STEP(st0, st6)            \
+  if constexpr (S == 8) SX_STEP(st0, st7)
   int s = 0;
-  if (NH == 1) {
-    for (; s + 3 <= NB; s += 3) {
-      SX_SLAB(st0, st2)
-      SX_SLAB(st1, st0)
-      SX_SLAB(st2, st1)
-    }
-    if (s < NB) {
-      SX_SLAB(st0, st2)
-      if (s + 1 < NB) { SX_SLAB(st1, st0) }
-    }
-  } else {
-    SX_COPY(st2)
-    for (; s + 4 <= NB; s += 4) {
-      SX_SLAB(st0, st3)
-      SX_SLAB(st1, st0)
-      SX_SLAB(st2, st1)
-      SX_SLAB(st3, st2)
-    }
-    if (s < NB) {
-      SX_SLAB(st0, st3)
-      if (s + 1 < NB) { SX_SLAB(st1, st0) }
-      if (s + 2 < NB) { SX_SLAB(st2, st1) }
+  for (; s + S <= NB; s += S) {
+    SX_STEP0()
+    SX_STEP(st1, st0)
+    SX_STEP(st2, st1)
+    if constexpr (S > 3) SX_STEP(st3, st2)
+    if constexpr (S > 4) SX_STEP(st4, st3)
+    if constexpr (S > 5) SX_STEP(st5, st4)
+    if constexpr (S > 6) SX_STEP(st6, st5)
+    if constexpr (S > 7) SX_STEP(st7, st6)
+  }
+  s = NB - s;  // slabs left, fewer than S
+  if (s > 0) {
+    SX_STEP0()
+    if (s > 1) {
+      SX_STEP(st1, st0)
+      if (S > 3 && s > 2) {
+        SX_STEP(st2, st1)
+        if constexpr (S > 4) if (s > 3) {
+          SX_STEP(st3, st2)
+          if constexpr (S > 5) if (s > 4) {
+            SX_STEP(st4, st3)
+            if constexpr (S > 6) if (s > 5) {
+              SX_STEP(st5, st4)
+              if constexpr (S > 7) if (s > 6) SX_STEP(st6, st5)
+            }
+          }
+        }
+      }
     }
   }
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);  // copies past the end of K must land before the LDS is released
-  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");  // the matrix pipe's last results (hand-written MFMAs)
+  SX_WAIT(0)  // every copy is in and every stage is read: the LDS is free
+#undef SX_STEP0
+#undef SX_STEP
 #undef SX_SLAB
-#undef SX_MFMA
 #undef SX_COPY
+#undef SX_WAIT
 
-  // ---- K split: partial sums meet in memory, the last workgroup to arrive adds them in part order -------------
-  // (device-scope stores and loads, stores complete before the counter's atomic: see the wide kernel)
+  // ---- the tile is dealt out anew through LDS, block after block of 16 x 16 as the lanes hold them: block b = j NCB + column
+  // block belongs to wave b % NW (pairs: their number, likewise)
+  auto slot = [&](int b) -> unsigned char* {
+    constexpr int PER_STAGE = kStage / 1024;
+    const int stage = b / PER_STAGE;
+    return (stage == 0 ? st0 : stage == 1 ? st1 : stage == 2 ? st2 : stage == 3 ? st3 : stage == 4 ? st4 : st5) +
+           (b - stage * PER_STAGE) * 1024 + lane * 16;
+  };
+  static_assert(BLOCKS <= (S < 6 ? S : 6) * (kStage / 1024), "a block lies in one stage");
+#pragma unroll
+  for (int i = 0; i < WB; ++i)
+#pragma unroll
+    for (int j = 0; j < RW; ++j)
+      if (RB % RG == 0 || RW * wr + j < RB) *reinterpret_cast<f32x4*>(slot((RW * wr + j) * NCB + WB * wc + i)) = acc[i][j];
+  __syncthreads();
+  constexpr int PER = kPairs ? 2 : 1;                        // blocks of a unit, side by side in a row of blocks
+  constexpr int UNITS = BLOCKS / PER, NU = (UNITS + NW - 1) / NW;  // per wave
+  f32x4 v[NU][PER];
+#pragma unroll
+  for (int u = 0; u < NU; ++u)
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      v[u][e] = *reinterpret_cast<const f32x4*>(slot(min(wave + u * NW, UNITS - 1) * PER + e));
+
+  // ---- K split: partial sums meet in memory, the last workgroup to arrive adds them in part order
+  // (device-scope stores and loads, stores complete before the counter's device-scope atomic is issued)
   if (a.split > 1) {
     constexpr int kScopeDevice = 16;
     __shared__ int s_last;
     const __amdgpu_buffer_rsrc_t pres = make_rsrc(a.part);
-    const unsigned mine = (unsigned)((tile_n * a.split + kpart) * kPartFloats + wave * (8 * 256) + lane * 4) * 4u;
+    const unsigned all = (unsigned)(tile_n * a.split * kPartFloats + lane * 4) * 4u;  // bytes
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int u = 0; u < NU; ++u)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), pres, mine + (i * 4 + j) * 1024, 0,
-                                               kScopeDevice);
+      for (int e = 0; e < PER; ++e) {
+        const int b = min(wave + u * NW, UNITS - 1) * PER + e;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[u][e]), pres,
+                                               all + (unsigned)kpart * (kPartFloats * 4u) + b * 1024, 0, kScopeDevice);
+      }
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+    __builtin_amdgcn_s_waitcnt(wait_vm(0));
     __syncthreads();
     if (tid == 0) {
       const int before = atomicAdd(a.part_cnt + tile_n, 1);
       s_last = before == a.split - 1;
-      if (s_last) a.part_cnt[tile_n] = 0;
+      if (s_last) a.part_cnt[tile_n] = 0;  // ready for the next launch
     }
     __syncthreads();
     if (!s_last) return;
-    // all 8 blocks of a part are requested together (one memory round trip per part, not one per block); the
-    // workgroup's own part comes from its registers (the same bits it stored); parts are added in part order
-    const unsigned all = (unsigned)(tile_n * a.split * kPartFloats + wave * (8 * 256) + lane * 4) * 4u;
-    f32x4 sum[8];
+    // all blocks of a part are requested together (one memory round trip per part, not one per block); the workgroup's own
+    // part comes from its registers (the same bits that it stored)
+    f32x4 sum[NU][PER];
     for (int p = 0; p < a.split; ++p) {
-      f32x4 t[8];
+      f32x4 x[NU][PER];
       if (p == kpart) {
 #pragma unroll
-        for (int b = 0; b < 8; ++b) t[b] = acc[b >> 2][b & 3];
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+          for (int e = 0; e < PER; ++e) x[u][e] = v[u][e];
       } else {
 #pragma unroll
-        for (int b = 0; b < 8; ++b)
-          t[b] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                                               pres, all + (unsigned)p * (kPartFloats * 4u) + b * 1024, 0, kScopeDevice));
+        for (int u = 0; u < NU; ++u)
+#pragma unroll
+          for (int e = 0; e < PER; ++e)
+            x[u][e] = __builtin_bit_cast(
+                f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                           pres, all + (unsigned)p * (kPartFloats * 4u) + (min(wave + u * NW, UNITS - 1) * PER + e) * 1024, 0,
+                           kScopeDevice));
       }
 #pragma unroll
-      for (int b = 0; b < 8; ++b) sum[b] = p == 0 ? t[b] : sum[b] + t[b];
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < PER; ++e) sum[u][e] = p == 0 ? x[u][e] : sum[u][e] + x[u][e];
     }
 #pragma unroll
-    for (int b = 0; b < 8; ++b) acc[b >> 2][b & 3] = sum[b];
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+      for (int e = 0; e < PER; ++e) v[u][e] = sum[u][e];
   }
-
-  // ---- epilogue.  acc[i][j][e]: output row 64 wm + 16 j + l16, W row 32 wn + 16 i + 4 lq + e ------------------
-  const bool vec = (a.N & 3) == 0;
-  if (MODE == SX_GEMM_SWIGLU) {
-    unsigned short* Y = static_cast<unsigned short*>(a.Y);
-    const int f = tile_n * (BN / 2) + (2 * wh + wn) * 16 + 4 * lq;
+  // ---- epilogue.  v[u][.][e]: output row 16 j + l16, column 4 lq + e of its block
+  if constexpr (MODE == SX_GEMM_SWIGLU) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = wm * 64 + 16 * j + l16;
-      if (m >= a.M || f >= a.N) continue;
-      unsigned short h[4];
+    for (int u = 0; u < NU; ++u) {
+      const int b = wave + u * NW, m = b / (NCB / 2) * 16 + l16, f = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
+      if (b >= UNITS || m >= a.M || f >= a.N) continue;
+      float h[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float g = acc[0][j][e], u = acc[1][j][e];
-        h[e] = (unsigned short)f32_to_bf16_bits(silu_mul_bf16_bound(g, u));
-      }
-      unsigned short* y = Y + (size_t)m * a.N + f;
-      if (vec) {
-        u32x2 v;
-        v[0] = h[0] | ((uint32_t)h[1] << 16);
-        v[1] = h[2] | ((uint32_t)h[3] << 16);
-        *reinterpret_cast<u32x2*>(y) = v;
+      for (int e = 0; e < 4; ++e) h[e] = silu_mul_bf16_bound(v[u][0][e], v[u][PER - 1][e]);
+      unsigned short* y = static_cast<unsigned short*>(a.Y) + (size_t)m * a.N + f;
+      u32x2 o;
+      o[0] = pack_bf16x2(h[0], h[1]);
+      o[1] = pack_bf16x2(h[2], h[3]);
+      if ((a.N & 3) == 0) {
+        *reinterpret_cast<u32x2*>(y) = o;
       } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          if (f + e < a.N) y[e] = h[e];
+          if (f + e < a.N) y[e] = (unsigned short)(o[e >> 1] >> (16 * (e & 1)));
       }
     }
-  } else if (MODE == SX_GEMM_QKV_ROPE) {
-    // acc[0] and acc[1] hold the pairs that the rotary embedding turns by the row's angle; rounded once, after it.
-    // (A launch of its own over the fp32 product cost 4.3 us and the gap before it; the wide kernel's tiles are too few:
-    // 128 rows, 4096 wide, 32 heads 50.6 -> 37.8 us with the table and the counters, 64/8 heads of 8192 at 77 rows 65 -> 44.)
-    const int p = tile_n * (BN / 2) + (2 * wh + wn) * 16 + 4 * lq, head = p >> 6, w = p & 63;
-    const bool is_v = head >= a.hq + a.hkv;
-    const int nheads = head < a.hq ? a.hq : a.hkv;
-    const int first = is_v ? a.hq + a.hkv : head >= a.hq ? a.hq : 0;
-    unsigned short* Y = (head < a.hq ? a.q : is_v ? a.v : a.k) + (size_t)(head - first) * 128 + w;
-    f32x4 t[4][2];
+  } else if constexpr (MODE == SX_GEMM_QKV_ROPE) {
+    // a unit's blocks hold the pairs that the rotary embedding turns by the row's angle; rounded once, after it
+    const int hq = a.n0 >> 7, hkv = a.n1 >> 7;
+    f32x4 t[NU][2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {  // all rows' angles are requested before the first is used
-      const f32x4* c = reinterpret_cast<const f32x4*>(a.cs + (size_t)min(wm * 64 + 16 * j + l16, a.M - 1) * 64 + w);
-      t[j][0] = c[0];
-      t[j][1] = c[1];
+    for (int u = 0; u < NU; ++u) {  // all rows' angles are requested before the first is used
+      const int b = min(wave + u * NW, UNITS - 1), p = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
+      const f32x4* c = reinterpret_cast<const f32x4*>(a.cs + (size_t)min(b / (NCB / 2) * 16 + l16, a.M - 1) * 64 + (p & 63));
+      t[u][0] = c[0];
+      t[u][1] = c[1];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = wm * 64 + 16 * j + l16;
-      if (m >= a.M) continue;
+    for (int u = 0; u < NU; ++u) {
+      const int b = wave + u * NW, m = b / (NCB / 2) * 16 + l16, p = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
+      if (b >= UNITS || m >= a.M || 2 * p >= a.N) continue;
+      const int head = p >> 6;
+      const bool is_v = head >= hq + hkv;
+      const int nheads = head < hq ? hq : hkv, first_head = is_v ? hq + hkv : head >= hq ? hq : 0;
+      unsigned short* y = (head < hq ? a.q : is_v ? a.v : a.k) + ((size_t)m * nheads + head - first_head) * 128 + (p & 63);
       float lo[4], hi[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float x0 = acc[0][j][e], x1 = acc[1][j][e];
-        const float c = t[j][e >> 1][2 * (e & 1)], s = t[j][e >> 1][2 * (e & 1) + 1];
-        rope_turn(x0, x1, c, s, lo[e], hi[e]);
+        const float x0 = v[u][0][e], x1 = v[u][PER - 1][e];
+        rope_turn(x0, x1, t[u][e >> 1][2 * (e & 1)], t[u][e >> 1][2 * (e & 1) + 1], lo[e], hi[e]);
         if (is_v) lo[e] = x0, hi[e] = x1;
       }
-      unsigned short* y = Y + (size_t)m * nheads * 128;
       u32x2 o;
       o[0] = pack_bf16x2(lo[0], lo[1]);
       o[1] = pack_bf16x2(lo[2], lo[3]);
@@ -326,99 +369,106 @@ __global__ __launch_bounds__(256 * NH, 3 - NH) void gemm_skinny_bf16_kernel(Skin
       o[1] = pack_bf16x2(hi[2], hi[3]);
       *reinterpret_cast<u32x2*>(y + 64) = o;
     }
-  } else if (vec && tile_n * BN + BN <= a.N) {
-    // whole column tile: the residual of all 8 blocks is requested before the first add (rows past M read row M - 1
-    // and store nothing); block by block the epilogue was 8 memory round trips long
-    float* Yb = static_cast<float*>(a.Y) + (tile_n * BN + wh * 64 + wn * 32 + 4 * lq);
-    f32x4 r[4][2];
+  } else if ((a.N & 3) == 0) {
+    // the residual of all blocks is requested before the first add (rows and columns past the end read the last ones and
+    // store nothing); block by block the epilogue was a chain of memory round trips
+    float* Y = static_cast<float*>(a.Y);
+    f32x4 r[NU];
     if (MODE == SX_GEMM_RESIDUAL) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          r[j][i] = *reinterpret_cast<const f32x4*>(Yb + (size_t)min(wm * 64 + 16 * j + l16, a.M - 1) * a.N + 16 * i);
+      for (int u = 0; u < NU; ++u) {
+        const int b = min(wave + u * NW, UNITS - 1), m = min(b / NCB * 16 + l16, a.M - 1);
+        r[u] = *reinterpret_cast<const f32x4*>(Y + (size_t)m * a.N + min(tile_n * BN + b % NCB * 16 + 4 * lq, a.N - 4));
+      }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = wm * 64 + 16 * j + l16;
-      if (m >= a.M) continue;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        f32x4 v = acc[i][j];
-        if (MODE == SX_GEMM_RESIDUAL) v += r[j][i];
-        *reinterpret_cast<f32x4*>(Yb + (size_t)m * a.N + 16 * i) = v;
-      }
+    for (int u = 0; u < NU; ++u) {
+      const int b = wave + u * NW, m = b / NCB * 16 + l16, n = tile_n * BN + b % NCB * 16 + 4 * lq;
+      if (b >= UNITS) continue;
+      if (m >= a.M || n >= a.N) continue;
+      f32x4 x = v[u][0];
+      if (MODE == SX_GEMM_RESIDUAL) x += r[u];
+      *reinterpret_cast<f32x4*>(Y + (size_t)m * a.N + n) = x;
     }
   } else {
     float* Y = static_cast<float*>(a.Y);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = wm * 64 + 16 * j + l16;
+    for (int u = 0; u < NU; ++u) {
+      const int b = wave + u * NW, m = b / NCB * 16 + l16, n = tile_n * BN + b % NCB * 16 + 4 * lq;
+      if (b >= UNITS || m >= a.M) continue;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int n = tile_n * BN + wh * 64 + wn * 32 + 16 * i + 4 * lq;
-        if (m >= a.M || n >= a.N) continue;
-        float* y = Y + (size_t)m * a.N + n;
-        if (vec) {
-          f32x4 v = acc[i][j];
-          if (MODE == SX_GEMM_RESIDUAL) v += *reinterpret_cast<const f32x4*>(y);
-          *reinterpret_cast<f32x4*>(y) = v;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (n + e < a.N) {
-              if (MODE == SX_GEMM_RESIDUAL) y[e] += acc[i][j][e];
-              else y[e] = acc[i][j][e];
-            }
+      for (int e = 0; e < 4; ++e)
+        if (n + e < a.N) {
+          float* y = Y + (size_t)m * a.N + n + e;
+          if (MODE == SX_GEMM_RESIDUAL) *y += v[u][0][e];
+          else *y = v[u][0][e];
         }
-      }
     }
   }
 }
-#undef SX_WAIT_BARRIER
+
+// Tiles of 128, 96 or 64 columns and cut of K.  The figures are fitted to 5100 launches at 1 to 128 rows, 40 products of 1024 to
+// 57000 columns and K of 2048 to 28672, in all these forms, weights from memory: 2.1 us a round; a compute unit's copies at
+// 63 GB/s and the weights from memory at 5.2 TB/s, which hinder each other (root of the sum of squares); and, cut, what the
+// last arriver does.  The choice is within 0.6 % of the best launch on average, 8 % at worst.
+// 96 columns only where columns come in pairs: they are for gate|up of 2 x 11008 rows (128 columns 41.6 us at 100 rows, 96 38.0)
+// and QKV of 12288 (cut in two 29.4 and 25.8); none of the plain products of the models' layers is best with them.
+struct SkinnyPlan {
+  int columns, split;
+};
+SkinnyPlan plan_skinny(int M, int cols, int K, bool pairs, bool have_ws, size_t split_ws_bytes) {
+  const int cus = sx_compute_units(), nb = K / BK, rb = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : M <= 80 ? 5 : M <= 112 ? 7 : 8;
+  SkinnyPlan p = {64, 1};
+  float best = 1e30f;
+  for (int bn = 128; bn >= 64; bn -= 32) {
+    if (bn == 96 && !pairs) continue;
+    const int tiles = (cols + bn - 1) / bn;
+    for (int split = 1; split <= 16; ++split) {
+      const double part = split > 1 ? (double)split * rb * 16 * bn * sizeof(float) : 0.;  // bytes per tile
+      if (split > 1 && (!have_ws || tiles > 256 || tiles * split > cus || nb / split < 6 || split_ws_bytes < 1024 + tiles * part))
+        break;
+      const int rounds = (tiles * split + cus - 1) / cus;
+      const float unit = rounds * ((nb + split - 1) / split) * (rb * 2048 + bn * 128) / 63e3f;
+      const float weights = (float)tiles * nb * bn * 128 / 5.2e6f;
+      const float cost = 2.1f * rounds + sqrtf(unit * unit + weights * weights) +
+                         (split > 1 ? 1.3f + 0.07f * split + 2.5e-5f * (float)part : 0.f);
+      if (cost < best) best = cost, p = {bn, split};
+    }
+  }
+  return p;
+}
+
+template <int MODE, int CG, int RG, int WB>
+void launch_rows(const SkinnyArgs& a, hipStream_t st) {
+  // (fewer blocks of rows than row groups: the groups that are over multiply along, since all are wanted for the copies)
+  const int grid = a.tiles * a.split;
+  if (a.M <= 16) gemm_skinny_bf16_kernel<MODE, CG, 2, WB, 1><<<grid, 64 * CG * 2, 0, st>>>(a);
+  else if (a.M <= 32) gemm_skinny_bf16_kernel<MODE, CG, RG, WB, 2><<<grid, 64 * CG * RG, 0, st>>>(a);
+  else if (a.M <= 64) gemm_skinny_bf16_kernel<MODE, CG, RG, WB, 4><<<grid, 64 * CG * RG, 0, st>>>(a);
+  else if (a.M <= 80) gemm_skinny_bf16_kernel<MODE, CG, RG, WB, 5><<<grid, 64 * CG * RG, 0, st>>>(a);
+  else if (a.M <= 112) gemm_skinny_bf16_kernel<MODE, CG, RG, WB, 7><<<grid, 64 * CG * RG, 0, st>>>(a);
+  else gemm_skinny_bf16_kernel<MODE, CG, RG, WB, 8><<<grid, 64 * CG * RG, 0, st>>>(a);
+}
 
 // cols: rows of W that the launch walks
-void plan_skinny(SkinnyArgs& a, int cols, void* split_ws, size_t split_ws_bytes) {
-  // Cut K only while there are fewer tiles than compute units (measured: with a tile per unit or more the extra
-  // parts cost more in partial sums and short K loops than they gain), parts of at least 4 slabs, and only as
-  // far as the caller's memory for partial sums (and its 256 counters) goes.
-  // 128-column tiles (8 waves) where they need no cut or the parts of the cut stay long (40 slabs: the 7B QKV
-  // projection, cut in two parts of 32, is better off with 192 uncut 64-column tiles; the 70B one, three parts of
-  // 42, is not); otherwise twice as many 64-column tiles.
-  const int slots = sx_compute_units(), nb = a.K / BK;
-  auto plan = [&](int bn, int& tiles, int& split) {
-    tiles = (cols + bn - 1) / bn;
-    split = 1;
-    if (split_ws && tiles <= 256 && 2 * tiles <= slots) {
-      split = slots / tiles;
-      if (split > 8) split = 8;
-      while (split > 1 && nb / split < 4) --split;
-      if (split_ws_bytes < 1024 + (size_t)tiles * split * BM * bn * sizeof(float)) split = 1;
-    }
-  };
-  int nh = 1, tiles = 0, split = 1;
-  if (cols >= 128) {
-    plan(128, tiles, split);
-    if (split == 1 ? 2 * tiles > slots : nb / split >= kWideMinSlabs) nh = 2;
-  }
-  if (nh == 1) plan(64, tiles, split);
-  a.nh = nh;
-  a.tilesN = tiles;
-  a.split = split;
-  a.part = nullptr;
-  a.part_cnt = nullptr;
-  if (split > 1) {
+template <int MODE>
+int launch(SkinnyArgs& a, int cols, void* split_ws, size_t split_ws_bytes, hipStream_t st) {
+  constexpr bool pairs = MODE == SX_GEMM_SWIGLU || MODE == SX_GEMM_QKV_ROPE;
+  const SkinnyPlan p = plan_skinny(a.M, cols, a.K, pairs, split_ws != nullptr, split_ws_bytes);
+  a.tiles = (cols + p.columns - 1) / p.columns;
+  a.split = p.split;
+  a.rounds = (a.tiles * a.split + sx_compute_units() - 1) / sx_compute_units();
+  if (a.split > 1) {
     a.part_cnt = static_cast<int*>(split_ws);
     a.part = reinterpret_cast<float*>(static_cast<char*>(split_ws) + 1024);
   }
-  a.rounds = (a.tilesN * a.split + slots - 1) / slots;
-}
-
-template <int MODE>
-int launch(const SkinnyArgs& a, hipStream_t st) {
-  const int grid = a.tilesN * a.split;
-  if (a.nh == 2) gemm_skinny_bf16_kernel<MODE, 2><<<grid, 512, 0, st>>>(a);
-  else gemm_skinny_bf16_kernel<MODE, 1><<<grid, 256, 0, st>>>(a);
+  if (p.columns == 128) {
+    launch_rows<MODE, 4, 2, 2>(a, st);
+  } else if (p.columns == 64) {
+    launch_rows<MODE, 2, 4, 2>(a, st);
+  } else if constexpr (pairs) {
+    launch_rows<MODE, 2, 4, 3>(a, st);
+  }
   SX_LAUNCH_CHECK();
   return SX_OK;
 }
@@ -428,16 +478,16 @@ int launch(const SkinnyArgs& a, hipStream_t st) {
 // M <= 128.  Arguments as sx_launch_gemm_bf16 (modes store, residual, SwiGLU).
 int sx_launch_gemm_skinny_bf16(const void* X, const void* W0, const void* W1, const void* W2, int n0, int n1, int n2,
                                void* Y, int M, int K, int mode, void* split_ws, size_t split_ws_bytes, hipStream_t st) {
-  if (M < 1 || M > BM || K < BK || K % BK != 0 || n0 < 1 || n1 < 0 || n2 < 0) return SX_ERR_SHAPE;
+  if (M < 1 || M > 128 || K < BK || K % BK != 0 || n0 < 1 || n1 < 0 || n2 < 0) return SX_ERR_SHAPE;
   if (!sx_operand_fits_u32(M, 2ll * K) || !sx_operand_fits_u32(n0, 2ll * K) || !sx_operand_fits_u32(n1, 2ll * K) ||
       !sx_operand_fits_u32(n2, 2ll * K))
     return SX_ERR_SHAPE;
   if (mode != SX_GEMM_SWIGLU && ((n1 > 0 && n0 % 8 != 0) || (n2 > 0 && n1 % 8 != 0))) return SX_ERR_SHAPE;
   SkinnyArgs a = {};
   a.X = static_cast<const unsigned short*>(X);
-  a.W0 = static_cast<const unsigned short*>(W0);
-  a.W1 = static_cast<const unsigned short*>(W1 ? W1 : W0);
-  a.W2 = static_cast<const unsigned short*>(W2 ? W2 : W0);
+  a.W[0] = W0;
+  a.W[1] = W1 ? W1 : W0;
+  a.W[2] = W2 ? W2 : W0;
   a.n0 = n0;
   a.n1 = n1;
   a.n2 = n2;
@@ -453,11 +503,10 @@ int sx_launch_gemm_skinny_bf16(const void* X, const void* W0, const void* W1, co
     a.N = n0 + n1 + n2;
     cols = a.N;
   }
-  plan_skinny(a, cols, split_ws, split_ws_bytes);
   switch (mode) {
-    case SX_GEMM_STORE: return launch<SX_GEMM_STORE>(a, st);
-    case SX_GEMM_RESIDUAL: return launch<SX_GEMM_RESIDUAL>(a, st);
-    case SX_GEMM_SWIGLU: return launch<SX_GEMM_SWIGLU>(a, st);
+    case SX_GEMM_STORE: return launch<SX_GEMM_STORE>(a, cols, split_ws, split_ws_bytes, st);
+    case SX_GEMM_RESIDUAL: return launch<SX_GEMM_RESIDUAL>(a, cols, split_ws, split_ws_bytes, st);
+    case SX_GEMM_SWIGLU: return launch<SX_GEMM_SWIGLU>(a, cols, split_ws, split_ws_bytes, st);
   }
   return SX_ERR_SHAPE;
 }
@@ -466,39 +515,34 @@ int sx_launch_gemm_skinny_bf16(const void* X, const void* W0, const void* W1, co
 int sx_launch_gemm_skinny_qkv_rope_bf16(const void* X, const void* Wq, const void* Wk, const void* Wv, int hq, int hkv,
                                         const float2* rope_cs, void* q, void* k, void* v, int M, int K, void* split_ws,
                                         size_t split_ws_bytes, hipStream_t st) {
-  if (M < 1 || M > BM || K < BK || K % BK != 0 || hq < 1 || hkv < 1) return SX_ERR_SHAPE;
+  if (M < 1 || M > 128 || K < BK || K % BK != 0 || hq < 1 || hkv < 1) return SX_ERR_SHAPE;
   if (!sx_operand_fits_u32(M, 2ll * K) || !sx_operand_fits_u32(128ll * hq, 2ll * K) ||
       !sx_operand_fits_u32(128ll * hkv, 2ll * K))
     return SX_ERR_SHAPE;
   SkinnyArgs a = {};
   a.X = static_cast<const unsigned short*>(X);
-  a.W0 = static_cast<const unsigned short*>(Wq);
-  a.W1 = static_cast<const unsigned short*>(Wk);
-  a.W2 = static_cast<const unsigned short*>(Wv);
+  a.W[0] = Wq;
+  a.W[1] = Wk;
+  a.W[2] = Wv;
   a.n0 = hq * 128;
   a.n1 = a.n2 = hkv * 128;
   a.M = M;
-  a.N = a.n0 + a.n1 + a.n2;  // whole heads: every tile of 64 or 128 columns is full
+  a.N = a.n0 + a.n1 + a.n2;
   a.K = K;
   a.cs = rope_cs;
   a.q = static_cast<unsigned short*>(q);
   a.k = static_cast<unsigned short*>(k);
   a.v = static_cast<unsigned short*>(v);
-  a.hq = hq;
-  a.hkv = hkv;
-  plan_skinny(a, a.N, split_ws, split_ws_bytes);
-  return launch<SX_GEMM_QKV_ROPE>(a, st);
+  return launch<SX_GEMM_QKV_ROPE>(a, a.N, split_ws, split_ws_bytes, st);
 }
 
 extern "C" int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t* tile_columns,
                                         int32_t* k_parts) {
   if (!tile_columns || !k_parts) return SX_ERR_NULL;
   if (mode < 0 || mode > 2 || N < 1 || K < BK || K % BK != 0) return SX_ERR_SHAPE;
-  SkinnyArgs a = {};
-  a.K = K;
-  int32_t somewhere = 0;  // (only whether there is memory is asked)
-  plan_skinny(a, mode == SX_GEMM_SWIGLU ? 2 * N : N, workspace_bytes ? &somewhere : nullptr, workspace_bytes);
-  *tile_columns = 64 * a.nh;
-  *k_parts = a.split;
+  const SkinnyPlan p = plan_skinny(128, mode == SX_GEMM_SWIGLU ? 2 * N : N, K, mode == SX_GEMM_SWIGLU,
+                                   workspace_bytes != 0, workspace_bytes);
+  *tile_columns = p.columns;
+  *k_parts = p.split;
   return SX_OK;
 }
