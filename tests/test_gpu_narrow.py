@@ -12,7 +12,7 @@ from test_gpu_verify import dev, sx, test_qkv_projection_with_rotary_epilogue as
 SHAPES = [
     (0, 72, 64, 64, False), (0, 250, 1088, 64, True), (1, 1000, 2048, 64, True), (0, 16500, 192, 128, False),
     (1, 9000, 4096, 128, True), (2, 40, 64, 64, False), (2, 1500, 4096, 64, True), (2, 8200, 192, 96, False),
-    (2, 5000, 4096, 96, True), (2, 12000, 320, 128, False),
+    (2, 5000, 4096, 96, True), (2, 14000, 320, 128, False),
 ]
 
 
