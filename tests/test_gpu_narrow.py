@@ -1,10 +1,11 @@
-"""The narrow bf16 GEMM (at most 128 rows): every number of row blocks, every tile width, whole and with K cut."""
+"""The narrow GEMMs (at most 128 rows): every number of row blocks, every tile width, whole and with K cut."""
 import numpy as np
 import pytest
 import torch
 
 import workloads as wl
 from helpers import bf16_ulp
+from test_gpu_w4_model import test_paired_columns_of_4bit_products as check_pairs
 from test_gpu_verify import dev, sx, test_qkv_projection_with_rotary_epilogue as check_qkv  # noqa: F401
 
 # (mode, N, K, columns of a tile, K is cut) at 128 rows, with the workspace; ragged columns, K of one slab, of less than the
@@ -55,3 +56,30 @@ def test_qkv_row_blocks(sx, T):
     """The rotating form: 64 columns, whole and cut; 96 (18432 columns whole, 12288 cut); 128."""
     for d, Hq, Hkv in ((64, 1, 1), (1088, 4, 2), (192, 112, 16), (4096, 32, 32), (2048, 64, 8)):
         check_qkv(sx, T, d, Hq, Hkv, None, None, None)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M", [1, 16, 17, 32, 33, 64, 65, 80, 81, 112, 113, 128])
+def test_row_blocks_4bit(sx, M):
+    """The form with 4-bit weights at the same edges: 64 columns whole and cut, 96 whole and cut, 128 whole and cut, against the
+    product with bf16(scale * (code - zero)) in 64 bits."""
+    ws = torch.zeros(sx.lib.sx_gemm_w4a16_workspace(), dtype=torch.uint8, device=dev())
+    for mode, N, K, group in ((0, 250, 384, 128), (1, 3072, 4096, 512), (0, 20500, 512, 64), (1, 12300, 4096, 128),
+                              (0, 30010, 256, 256), (1, 10200, 8192, 128)):
+        X = wl.hash_normal(64, (M, K), dtype=torch.bfloat16, device=dev())
+        q, s, z = (t.to(dev()) for t in wl.gen_w4(N, K, group, seed=65))
+        codes = torch.stack([(q >> (4 * j)) & 15 for j in range(8)], 2).reshape(N, K).float()
+        W = (s.float().repeat_interleave(group, 1) * (codes - z.float().repeat_interleave(group, 1))).to(torch.bfloat16)
+        want = X.double() @ W.double().T
+        tol = 1e-5 * np.sqrt(K) * float(want.abs().max()) + 1e-6
+        for work in (None, ws):
+            Y = torch.full((M + 16, N), 7.0, dtype=torch.float32, device=dev())
+            sx.gemm_w4a16_bf16(X, q, s, z, Y[:M], group, mode=mode, workspace=work)
+            assert float((Y[:M].double() - want - (7.0 if mode == 1 else 0.0)).abs().max()) <= tol, (mode, N, K)
+            assert bool((Y[M:] == 7.0).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [16, 100])
+def test_paired_4bit_columns_in_tiles_of_96(sx, T):
+    check_pairs(sx, T, (1, 256, 128, 16, 128, 10240, 500))
