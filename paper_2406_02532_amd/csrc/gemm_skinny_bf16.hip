@@ -10,15 +10,15 @@
 // What bounds it: HBM up to some 32 rows (5.5 to 6.6 TB/s of weights where the chip is full); beyond that the copies into LDS
 // as a whole, weights and X together, at 10 to 11 TB/s: every column tile copies all of X again, at 100 rows and 128 columns
 // as many bytes as of W.  Hence:
-//   the tile has as many blocks of 16 rows as M asks for (1, 2, 4, 5, 7 or 8), whose room goes to further stages;
+//   the tile has as many blocks of 16 rows as M asks for (1, 2, 4, 5, 7 or 8), whose room goes to further stages (up to five);
 //   96 columns where 128 leave a third of the chip idle (gate|up of 2 x 11008: 172 tiles or 230);
 //   of 96 columns on, W goes past the caches' other contents (nontemporal), which leaves X there.  With 64 columns, cut, that
 //   was 2 to 7 % slower.
 // Weights from memory, us, the kernel before (128 rows of X always, 64 or 128 columns, three or four stages) -> now, at 16,
-// 64, 100 and 128 rows: 7B O 13.4 -> 10.5, 14.0 -> 12.5, 14.7 -> 14.2, 15.1 -> 15.2; down 24.7 -> 18.9, 25.6 -> 22.4, 26.8 ->
-// 26.6, 29.0 -> 29.1; gate|up 36.2 -> 30.5, 39.0 -> 33.5, 42.1 -> 37.3, 45.4 -> 40.7; head of 32000 46.6 -> 44.2, 47.7 -> 44.4,
-// 49.3 -> 46.9, 52.6 -> 51.4; 70B O 32.4 -> 26.3, 34.0 -> 28.5, 35.4 -> 34.0, 37.1 -> 38.2; down 89.4 -> 73.5, 94.0 -> 80.9, 99.7
-// -> 89.4, 104.7 -> 98.1.  Twelve shapes at 12 row counts: 0.85 of the time; 64 columns at 128 rows up to 3 % slower.
+// 64, 100 and 128 rows: 7B O 13.4 -> 10.2, 14.0 -> 11.7, 14.6 -> 14.1, 15.1 -> 15.1; down 24.7 -> 18.7, 25.8 -> 22.3, 27.3 ->
+// 27.6, 29.6 -> 29.6; gate|up 36.7 -> 29.8, 39.4 -> 32.2, 42.2 -> 38.2, 45.5 -> 39.9; head of 32000 47.1 -> 43.5, 48.4 -> 43.8,
+// 50.7 -> 47.4, 53.6 -> 51.4; 70B O 32.5 -> 26.3, 34.0 -> 28.3, 35.7 -> 34.1, 37.8 -> 37.5; down 89.3 -> 72.3, 94.4 -> 79.4, 100.3
+// -> 90.6, 105.5 -> 97.0.  Fourteen shapes at 7 row counts: 0.86 of the time; 5632-wide gate|up at 128 rows 2 % more.
 // Measured and not kept: W straight into registers in the layout of the MFMA operand (a load then touches 16 rows, 64 bytes
 // each, and the address unit bounds it: head at 100 rows 59 us); 32 columns (7B O at 16 rows 9.2, no better from 64 rows on); a
 // walk that starts at the same slab everywhere (see the rotation below).
@@ -44,8 +44,9 @@ struct SkinnyArgs {
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000);
+// (bytes 0: reads nothing)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int bytes = -1) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
 // all LDS reads of this wave done, at most N of its vector-memory operations outstanding
@@ -55,10 +56,11 @@ constexpr int wait_vm(int n) { return 0x0070 | (n & 15) | ((n >> 4) << 14); }
 // of its own in the stage for those that are over.
 constexpr int copies(int rb, int bn) { return rb * 2 + bn / 8; }
 constexpr int stage_kb(int rb, int bn, int waves) { return copies(rb, bn) + (copies(rb, bn) % waves != 0); }
-// stages of a tile: as many as fit the 160 KB of LDS, up to 8
+// stages of a tile: as many as fit the 160 KB of LDS, up to 5 (eight were no faster: 0.856 of the time of the kernel before over
+// 14 shapes at 1 to 128 rows, five 0.849, four 0.850, three 0.889)
 constexpr int stages(int rb, int bn, int waves) {
   const int s = (160 * 1024 - 1024) / (stage_kb(rb, bn, waves) * 1024);
-  return s < 8 ? s : 8;
+  return s < 5 ? s : 5;
 }
 
 // CG column groups of WB blocks of 16 columns, times RG groups of rows: a wave each; RB blocks of 16 rows.
@@ -77,16 +79,13 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
   constexpr bool kStream = BN >= 96;            // W past the caches' other contents, where an instruction is all W
   constexpr int kNt = 2;
   constexpr bool kPairs = MODE == SX_GEMM_SWIGLU || MODE == SX_GEMM_QKV_ROPE;
-  static_assert(CP <= 8 && S >= 3, "");
+  static_assert(CP <= 8 && S >= 3 && S <= 5, "");
   // one array per stage: X rows then W rows, 128 bytes each, 16-byte chunk c of row r at position c ^ ((r >> 1) & 7)
   __shared__ __attribute__((aligned(1024))) unsigned char st0[kStage];
   __shared__ __attribute__((aligned(1024))) unsigned char st1[kStage];
   __shared__ __attribute__((aligned(1024))) unsigned char st2[kStage];
   __shared__ __attribute__((aligned(S > 3 ? 1024 : 16))) unsigned char st3[S > 3 ? kStage : 16];
   __shared__ __attribute__((aligned(S > 4 ? 1024 : 16))) unsigned char st4[S > 4 ? kStage : 16];
-  __shared__ __attribute__((aligned(S > 5 ? 1024 : 16))) unsigned char st5[S > 5 ? kStage : 16];
-  __shared__ __attribute__((aligned(S > 6 ? 1024 : 16))) unsigned char st6[S > 6 ? kStage : 16];
-  __shared__ __attribute__((aligned(S > 7 ? 1024 : 16))) unsigned char st7[S > 7 ? kStage : 16];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -120,12 +119,12 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
       res[t] = make_rsrc(which == 2 ? a.W[2] : which == 1 ? a.W[1] : a.W[0]);
       off[t] = (int)(((unsigned)n * (unsigned)a.K + chunk * 8) * 2u);
     } else {
-      res[t] = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(a.X), 0, 0, 0x00020000);
+      res[t] = make_rsrc(a.X, 0);
       off[t] = 0;
     }
   }
-  // Slabs [first, first + NB) of K from slab first + rot on and round; past the end of the walk its last slab again, which
-  // nobody reads any more.
+  // Slabs [first, first + NB) of K from slab first + rot on and round.  Past the end of the walk the copies read nothing (with
+  // the last slab again, a part of 16 slabs in five stages copied a quarter as much once more).
   const int nb_all = a.K / BK;
   const int first = kpart * nb_all / a.split;
   const int NB = (kpart + 1) * nb_all / a.split - first;
@@ -135,17 +134,19 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
   // predecessor 7B gate|up at 100 rows 46.8 -> 41.5 us, head of 32000 rows 61.3 -> 50.7, of 128256 rows 236 -> 204.
   const int rot = (int)((a.rounds > 1 ? 5u * blockIdx.x : blockIdx.x >> 3) % (unsigned)NB);
   const int so_begin = first * (BK * 2), so_end = so_begin + NB * (BK * 2);
-  const int so_start = so_begin + rot * (BK * 2);
-  int so = so_start;  // of the next slab to copy
+  int so = so_begin + rot * (BK * 2), left = NB;  // the next slab to copy; slabs to copy
+  const __amdgpu_buffer_rsrc_t nothing = make_rsrc(a.X, 0);
 #define SX_COPY(STG_)                                                                                            \
   {                                                                                                              \
+    const bool some = __builtin_amdgcn_readfirstlane(left) > 0;                                                  \
     _Pragma("unroll") for (int t = 0; t < CP; ++t) {                                                             \
       const lds_void_ptr to = (lds_void_ptr)(STG_ + min(wave + t * NW, COPIES) * 1024);                          \
-      if (kStream && t * NW >= RB * 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(res[t], to, 16, off[t], so, 0, kNt); \
-      else __builtin_amdgcn_raw_ptr_buffer_load_lds(res[t], to, 16, off[t], so, 0, 0);                           \
+      const __amdgpu_buffer_rsrc_t from = some ? res[t] : nothing;                                               \
+      if (kStream && t * NW >= RB * 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(from, to, 16, off[t], so, 0, kNt); \
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(from, to, 16, off[t], so, 0, 0);                             \
     }                                                                                                            \
-    const int next = so + BK * 2 == so_end ? so_begin : so + BK * 2;                                             \
-    so = next == so_start ? so : next;                                                                           \
+    so = so + BK * 2 == so_end ? so_begin : so + BK * 2;                                                         \
+    --left;                                                                                                      \
     asm volatile("" ::: "memory"); /* (the waits count copies, which must go out slab by slab) */                \
   }
 // this wave's copies but those of the N_ youngest slabs are in; then everybody's
@@ -181,9 +182,6 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
   SX_COPY(st1)
   if constexpr (S > 3) SX_COPY(st2)
   if constexpr (S > 4) SX_COPY(st3)
-  if constexpr (S > 5) SX_COPY(st4)
-  if constexpr (S > 6) SX_COPY(st5)
-  if constexpr (S > 7) SX_COPY(st6)
 #define SX_STEP(STG_, PREV_)             \
   {                                      \
     SX_WAIT(S - 2)                       \
@@ -193,10 +191,7 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
 #define SX_STEP0()                                   \
   if constexpr (S == 3) SX_STEP(st0, st2)            \
   if constexpr (S == 4) SX_STEP(st0, st3)            \
-  if constexpr (S == 5) SX_STEP(st0, st4)            \
-  if constexpr (S == 6) SX_STEP(st0, st5)            \
-  if constexpr (S == 7) SX_STEP(st0, st6)            \
-  if constexpr (S == 8) SX_STEP(st0, st7)
+  if constexpr (S == 5) SX_STEP(st0, st4)
   int s = 0;
   for (; s + S <= NB; s += S) {
     SX_STEP0()
@@ -204,9 +199,6 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
     SX_STEP(st2, st1)
     if constexpr (S > 3) SX_STEP(st3, st2)
     if constexpr (S > 4) SX_STEP(st4, st3)
-    if constexpr (S > 5) SX_STEP(st5, st4)
-    if constexpr (S > 6) SX_STEP(st6, st5)
-    if constexpr (S > 7) SX_STEP(st7, st6)
   }
   s = NB - s;  // slabs left, fewer than S
   if (s > 0) {
@@ -215,16 +207,7 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
       SX_STEP(st1, st0)
       if (S > 3 && s > 2) {
         SX_STEP(st2, st1)
-        if constexpr (S > 4) if (s > 3) {
-          SX_STEP(st3, st2)
-          if constexpr (S > 5) if (s > 4) {
-            SX_STEP(st4, st3)
-            if constexpr (S > 6) if (s > 5) {
-              SX_STEP(st5, st4)
-              if constexpr (S > 7) if (s > 6) SX_STEP(st6, st5)
-            }
-          }
-        }
+        if constexpr (S > 4) if (s > 3) SX_STEP(st3, st2)
       }
     }
   }
@@ -240,10 +223,10 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
   auto slot = [&](int b) -> unsigned char* {
     constexpr int PER_STAGE = kStage / 1024;
     const int stage = b / PER_STAGE;
-    return (stage == 0 ? st0 : stage == 1 ? st1 : stage == 2 ? st2 : stage == 3 ? st3 : stage == 4 ? st4 : st5) +
+    return (stage == 0 ? st0 : stage == 1 ? st1 : stage == 2 ? st2 : stage == 3 ? st3 : st4) +
            (b - stage * PER_STAGE) * 1024 + lane * 16;
   };
-  static_assert(BLOCKS <= (S < 6 ? S : 6) * (kStage / 1024), "a block lies in one stage");
+  static_assert(BLOCKS <= S * (kStage / 1024), "a block lies in one stage");
 #pragma unroll
   for (int i = 0; i < WB; ++i)
 #pragma unroll

@@ -64,8 +64,9 @@ struct W4RegArgs {
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00020000);
+// (bytes 0: reads nothing)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, int bytes = -1) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 // eight codes of one word -> eight bf16 in k order; sc = scale, nzs = -zero * scale (both exact in fp32, and so is
 // code * sc + nzs = sc * (code - zero): 8 significant bits times at most 4)
@@ -126,13 +127,13 @@ __global__ __launch_bounds__(128 * CG) void gemm_w4_regs_kernel(W4RegArgs a) {
   // 16 lanes at a time -- eight rows 0..3 and 12..15 of one chunk with rows 4..11 of the next lane quarter's, or the other
   // eight of each -- and with f those fall on 16 different groups of banks.
   auto swizzle = [](int r) { return (r & 15) ^ (((r >> 2) ^ (r >> 3)) & 1) << 2; };
-  const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.X);
+  const __amdgpu_buffer_rsrc_t xres = make_rsrc(a.X), nothing = make_rsrc(a.X, 0);
   __amdgpu_buffer_rsrc_t xr[4];
   int xoff[4];  // [CP] (of sizes that the template does not give the host pass drops the kernel)
 #pragma unroll
   for (int t = 0; t < CP; ++t) {
     const int id = wave + t * NW, r = 4 * id + (lane >> 4);
-    xr[t] = id < RB * 4 ? xres : __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned short*>(a.X), 0, 0, 0x00020000);
+    xr[t] = id < RB * 4 ? xres : nothing;
     xoff[t] = (int)(((unsigned)min(r, a.M - 1) * (unsigned)a.K + ((lane & 15) ^ swizzle(r)) * 8) * 2u);
   }
 
@@ -154,16 +155,17 @@ __global__ __launch_bounds__(128 * CG) void gemm_w4_regs_kernel(W4RegArgs a) {
   };
   WRegs w0, w1, w2, w3;
 
-  // Slabs [first_slab, first_slab + NB) of K.  Past the end the last slab is fetched again.
+  // Slabs [first_slab, first_slab + NB) of K.  Past the end the copies of X read nothing, the words are those of the last slab.
   const int nb_all = a.K / BK;
   const int first_slab = kpart * nb_all / a.split;
   const int NB = (kpart + 1) * nb_all / a.split - first_slab;
 #define SX_SLAB_AT(i) (first_slab + min((i), NB - 1))
-#define SX_COPY(STG_, SLAB_)                                                                                     \
+#define SX_COPY(STG_, T_)                                                                                        \
   {                                                                                                              \
-    const int so = (SLAB_) * (BK * 2);                                                                           \
+    const int so = (first_slab + (T_)) * (BK * 2);                                                               \
+    const bool some = __builtin_amdgcn_readfirstlane(T_) < NB;                                                   \
     _Pragma("unroll") for (int t = 0; t < CP; ++t) __builtin_amdgcn_raw_ptr_buffer_load_lds(                     \
-        xr[t], (lds_void_ptr)(STG_ + min(wave + t * NW, RB * 4) * 1024), 16, xoff[t], so, 0, 0);                 \
+        some ? xr[t] : nothing, (lds_void_ptr)(STG_ + min(wave + t * NW, RB * 4) * 1024), 16, xoff[t], so, 0, 0); \
     asm volatile("" ::: "memory"); /* (the waits count operations: in this order) */                             \
   }
   // the words of slabs A_ and B_, which share their 128-byte lines
@@ -241,13 +243,13 @@ __global__ __launch_bounds__(128 * CG) void gemm_w4_regs_kernel(W4RegArgs a) {
   constexpr int kFly = 2 * CP + 2 * WB;
 #define SX_STEP(XS_, W_, XN_, T_)          \
   SX_WAIT_BARRIER(wait_vm(kFly))           \
-  SX_COPY(XN_, SX_SLAB_AT((T_) + 3))       \
+  SX_COPY(XN_, (T_) + 3)                   \
   SX_SLAB(XS_, W_, T_)
   const int par_slabs = a.group_log2 > 6 ? kParGroups : kParGroups / 2;  // slabs whose groups fit s_par
-  SX_COPY(sx0, first_slab)
+  SX_COPY(sx0, 0)
   SX_PAIR(w0, w1, 0)
-  SX_COPY(sx1, SX_SLAB_AT(1))
-  SX_COPY(sx2, SX_SLAB_AT(2))
+  SX_COPY(sx1, 1)
+  SX_COPY(sx2, 2)
   SX_PAIR(w2, w3, 2)
   fill(first_slab, first_slab + min(NB, par_slabs));
   int t = 0, refill = par_slabs;
