@@ -6,9 +6,11 @@
 // head: 128/G consecutive nodes x the G query heads that share the KV head; a wave owns 32 rows.
 // Few query nodes (a draft model's batch: not a workgroup per compute unit): 64 rows, two waves share 32 of them and take
 // one half of every tile's keys each (KS = 2); and with memory for partial results the key tiles are shared out among
-// as many workgroups as fill the chip once.  Such a launch is bound by the K/V stream's latency and its own beginning
-// and end: 128 nodes, 32 heads, 2048 prefix keys: 19.7 + 5.3 us against 30.9 + 5.6 with 32-row workgroups, three of whose
-// waves had no rows, and 512 of them.
+// as many workgroups as fill the chip once; the last of a row's workgroups to arrive puts the shares together.  Such a launch
+// is bound by a tile's own chain (scores, maximum, exponentials, P V: 1.4 us with one wave to a SIMD) and its beginning and
+// end: 128 nodes, 32 heads, 2048 prefix keys and 640 earlier nodes 23.7 us; 20.0 + 5.4 with the shares put together by a launch
+// of its own.  (Three tiles ahead in four stages, the lists through LDS: 1.43 us a tile instead of 1.3; twice as many shares,
+// two workgroups to a compute unit: 27.9 us.)
 // Keys come in tiles of 64: first the dense prefix (no mask), then the tile's tree keys -- not all
 // T tree tokens, only the sorted union of the ancestors of the tile's nodes (a few dozen for
 // best-first trees), gathered by index, with a 64-bit per-node mask saying which of them are that
@@ -54,10 +56,11 @@ struct AttnArgs {
   const unsigned long long* rowmask;  // [T][W64]
   unsigned short* out;             // [T][Hq][128]
   int T, Tq, P, Hq, Hkv, G, npt, W64;  // T: nodes of the tree (klist stride); Tq: query nodes in q/out
-  // splits > 1: blockIdx.z takes a contiguous share of the key tiles and leaves, per query row, its
-  // unnormalised output, reference maximum and sum for attn_combine_kernel
+  // splits > 1: blockIdx.z takes a contiguous share of the key tiles and leaves, per query row, its unnormalised output,
+  // reference maximum and sum; the last of a row's workgroups to arrive puts them together
   int splits;
-  float *part_o, *part_m, *part_l;  // [splits][Tq * Hq][128], [splits][Tq * Hq] x 2
+  float *part_o, *part_m, *part_l;  // [splits][Tq * Hq][128] (rows of a workgroup interleaved), [splits][Tq * Hq] x 2
+  int* part_cnt;                    // per workgroup without the shares, zero before and after the launch
 };
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
@@ -321,7 +324,6 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
       s_l[wave & 1][lane] = l_run;
     }
     __syncthreads();
-    if (half == 1) return;
     const float m1 = s_m[wave & 1][lane], l1 = s_l[wave & 1][lane], mx = fmaxf(m_ref, m1);
     // a half without keys of the row has m = -inf and zeros
     const float w0 = m_ref == NEG_INF ? 0.f : __builtin_amdgcn_exp2f((m_ref - mx) * c2);
@@ -336,23 +338,91 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
 
   // ---- normalise and store -------------------------------------------------------------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  if (a.splits > 1) {
-    if (row_ok) {
-      const size_t qrow = (size_t)node * a.Hq + head, nrow = (size_t)a.Tq * a.Hq;
-      float* po = a.part_o + ((size_t)blockIdx.z * nrow + qrow) * DH;
+  if constexpr (KS == 2) {
+    if (a.splits > 1) {  // device-scope stores and loads; stores complete before the counter's device-scope atomic is issued
+      constexpr int kScopeDevice = 16;
+      __shared__ int s_last;
+      const int wg = blockIdx.x + gridDim.x * blockIdx.y;
+      const __amdgpu_buffer_rsrc_t ores = make_rsrc(a.part_o), mres = make_rsrc(a.part_m), lres = make_rsrc(a.part_l);
+      // the workgroup's nr rows of the share: quad i of row r's lane half lh at 16-byte word (i nr + r) 2 + lh
+      const int nr = min(a.npt, a.Tq - n0) * a.G, row = min(r, nr - 1), row0 = (kvh * a.Tq + n0) * a.G;
+      const unsigned nrow = (unsigned)a.Tq * a.Hq, ostep = nrow * (DH * 4u), mstep = nrow * 4u;
+      const unsigned o0 = (unsigned)row0 * (DH * 4u) + (unsigned)(row * 2 + lh) * 16u, oquad = (unsigned)nr * 32u;
+      const unsigned m0 = (unsigned)(row0 + row) * 4u;
+      if (half == 0 && row_ok) {
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+        for (int i = 0; i < 16; ++i) {
+          f32x4 w;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          f32x4 w = {oacc[db][4 * g + 0], oacc[db][4 * g + 1], oacc[db][4 * g + 2], oacc[db][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(po + 32 * db + 8 * g + 4 * lh) = w;
+          for (int e = 0; e < 4; ++e) w[e] = oacc[i >> 2][4 * (i & 3) + e];
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), ores, o0 + blockIdx.z * ostep + i * oquad, 0,
+                                                 kScopeDevice);
         }
-      if (lh == 0) {
-        a.part_m[(size_t)blockIdx.z * nrow + qrow] = m_ref;
-        a.part_l[(size_t)blockIdx.z * nrow + qrow] = l_tot;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_ref), mres, m0 + blockIdx.z * mstep, 0, kScopeDevice);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(l_tot), lres, m0 + blockIdx.z * mstep, 0, kScopeDevice);
       }
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(kWaitAll);
+      __syncthreads();
+      if (tid == 0) {
+        const int before = atomicAdd(a.part_cnt + wg, 1);
+        s_last = before == a.splits - 1;
+        if (s_last) a.part_cnt[wg] = 0;
+      }
+      __syncthreads();
+      if (!s_last) return;
+      // O = sum_z O_z 2^((m_z - M) c), l likewise, M = max_z m_z (m_z = -inf, l_z = 0 for a share without keys of the row).  Every
+      // wave takes half of the columns of its rows (the workgroup's own share too: the same bits), four shares in flight.
+      float mz[8], lz[8], M = NEG_INF;
+#pragma unroll
+      for (int z = 0; z < 8; ++z) {
+        const unsigned at = m0 + (unsigned)min(z, a.splits - 1) * mstep;
+        mz[z] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(mres, at, 0, kScopeDevice));
+        lz[z] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lres, at, 0, kScopeDevice));
+      }
+      f32x4 sum[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
+#pragma unroll
+      for (int z0 = 0; z0 < 8; z0 += 4) {
+        if (z0 < a.splits) {
+          f32x4 w[4][8];
+#pragma unroll
+          for (int z = 0; z < 4; ++z)
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+              w[z][i] = __builtin_bit_cast(
+                  f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                             ores, o0 + (unsigned)min(z0 + z, a.splits - 1) * ostep + (unsigned)(half * 8 + i) * oquad, 0,
+                             kScopeDevice));
+          if (z0 == 0) {
+#pragma unroll
+            for (int z = 0; z < 8; ++z) M = fmaxf(M, mz[z]);
+          }
+#pragma unroll
+          for (int z = 0; z < 4; ++z) {
+            const bool none = z0 + z >= a.splits || mz[z0 + z] == NEG_INF;
+            const float f = none ? 0.f : __builtin_amdgcn_exp2f((mz[z0 + z] - M) * c2);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum[i] = none ? sum[i] : sum[i] + w[z][i] * f;
+            den = none ? den : den + lz[z0 + z] * f;
+          }
+        }
+      }
+      if (!row_ok || !(den > 0.f)) return;
+      unsigned short* op = a.out + ((size_t)node * a.Hq + head) * DH;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int d = 32 * (2 * half + (i >> 2)) + 8 * (i & 3) + 4 * lh;
+        u32x2 w;
+        w[0] = cvt_pk_bf16(sum[i][0] / den, sum[i][1] / den);
+        w[1] = cvt_pk_bf16(sum[i][2] / den, sum[i][3] / den);
+        *reinterpret_cast<u32x2*>(op + d) = w;
+      }
+      return;
     }
-    return;
+    if (half == 1) return;
   }
   if (row_ok && l_tot > 0.f) {
     const float inv = 1.0f / l_tot;
@@ -370,40 +440,6 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
   }
 }
 
-// out[row][d] = sum_z O_z[row][d] 2^((m_z - M) c) / sum_z l_z 2^((m_z - M) c), M = max_z m_z: the softmax over all
-// keys put together from the shares of the key tiles (m_z = -inf, l_z = 0 for a share without keys of the row)
-// Half a wave takes a row, 16 bytes per lane, 8 rows to a workgroup (4096 rows in 4 shares: 5.3 us, of which an empty
-// launch is 4.6; 5.8 with a workgroup per row).
-constexpr int kCombineRows = 8;
-__global__ __launch_bounds__(32 * kCombineRows) void attn_combine_kernel(const float* __restrict__ part_o,
-                                                                         const float* __restrict__ part_m,
-                                                                         const float* __restrict__ part_l, int splits,
-                                                                         int nrow, unsigned short* __restrict__ out) {
-  const int row = blockIdx.x * kCombineRows + (threadIdx.x >> 5), d = 4 * (threadIdx.x & 31);
-  if (row >= nrow) return;
-  const float c2 = kLog2e * 0.08838834764831845f;
-  float M = -__builtin_huge_valf();
-  for (int z = 0; z < splits; ++z) M = fmaxf(M, part_m[(size_t)z * nrow + row]);
-  f32x4 num = {0.f, 0.f, 0.f, 0.f};
-  float den = 0.f;
-#pragma unroll 4
-  for (int z = 0; z < splits; ++z) {
-    const float m = part_m[(size_t)z * nrow + row];
-    const f32x4 o = *reinterpret_cast<const f32x4*>(part_o + ((size_t)z * nrow + row) * DH + d);
-    const float l = part_l[(size_t)z * nrow + row];
-    if (m == -__builtin_huge_valf()) continue;
-    const float wgt = __builtin_amdgcn_exp2f((m - M) * c2);
-    num += o * wgt;
-    den += l * wgt;
-  }
-  u32x2 w = {0u, 0u};
-  if (den > 0.f) {
-    w[0] = pack_bf16x2(num[0] / den, num[1] / den);
-    w[1] = pack_bf16x2(num[2] / den, num[3] / den);
-  }
-  *reinterpret_cast<u32x2*>(out + (size_t)row * DH + d) = w;
-}
-
 }  // namespace
 
 size_t sx_tree_attn_split_workspace(int Tq_max, int Hq) {
@@ -413,7 +449,7 @@ size_t sx_tree_attn_split_workspace(int Tq_max, int Hq) {
 int sx_launch_tree_attn_bf16(const void* q, const void* k_tree, const void* v_tree, const void* k_prefix,
                              const void* v_prefix, const int32_t* klist, const int32_t* kcnt,
                              const unsigned long long* rowmask, int T, int Tq, int P, int Hq, int Hkv, void* out,
-                             void* split_ws, size_t split_ws_bytes, hipStream_t st) {
+                             void* split_ws, size_t split_ws_bytes, int32_t* counters, hipStream_t st) {
   const int G = Hq / Hkv;
   if (Hq % Hkv != 0 || !(G == 1 || G == 2 || G == 4 || G == 8)) return SX_ERR_SHAPE;
   // the copies address rows with 32-bit byte offsets from the start of each K/V array
@@ -439,18 +475,19 @@ int sx_launch_tree_attn_bf16(const void* q, const void* k_tree, const void* v_tr
   dim3 grid((Tq + a.npt - 1) / a.npt, Hkv);
   // few query rows (a batch of the draft model): the grid leaves most of the chip idle while each workgroup
   // walks all key tiles one after the other; give shares of the key tiles to up to 8 workgroups instead.  One workgroup
-  // per compute unit: with two, each one's tiles halve but the partial results double (22.0 + 9.4 us for 19.7 + 5.3).  With
+  // per compute unit (see above).  With
   // more workgroups than half the compute units nothing is shared (80 / 10 heads, 128 nodes: 160 workgroups, 13.8, 23.7 and
   // 65.8 us at 300, 1024 and 4096 keys; 20.1, 43.6 and 143.9 with 32-row workgroups in up to three shares)
   a.splits = 1;
   a.part_o = a.part_m = a.part_l = nullptr;
+  a.part_cnt = counters;
   const int wgs = (int)(grid.x * grid.y), npre = (P + KTILE - 1) / KTILE, cus = sx_compute_units();
-  if (split_ws && wgs < cus && npre >= 4) {
+  if (split_ws && counters && wgs < cus && wgs <= 256 && npre >= 4) {
     int s = cus / wgs;
     if (s > 8) s = 8;
     if (s > npre / 2) s = npre / 2;
-    // putting the results together is a launch of its own, about six key tiles' time (0.9 us each): 128 nodes, 64 / 32 heads,
-    // 300 prefix keys in two shares 17.1 us, whole 14.7
+    // what a share costs besides its tiles: the partial results, the counter, and reading them back (3.7 us in four shares; when
+    // it was a launch, 128 nodes, 64 / 32 heads, 300 prefix keys in two shares took 17.1 us, whole 14.7)
     if (npre * (s - 1) < 6 * s) s = 1;
     const size_t nrow = (size_t)Tq * Hq;
     if (s > 1 && split_ws_bytes >= (size_t)s * nrow * (DH + 2) * sizeof(float)) {
@@ -464,10 +501,5 @@ int sx_launch_tree_attn_bf16(const void* q, const void* k_tree, const void* v_tr
   if (a.npt * G >= QROWS) tree_attn_bf16_kernel<1><<<grid, kThreads, 0, st>>>(a);
   else tree_attn_bf16_kernel<2><<<grid, kThreads, 0, st>>>(a);
   SX_LAUNCH_CHECK();
-  if (a.splits > 1) {
-    attn_combine_kernel<<<(Tq * Hq + kCombineRows - 1) / kCombineRows, 32 * kCombineRows, 0, st>>>(
-        a.part_o, a.part_m, a.part_l, a.splits, Tq * Hq, a.out);
-    SX_LAUNCH_CHECK();
-  }
   return SX_OK;
 }

@@ -309,7 +309,8 @@ int sx_verify_tree_range_impl(const sx_weights* w, const void* prefix_k, const v
       SX_TIMED(SX_K_ROPE, sx_launch_rope_split(L.qkv, rope_cs, n, Hq, Hkv, Dh, c.dtype, L.q, tk, tv, st));
     if (bf) {
       SX_TIMED(SX_K_ATTN, sx_launch_tree_attn_bf16(L.q, tkb, tvb, pk, pv, L.klist, L.kcnt, L.rowmask, T, n, P, Hq, Hkv,
-                                                   L.o, n <= 128 ? L.attn_split_ws : nullptr, L.attn_split_bytes, st));
+                                                   L.o, n <= 128 ? L.attn_split_ws : nullptr, L.attn_split_bytes,
+                                                   static_cast<int32_t*>(split_ws), st));
       if (q4) {
         const int one_d[1] = {d};
         const sx_w4_matrix gu[2] = {q4->w_gate, q4->w_up};
@@ -478,7 +479,7 @@ extern "C" int sx_tree_attention_bf16(const void* q, const void* k_tree, const v
     SX_TRY(sx_launch_qtile_prep(L.par_s, T, npt, 0, L.klist, L.kcnt, L.rowmask, st));
   }
   return sx_launch_tree_attn_bf16(q, k_tree, v_tree, k_prefix, v_prefix, L.klist, L.kcnt, L.rowmask, T, T, P, n_q_heads,
-                                  n_kv_heads, out, nullptr, 0, st);
+                                  n_kv_heads, out, nullptr, 0, nullptr, st);
 }
 
 // cos/sin table, then (256-byte aligned) the K-split counters and partial sums of the GEMM
