@@ -12,11 +12,13 @@
 // the A operand, X rows the B operand), so a lane ends up with 4 consecutive output columns of one
 // row: 16-byte stores.
 //
-// K is walked in slabs of 64 (two MFMA k-steps, 16 JB MFMAs per wave) held in LDS stages of 32 + 4 JB KB: two, or three
-// where those fit the 160 KB (JB = 4 and 5).  With two a copy has one slab's MFMAs to arrive, 0.6 us at 160 rows, and weights
-// from HBM take longer: a slab took 1.3 to 1.4 us whatever the height.  With three it has two slabs': 0.95 to 1.1 us (0.6
-// with the operands in L2).  70B gate|up at 300 rows 346 -> 274 us, O at 1000 rows 139 -> 112, 7B O at 300 rows 51 -> 36; 756
-// layer products of the 1B to 70B shapes and heads at 129 to 4096 rows take 0.87 of the time on average.
+// K is walked in slabs of 64 (two MFMA k-steps, 16 JB MFMAs per wave) held in LDS stages of 4 JB KB of X and 32 KB of W.
+// With two stages a copy has one slab's MFMAs to arrive, 0.6 us at 160 rows, and weights from HBM take longer: a slab took
+// 1.3 to 1.5 us whatever the height.  With three it has two slabs': 0.95 to 1.1 us (0.6 with the operands in L2).  Three of
+// both fit the 160 KB at JB = 4 and 5.  From JB = 6 on W has three and X two (160 KB to the byte at JB = 8): X is small
+// and comes from L2, it is the weights that are late.  As two stages of both, now three of W: a slab of 192 rows 1.40 -> 1.04 us, of 224 1.48 -> 1.16
+// and of 256 1.50 -> 1.30; 70B gate|up at 512 rows 417 -> 361 us, 7B gate|up at 396 rows 99 -> 74, 32000 columns, K = 4096,
+// at 337 rows 109 -> 84; 250 products of the 1B to 70B shapes at 129 to 2500 rows take 0.96 of the time on average.
 //
 // Global -> LDS without registers.  Operand slabs are copied by buffer loads that write LDS
 // directly (16 bytes per lane, a wave fills 1 KB of consecutive LDS per instruction), so the K loop
@@ -28,10 +30,10 @@
 // one whole 128-byte line.  That matters: the copy stream of this kernel alone (no math) runs at
 // 17 TB/s L2 -> LDS with whole-line requests and at 11.5 TB/s with half-line ones, which would make
 // the copies, not the MFMAs, the bound.  Whole lines are why a stage holds 64 K-elements.
-// Each stage is its own __shared__ array: the compiler tracks outstanding loads-to-LDS per array,
+// Each stage of each operand is its own __shared__ array: the compiler tracks outstanding loads-to-LDS per array,
 // so a fragment read of one stage does not wait for the copies in flight to the other.
 //
-// Schedule of a slab (stage S, other stage S'): phase 1 runs the MFMAs of k-step 0 and reads the
+// Schedule of a slab, with two stages (S, the other S'; with three a copy may take a slab longer): phase 1 runs the MFMAs of k-step 0 and reads the
 // fragments of k-step 1; then one barrier, before which every wave waits for its own copies of the
 // next slab (now S' is complete and S is read out); phase 2 runs the MFMAs of k-step 1, starts the
 // copies of the slab after next into S and reads the next slab's k-step 0 from S'.  One barrier
@@ -57,8 +59,10 @@ constexpr int kThreads = 256;
 constexpr int kWBytes = BN * BK * 2;                  // 32 KB: W's part of a slab
 constexpr int kPfDist = 3;                            // slabs between an L2 prefetch and the copy of the same lines
 
-// LDS stages of a tile of 32 jb rows: three where they fit the 160 KB
-constexpr int stages(int jb) { return 3 * (jb * 4096 + kWBytes) <= 160 * 1024 - 64 ? 3 : 2; }
+constexpr int kLds = 160 * 1024;
+// LDS stages of X's and of W's slabs of a tile of 32 jb rows: three where they fit the 160 KB (jb <= 5), W's alone up to 8
+constexpr int stages(int jb) { return 3 * (jb * 4096 + kWBytes) <= kLds - 2048 ? 3 : 2; }
+constexpr int w_stages(int jb, bool pf) { return stages(jb) == 3 || (!pf && 2 * jb * 4096 + 3 * kWBytes <= kLds) ? 3 : 2; }
 
 struct GemmArgs {
   const unsigned short* X;
@@ -109,10 +113,9 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   // chunk c of the row sits at position c ^ ((r >> 1) & 7).  The LDS serves 16 lanes x 16 bytes per
   // cycle (64 banks): 16 consecutive rows reading the same k chunk fall on 16 different bank groups.
   constexpr int BM = 32 * JB, kXBytes = BM * BK * 2;
-  __shared__ __attribute__((aligned(1024))) unsigned char stA[kXBytes + kWBytes];  // X slab, then W slab
-  __shared__ __attribute__((aligned(1024))) unsigned char stB[kXBytes + kWBytes];
-  constexpr int NS = stages(JB), kCopies = 8 + JB;  // copies of a slab per wave
-  __shared__ __attribute__((aligned(1024))) unsigned char stC[NS == 3 ? kXBytes + kWBytes : 16];
+  constexpr int NS = stages(JB), NW = w_stages(JB, PF), kCopies = 8 + JB;  // copies of a slab per wave
+  __shared__ __attribute__((aligned(1024))) unsigned char xA[kXBytes], xB[kXBytes], wA[kWBytes], wB[kWBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char xC[NS == 3 ? kXBytes : 16], wC[NW == 3 ? kWBytes : 16];
   constexpr int kAhead = 4;
   constexpr bool TOUCH = PF && NS == 3, SHARE = PF && NS == 2;
   __shared__ __attribute__((aligned(256))) unsigned char dump[TOUCH ? 1024 : 16];  // where touched lines end up
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
       woff[t] = (int)(((unsigned)(n - first) * (unsigned)a.K + cchunk * 8) * 2u);
     }
   }
-  const int xdst = wave * (JB * 1024), wdst = kXBytes + wave * 8192;  // this wave's share of X's and of W's slab
+  const int xdst = wave * (JB * 1024), wdst = wave * 8192;  // this wave's share of X's and of W's slab
 
   // ---- L2 prefetch (PF kernels: 8 row tiles, column tiles a multiple of 4) ---------------------------
   // The 32 workgroups that run side by side on an XCD are then 8 row tiles x 4 column tiles: an X tile
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   // fragment addresses: row (quadrant base + 16 i + l16), k chunk 4 ks + lq at position ^ ((row >> 1) & 7)
   const int fsw = (l16 >> 1) & 7;
   const int xrow = (wm * (16 * JB) + l16) * (BK * 2);
-  const int wrow = kXBytes + (wn * 128 + l16) * (BK * 2);
+  const int wrow = (wn * 128 + l16) * (BK * 2);
   const int kc0 = ((lq ^ fsw) << 4), kc1 = (((4 + lq) ^ fsw) << 4);
   bf16x8 fx0[JB], fw0[8], fx1[JB], fw1[8];   // k-step 0 and k-step 1 of a slab
 
@@ -271,10 +274,10 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(wres[t], (lds_void_ptr)(STG_ + wdst + (t) * 1024), 16, woff[t], SO_, 0, 0); \
   else if ((t) < JB)                                                                                           \
     __builtin_amdgcn_raw_ptr_buffer_load_lds(xres, (lds_void_ptr)(STG_ + xdst + (t) * 1024), 16, xoff[(t) % JB], SO_, 0, 0);
-#define SX_COPY(STG_, SO_)                                                                                     \
+#define SX_COPY(XSTG_, WSTG_, SO_)                                                                            \
   _Pragma("unroll") for (int t = 0; t < 8; ++t) {                                                             \
-    SX_COPY1(STG_, SO_, 0, t)                                                                                  \
-    SX_COPY1(STG_, SO_, 1, t)                                                                                  \
+    SX_COPY1(XSTG_, SO_, 0, t)                                                                                 \
+    SX_COPY1(WSTG_, SO_, 1, t)                                                                                 \
   }
 #define SX_READW(STG_, FW, i, KC) FW[i] = *reinterpret_cast<const bf16x8*>(STG_ + wrow + (i) * (16 * BK * 2) + KC);
 #define SX_READX(STG_, FX, i, KC) if ((i) < JB) FX[(i) % JB] = *reinterpret_cast<const bf16x8*>(STG_ + xrow + (i) * (16 * BK * 2) + KC);
@@ -285,59 +288,63 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 #define SX_MFMA(ACC, A, B) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(A), "v"(B));
 // byte offset along K of this workgroup's i-th slab (past the last one: the last one's)
 #define SX_OFFSET(i) ((first + min((i), NB - 1) + rot - (min((i), NB - 1) + rot < NB ? 0 : NB)) * (BK * 2))
-// The 16 fragment reads of a k-step, dealt over the 8 row blocks of the phase before it in the order
+// The 8 + JB fragment reads of a k-step, dealt over the 8 row blocks of the phase before it in the order
 // the next phase needs them: W block 0 and all X blocks first, then W blocks 1..7.
-#define SX_READS_A(STG_, FX, FW, KC, r)                                                                        \
-  if (r == 0) { SX_READW(STG_, FW, 0, KC) SX_READX(STG_, FX, 0, KC) }                                          \
-  if (r == 1) { SX_READX(STG_, FX, 2, KC) SX_READX(STG_, FX, 3, KC) }                                          \
-  if (r == 2) { SX_READX(STG_, FX, 5, KC) SX_READX(STG_, FX, 6, KC) }                                          \
-  if (r == 3) { SX_READW(STG_, FW, 1, KC) }                                                                    \
-  if (r == 4) { SX_READW(STG_, FW, 3, KC) }                                                                    \
-  if (r == 5) { SX_READW(STG_, FW, 5, KC) }                                                                    \
-  if (r == 6) { SX_READW(STG_, FW, 7, KC) }
-#define SX_READS_B(STG_, FX, FW, KC, r)                                                                        \
-  if (r == 0) { SX_READX(STG_, FX, 1, KC) }                                                                    \
-  if (r == 1) { SX_READX(STG_, FX, 4, KC) }                                                                    \
-  if (r == 2) { SX_READX(STG_, FX, 7, KC) }                                                                    \
-  if (r == 3) { SX_READW(STG_, FW, 2, KC) }                                                                    \
-  if (r == 4) { SX_READW(STG_, FW, 4, KC) }                                                                    \
-  if (r == 5) { SX_READW(STG_, FW, 6, KC) }
-// One slab from stage STG_ (its k-step 0 already in fx0/fw0):
+#define SX_READS_A(XSTG_, WSTG_, FX, FW, KC, r)                                                                \
+  if (r == 0) { SX_READW(WSTG_, FW, 0, KC) SX_READX(XSTG_, FX, 0, KC) }                                        \
+  if (r == 1) { SX_READX(XSTG_, FX, 2, KC) SX_READX(XSTG_, FX, 3, KC) }                                        \
+  if (r == 2) { SX_READX(XSTG_, FX, 5, KC) SX_READX(XSTG_, FX, 6, KC) }                                        \
+  if (r == 3) { SX_READW(WSTG_, FW, 1, KC) }                                                                   \
+  if (r == 4) { SX_READW(WSTG_, FW, 3, KC) }                                                                   \
+  if (r == 5) { SX_READW(WSTG_, FW, 5, KC) }                                                                   \
+  if (r == 6) { SX_READW(WSTG_, FW, 7, KC) }
+#define SX_READS_B(XSTG_, WSTG_, FX, FW, KC, r)                                                                \
+  if (r == 0) { SX_READX(XSTG_, FX, 1, KC) }                                                                   \
+  if (r == 1) { SX_READX(XSTG_, FX, 4, KC) }                                                                   \
+  if (r == 2) { SX_READX(XSTG_, FX, 7, KC) }                                                                   \
+  if (r == 3) { SX_READW(WSTG_, FW, 2, KC) }                                                                   \
+  if (r == 4) { SX_READW(WSTG_, FW, 4, KC) }                                                                   \
+  if (r == 5) { SX_READW(WSTG_, FW, 6, KC) }
+// The copies of a slab, dealt over the 16 half row blocks of a phase: X's before W's where W has a stage more, since then
+// the barrier waits for X's and leaves W's in flight; one of each in turn otherwise.
+#define SX_COPIES(XSTG_, WSTG_, XSO_, WSO_, h)                                                                 \
+  if (NW > NS) {                                                                                               \
+    if ((h) < JB) { SX_COPY1(XSTG_, XSO_, 0, h) }                                                              \
+    else if ((h) < JB + 8) { SX_COPY1(WSTG_, WSO_, 1, ((h) - JB) & 7) }                                        \
+  } else {                                                                                                     \
+    if ((h) & 1) { SX_COPY1(WSTG_, WSO_, 1, (h) / 2) } else { SX_COPY1(XSTG_, XSO_, 0, (h) / 2) }              \
+  }
+// One slab from stages XSTG_ and WSTG_ (its k-step 0 already in fx0/fw0):
 //   phase 1: the 8 JB MFMAs of k-step 0, with the fragment reads of k-step 1 between them;
-//   barrier: everybody has read all of STG_, and everybody's copies of the next slab (stage STG_N) are in (three stages:
-//   those of the slab after it may be in flight);
-//   phase 2: the 8 JB MFMAs of k-step 1, with the copies of the slab that takes this one's stage (NEXT_) into STG_
-//   and the reads of the next slab's k-step 0 between them.  The copies go out early in the phase
-//   (kCopyRows row blocks): they have until the next barrier, a slab's worth of MFMAs away.
-#define SX_SLAB(STG_, STG_N, NEXT_)                                                                                     \
-  const int so_next = SX_OFFSET(NEXT_);                                                                        \
+//   barrier: everybody has read all of both stages, and everybody's copies of the next slab (stages XSTG_N, WSTG_N) are in
+//   (three stages: those of the slab after it may be in flight, three of W alone: its W copies);
+//   phase 2: the 8 JB MFMAs of k-step 1, with the copies of the slabs that take these stages (XNEXT_, WNEXT_)
+//   and the reads of the next slab's k-step 0 between them.  The copies have until the next barrier, a slab's
+//   worth of MFMAs away, or until the one after it.
+#define SX_SLAB(XSTG_, XSTG_N, XNEXT_, WSTG_, WSTG_N, WNEXT_)                                                  \
+  const int xso = SX_OFFSET(XNEXT_), wso = SX_OFFSET(WNEXT_);                                                  \
   _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                                             \
-    _Pragma("unroll") for (int j = 0; j < JB / 2; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
-    SX_READS_A(STG_, fx1, fw1, kc1, r)                                                                         \
-    _Pragma("unroll") for (int j = JB / 2; j < JB; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                           \
-    SX_READS_B(STG_, fx1, fw1, kc1, r)                                                                         \
+    _Pragma("unroll") for (int j = 0; j < JB / 2; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                  \
+    SX_READS_A(XSTG_, WSTG_, fx1, fw1, kc1, r)                                                                 \
+    _Pragma("unroll") for (int j = JB / 2; j < JB; ++j) SX_MFMA(acc[r][j], fw0[r], fx0[j])                 \
+    SX_READS_B(XSTG_, WSTG_, fx1, fw1, kc1, r)                                                                 \
   }                                                                                                            \
-  SX_WAIT_BARRIER(NS == 3 ? wait_vm(kCopies + (TOUCH ? 1 : 0)) : SHARE ? kWaitVm2 : kWaitVm0)                                                                      \
+  SX_WAIT_BARRIER(NS == 3 ? wait_vm(kCopies + (TOUCH ? 1 : 0)) : NW == 3 ? wait_vm(8) : SHARE ? kWaitVm2 : kWaitVm0) \
   _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                                             \
-    _Pragma("unroll") for (int j = 0; j < JB / 2; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
-    if (r < kCopyRows) {                                                                                       \
-      _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, so_next, 0, r * (8 / kCopyRows) + c) \
-    }                                                                                                          \
-    SX_READS_A(STG_N, fx0, fw0, kc0, r)                                                                        \
-    _Pragma("unroll") for (int j = JB / 2; j < JB; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                           \
-    if (r < kCopyRows) {                                                                                       \
-      _Pragma("unroll") for (int c = 0; c < 8 / kCopyRows; ++c) SX_COPY1(STG_, so_next, 1, r * (8 / kCopyRows) + c) \
-    }                                                                                                          \
-    SX_READS_B(STG_N, fx0, fw0, kc0, r)                                                                        \
+    _Pragma("unroll") for (int j = 0; j < JB / 2; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                  \
+    SX_COPIES(XSTG_, WSTG_, xso, wso, 2 * r)                                                                   \
+    SX_READS_A(XSTG_N, WSTG_N, fx0, fw0, kc0, r)                                                               \
+    _Pragma("unroll") for (int j = JB / 2; j < JB; ++j) SX_MFMA(acc[r][j], fw1[r], fx1[j])                 \
+    SX_COPIES(XSTG_, WSTG_, xso, wso, 2 * r + 1)                                                               \
+    SX_READS_B(XSTG_N, WSTG_N, fx0, fw0, kc0, r)                                                               \
   }                                                                                                            \
-  if (TOUCH) { asm volatile("" ::: "memory"); SX_TOUCH((NEXT_) + kAhead) asm volatile("" ::: "memory"); } \
-  if (SHARE) { /* youngest in the queue: the barrier's wait lets these two loads stay in flight */                \
+  if (TOUCH) { asm volatile("" ::: "memory"); SX_TOUCH((WNEXT_) + kAhead) asm volatile("" ::: "memory"); }    \
+  if (SHARE) { /* youngest in the queue: the barrier's wait lets these two loads stay in flight */             \
     asm volatile("" ::"v"(pfx), "v"(pfw) : "memory"); /* and they stay behind the copies issued above */       \
-    const int pso = SX_OFFSET((NEXT_) + kPfDist);                                                              \
+    const int pso = SX_OFFSET((WNEXT_) + kPfDist);                                                             \
     pfx = __builtin_amdgcn_raw_buffer_load_b32(xres, pfxoff, pso, 0);                                          \
     pfw = __builtin_amdgcn_raw_buffer_load_b32(pfwres, pfwoff, pso, 0);                                        \
   }
-  constexpr int kCopyRows = 8;
 
   // The loop body is branch-free: past the end of K it copies the last slab again, into a stage nobody
   // reads any more, and reads fragments nobody uses.
@@ -351,9 +358,9 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   const int rot = SHARE || !a.rotate ? 0 : xcd * NB / 8;
   // (The waits count operations, so the slabs' copies have to go out in this order; they write arrays of their own, and
   // nothing else keeps the compiler from mixing them.)
-  SX_COPY(stA, SX_OFFSET(0))
+  SX_COPY(xA, wA, SX_OFFSET(0))
   asm volatile("" ::: "memory");
-  SX_COPY(stB, SX_OFFSET(1))
+  SX_COPY(xB, wB, SX_OFFSET(1))
   if (SHARE) {
     // The in-loop barriers let the two youngest operations stay in flight, taking them to be a slab's two
     // prefetch loads.  Before the first slab has issued any, the two youngest would be the last copies into the
@@ -364,30 +371,59 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     pfx = __builtin_amdgcn_raw_buffer_load_b32(xres, pfxoff, pso, 0);
     pfw = __builtin_amdgcn_raw_buffer_load_b32(pfwres, pfwoff, pso, 0);
   }
-  if (NS == 3) { asm volatile("" ::: "memory"); SX_COPY(stC, SX_OFFSET(2)) }
+  if constexpr (NS == 3) { asm volatile("" ::: "memory"); SX_COPY(xC, wC, SX_OFFSET(2)) }
+  else if constexpr (NW == 3) {
+    asm volatile("" ::: "memory");
+    _Pragma("unroll") for (int t = 0; t < 8; ++t) SX_COPY1(wC, SX_OFFSET(2), 1, t)
+  }
   if (TOUCH) { asm volatile("" ::: "memory"); SX_TOUCH(2 + kAhead) asm volatile("" ::: "memory"); }
-  SX_WAIT_BARRIER(wait_vm((NS - 1) * kCopies + (SHARE ? 2 : TOUCH ? 1 : 0)))
-  _Pragma("unroll") for (int i = 0; i < 8; ++i) { SX_READW(stA, fw0, i, kc0) SX_READX(stA, fx0, i, kc0) }
+  SX_WAIT_BARRIER(wait_vm((NS - 1) * JB + (NW - 1) * 8 + (SHARE ? 2 : TOUCH ? 1 : 0)))
+  _Pragma("unroll") for (int i = 0; i < 8; ++i) { SX_READW(wA, fw0, i, kc0) }
+  _Pragma("unroll") for (int i = 0; i < JB; ++i) { SX_READX(xA, fx0, i, kc0) }
   int s = 0;
   if constexpr (NS == 3) {
     for (; s + 3 <= NB; s += 3) {
-      { SX_SLAB(stA, stB, s + 3) }
-      { SX_SLAB(stB, stC, s + 4) }
-      { SX_SLAB(stC, stA, s + 5) }
+      { SX_SLAB(xA, xB, s + 3, wA, wB, s + 3) }
+      { SX_SLAB(xB, xC, s + 4, wB, wC, s + 4) }
+      { SX_SLAB(xC, xA, s + 5, wC, wA, s + 5) }
     }
     if (s < NB) {
-      SX_SLAB(stA, stB, NB)
+      SX_SLAB(xA, xB, NB, wA, wB, NB)
     }
     if (s + 1 < NB) {
-      SX_SLAB(stB, stC, NB)
+      SX_SLAB(xB, xC, NB, wB, wC, NB)
+    }
+  } else if constexpr (NW == 3) {
+    for (; s + 6 <= NB; s += 6) {
+      { SX_SLAB(xA, xB, s + 2, wA, wB, s + 3) }
+      { SX_SLAB(xB, xA, s + 3, wB, wC, s + 4) }
+      { SX_SLAB(xA, xB, s + 4, wC, wA, s + 5) }
+      { SX_SLAB(xB, xA, s + 5, wA, wB, s + 6) }
+      { SX_SLAB(xA, xB, s + 6, wB, wC, s + 7) }
+      { SX_SLAB(xB, xA, s + 7, wC, wA, s + 8) }
+    }
+    if (s < NB) {
+      SX_SLAB(xA, xB, s + 2, wA, wB, s + 3)
+    }
+    if (s + 1 < NB) {
+      SX_SLAB(xB, xA, s + 3, wB, wC, s + 4)
+    }
+    if (s + 2 < NB) {
+      SX_SLAB(xA, xB, s + 4, wC, wA, NB)
+    }
+    if (s + 3 < NB) {
+      SX_SLAB(xB, xA, NB, wA, wB, NB)
+    }
+    if (s + 4 < NB) {
+      SX_SLAB(xA, xB, NB, wB, wC, NB)
     }
   } else {
     for (; s + 2 <= NB; s += 2) {
-      { SX_SLAB(stA, stB, s + 2) }
-      { SX_SLAB(stB, stA, s + 3) }
+      { SX_SLAB(xA, xB, s + 2, wA, wB, s + 2) }
+      { SX_SLAB(xB, xA, s + 3, wB, wA, s + 3) }
     }
     if (s < NB) {  // one slab left, in stage A
-      SX_SLAB(stA, stB, NB)
+      SX_SLAB(xA, xB, NB, wA, wB, NB)
     }
   }
   // Copies past the end of K may still be in flight: they must land before this workgroup's LDS is released.
@@ -406,6 +442,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 #undef SX_SLAB
 #undef SX_READS_A
 #undef SX_READS_B
+#undef SX_COPIES
 
   // ---- K-split tail: the partial sums meet in memory, the last workgroup to arrive adds them up ---------
   // Every part writes its accumulators (register layout, 1 KB per wave and block: coalesced) and
@@ -418,7 +455,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   // invalidating the whole L2 under the feet of the workgroups still computing (measured: +40 us).
   if (ksplit > 1) {
     constexpr int kScopeDevice = 16;  // cache-policy bit sc1
-    __shared__ int s_last;
+    int& s_last = *reinterpret_cast<int*>(xA);  // the stages are read out, and may fill the LDS
     const int tail_tile = lin - a.full_tiles;
     const __amdgpu_buffer_rsrc_t pres = make_rsrc(a.part);
     const unsigned mine = (unsigned)(((tail_tile * ksplit + kpart) * 4 + wave) * (JB * 8 * 256) + lane * 4) * 4u;  // bytes
@@ -475,11 +512,12 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
     // register) are the pair the rotary embedding turns by the row's angle (Alg. 1: node at position
     // P + depth); the values are rounded to bf16 once, after the rotation.
     // The tile's rows of the cos/sin table (512 bytes each) are first copied into the LDS the K loop has
-    // left free -- the first half of them into the first stage's array, the rest into the second's -- and read from there:
+    // left free -- 64 to a slab's stage -- and read from there:
     // loaded from memory row block by row block, every load waited behind the stores of the block before (one
     // counter covers both on this chip), 32 memory round trips per tile.  16-byte chunk c of table row r sits at
     // chunk position (c & 16) | ((c ^ r) & 15) of its 512 bytes: the 16 rows a read instruction covers fall on 16
     // bank groups.
+    auto table = [&](int r64) -> unsigned char* { return r64 == 0 ? wA : r64 == 1 ? wB : NW == 3 ? (r64 == 2 ? wC : xA) : r64 == 2 ? xA : xB; };
     const int head = tile_n * 2 + wn;
     const bool is_v = head >= a.hq + a.hkv;
     unsigned short* dst = head < a.hq ? a.q : is_v ? a.v : a.k;
@@ -489,13 +527,12 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
       __syncthreads();  // every wave is past its last fragment reads of the stages
       const __amdgpu_buffer_rsrc_t cres = make_rsrc(a.cs);
 #pragma unroll
-      for (int t = 0; t < 4 * JB; ++t) {  // copy t of wave w: table rows 2 (2 JB w + t % 2 JB) and + 1 of half t / 2 JB
-        const int blk = 2 * JB * wave + t % (2 * JB), r = 2 * blk + (lane >> 5);
-        int m = tile_m * BM + t / (2 * JB) * (16 * JB) + r;
+      for (int t = 0; t < 4 * JB; ++t) {  // copy t of wave w: table rows 2 blk and 2 blk + 1
+        const int blk = 4 * t + wave, r = 2 * blk + (lane >> 5);
+        int m = tile_m * BM + r;
         m = m < a.M ? m : a.M - 1;
         const int pch = lane & 31, c = (pch & 16) | ((pch ^ r) & 15);
-        unsigned char* stg = t >= 2 * JB ? stB : stA;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(cres, (lds_void_ptr)(stg + blk * 1024), 16,
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(cres, (lds_void_ptr)(table(t / 8) + blk % 32 * 1024), 16,
                                                  (int)((unsigned)m * 512u + (unsigned)c * 16u), 0, 0, 0);
       }
       asm volatile("" ::: "memory");
@@ -504,7 +541,6 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
       asm volatile("" ::: "memory");
     }
     if (head < a.hq + 2 * a.hkv) {
-      const unsigned char* tb = wm ? stB : stA;
 #pragma unroll
       for (int j = 0; j < JB; ++j) {
         const int m = mbase + 16 * j + l16;
@@ -519,8 +555,8 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
             *reinterpret_cast<u32x2*>(y + 16 * i) = o;
           }
         } else {
-          const int r = 16 * j + l16;
-          const unsigned char* trow = tb + r * 512;
+          const int r = wm * (16 * JB) + 16 * j + l16;
+          const unsigned char* trow = table((wm * JB + j) / 4) + r % 64 * 512;
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             // (cos, sin) of pairs 16 i + 4 lq + 0..3: chunks 8 i + 2 lq and + 1 of the row
@@ -650,10 +686,10 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
 // mostly take the narrow-tile kernel instead: for them a partial tile outweighs the weights a part streams.)
 // The figures are fitted to 7100 launches: tiles of 128 to 256 rows, with and without the prefetch, uncut and cut in all
 // these ways, the layer shapes of widths 2048 to 8192 (1B to 70B) at 25 row counts from 129 to 3000, weights from memory.  A
-// slab's time is a stage's copies and MFMAs: at 128 and 160 rows three stages fit the LDS, at 224 and 256 two, where the time
-// of a memory access shows (with two stages a slab of 160 rows took 1.33).
+// slab's time is a stage's copies and MFMAs; those from 192 rows on are of 1120 launches with three stages of W (10 shapes, 16
+// row counts).  (256 rows are bound by power where they fill the chip for many rounds, 1.4 to 1.5; the choice does not change.)
 constexpr int kMaxRows = 256;
-constexpr float slab_us(int jb) { return jb == 4 ? 0.815f : jb == 5 ? 0.975f : jb == 6 ? 1.40f : jb == 7 ? 1.48f : 1.50f; }
+constexpr float slab_us(int jb) { return jb == 4 ? 0.815f : jb == 5 ? 0.975f : jb == 6 ? 1.04f : jb == 7 ? 1.16f : 1.30f; }
 constexpr float kRoundUs = 4.1f;   // a round's beginning and end: first copies, epilogue
 constexpr float kCutUs = 2.5f, kWayUs = 5.2f, kPartsUs = 16.f;  // 256-row tiles: a cut, per way, per chip full of parts
 constexpr int kCutMaxWays = 16, kTailMaxWays = 6;
@@ -695,16 +731,17 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
 
 // What a launch looks like: tile height 32 jb, the prefetching form or not, and a's split and rotation.
 //
-// The height: the one that plan_split's figures expect to be fastest.  Over the 400 products of the fit the choice among 256,
-// 224, 160 and 128 rows is within 0.8 % of the best launch on average, 12 % at worst.  192 rows, two stages, were the best of
-// three of the 400, by 3 % at most, but are where the others come out uneven: 12288 columns, K = 4096 at 850 rows 90 us, 256
-// rows 96 and 224 rows 97; 32000 columns at 330 rows 104, 224 rows 103, 160 rows 122.
-// Two things the figures do not know speak for 256 rows:
-//   the prefetching form (8 row tiles, whole groups of 4 column tiles), unless every tile is cut, streams the weights better
-//   than they say: a tenth;
-//   224 rows in as many row tiles as of 256 only drop padding, which costs little once the chip is full: repeated
-//   rows draw little power, and power is what bounds it then (224 rows for 256 at 1100 rows, 7B QKV 105.3 against 101.5 us,
-//   gate|up 194 against 186): not from five row tiles on.
+// The height: the one that plan_split's figures expect to be fastest.  Over the 160 products of the second fit the choice is
+// within 0.3 % of the best launch on average, 6 % at worst.
+// Three things the figures do not know:
+//   the prefetching form of 256 rows (8 row tiles, whole groups of 4 column tiles), unless every tile is cut, streams the
+//   weights better than they say: a tenth;
+//   so does that of 128 and 160 rows over several rounds, none of them cut (8192 x 8192 at 2500 rows, two rounds of 160 rows
+//   278 us, 256 rows with 64 tiles cut 309): a twentieth;
+//   short parts of K gain less from W's third stage: two stages of X and all tiles cut, 6 % (7B down at 670 rows, 64 tiles
+//   of 192 rows in four parts 81 us, 80 of 160 rows in three 76).
+// (224 rows in as many row tiles as of 256 only drop padding, and are still faster: 7B QKV at 1100 rows 84 us for 93, gate|up 153
+// for 169, 32000 columns, K = 4096, at 1300 rows 260 for 295.)
 //
 // The prefetch at 128 and 160 rows: from three row tiles on, where they share the touched lines, and only where they are all
 // but full: 4 % on average, up to 18 (70B down, 640 rows in five tiles, 397 -> 336 us).  A row tile that is mostly padding
@@ -726,19 +763,24 @@ struct Plan {
 Plan pick_plan(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
   Plan p = {8, false};
   const float tall = plan_split(a, 8, split_ws, split_ws_bytes);
-  const int rows8 = a.tilesM;
+  const int cus = sx_compute_units();
   const bool can_prefetch = a.tilesM == 8 && a.tilesN % 4 == 0;
-  float best = (can_prefetch && !(a.split > 1 && a.full_tiles == 0) ? 0.9f : 1.f) * tall;
+  auto touch = [&](int jb) {  // the prefetching form of three stages, for the plan that a holds
+    const int tiles = a.tilesM * a.tilesN;
+    const bool nearly_whole = a.split == 1 && tiles > cus && tiles % cus * 10 >= 9 * cus;
+    return stages(jb) == 3 && a.tilesM >= 3 && a.M * 25ll >= 23ll * 32 * jb * a.tilesM && !nearly_whole;
+  };
+  const bool all_cut8 = a.split > 1 && a.full_tiles == 0;
+  float best = (all_cut8 ? 1.06f : can_prefetch ? 0.9f : 1.f) * tall;
   for (int t = 7; t >= 4; --t) {
-    const float cost = plan_split(a, t, split_ws, split_ws_bytes);
-    if (stages(t) == 2 && a.tilesM == rows8 && rows8 > 4) continue;
-    if (cost * (stages(t) == 2 ? 1.f : 1.03f) < best) best = cost, p.jb = t;
+    float cost = plan_split(a, t, split_ws, split_ws_bytes);
+    if (a.split == 1 && a.tilesM * a.tilesN > cus && touch(t)) cost *= 0.95f;
+    if (a.split > 1 && a.full_tiles == 0 && stages(t) == 2) cost *= 1.06f;
+    if (cost < best) best = cost, p.jb = t;
   }
   plan_split(a, p.jb, split_ws, split_ws_bytes);
   if (stages(p.jb) == 3) {
-    const int cus = sx_compute_units(), tiles = a.tilesM * a.tilesN;
-    const bool nearly_whole = a.split == 1 && tiles > cus && tiles % cus * 10 >= 9 * cus;
-    p.prefetch = a.tilesM >= 3 && a.M * 25ll >= 23ll * 32 * p.jb * a.tilesM && !nearly_whole;
+    p.prefetch = touch(p.jb);
     a.rotate = 1;
   } else {
     p.prefetch = p.jb == 8 && can_prefetch;
