@@ -10,7 +10,8 @@
 // (value descending, index ascending).  Rows where the bound is useless (massive ties) fall back
 // to an exact bitwise threshold search over the same registers.
 //
-// Vocabularies above 32768 do not fit the registers of such a workgroup; row_topk_stream_kernel
+// Vocabularies above 32768 do not fit the registers of such a workgroup: several share the row and
+// merge_shares_kernel puts their lists together, or, for few rows and for large k, row_topk_stream_kernel
 // streams the row instead (running maximum and rescaled sum per lane) and takes the candidates
 // from a second sweep that L2 serves.
 //
@@ -63,14 +64,22 @@ __device__ __noinline__ int exact_topk_from_memory(const float* __restrict__ x, 
   return C;
 }
 
+// Long rows shared out among several workgroups: each takes `len` entries of a row (a multiple of four) and leaves its k
+// best as sort keys, in order, and its maximum and sum of exponentials; merge_shares_kernel puts a row's shares together.
+struct RowShares {
+  int parts, len;
+  unsigned long long* keys;  // [N][parts][k]: (~order key of the value) << 32 | index in the row, ascending
+  float2* ms;                // [N][parts]
+};
+
 // THREADS lanes, each holding IPT4 float4 of the row.  Element (j, c) of a lane is index
-// (j*THREADS + tid)*4 + c.
-template <int THREADS, int IPT4, bool VEC>
+// (j*THREADS + tid)*4 + c.  SHARE: of this workgroup's share of the row.
+template <int THREADS, int IPT4, bool VEC, bool SHARE>
 __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restrict__ logits,
-                                                           const float* __restrict__ cum_logp, int V, int k,
+                                                           const float* __restrict__ cum_logp, int V_row, int k,
                                                            float* __restrict__ topk_logp,
                                                            int* __restrict__ topk_idx,
-                                                           float* __restrict__ score) {
+                                                           float* __restrict__ score, RowShares sh) {
   constexpr int NW = THREADS / 64;
   __shared__ float smax[THREADS];
   __shared__ float redf[32];
@@ -82,8 +91,10 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
   __shared__ unsigned long long cand[kCandCap];
 
   const int tid = threadIdx.x;
-  const size_t row = blockIdx.x;
-  const float* x = logits + row * (size_t)V;
+  const size_t row = SHARE ? blockIdx.x / sh.parts : blockIdx.x;
+  const int first = SHARE ? (int)(blockIdx.x % sh.parts) * sh.len : 0;
+  const int V = SHARE ? min(sh.len, V_row - first) : V_row;
+  const float* x = logits + row * (size_t)V_row + first;
   const float NEG_INF = -__builtin_huge_valf();
 
   float v[IPT4 * 4];
@@ -160,6 +171,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
 #pragma unroll
   for (int w = 0; w < NW; ++w) S += redf[NW + w];
   const float lse = M + logf(S);
+  if (SHARE && tid == 0) sh.ms[blockIdx.x] = make_float2(M, S);
   float t0;
   if (small_k) {  // exactly one group has rank k - 1 (ranks are a permutation of 0..63)
     int rank = 0;
@@ -213,7 +225,10 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
     int place = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) place += s_part[w][lane];
-    if (tid < C && place < k) {
+    if (SHARE) {
+      if (tid < C ? place < k : tid < k)  // (fewer than k candidates: a share of NaNs)
+        sh.keys[blockIdx.x * (size_t)k + (tid < C ? place : tid)] = tid < C ? x64 + (unsigned)first : ~0ull;
+    } else if (tid < C && place < k) {
       const float val = f32_from_order_key(~xhi);
       const float lp = val - lse;
       const size_t o = row * (size_t)k + place;
@@ -234,6 +249,10 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
   block_bitonic_sort_u64<THREADS>(cand, n);
   for (int c = tid; c < k; c += THREADS) {
     const unsigned long long e = cand[c];
+    if (SHARE) {
+      sh.keys[blockIdx.x * (size_t)k + c] = e == ~0ull ? e : e + (unsigned)first;
+      continue;
+    }
     const float val = f32_from_order_key(~(unsigned)(e >> 32));
     const float lp = val - lse;
     const size_t o = row * (size_t)k + c;
@@ -246,7 +265,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
 // Lane `tid` owns the float4 slots tid, tid + THREADS, ... of the row (element index 4 * slot + c).
 // Pass 1 streams the row from HBM four slots at a time, keeping only a running maximum and a sum of
 // exponentials relative to it; pass 2 streams it again, now from L2, and keeps the few entries >= t0.
-// Few registers whatever V is: used for vocabularies too large for the register-resident kernel above.
+// Few registers whatever V is: used for vocabularies too large for the register-resident kernel above and not shared out.
 template <int THREADS, bool VEC>
 __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* __restrict__ logits,
                                                            const float* __restrict__ cum_logp, int V, int k,
@@ -420,6 +439,48 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
     topk_idx[o] = (int)(unsigned)(e & 0xFFFFFFFFull);
     topk_logp[o] = lp;
     if (score) score[o] = cl + lp;
+  }
+}
+
+// A row's shares put together: a key's place is its place in its own list and the number of smaller keys in the others, by
+// binary search.  Dynamic LDS: the parts * k keys.
+constexpr int kMergeThreads = 256, kMaxShares = 8;
+__global__ __launch_bounds__(kMergeThreads) void merge_shares_kernel(RowShares sh, const float* __restrict__ cum_logp, int k,
+                                                                     float* __restrict__ topk_logp, int* __restrict__ topk_idx,
+                                                                     float* __restrict__ score) {
+  extern __shared__ unsigned long long lists[];
+  const size_t row = blockIdx.x;
+  const int n = sh.parts * k;
+  for (int i = threadIdx.x; i < n; i += kMergeThreads) lists[i] = sh.keys[row * n + i];
+  float M = -__builtin_huge_valf(), S = 0.f;
+  for (int p = 0; p < sh.parts; ++p) M = fmaxf(M, sh.ms[row * sh.parts + p].x);
+  for (int p = 0; p < sh.parts; ++p) {  // a share of -inf alone adds nothing
+    const float2 t = sh.ms[row * sh.parts + p];
+    if (t.x != -__builtin_huge_valf()) S += t.y * (t.x == M ? 1.f : __builtin_amdgcn_exp2f((t.x - M) * kLog2e));
+  }
+  const float lse = M + logf(S), cl = cum_logp ? cum_logp[row] : 0.f;
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += kMergeThreads) {
+    const unsigned long long e = lists[i];
+    const int p = i / k;
+    int place = i - p * k;
+    for (int q = 0; q < sh.parts; ++q) {
+      if (q == p) continue;
+      int lo = 0, hi = k;  // smaller keys of list q
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (lists[q * k + mid] < e) lo = mid + 1;
+        else hi = mid;
+      }
+      place += lo;
+    }
+    if (place < k && e != ~0ull) {
+      const float lp = f32_from_order_key(~(unsigned)(e >> 32)) - lse;
+      const size_t o = row * (size_t)k + place;
+      topk_idx[o] = (int)(unsigned)e;
+      topk_logp[o] = lp;
+      if (score) score[o] = cl + lp;
+    }
   }
 }
 
@@ -1068,13 +1129,42 @@ void launch_row(const float* logits, const float* cum, int N, int V, int k, floa
                 hipStream_t st) {
   const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
   if (vec)
-    row_topk_kernel<THREADS, IPT4, true><<<N, THREADS, 0, st>>>(logits, cum, V, k, lp, idx, score);
+    row_topk_kernel<THREADS, IPT4, true, false><<<N, THREADS, 0, st>>>(logits, cum, V, k, lp, idx, score, RowShares{});
   else
-    row_topk_kernel<THREADS, IPT4, false><<<N, THREADS, 0, st>>>(logits, cum, V, k, lp, idx, score);
+    row_topk_kernel<THREADS, IPT4, false, false><<<N, THREADS, 0, st>>>(logits, cum, V, k, lp, idx, score, RowShares{});
+}
+
+// Workgroups that share a row too long for the registers of one; 1: none.  A row streamed by one workgroup is read twice: with
+// the selection, k = 32, 2048 rows of 128256 357 -> 194 us (5.4 TB/s), of 50000 140 -> 100, 256 rows of 128256 51 -> 42.  Not
+// for at most 128 rows: alone 100 of 128256 gain too (30.2 -> 25.8), but right after the head that made them the two
+// together took 235.9 us for 226.8, the head being slower by more than that.  Shares find k from 33 on too often by
+// sorting: their 64 group maxima bound it loosely (600 rows of 80000, k = 56, 88 -> 108 us).
+// Rows whose entries are loaded one by one (V not a multiple of 4) gain from lanes instead, up to 128 rows and k = 56 (16 rows of
+// 100003, k = 32, 56 -> 22 us), and lose beyond: 2048 rows of 40001 167 -> 179.
+constexpr int kShareMaxK = 56;
+int row_parts(int N, int V, int k, bool vec) {
+  if (V <= 32768 || (vec ? N <= 128 || k > 32 : N > 128 || k > kShareMaxK)) return 1;
+  return V <= 65536 ? (N <= 8 ? 4 : 2) : (N <= 16 ? 8 : 4);
+}
+size_t shares_bytes(int N, int V, int k) {
+  const int parts = row_parts(N, V, k, V % 4 == 0);
+  return parts == 1 ? 0 : sx_align_up((size_t)N * parts * 8, 256) + sx_align_up((size_t)N * parts * k * 8, 256);
+}
+template <bool VEC>
+void launch_shares(const float* logits, const float* cum, int N, int V, int k, float* lp, int* idx, float* score, void* scratch,
+                   hipStream_t st) {
+  RowShares sh;
+  sh.parts = row_parts(N, V, k, V % 4 == 0);
+  sh.len = ((V + sh.parts - 1) / sh.parts + 3) & ~3;
+  sh.ms = static_cast<float2*>(scratch);
+  sh.keys = reinterpret_cast<unsigned long long*>(static_cast<char*>(scratch) + sx_align_up((size_t)N * sh.parts * 8, 256));
+  if (sh.len <= 16384) row_topk_kernel<256, 16, VEC, true><<<N * sh.parts, 256, 0, st>>>(logits, cum, V, k, lp, idx, score, sh);
+  else row_topk_kernel<512, 16, VEC, true><<<N * sh.parts, 512, 0, st>>>(logits, cum, V, k, lp, idx, score, sh);
+  merge_shares_kernel<<<N, kMergeThreads, (size_t)sh.parts * k * 8, st>>>(sh, cum, k, lp, idx, score);
 }
 
 int row_topk_dispatch(const float* logits, const float* cum, int N, int V, int k, float* lp, int* idx, float* score,
-                      hipStream_t st) {
+                      void* scratch, hipStream_t st) {
   // lanes x float4-per-lane sized so that a row fits in registers with >= 2 workgroups per CU
   if (V <= 1024) launch_row<256, 1>(logits, cum, N, V, k, lp, idx, score, st);
   else if (V <= 4096) launch_row<256, 4>(logits, cum, N, V, k, lp, idx, score, st);
@@ -1082,6 +1172,12 @@ int row_topk_dispatch(const float* logits, const float* cum, int N, int V, int k
   else if (V <= 32768) launch_row<512, 16>(logits, cum, N, V, k, lp, idx, score, st);
   else {  // the row no longer fits the registers of a workgroup that leaves room for a second one
     const bool vec = (V % 4 == 0) && ((reinterpret_cast<uintptr_t>(logits) & 15) == 0);
+    if (scratch && (vec || V % 4 != 0) && row_parts(N, V, k, vec) > 1) {
+      if (vec) launch_shares<true>(logits, cum, N, V, k, lp, idx, score, scratch, st);
+      else launch_shares<false>(logits, cum, N, V, k, lp, idx, score, scratch, st);
+      SX_LAUNCH_CHECK();
+      return SX_OK;
+    }
     // No more rows than compute units: a row has one to itself, and what it can keep in flight is the bound (64 bytes per
     // lane), so twice the lanes: 100 rows of 128256 36 -> 28.7 us.  Not for k > 64, where every lane ranks its maximum
     // among those of all lanes, which then takes longer than the row (k = 200: 57.7 us with 512 lanes, 68 with 1024).
@@ -1105,7 +1201,7 @@ int sx_launch_row_scores(const float* logits, const float* cum_logp, int N, int 
                          hipStream_t st) {
   if (!row_shape_ok(N, V, k)) return SX_ERR_SHAPE;
   sx_prof_begin(SX_K_ROW_TOPK, st);
-  const int rc = row_topk_dispatch(logits, cum_logp, N, V, k, lp, idx, score, st);
+  const int rc = row_topk_dispatch(logits, cum_logp, N, V, k, lp, idx, score, nullptr, st);
   sx_prof_end(st);
   return rc;
 }
@@ -1114,16 +1210,15 @@ extern "C" int sx_row_logsoftmax_topk(const float* logits, int32_t N, int32_t V,
                                       int32_t* topk_idx, void* stream) {
   if (!logits || !topk_logp || !topk_idx) return SX_ERR_NULL;
   if (!row_shape_ok(N, V, k)) return SX_ERR_SHAPE;
-  return row_topk_dispatch(logits, nullptr, N, V, k, topk_logp, topk_idx, nullptr, (hipStream_t)stream);
+  return row_topk_dispatch(logits, nullptr, N, V, k, topk_logp, topk_idx, nullptr, nullptr, (hipStream_t)stream);
 }
 
-// workspace: header | score f32[N*k] | topk_logp f32[N*k] | topk_idx i32[N*k]
+// workspace: header | score f32[N*k] | topk_logp f32[N*k] | topk_idx i32[N*k] | shares of long rows (used if there)
+static size_t expand_min_workspace(int32_t N, int32_t k) { return SX_WS_HEADER + 3 * sx_align_up((size_t)N * (size_t)k * 4, 256); }
 extern "C" size_t sx_expand_topk_workspace(int32_t N, int32_t V, int32_t k, int32_t B) {
-  (void)V;
   (void)B;
   if (N < 1 || k < 1) return 0;
-  const size_t nk = sx_align_up((size_t)N * (size_t)k * 4, 256);
-  return SX_WS_HEADER + 3 * nk;
+  return expand_min_workspace(N, k) + shares_bytes(N, V, k);
 }
 
 namespace {
@@ -1155,11 +1250,11 @@ int select_blocks(int n, int Bsel) {
 }
 
 int expand_topk_run(const float* logits, const float* cum_logp, int N, int V, int k, int B, int* out_row,
-                    int* out_token, float* out_cum_logp, int* n_out, float* score, float* lp, int* idx,
+                    int* out_token, float* out_cum_logp, int* n_out, float* score, float* lp, int* idx, void* scratch,
                     hipStream_t st) {
   SX_TRY(configure_select_once());
   sx_prof_begin(SX_K_ROW_TOPK, st);
-  const int rc = row_topk_dispatch(logits, cum_logp, N, V, k, lp, idx, score, st);
+  const int rc = row_topk_dispatch(logits, cum_logp, N, V, k, lp, idx, score, scratch, st);
   sx_prof_end(st);
   if (rc != SX_OK) return rc;
   const int n = N * k;
@@ -1185,13 +1280,15 @@ extern "C" int sx_expand_topk(const float* logits, const float* cum_logp, int32_
   if (!logits || !cum_logp || !out_row || !out_token || !out_cum_logp || !n_out) return SX_ERR_NULL;
   if (!row_shape_ok(N, V, k) || B < 1 || B > 8192) return SX_ERR_SHAPE;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) ||
-      workspace_bytes < sx_expand_topk_workspace(N, V, k, B))
+      workspace_bytes < expand_min_workspace(N, k))
     return SX_ERR_WORKSPACE;
+  const bool shares = workspace_bytes >= sx_expand_topk_workspace(N, V, k, B);
   const size_t nk = sx_align_up((size_t)N * (size_t)k * 4, 256);
   char* ws = static_cast<char*>(workspace);
   return expand_topk_run(logits, cum_logp, N, V, k, B, out_row, out_token, out_cum_logp, n_out,
                          reinterpret_cast<float*>(ws + SX_WS_HEADER), reinterpret_cast<float*>(ws + SX_WS_HEADER + nk),
-                         reinterpret_cast<int*>(ws + SX_WS_HEADER + 2 * nk), (hipStream_t)stream);
+                         reinterpret_cast<int*>(ws + SX_WS_HEADER + 2 * nk), shares ? ws + SX_WS_HEADER + 3 * nk : nullptr,
+                         (hipStream_t)stream);
 }
 
 // ---- the same step for callers that cannot allocate ----------------------------------------------------
@@ -1223,5 +1320,5 @@ extern "C" int sx_expand_topk_static(const float* logits, const float* cum_logp,
   const size_t nk = (size_t)kStaticMaxCand * 4;
   return expand_topk_run(logits, cum_logp, N, V, k, B, out_row, out_token, out_cum_logp, n_out,
                          reinterpret_cast<float*>(base), reinterpret_cast<float*>(base + nk),
-                         reinterpret_cast<int*>(base + 2 * nk), (hipStream_t)stream);
+                         reinterpret_cast<int*>(base + 2 * nk), nullptr, (hipStream_t)stream);
 }

@@ -319,3 +319,40 @@ def test_ties_at_the_threshold_fill_the_picks_in_index_order(sx, n, B, kind):
     assert got == B and not tok.any()
     np.testing.assert_array_equal(row, want)
     np.testing.assert_array_equal(score, flat[want])
+
+
+@pytest.mark.parametrize("N,V,k", [(3, 32769, 1), (129, 32772, 32), (9, 40001, 56), (17, 65537, 32), (129, 65540, 4),
+                                   (130, 131072, 32), (16, 100003, 32), (3, 131069, 33)])
+def test_long_rows_shared_among_workgroups(sx, N, V, k):
+    """Rows of more than 32768 entries, put together from their shares (2, 4 and 8 of them, V a multiple of 4 and not), have the
+    tokens of the oracle in its order: equal entries across all shares, shares of -inf alone, the best at the edges of shares.
+    A workspace without room for the shares takes the streaming kernel, with the same tokens."""
+    rng = np.random.default_rng(V)
+    logits = (rng.standard_normal((N, V)) * 3).astype(np.float32)
+    logits[0] = 1.25
+    logits[1] = -np.inf
+    logits[1, [7, V // 2, V - 1]] = [0.5, 2.0, 0.5]
+    for parts in (2, 4, 8):
+        edge = ((V + parts - 1) // parts + 3) & ~3
+        logits[2, [edge - 1, edge]] = 15.0 + 1.0 / parts
+    # rows far enough apart that the selection of all candidates leaves each row's in their order
+    spacing = 64.0
+    cum = (-spacing * np.arange(N)).astype(np.float32)
+    ref_idx = oracle.row_topk(logits, k)
+    ref_lp = np.take_along_axis(oracle.log_softmax(logits), ref_idx, -1)
+    shares = sx.lib.sx_expand_topk_workspace(N, V, k, N * k)
+    least = 256 + 3 * ((N * k * 4 + 255) // 256 * 256)
+    assert shares > least
+    for nbytes in (shares, least):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev())
+        r, t, s, n, _ = sx.expand_topk(to_dev(logits), to_dev(cum), k, N * k, workspace=ws)
+        r, t, s = r.cpu().numpy(), t.cpu().numpy(), s.cpu().numpy().astype(np.float64)
+        assert int(n.item()) == N * k
+        for i in range(N):
+            at = r == i
+            np.testing.assert_array_equal(t[at], ref_idx[i], err_msg=f"row {i}")
+            got, want = s[at], ref_lp[i] + cum[i]
+            fin = np.isfinite(want)
+            assert np.array_equal(np.isneginf(got), ~fin)
+            # the sum of score and log-probability rounds once at the size of the row's offset
+            assert np.abs(got[fin] - want[fin]).max() <= LOGP_TOL + spacing * (N + 1) * 2.0 ** -24
