@@ -371,7 +371,8 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
       }
       __syncthreads();
       if (!s_last) return;
-      // O = sum_z O_z 2^((m_z - M) c), l likewise, M = max_z m_z (m_z = -inf, l_z = 0 for a share without keys of the row).  Every
+      // O = sum_z O_z 2^((m_z - M) c), l likewise, M = max_z m_z (m_z = -inf, l_z = 0 for a share without keys of the row; l_z = NaN
+      // where all of its scores are NaN, which m_z does not show).  Every
       // wave takes half of the columns of its rows (the workgroup's own share too: the same bits), four shares in flight.
       float mz[8], lz[8], M = NEG_INF;
 #pragma unroll
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
           }
 #pragma unroll
           for (int z = 0; z < 4; ++z) {
-            const bool none = z0 + z >= a.splits || mz[z0 + z] == NEG_INF;
+            const bool none = z0 + z >= a.splits || (mz[z0 + z] == NEG_INF && lz[z0 + z] == 0.f);
             const float f = none ? 0.f : __builtin_amdgcn_exp2f((mz[z0 + z] - M) * c2);
 #pragma unroll
             for (int i = 0; i < 8; ++i) sum[i] = none ? sum[i] : sum[i] + w[z][i] * f;
@@ -410,7 +411,8 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
           }
         }
       }
-      if (!row_ok || !(den > 0.f)) return;
+      if (!row_ok) return;
+      den = den == 0.f ? 1.f : den;
       unsigned short* op = a.out + ((size_t)node * a.Hq + head) * DH;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -424,8 +426,9 @@ __global__ __launch_bounds__(kThreads, 2) void tree_attn_bf16_kernel(AttnArgs a)
     }
     if (half == 1) return;
   }
-  if (row_ok && l_tot > 0.f) {
-    const float inv = 1.0f / l_tot;
+  // every row of the launch is stored: zeros where no score is above -inf, NaN where one is NaN or +inf
+  if (row_ok) {
+    const float inv = 1.0f / (l_tot == 0.f ? 1.f : l_tot);
     unsigned short* op = a.out + ((size_t)node * a.Hq + head) * DH;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
