@@ -24,6 +24,9 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kCandCap = 1024;  // LDS slots for row candidates before the exact fallback is taken
 
+// An entry's place among the others of its row: NaN behind every number (a comparison with the bound passes it by as well).
+__device__ __forceinline__ unsigned row_order_key(float x) { return x == x ? f32_order_key(x) : 0u; }
+
 // Exact selection for rows the cheap bound cannot handle.  Bitwise search for the k-th largest
 // order key, then for the index below which ties are taken, each probe being one pass over the
 // row (served by L2: the row was just read).  Leaves exactly k entries in cand[], returns k.
@@ -36,23 +39,23 @@ __device__ __noinline__ int exact_topk_from_memory(const float* __restrict__ x, 
   for (int bit = 31; bit >= 0; --bit) {
     const unsigned trial = K | (1u << bit);
     int c = 0;
-    for (int i = tid; i < V; i += THREADS) c += (f32_order_key(x[i]) >= trial) ? 1 : 0;
+    for (int i = tid; i < V; i += THREADS) c += (row_order_key(x[i]) >= trial) ? 1 : 0;
     if (block_sum_i<NW>(c, redi) >= k) K = trial;
   }
   int cg = 0;
-  for (int i = tid; i < V; i += THREADS) cg += (f32_order_key(x[i]) > K) ? 1 : 0;
+  for (int i = tid; i < V; i += THREADS) cg += (row_order_key(x[i]) > K) ? 1 : 0;
   const int need = k - block_sum_i<NW>(cg, redi);  // ties to take, >= 1
   unsigned Y = 0;                                 // largest Y with #(tie, idx < Y) <= need
   for (int bit = 17; bit >= 0; --bit) {
     const unsigned trial = Y | (1u << bit);
     int c = 0;
-    for (int i = tid; i < V && (unsigned)i < trial; i += THREADS) c += (f32_order_key(x[i]) == K) ? 1 : 0;
+    for (int i = tid; i < V && (unsigned)i < trial; i += THREADS) c += (row_order_key(x[i]) == K) ? 1 : 0;
     if (block_sum_i<NW>(c, redi) <= need) Y = trial;
   }
   if (tid == 0) *s_cnt = 0;
   __syncthreads();
   for (int i = tid; i < V; i += THREADS) {
-    const unsigned key = f32_order_key(x[i]);
+    const unsigned key = row_order_key(x[i]);
     if (key > K || (key == K && (unsigned)i < Y)) {
       const int pos = atomicAdd(s_cnt, 1);
       if (pos < kCandCap) cand[pos] = ((unsigned long long)(~key) << 32) | (unsigned)i;
@@ -153,7 +156,8 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
     s_part[wave][lane] = prank;
   }
   float se = 0.f;
-  const float mshift = -M * kLog2e;
+  // (a share without a number above -inf: its sum is 0, and NaN where it holds one, which its maximum does not show)
+  const float mshift = SHARE && M == NEG_INF ? 0.f : -M * kLog2e;
 #pragma unroll
   for (int e = 0; e < IPT4 * 4; ++e) se += __builtin_amdgcn_exp2f(fmaf(v[e], kLog2e, mshift));
   se = wave_sum(se);
@@ -204,6 +208,8 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
   __syncthreads();  // (3)
   int C = s_cnt;
   const float cl = cum_logp ? cum_logp[row] : 0.f;
+  // the bound was useless (massive ties), or the row has fewer than k numbers: exact search, re-reading the row from L2
+  if (C > kCandCap || C < k) C = exact_topk_from_memory<THREADS>(x, V, k, redi, &s_cnt, cand);
 
   if (small_k && C <= 64) {
     // ---- the usual case: a few dozen candidates, ordered in registers ------------------------------------
@@ -226,8 +232,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
 #pragma unroll
     for (int w = 0; w < NW; ++w) place += s_part[w][lane];
     if (SHARE) {
-      if (tid < C ? place < k : tid < k)  // (fewer than k candidates: a share of NaNs)
-        sh.keys[blockIdx.x * (size_t)k + (tid < C ? place : tid)] = tid < C ? x64 + (unsigned)first : ~0ull;
+      if (tid < C && place < k) sh.keys[blockIdx.x * (size_t)k + place] = x64 + (unsigned)first;
     } else if (tid < C && place < k) {
       const float val = f32_from_order_key(~xhi);
       const float lp = val - lse;
@@ -239,9 +244,6 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
     return;
   }
   __syncthreads();
-  if (C > kCandCap) {  // the bound was useless (massive ties): exact search, re-reading the row from L2
-    C = exact_topk_from_memory<THREADS>(x, V, k, redi, &s_cnt, cand);
-  }
 
   // ---- general case: order the candidates in LDS and emit the first k --------------------------------
   const int n = next_pow2(C < 2 ? 2 : C);
@@ -250,7 +252,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
   for (int c = tid; c < k; c += THREADS) {
     const unsigned long long e = cand[c];
     if (SHARE) {
-      sh.keys[blockIdx.x * (size_t)k + c] = e == ~0ull ? e : e + (unsigned)first;
+      sh.keys[blockIdx.x * (size_t)k + c] = e + (unsigned)first;
       continue;
     }
     const float val = f32_from_order_key(~(unsigned)(e >> 32));
@@ -319,10 +321,9 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
       se *= __builtin_amdgcn_exp2f((tm - cm) * kLog2e);
       tm = cm;
     }
-    if (tm > NEG_INF) {
+    const float ref = tm > NEG_INF ? tm : 0.f;  // nothing above -inf yet: adds 0, or NaN
 #pragma unroll
-      for (int e = 0; e < U * 4; ++e) se += __builtin_amdgcn_exp2f((c[e] - tm) * kLog2e);
-    }
+    for (int e = 0; e < U * 4; ++e) se += __builtin_amdgcn_exp2f((c[e] - ref) * kLog2e);
   }
 
   // ---- maxima: per group of GS lanes (64 groups), per wave ---------------------------------------------
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
   // t0 = k-th largest of a set of group maxima (rank by value, then group id) is a lower bound of
   // the k-th largest entry.  k <= 64: 64 groups ranked by one wave with lane broadcasts (hardly
   // looser than per-lane maxima and far cheaper); else every lane is a group.
-  se = tm > NEG_INF ? se * __builtin_amdgcn_exp2f((tm - M) * kLog2e) : 0.f;
+  se = tm > NEG_INF ? se * __builtin_amdgcn_exp2f((tm - M) * kLog2e) : se;
   se = wave_sum(se);
   if ((tid & 63) == 0) redf[NW + (tid >> 6)] = se;
   if (small_k) {
@@ -398,6 +399,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
   __syncthreads();  // (3)
   int C = s_cnt;
   const float cl = cum_logp ? cum_logp[row] : 0.f;
+  if (C > kCandCap || C < k) C = exact_topk_from_memory<THREADS>(x, V, k, redi, &s_cnt, cand);  // as above
 
   if (small_k && C <= 64) {
     // ---- the usual case: a few dozen candidates, placed by one wave in registers --------------------
@@ -423,9 +425,6 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
     return;
   }
   __syncthreads();
-  if (C > kCandCap) {  // the bound was useless (massive ties): exact search, re-reading the row from L2
-    C = exact_topk_from_memory<THREADS>(x, V, k, redi, &s_cnt, cand);
-  }
 
   // ---- general case: order the candidates in LDS and emit the first k --------------------------------
   const int n = next_pow2(C < 2 ? 2 : C);
@@ -454,9 +453,9 @@ __global__ __launch_bounds__(kMergeThreads) void merge_shares_kernel(RowShares s
   for (int i = threadIdx.x; i < n; i += kMergeThreads) lists[i] = sh.keys[row * n + i];
   float M = -__builtin_huge_valf(), S = 0.f;
   for (int p = 0; p < sh.parts; ++p) M = fmaxf(M, sh.ms[row * sh.parts + p].x);
-  for (int p = 0; p < sh.parts; ++p) {  // a share of -inf alone adds nothing
+  for (int p = 0; p < sh.parts; ++p) {  // (a share of -inf alone adds 0, one with a NaN makes the row's sum NaN)
     const float2 t = sh.ms[row * sh.parts + p];
-    if (t.x != -__builtin_huge_valf()) S += t.y * (t.x == M ? 1.f : __builtin_amdgcn_exp2f((t.x - M) * kLog2e));
+    S += t.y * (t.x == M ? 1.f : __builtin_amdgcn_exp2f((t.x - M) * kLog2e));
   }
   const float lse = M + logf(S), cl = cum_logp ? cum_logp[row] : 0.f;
   __syncthreads();
@@ -474,7 +473,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_shares_kernel(RowShares s
       }
       place += lo;
     }
-    if (place < k && e != ~0ull) {
+    if (place < k) {
       const float lp = f32_from_order_key(~(unsigned)(e >> 32)) - lse;
       const size_t o = row * (size_t)k + place;
       topk_idx[o] = (int)(unsigned)e;

@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import workloads as wl
 from helpers import dev, to_dev, weights_to
 
@@ -73,3 +74,54 @@ def test_forward_of_a_small_batch_over_a_key_of_nan(sx, P):
             got, _ = sx.verify_tree(mw, bad, pv, to_dev(tok), to_dev(par), workspace=ws)
             assert sx.check_status(ws) == 0
             assert bool(torch.isnan(got).all()), (layer, fill)
+
+
+def _rows_with_nan(N, V, k):
+    rng = np.random.default_rng(V + k)
+    x = (rng.standard_normal((N, V)) * 3).astype(np.float32)
+    x[0, V // 3] = np.nan
+    x[1, :V // 8] = np.nan                       # a share of NaN alone
+    x[2] = -np.inf
+    x[2, 5], x[2, [0, V // 2, V - 1]] = np.nan, [1.0, 2.0, 1.0]
+    x[3] = np.nan
+    x[4] = np.nan
+    x[4, [3, V - 2]] = [-1.0, 4.0]               # fewer numbers than picks
+    x[5] = -np.inf
+    x[5, V // 2:V // 2 + k - 1] = 1.5            # no NaN: the other picks are -inf
+    x[6] = -np.inf
+    x[6, V - 1] = np.nan
+    x[7, V - V // 8:] = -np.inf
+    x[7, V - 1] = np.nan                         # a NaN in a share of -inf
+    nan = np.isnan(x).any(1)
+    with np.errstate(invalid="ignore"):
+        lp = np.take_along_axis(oracle.log_softmax(np.where(nan[:, None], 0, x)), oracle.row_topk(x, k), -1)
+    lp[nan] = np.nan
+    return x, oracle.row_topk(x, k), lp
+
+
+@pytest.mark.parametrize("V,k", [(500, 7), (4096, 100), (9000, 64), (32768, 32), (40001, 8), (65540, 70), (131072, 200)])
+def test_row_topk_of_rows_with_nan(sx, V, k):
+    """NaN comes behind every number, by index, and the log-probabilities of a row that holds one are NaN: the register and the
+    streaming kernel, small and large k.  Every place is written."""
+    x, idx, lp = _rows_with_nan(9, V, k)
+    got_lp = torch.full((9, k), 7.0, device=dev())
+    got_idx = torch.full((9, k), -7, dtype=torch.int32, device=dev())
+    sx.row_logsoftmax_topk(to_dev(x), k, topk_logp=got_lp, topk_idx=got_idx)
+    np.testing.assert_array_equal(got_idx.cpu().numpy(), idx)
+    np.testing.assert_allclose(got_lp.cpu().numpy(), lp, rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("N,V,k", [(17, 65537, 32), (9, 40001, 56), (129, 65540, 8), (130, 131072, 32)])
+def test_expansion_of_long_rows_with_nan(sx, N, V, k):
+    """The same for rows shared among workgroups, and with a workspace that has no room for the shares."""
+    x, idx, lp = _rows_with_nan(N, V, k)
+    cum = np.zeros(N, np.float32)
+    for nbytes in (sx.lib.sx_expand_topk_workspace(N, V, k, N * k), 256 + 3 * ((N * k * 4 + 255) // 256 * 256)):
+        ws = torch.full((nbytes,), 0x3C, dtype=torch.uint8, device=dev())
+        r, t, s, n, _ = sx.expand_topk(to_dev(x), to_dev(cum), k, N * k, workspace=ws)
+        r, t, s = r.cpu().numpy(), t.cpu().numpy(), s.cpu().numpy()
+        assert int(n.item()) == N * k
+        for i in range(N):
+            at = np.argsort(t[r == i])  # (rows with equal scores meet in the selection; a row's own order is tested above)
+            np.testing.assert_array_equal(t[r == i][at], np.sort(idx[i]), err_msg=f"row {i}")
+            np.testing.assert_allclose(s[r == i][at], lp[i][np.argsort(idx[i])], rtol=0, atol=1e-4, err_msg=f"row {i}")
