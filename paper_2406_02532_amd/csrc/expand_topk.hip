@@ -27,14 +27,64 @@ constexpr int kCandCap = 1024;  // LDS slots for row candidates before the exact
 // An entry's place among the others of its row: NaN behind every number (a comparison with the bound passes it by as well).
 __device__ __forceinline__ unsigned row_order_key(float x) { return x == x ? f32_order_key(x) : 0u; }
 
-// Exact selection for rows the cheap bound cannot handle.  Bitwise search for the k-th largest
-// order key, then for the index below which ties are taken, each probe being one pass over the
-// row (served by L2: the row was just read).  Leaves exactly k entries in cand[], returns k.
+// The first entries equal to t0, in the order of their indices, behind the C entries in cand[] until there are k (fewer if the
+// row has no more).  The row comes from L2, from its beginning on: where this is needed ties are the many.
 template <int THREADS>
-__device__ __noinline__ int exact_topk_from_memory(const float* __restrict__ x, int V, int k, int* redi, int* s_cnt,
+__device__ __noinline__ int append_ties(const float* __restrict__ x, int V, int k, float t0, int C, int* redi,
+                                        unsigned long long* cand) {
+  constexpr int NW = THREADS / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int i0 = 0; i0 < V && C < k; i0 += THREADS) {
+    const int i = i0 + tid;
+    const bool tie = i < V && x[i] == t0;
+    const unsigned long long b = __builtin_amdgcn_ballot_w64(tie);
+    if (lane == 0) redi[wave] = __builtin_popcountll(b);
+    __syncthreads();
+    int pos = C + __builtin_popcountll(b & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      if (w < wave) pos += redi[w];
+      C += redi[w];
+    }
+    if (tie && pos < k) cand[pos] = ((unsigned long long)(~f32_order_key(t0)) << 32) | (unsigned)i;
+    __syncthreads();
+    C = min(C, k);
+  }
+  return C;
+}
+
+// Exact selection for rows the cheap bound t0 (at most the k-th largest entry) cannot handle, from L2: the row was just read.
+// Mostly the entries equal to t0 are the many (a masked row, or a masked share of one: -inf or one low value almost
+// everywhere): one sweep takes those above it, and if there are fewer than k the first equal ones follow.  Otherwise bitwise search for the k-th largest order key, then for the index below which
+// ties are taken, each probe being one pass over the row.  (By the search alone 128 rows of 128256 with all but 300 entries
+// masked took 2177 us, now 66.)  Returns the number of entries left in cand[], at least k.
+template <int THREADS>
+__device__ __noinline__ int exact_topk_from_memory(const float* __restrict__ x, int V, int k, float t0, int* redi, int* s_cnt,
                                                    unsigned long long* cand) {
   constexpr int NW = THREADS / 64;
   const int tid = threadIdx.x;
+  __syncthreads();  // (everybody has read the count that led here)
+  if (tid == 0) *s_cnt = 0;
+  __syncthreads();
+  constexpr int U = 8;  // loads in flight per lane
+  for (int i0 = 0; i0 < V; i0 += U * THREADS) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = i0 + u * THREADS + tid < V ? x[i0 + u * THREADS + tid] : t0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (v[u] > t0) {
+        const int pos = atomicAdd(s_cnt, 1);
+        if (pos < kCandCap)
+          cand[pos] = ((unsigned long long)(~f32_order_key(v[u])) << 32) | (unsigned)(i0 + u * THREADS + tid);
+      }
+  }
+  __syncthreads();
+  int C = *s_cnt;
+  if (C <= kCandCap) {
+    C = append_ties<THREADS>(x, V, k, t0, C, redi, cand);
+    if (C >= k) return C;
+  }
   unsigned K = 0;
   for (int bit = 31; bit >= 0; --bit) {
     const unsigned trial = K | (1u << bit);
@@ -62,7 +112,7 @@ __device__ __noinline__ int exact_topk_from_memory(const float* __restrict__ x, 
     }
   }
   __syncthreads();
-  const int C = min(*s_cnt, kCandCap);
+  C = min(*s_cnt, kCandCap);
   __syncthreads();
   return C;
 }
@@ -186,6 +236,11 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
   } else {
     t0 = s_t0;
   }
+  // A share may lie in the masked part of its row while others do not: with many groups at the bound only what is above it is
+  // gathered, and ties follow below.  (600 rows of 128256, k = 32, a third masked: 3680 us with the bitwise search, 141 with the
+  // sweep from memory, 76 so and without a mask.)
+  const bool above = SHARE && __builtin_popcountll(__builtin_amdgcn_ballot_w64(gmine == t0)) > 16;
+  const float bound = above ? f32_from_order_key(f32_order_key(t0) + 1u) : t0;  // (above +inf: NaN, which nothing reaches)
 
   // ---- gather candidates >= t0 ---------------------------------------------------------------
   // Hits are rare (a few dozen per row): the four values of a register quad are looked at only where the
@@ -193,11 +248,11 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
 #pragma unroll
   for (int j = 0; j < IPT4; ++j) {
     const float m4 = fmaxf(fmaxf(v[4 * j + 0], v[4 * j + 1]), fmaxf(v[4 * j + 2], v[4 * j + 3]));
-    if (__builtin_amdgcn_ballot_w64(m4 >= t0) != 0ull) {
+    if (__builtin_amdgcn_ballot_w64(m4 >= bound) != 0ull) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int idx = (j * THREADS + tid) * 4 + c;
-        if (v[4 * j + c] >= t0 && idx < V) {
+        if (v[4 * j + c] >= bound && idx < V) {
           const int pos = atomicAdd(&s_cnt, 1);
           if (pos < kCandCap)
             cand[pos] = ((unsigned long long)(~f32_order_key(v[4 * j + c])) << 32) | (unsigned)idx;
@@ -208,8 +263,9 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
   __syncthreads();  // (3)
   int C = s_cnt;
   const float cl = cum_logp ? cum_logp[row] : 0.f;
+  if (SHARE && above && C < k) C = append_ties<THREADS>(x, V, k, t0, C, redi, cand);
   // the bound was useless (massive ties), or the row has fewer than k numbers: exact search, re-reading the row from L2
-  if (C > kCandCap || C < k) C = exact_topk_from_memory<THREADS>(x, V, k, redi, &s_cnt, cand);
+  if (C > kCandCap || C < k) C = exact_topk_from_memory<THREADS>(x, V, k, t0, redi, &s_cnt, cand);
 
   if (small_k && C <= 64) {
     // ---- the usual case: a few dozen candidates, ordered in registers ------------------------------------
@@ -321,9 +377,13 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
       se *= __builtin_amdgcn_exp2f((tm - cm) * kLog2e);
       tm = cm;
     }
-    const float ref = tm > NEG_INF ? tm : 0.f;  // nothing above -inf yet: adds 0, or NaN
+    if (tm > NEG_INF) {
 #pragma unroll
-    for (int e = 0; e < U * 4; ++e) se += __builtin_amdgcn_exp2f((c[e] - ref) * kLog2e);
+      for (int e = 0; e < U * 4; ++e) se += __builtin_amdgcn_exp2f((c[e] - tm) * kLog2e);
+    } else {  // nothing above -inf yet: adds 0, or NaN
+#pragma unroll
+      for (int e = 0; e < U * 4; e += 2) se = __builtin_isunordered(c[e], c[e + 1]) ? __builtin_nanf("") : se;
+    }
   }
 
   // ---- maxima: per group of GS lanes (64 groups), per wave ---------------------------------------------
@@ -399,7 +459,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
   __syncthreads();  // (3)
   int C = s_cnt;
   const float cl = cum_logp ? cum_logp[row] : 0.f;
-  if (C > kCandCap || C < k) C = exact_topk_from_memory<THREADS>(x, V, k, redi, &s_cnt, cand);  // as above
+  if (C > kCandCap || C < k) C = exact_topk_from_memory<THREADS>(x, V, k, t0, redi, &s_cnt, cand);  // as above
 
   if (small_k && C <= 64) {
     // ---- the usual case: a few dozen candidates, placed by one wave in registers --------------------

@@ -356,3 +356,59 @@ def test_long_rows_shared_among_workgroups(sx, N, V, k):
             assert np.array_equal(np.isneginf(got), ~fin)
             # the sum of score and log-probability rounds once at the size of the row's offset
             assert np.abs(got[fin] - want[fin]).max() <= LOGP_TOL + spacing * (N + 1) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,V,k", [(130, 131072, 32), (9, 40001, 56), (129, 32772, 1), (5, 100000, 100), (6, 32000, 32)])
+def test_masked_rows(sx, N, V, k):
+    """Rows of one low value (-inf, -1e9) but for a range of tokens: fewer than k, k, a few hundred, more than
+    the candidates' slots, at the beginning, in the middle and at the end; shared among workgroups, streamed, and in registers."""
+    rng = np.random.default_rng(V + k)
+    logits = (rng.standard_normal((N, V)) * 3).astype(np.float32)
+    lows = (-np.inf, -1e9)
+    for i, count in enumerate((1, k, 300, 1500, 2 * V // 3)):
+        first = (0, V // 2, V - count, V // 4 - count // 2, 0)[i]
+        kept = logits[i, first:first + count].copy()
+        logits[i] = lows[i % 2]
+        logits[i, first:first + count] = kept
+    idx = oracle.row_topk(logits, k)
+    lp = np.take_along_axis(oracle.log_softmax(logits), idx, -1)
+    got_lp, got_idx = sx.row_logsoftmax_topk(to_dev(logits), k)
+    np.testing.assert_array_equal(got_idx.cpu().numpy(), idx)
+    rows = np.arange(N, dtype=np.float32)
+    for nbytes in (sx.lib.sx_expand_topk_workspace(N, V, k, N * k), 256 + 3 * ((N * k * 4 + 255) // 256 * 256)):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev())
+        r, t, s, n, _ = sx.expand_topk(to_dev(logits), to_dev(-64.0 * rows), k, N * k, workspace=ws)
+        r, t, s = r.cpu().numpy(), t.cpu().numpy(), s.cpu().numpy().astype(np.float64)
+        assert int(n.item()) == N * k
+        for i in range(N):
+            np.testing.assert_array_equal(t[r == i], idx[i], err_msg=f"row {i}")
+            want = lp[i] - 64.0 * i
+            fin = np.isfinite(want)
+            assert np.array_equal(np.isneginf(s[r == i]), ~fin)
+            # the sum of score and log-probability rounds once, at its own size
+            assert (np.abs(s[r == i][fin] - want[fin]) <= LOGP_TOL + np.abs(want[fin]) * 2.0 ** -22).all()
+
+
+def test_masked_rows_take_no_longer(sx):
+    """A third of every row masked, so that a whole share of it is: no more than three times the time of rows without a mask
+    (fifty times, when such a share was searched bit by bit)."""
+    N, V, k, B = 600, 128256, 32, 2048
+    x = wl.hash_normal(5, (N, V), std=3.0, device=dev())
+    masked = x.clone()
+    masked[:, 2 * V // 3:] = -float("inf")
+    cum = torch.zeros(N, device=dev())
+    ws = torch.empty(sx.lib.sx_expand_topk_workspace(N, V, k, B), dtype=torch.uint8, device=dev())
+
+    def us(t):
+        best = 1e9
+        for _ in range(5):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            sx.expand_topk(t, cum, k, B, workspace=ws)
+            e[1].record()
+            e[1].synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        return best
+
+    plain, with_mask = us(x), us(masked)
+    assert with_mask <= 3 * plain, (plain, with_mask)
