@@ -206,10 +206,15 @@ __global__ __launch_bounds__(THREADS) void row_topk_kernel(const float* __restri
     s_part[wave][lane] = prank;
   }
   float se = 0.f;
-  // (a share without a number above -inf: its sum is 0, and NaN where it holds one, which its maximum does not show)
-  const float mshift = SHARE && M == NEG_INF ? 0.f : -M * kLog2e;
+  if (fabsf(M) < 1e37f) {
+    const float mshift = -M * kLog2e;
 #pragma unroll
-  for (int e = 0; e < IPT4 * 4; ++e) se += __builtin_amdgcn_exp2f(fmaf(v[e], kLog2e, mshift));
+    for (int e = 0; e < IPT4 * 4; ++e) se += __builtin_amdgcn_exp2f(fmaf(v[e], kLog2e, mshift));
+  } else {  // the shift would overflow (a row, or a share of one, masked with the lowest number); -inf alone: 0, or NaN with a NaN
+    const float ref = M == NEG_INF ? 0.f : M;
+#pragma unroll
+    for (int e = 0; e < IPT4 * 4; ++e) se += __builtin_amdgcn_exp2f((v[e] - ref) * kLog2e);
+  }
   se = wave_sum(se);
   if ((tid & 63) == 0) redf[NW + (tid >> 6)] = se;
   if (!small_k) {

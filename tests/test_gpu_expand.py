@@ -360,15 +360,15 @@ def test_long_rows_shared_among_workgroups(sx, N, V, k):
 
 @pytest.mark.parametrize("N,V,k", [(130, 131072, 32), (9, 40001, 56), (129, 32772, 1), (5, 100000, 100), (6, 32000, 32)])
 def test_masked_rows(sx, N, V, k):
-    """Rows of one low value (-inf, -1e9) but for a range of tokens: fewer than k, k, a few hundred, more than
+    """Rows of one low value (-inf, the lowest number, -1e9) but for a range of tokens: fewer than k, k, a few hundred, more than
     the candidates' slots, at the beginning, in the middle and at the end; shared among workgroups, streamed, and in registers."""
     rng = np.random.default_rng(V + k)
     logits = (rng.standard_normal((N, V)) * 3).astype(np.float32)
-    lows = (-np.inf, -1e9)
+    lows = (-np.inf, np.finfo(np.float32).min, -1e9)
     for i, count in enumerate((1, k, 300, 1500, 2 * V // 3)):
         first = (0, V // 2, V - count, V // 4 - count // 2, 0)[i]
         kept = logits[i, first:first + count].copy()
-        logits[i] = lows[i % 2]
+        logits[i] = lows[i % 3]
         logits[i, first:first + count] = kept
     idx = oracle.row_topk(logits, k)
     lp = np.take_along_axis(oracle.log_softmax(logits), idx, -1)
