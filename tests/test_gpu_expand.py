@@ -412,3 +412,14 @@ def test_masked_rows_take_no_longer(sx):
 
     plain, with_mask = us(x), us(masked)
     assert with_mask <= 3 * plain, (plain, with_mask)
+
+
+@pytest.mark.parametrize("N,V,k", [(256, 50000, 8), (200, 128256, 32), (64, 100003, 56)])
+def test_log_sum_exp_of_shared_rows_is_rounded_once(sx, N, V, k):
+    """Logits around 5000: value and log-sum-exp are multiples of 2^-12 and their difference is exact, so a score's error is the
+    log-sum-exp's rounding, half a unit in its last place (2^-12), and a little for the sum before it."""
+    logits = wl.hash_normal(77, (N, V), std=3.0, mean=5000.0, device=dev())
+    r, t, s, n, _ = sx.expand_topk(logits, torch.zeros(N, device=dev()), k, N * k)
+    want = torch.log_softmax(logits.double(), 1)[r.long(), t.long()]
+    assert int(n.item()) == N * k
+    assert float((s.double() - want).abs().max()) <= 2.0 ** -12 * 1.02
