@@ -43,7 +43,7 @@ typedef enum sx_status {
   SX_OK = 0,
   SX_ERR_NULL = -1,       /* a required pointer is NULL */
   SX_ERR_SHAPE = -2,      /* a size is out of the supported range (see each call) */
-  SX_ERR_WORKSPACE = -3,  /* workspace missing, misaligned or smaller than the query says */
+  SX_ERR_WORKSPACE = -3,  /* workspace missing, misaligned or too small */
   SX_ERR_DTYPE = -4,      /* cfg.dtype is neither SX_F32 nor SX_BF16 */
   SX_ERR_HIP = -5,        /* a HIP call or kernel launch failed */
   SX_ERR_TREE = -6        /* device data: parent_idx not in {-1} U [0,i), or token outside [0,V) */
@@ -218,6 +218,9 @@ int sx_accept_walk(const float *logits, const float *draft_probs, const int32_t 
  *   out_row, out_token   device int32 [B];  out_cum_logp  device float [B]
  *   n_out      device int32 [1] = min(B, N*k)
  * Supported: 1 <= k <= min(V, 256), V <= 131072, 1 <= B <= 8192, N >= 1, N*k < 2^31.
+ * Workspace: sx_expand_topk_workspace(N, V, k, B) bytes let several workgroups share a row of more than 32768 entries; a
+ * workspace made for a larger N, V or k serves every smaller one.  With less, down to sx_expand_topk_workspace(N, 1, k, B), one
+ * workgroup streams each row: the same tokens, up to twice the time.
  * ---------------------------------------------------------------------------------------- */
 size_t sx_expand_topk_workspace(int32_t N, int32_t V, int32_t k, int32_t B);
 int sx_expand_topk(const float *logits, const float *cum_logp, int32_t N, int32_t V, int32_t k,
@@ -290,7 +293,8 @@ int sx_specexec_round(const sx_weights *w, void *cache_k, void *cache_v, int32_t
  * Supported: D * B <= 16384, k <= 256 (k is clamped to the vocabulary), min(K, B k) <= 8192,
  * K + min(K, B k) <= 16384, and the model shapes of sx_verify_tree with T = D * B.  A draft model with 4-bit
  * layers (w->layers_w4) needs B <= 128 (its batches then read the 4-bit weights directly; no scratch copy).
- * workspace: sx_draft_tree_workspace bytes, 256-byte aligned; sx_check_status on it reports an error of
+ * workspace: sx_draft_tree_workspace bytes, 256-byte aligned (one made for a larger K, B or k serves the smaller ones; of
+ * a vocabulary beyond 32768 the part for shared rows, sx_expand_topk's, may be missing); sx_check_status on it reports an error of
  * any of the D forward passes (the first pass resets the status word, the later ones leave an error in place).
  * ---------------------------------------------------------------------------------------- */
 size_t sx_draft_tree_workspace(const sx_model_cfg *cfg, int32_t P, int32_t K, int32_t D, int32_t B,

@@ -283,7 +283,7 @@ struct DraftLayout {
   int32_t *sel_row, *sel_tok, *sel_n, *newidx;
   float* sel_score;
   void *expand_ws, *tree_k, *tree_v, *verify_ws;
-  size_t expand_ws_bytes, verify_ws_bytes, bytes;
+  size_t verify_ws_bytes, expand_at, least_bytes, bytes;  // expand_at: offset of the expansion's workspace, the last
   int S, logcap, hcap, ksel, bsel;
 };
 
@@ -326,11 +326,12 @@ DraftLayout draft_carve(const sx_model_cfg& c, int P, int K, int D, int B, int k
   L.sel_tok = cv.take<int32_t>(L.bsel);
   L.sel_score = cv.take<float>(L.bsel);
   L.sel_n = cv.take<int32_t>(1);
-  L.expand_ws_bytes = sx_expand_topk_workspace(B, c.vocab, L.ksel, L.bsel);
-  L.expand_ws = cv.take<char>(L.expand_ws_bytes);
   const size_t kv = (size_t)c.n_layers * L.S * c.n_kv_heads * c.head_dim * es;
   L.tree_k = cv.take<char>(kv);
   L.tree_v = cv.take<char>(kv);
+  L.expand_at = cv.off;
+  L.least_bytes = L.expand_at + sx_expand_topk_min_workspace(B, L.ksel);
+  L.expand_ws = cv.take<char>(sx_expand_topk_workspace(B, c.vocab, L.ksel, L.bsel));
   L.bytes = cv.off;
   return L;
 }
@@ -353,7 +354,7 @@ extern "C" int sx_draft_tree(const sx_weights* w, const void* prefix_k, const vo
   if (w->layers_w4 && B > 128) return SX_ERR_SHAPE;  // wider batches of a 4-bit model would need the bf16 scratch copy
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return SX_ERR_WORKSPACE;
   const DraftLayout L = draft_carve(c, P, K, D, B, k, workspace);
-  if (workspace_bytes < L.bytes) return SX_ERR_WORKSPACE;
+  if (workspace_bytes < L.least_bytes) return SX_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)stream;
 
   // few candidates: the take kernel picks the best of them itself
@@ -381,7 +382,7 @@ extern "C" int sx_draft_tree(const sx_weights* w, const void* prefix_k, const vo
       SX_TRY(sx_launch_row_scores(L.logits, L.b.cum + base, B, c.vocab, L.ksel, lp, cand_tok, cand_score, st));
     else
       SX_TRY(sx_expand_topk(L.logits, L.b.cum + base, B, c.vocab, L.ksel, L.bsel, L.sel_row, L.sel_tok, L.sel_score,
-                            L.sel_n, L.expand_ws, L.expand_ws_bytes, st));
+                            L.sel_n, L.expand_ws, workspace_bytes - L.expand_at, st));
   }
   draft_finish_kernel<<<1, kThreads, 0, st>>>(L.b, L.S, K, tree_tokens_out, parent_out, cum_logp_out, n_out, L.newidx);
   SX_LAUNCH_CHECK();

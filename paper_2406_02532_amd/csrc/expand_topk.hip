@@ -518,7 +518,7 @@ __global__ __launch_bounds__(THREADS) void row_topk_stream_kernel(const float* _
 
 // A row's shares put together: a key's place is its place in its own list and the number of smaller keys in the others, by
 // binary search.  Dynamic LDS: the parts * k keys.
-constexpr int kMergeThreads = 256, kMaxShares = 8;
+constexpr int kMergeThreads = 256;
 __global__ __launch_bounds__(kMergeThreads) void merge_shares_kernel(RowShares sh, const float* __restrict__ cum_logp, int k,
                                                                      float* __restrict__ topk_logp, int* __restrict__ topk_idx,
                                                                      float* __restrict__ score) {
@@ -1223,9 +1223,10 @@ int row_parts(int N, int V, int k, bool vec) {
   if (V <= 32768 || (vec ? N <= 128 || k > 32 : N > 128 || k > kShareMaxK)) return 1;
   return V <= 65536 ? (N <= 8 ? 4 : 2) : (N <= 16 ? 8 : 4);
 }
-size_t shares_bytes(int N, int V, int k) {
-  const int parts = row_parts(N, V, k, V % 4 == 0);
-  return parts == 1 ? 0 : sx_align_up((size_t)N * parts * 8, 256) + sx_align_up((size_t)N * parts * k * 8, 256);
+size_t shares_bytes(size_t shares, int k) { return sx_align_up(shares * 8, 256) + sx_align_up(shares * k * 8, 256); }
+// for every call of at most N rows, V entries and k picks, so that a workspace made for the largest serves the others as well
+size_t shares_bytes_up_to(int N, int V, int k) {
+  return V <= 32768 ? 0 : shares_bytes(N <= 16 ? 8 * (size_t)N : N <= 32 ? 128 : 4 * (size_t)N, k < kShareMaxK ? k : kShareMaxK);
 }
 template <bool VEC>
 void launch_shares(const float* logits, const float* cum, int N, int V, int k, float* lp, int* idx, float* score, void* scratch,
@@ -1291,11 +1292,11 @@ extern "C" int sx_row_logsoftmax_topk(const float* logits, int32_t N, int32_t V,
 }
 
 // workspace: header | score f32[N*k] | topk_logp f32[N*k] | topk_idx i32[N*k] | shares of long rows (used if there)
-static size_t expand_min_workspace(int32_t N, int32_t k) { return SX_WS_HEADER + 3 * sx_align_up((size_t)N * (size_t)k * 4, 256); }
+size_t sx_expand_topk_min_workspace(int N, int k) { return SX_WS_HEADER + 3 * sx_align_up((size_t)N * (size_t)k * 4, 256); }
 extern "C" size_t sx_expand_topk_workspace(int32_t N, int32_t V, int32_t k, int32_t B) {
   (void)B;
   if (N < 1 || k < 1) return 0;
-  return expand_min_workspace(N, k) + shares_bytes(N, V, k);
+  return sx_expand_topk_min_workspace(N, k) + shares_bytes_up_to(N, V, k);
 }
 
 namespace {
@@ -1357,9 +1358,10 @@ extern "C" int sx_expand_topk(const float* logits, const float* cum_logp, int32_
   if (!logits || !cum_logp || !out_row || !out_token || !out_cum_logp || !n_out) return SX_ERR_NULL;
   if (!row_shape_ok(N, V, k) || B < 1 || B > 8192) return SX_ERR_SHAPE;
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) ||
-      workspace_bytes < expand_min_workspace(N, k))
+      workspace_bytes < sx_expand_topk_min_workspace(N, k))
     return SX_ERR_WORKSPACE;
-  const bool shares = workspace_bytes >= sx_expand_topk_workspace(N, V, k, B);
+  const int parts = row_parts(N, V, k, V % 4 == 0);
+  const bool shares = parts > 1 && workspace_bytes - sx_expand_topk_min_workspace(N, k) >= shares_bytes((size_t)N * parts, k);
   const size_t nk = sx_align_up((size_t)N * (size_t)k * 4, 256);
   char* ws = static_cast<char*>(workspace);
   return expand_topk_run(logits, cum_logp, N, V, k, B, out_row, out_token, out_cum_logp, n_out,

@@ -146,6 +146,8 @@ static inline int sx_attn_nodes_per_tile(int Hq, int Hkv, int Tq) {
 }
 
 // ---- expansion (expand_topk.hip) --------------------------------------------------------------------------------
+// the least workspace that sx_expand_topk takes: without room for the shares of long rows, which are then streamed
+size_t sx_expand_topk_min_workspace(int N, int k);
 // the first half of sx_expand_topk: per row its k best (lp, idx, score = cum_logp + lp; [N][k]); k <= 256, k <= V
 int sx_launch_row_scores(const float* logits, const float* cum_logp, int N, int V, int k, float* lp, int32_t* idx, float* score,
                          hipStream_t st);

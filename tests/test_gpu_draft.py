@@ -286,3 +286,28 @@ def test_draft_tree_recorded_in_a_graph_replays_the_eager_result(sx):
         for a, b in zip(outs, eager):
             assert torch.equal(a, b), f"replay {rep} differs from the eager call"
     del junk
+
+
+@pytest.mark.parametrize("k", [4, 32, 56])
+def test_draft_tree_without_room_for_shared_rows(sx, k):
+    """A vocabulary whose rows the expansion shares among workgroups: a workspace without the room for that is taken, down to
+    the last byte of the rest, and gives the same tree."""
+    cfg = wl.ModelCfg(1, 128, 4, 2, 32, 256, 50257, dtype="fp32")
+    w = wl.gen_weights(cfg, seed=71)
+    mw = sx.ModelWeights(cfg, weights_to(dict(w, lm_head=w["lm_head"] * 12.0, embed=w["embed"] * 20.0), dev()))
+    P, K, D, B = 24, 200, 3, 64
+    kv = lambda key: wl.hash_normal(key, (1, P, 2, 32), device=dev())  # noqa: E731
+    root = torch.tensor([7], dtype=torch.int32, device=dev())
+    full = sx.draft_tree(mw, kv(1), kv(2), P, root, K, D, B, k)
+    q = sx.lib.sx_expand_topk_workspace
+    least = full[4].numel() - (q(B, cfg.vocab, k, K) - q(B, 1, k, K))
+    assert least < full[4].numel()
+    got = sx.draft_tree(mw, kv(1), kv(2), P, root, K, D, B, k, workspace=torch.empty(least, dtype=torch.uint8, device=dev()))
+    n = int(full[3].item())
+    assert n == int(got[3].item()) > 1
+    for i in range(2):
+        assert torch.equal(full[i][:n], got[i][:n])
+    np.testing.assert_allclose(got[2][:n].cpu().numpy(), full[2][:n].cpu().numpy(), rtol=0, atol=1e-4)
+    with pytest.raises(sx.SxError) as e:
+        sx.draft_tree(mw, kv(1), kv(2), P, root, K, D, B, k, workspace=torch.empty(least - 256, dtype=torch.uint8, device=dev()))
+    assert e.value.code == -3
