@@ -306,11 +306,15 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(GemmArgs a) {
   if (r == 4) { SX_READW(WSTG_, FW, 4, KC) }                                                                   \
   if (r == 5) { SX_READW(WSTG_, FW, 6, KC) }
 // The copies of a slab, dealt over the 16 half row blocks of a phase: X's before W's where W has a stage more, since then
-// the barrier waits for X's and leaves W's in flight; one of each in turn otherwise.
+// the barrier waits for X's and leaves W's in flight, by their number (the empty statement keeps the compiler from issuing one
+// of W's among X's: they write arrays of their own); one of each in turn otherwise.
 #define SX_COPIES(XSTG_, WSTG_, XSO_, WSO_, h)                                                                 \
   if (NW > NS) {                                                                                               \
     if ((h) < JB) { SX_COPY1(XSTG_, XSO_, 0, h) }                                                              \
-    else if ((h) < JB + 8) { SX_COPY1(WSTG_, WSO_, 1, ((h) - JB) & 7) }                                        \
+    else if ((h) < JB + 8) {                                                                                   \
+      if ((h) == JB) asm volatile("" ::: "memory");                                                            \
+      SX_COPY1(WSTG_, WSO_, 1, ((h) - JB) & 7)                                                                 \
+    }                                                                                                          \
   } else {                                                                                                     \
     if ((h) & 1) { SX_COPY1(WSTG_, WSO_, 1, (h) / 2) } else { SX_COPY1(XSTG_, XSO_, 0, (h) / 2) }              \
   }
