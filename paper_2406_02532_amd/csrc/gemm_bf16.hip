@@ -737,13 +737,17 @@ float plan_split(GemmArgs& a, int jb, void* split_ws, size_t split_ws_bytes) {
 //
 // The height: the one that plan_split's figures expect to be fastest.  Over the 160 products of the second fit the choice is
 // within 0.3 % of the best launch on average, 6 % at worst.
-// Three things the figures do not know:
+// Four things the figures do not know:
 //   the prefetching form of 256 rows (8 row tiles, whole groups of 4 column tiles), unless every tile is cut, streams the
 //   weights better than they say: a tenth;
 //   so does that of 128 and 160 rows over several rounds, none of them cut (8192 x 8192 at 2500 rows, two rounds of 160 rows
 //   278 us, 256 rows with 64 tiles cut 309): a twentieth;
 //   short parts of K gain less from W's third stage: two stages of X and all tiles cut, 6 % (7B down at 670 rows, 64 tiles
-//   of 192 rows in four parts 81 us, 80 of 160 rows in three 76).
+//   of 192 rows in four parts 81 us, 80 of 160 rows in three 76);
+//   a last row tile of several that is mostly padding takes less, which shows at 128 and 160 rows: without the discount 7B
+//   gate|up at 525 rows took 103.6 us with 192 rows for 100.8 with 128, 70B down at 165 rows 141.0 for 136.6, 13824 -> 5120 at
+//   525 rows 90.7 for 89.0.  (Not under a cut tail, where 70B down at 1040 rows would go from 419 to 438, nor with all tiles
+//   cut in two, 7B QKV at 145 rows 41.1 to 41.9; with 192 rows 13824-wide gate|up at 2497 rows would go from 513 to 537.)
 // (224 rows in as many row tiles as of 256 only drop padding, and are still faster: 7B QKV at 1100 rows 84 us for 93, gate|up 153
 // for 169, 32000 columns, K = 4096, at 1300 rows 260 for 295.)
 //
@@ -774,12 +778,18 @@ Plan pick_plan(GemmArgs& a, void* split_ws, size_t split_ws_bytes) {
     const bool nearly_whole = a.split == 1 && tiles > cus && tiles % cus * 10 >= 9 * cus;
     return stages(jb) == 3 && a.tilesM >= 3 && a.M * 25ll >= 23ll * 32 * jb * a.tilesM && !nearly_whole;
   };
+  auto padding = [&](int jb) {  // of the plan that a holds: less for a mostly empty last row tile
+    const float empty = a.tilesM - a.M / (32.f * jb);
+    const bool counts = stages(jb) == 3 && a.tilesM > 1 && (a.split == 1 || (a.full_tiles == 0 && a.split > 2));
+    return counts && empty > 0.6f ? 1.f - 0.12f * (empty - 0.6f) : 1.f;
+  };
   const bool all_cut8 = a.split > 1 && a.full_tiles == 0;
   float best = (all_cut8 ? 1.06f : can_prefetch ? 0.9f : 1.f) * tall;
   for (int t = 7; t >= 4; --t) {
     float cost = plan_split(a, t, split_ws, split_ws_bytes);
     if (a.split == 1 && a.tilesM * a.tilesN > cus && touch(t)) cost *= 0.95f;
     if (a.split > 1 && a.full_tiles == 0 && stages(t) == 2) cost *= 1.06f;
+    cost *= padding(t);
     if (cost < best) best = cost, p.jb = t;
   }
   plan_split(a, p.jb, split_ws, split_ws_bytes);

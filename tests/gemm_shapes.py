@@ -22,7 +22,7 @@ WIDE_SHAPES = [
     (2, 2001, 5120, 1088, 192, "none", False),
     # forms that none of these takes
     (0, 384, 72, 2048, 128, "all", True), (0, 381, 72, 576, 128, "none", True), (0, 162, 32928, 1088, 192, "none", False),
-    (0, 129, 10808, 3072, 128, "all", False), (0, 777, 4624, 3072, 160, "all", True),
+    (0, 129, 10808, 3072, 128, "all", False), (0, 777, 4624, 3072, 128, "none", False),
     (0, 130, 33416, 64, 160, "none", False), (0, 448, 16440, 64, 160, "none", True),
     (0, 259, 33304, 2048, 128, "none", False), (0, 779, 16824, 1536, 128, "none", False),
     (0, 165, 16520, 4096, 192, "all", False), (0, 644, 27176, 3072, 192, "none", False),
@@ -30,7 +30,7 @@ WIDE_SHAPES = [
     (2, 361, 80, 1088, 128, "all", True), (2, 383, 72, 64, 128, "none", True), (2, 165, 16456, 3072, 192, "none", False),
     (2, 132, 5480, 3072, 128, "all", False), (2, 1564, 1160, 3072, 128, "none", True),
     (2, 130, 16864, 192, 160, "none", False), (2, 773, 4728, 64, 160, "none", True),
-    (2, 132, 32912, 1088, 160, "tail", False), (2, 770, 8224, 4096, 160, "tail", True),
+    (2, 132, 32912, 1088, 160, "tail", False), (2, 770, 8224, 4096, 128, "none", False),
     (2, 161, 8256, 4096, 192, "all", False), (2, 165, 32904, 1024, 192, "none", False),
     (2, 645, 13728, 3072, 192, "none", False), (2, 683, 13672, 4096, 192, "none", False),
     (2, 1932, 5048, 3072, 192, "none", False),
@@ -39,9 +39,10 @@ WIDE_SHAPES = [
     (0, 770, 18896, 3072, 160, "tail", True), (0, 515, 26448, 3072, 192, "tail", False),
     (0, 388, 33208, 3072, 224, "tail", False), (0, 482, 33288, 4096, 256, "tail", False),
     (0, 1924, 12136, 3072, 256, "tail", True), (2, 226, 16640, 4096, 128, "tail", False),
-    (2, 134, 5408, 4096, 160, "all", False), (2, 793, 2376, 3072, 160, "all", True),
+    (2, 134, 5408, 4096, 160, "all", False), (2, 793, 2376, 3072, 128, "none", False),
     (2, 514, 13096, 3072, 192, "tail", False), (2, 404, 16424, 3072, 224, "tail", False),
     (2, 484, 16568, 4096, 256, "tail", False), (2, 1926, 6024, 3072, 256, "tail", True),
+    (0, 2251, 1040, 5120, 160, "all", True), (2, 2251, 520, 5120, 160, "all", True), (2, 780, 9376, 2560, 160, "tail", True),
     # what the suite has run all along, whatever the height
     (0, 160, 520, 192, None, None, None), (0, 161, 72, 1088, None, None, None), (0, 192, 512, 64, None, None, None),
     (0, 193, 250, 320, None, None, None), (0, 224, 264, 2048, None, None, None), (0, 257, 128, 704, None, None, None),
@@ -58,7 +59,7 @@ QKV_SHAPES = [
     (354, 1088, 1, 1, 128, "all", True), (1604, 3072, 64, 16, 192, "none", False), (131, 3072, 64, 16, 128, "all", False),
     (1543, 3072, 16, 2, 128, "none", True), (1282, 64, 16, 16, 160, "none", False), (1541, 64, 32, 4, 160, "none", True),
     (2054, 3072, 64, 8, 192, "none", False), (961, 64, 64, 8, 192, "none", False), (961, 64, 64, 16, 224, "none", False),
-    (1025, 64, 64, 16, 224, "none", False), (1794, 64, 4, 2, 256, "none", True),
+    (1025, 64, 64, 16, 224, "none", False), (1794, 64, 4, 2, 128, "none", True), (1838, 64, 4, 2, 256, "none", True),
     (2305, 64, 112, 16, 256, "none", False), (1983, 3072, 80, 8, 256, "tail", True)
 ]
 
