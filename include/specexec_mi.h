@@ -343,9 +343,12 @@ int sx_gemm_bf16_wide_plan(int32_t M, int32_t N, int32_t K, int32_t mode, size_t
                            int32_t *tile_rows, int32_t *k_parts, int32_t *cut_tiles, int32_t *prefetch);
 /* The same for the narrow tiles that most products of at most 128 rows and every QKV projection of that size take: columns
  * of a tile (64 or 128, mode 2 and the QKV projection also 96; rows of the gate and the up matrix both count) and parts that
- * K is cut in, for 128 rows (fewer may take another width or fewer parts). */
+ * K is cut in, for 128 rows (fewer may take another width or fewer parts); sx_gemm_bf16_narrow_plan_rows: for M <= 128 rows, and
+ * for the QKV projection of N columns in all as mode 3. */
 int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t *tile_columns,
                              int32_t *k_parts);
+int sx_gemm_bf16_narrow_plan_rows(int32_t M, int32_t N, int32_t K, int32_t mode, size_t workspace_bytes,
+                                  int32_t *tile_columns, int32_t *k_parts);
 
 /* QKV projection of the decoder layer (Alg. 1, FORWARD) with the rotary embedding applied in the
  * GEMM's epilogue, head_dim 128: q_out device bf16 [T][n_q_heads][128], k_out and v_out device
@@ -373,6 +376,9 @@ size_t sx_gemm_w4a16_workspace(void);
 int sx_gemm_w4a16_bf16(const void *X, const void *qweight, const void *scales, const void *zeros, void *Y,
                        int32_t M, int32_t N, int32_t K, int32_t group, int32_t mode, void *workspace,
                        size_t workspace_bytes, void *stream);
+/* How these products and the 4-bit layers' (N columns in all) are laid out: columns of a tile (64, 96 or 128) and parts that K
+ * is cut in, K a multiple of 128. */
+int sx_gemm_w4a16_plan(int32_t M, int32_t N, int32_t K, size_t workspace_bytes, int32_t *tile_columns, int32_t *k_parts);
 
 /* Tree attention alone (App. D merged mask), bf16: q device bf16 [T][Hq][128], tree K/V
  * [T][Hkv][128], prefix K/V [P][Hkv][128], out device bf16 [T][Hq][128]; n_q_heads/n_kv_heads in {1,2,4,8}.  workspace sized by

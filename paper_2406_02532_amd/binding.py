@@ -11,7 +11,8 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libspecexec
 EXPORTS = ["sx_verify_tree_workspace", "sx_verify_tree_w4_workspace", "sx_verify_tree", "sx_verify_tree_cached", "sx_verify_tree_range", "sx_commit_kv",
            "sx_specexec_round_workspace", "sx_specexec_round", "sx_draft_tree_workspace", "sx_draft_tree", "sx_accept_walk_workspace", "sx_accept_walk",
            "sx_expand_topk_workspace", "sx_expand_topk", "sx_expand_topk_static", "sx_check_status", "sx_status_string", "sx_version",
-           "sx_row_logsoftmax_topk", "sx_gemm_bf16", "sx_gemm_bf16_workspace", "sx_gemm_bf16_ws", "sx_gemm_bf16_wide_plan", "sx_gemm_bf16_narrow_plan", "sx_gemm_w4a16_workspace", "sx_gemm_w4a16_bf16", "sx_qkv_rope_workspace", "sx_qkv_rope_bf16", "sx_tree_attention_workspace", "sx_tree_attention_bf16",
+           "sx_row_logsoftmax_topk", "sx_gemm_bf16", "sx_gemm_bf16_workspace", "sx_gemm_bf16_ws", "sx_gemm_bf16_wide_plan", "sx_gemm_bf16_narrow_plan", "sx_gemm_bf16_narrow_plan_rows",
+           "sx_gemm_w4a16_workspace", "sx_gemm_w4a16_bf16", "sx_gemm_w4a16_plan", "sx_qkv_rope_workspace", "sx_qkv_rope_bf16", "sx_tree_attention_workspace", "sx_tree_attention_bf16",
            "sx_profile_enable", "sx_profile_select", "sx_profile_disable", "sx_profile_read"]
 
 SX_F32, SX_BF16 = 0, 1
@@ -105,6 +106,10 @@ def _load():
     L.sx_gemm_bf16_wide_plan.argtypes = [i32, i32, i32, i32, sz, vp, vp, vp, vp]
     L.sx_gemm_bf16_narrow_plan.restype = C.c_int
     L.sx_gemm_bf16_narrow_plan.argtypes = [i32, i32, i32, sz, vp, vp]
+    L.sx_gemm_bf16_narrow_plan_rows.restype = C.c_int
+    L.sx_gemm_bf16_narrow_plan_rows.argtypes = [i32, i32, i32, i32, sz, vp, vp]
+    L.sx_gemm_w4a16_plan.restype = C.c_int
+    L.sx_gemm_w4a16_plan.argtypes = [i32, i32, i32, sz, vp, vp]
     L.sx_gemm_w4a16_workspace.restype = sz
     L.sx_gemm_w4a16_workspace.argtypes = []
     L.sx_gemm_w4a16_bf16.restype = C.c_int
@@ -396,6 +401,21 @@ def gemm_bf16_narrow_plan(N: int, K: int, mode: int = 0, workspace_bytes: int = 
     """sx_gemm_bf16_narrow_plan: (columns of a tile, parts of K) of the narrow GEMM at this shape."""
     out = (C.c_int32 * 2)()
     _check(lib.sx_gemm_bf16_narrow_plan(N, K, mode, workspace_bytes, C.byref(out, 0), C.byref(out, 4)), "sx_gemm_bf16_narrow_plan")
+    return out[0], out[1]
+
+
+def gemm_bf16_narrow_plan_rows(M: int, N: int, K: int, mode: int = 0, workspace_bytes: int = 0):
+    """sx_gemm_bf16_narrow_plan_rows: the same for M rows; mode 3: the QKV projection."""
+    out = (C.c_int32 * 2)()
+    _check(lib.sx_gemm_bf16_narrow_plan_rows(M, N, K, mode, workspace_bytes, C.byref(out, 0), C.byref(out, 4)),
+           "sx_gemm_bf16_narrow_plan_rows")
+    return out[0], out[1]
+
+
+def gemm_w4a16_plan(M: int, N: int, K: int, workspace_bytes: int = 0):
+    """sx_gemm_w4a16_plan: (columns of a tile, parts of K) of the GEMM with 4-bit weights at this shape."""
+    out = (C.c_int32 * 2)()
+    _check(lib.sx_gemm_w4a16_plan(M, N, K, workspace_bytes, C.byref(out, 0), C.byref(out, 4)), "sx_gemm_w4a16_plan")
     return out[0], out[1]
 
 

@@ -519,13 +519,19 @@ int sx_launch_gemm_skinny_qkv_rope_bf16(const void* X, const void* Wq, const voi
   return launch<SX_GEMM_QKV_ROPE>(a, a.N, split_ws, split_ws_bytes, st);
 }
 
-extern "C" int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t* tile_columns,
-                                        int32_t* k_parts) {
+extern "C" int sx_gemm_bf16_narrow_plan_rows(int32_t M, int32_t N, int32_t K, int32_t mode, size_t workspace_bytes,
+                                             int32_t* tile_columns, int32_t* k_parts) {
   if (!tile_columns || !k_parts) return SX_ERR_NULL;
-  if (mode < 0 || mode > 2 || N < 1 || K < BK || K % BK != 0) return SX_ERR_SHAPE;
-  const SkinnyPlan p = plan_skinny(128, mode == SX_GEMM_SWIGLU ? 2 * N : N, K, mode == SX_GEMM_SWIGLU,
+  if (M < 1 || M > 128 || mode < 0 || mode > SX_GEMM_QKV_ROPE || N < 1 || K < BK || K % BK != 0) return SX_ERR_SHAPE;
+  const SkinnyPlan p = plan_skinny(M, mode == SX_GEMM_SWIGLU ? 2 * N : N, K, mode == SX_GEMM_SWIGLU || mode == SX_GEMM_QKV_ROPE,
                                    workspace_bytes != 0, workspace_bytes);
   *tile_columns = p.columns;
   *k_parts = p.split;
   return SX_OK;
+}
+
+extern "C" int sx_gemm_bf16_narrow_plan(int32_t N, int32_t K, int32_t mode, size_t workspace_bytes, int32_t* tile_columns,
+                                        int32_t* k_parts) {
+  if (tile_columns && k_parts && (mode < 0 || mode > 2)) return SX_ERR_SHAPE;
+  return sx_gemm_bf16_narrow_plan_rows(128, N, K, mode, workspace_bytes, tile_columns, k_parts);
 }

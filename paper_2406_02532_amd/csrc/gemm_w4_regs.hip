@@ -471,6 +471,34 @@ void launch_form(const W4RegArgs& a, int columns, dim3 grid, hipStream_t st) {
   else launch_rows<MODE, 4, 1>(a, grid, st);
 }
 
+// Columns per workgroup and cut of K, one workgroup to a compute unit, parts of at least 3 slabs.  The figures are fitted to
+// 1600 launches of 12 shapes (2048 to 57344 columns, K of 2048 to 28672) at 1 to 128 rows, weights from memory: a slab's
+// time grows with columns, rows and both; a cut costs what the last arriver does.  Within 0.3 % of the best launch on
+// average, 4 % at worst.
+struct W4Plan {
+  int columns, split;
+};
+W4Plan plan_w4(int M, int N, int K, bool have_ws, size_t split_ws_bytes) {
+  const int cus = sx_compute_units(), nb = K / BK;
+  const int rb = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : M <= 80 ? 5 : M <= 112 ? 7 : 8;
+  W4Plan p = {64, 1};
+  float best = 1e30f;
+  for (int bn = 128; bn >= 64; bn -= 32) {
+    const int tiles = (N + bn - 1) / bn;
+    const float c = bn / 128.f, r = rb / 8.f, slab = 0.045f + 0.531f * c + 0.316f * r + 0.331f * c * r;
+    for (int split = 1; split <= 16; ++split) {
+      const size_t part = split > 1 ? (size_t)split * rb * 16 * bn * sizeof(float) : 0;  // bytes per tile
+      if (split > 1 && (!have_ws || tiles > 256 || tiles * split > cus || nb / split < 3 || split_ws_bytes < 1024 + tiles * part))
+        break;
+      const int rounds = (tiles * split + cus - 1) / cus;
+      const float cost = rounds * (0.42f + (nb + split - 1) / split * slab) +
+                         (split > 1 ? 1.8f + 0.33f * split + 1.8e-5f * (float)part : 0.f);
+      if (cost < best) best = cost, p = {bn, split};
+    }
+  }
+  return p;
+}
+
 // Stacked 4-bit matrices (n1, n2 may be 0; every non-final segment a multiple of 64 rows), M <= 128, K a multiple of 128,
 // group a power of two >= 64 dividing K.  Y fp32 [M][ldy] (ldy >= n0 + n1 + n2), mode store or residual.
 // split_ws: 1 KB of counters (zero before the first launch; the kernel leaves them zero) followed by room for the
@@ -503,28 +531,9 @@ int launch_w4(W4RegArgs& a, const void* X, const sx_w4_matrix* mats, const int* 
   a.M = M;
   a.N = N;
   a.K = K;
-  // Columns per workgroup and cut of K, one workgroup to a compute unit, parts of at least 3 slabs.  The figures are fitted to
-  // 1600 launches of 12 shapes (2048 to 57344 columns, K of 2048 to 28672) at 1 to 128 rows, weights from memory: a slab's
-  // time grows with columns, rows and both; a cut costs what the last arriver does.  Within 0.3 % of the best launch on
-  // average, 4 % at worst.
-  const int cus = sx_compute_units(), nb = K / BK;
-  const int rb = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : M <= 80 ? 5 : M <= 112 ? 7 : 8;
-  int columns = 64;
-  a.split = 1;
-  float best = 1e30f;
-  for (int bn = 128; bn >= 64; bn -= 32) {
-    const int tiles = (N + bn - 1) / bn;
-    const float c = bn / 128.f, r = rb / 8.f, slab = 0.045f + 0.531f * c + 0.316f * r + 0.331f * c * r;
-    for (int split = 1; split <= 16; ++split) {
-      const size_t part = split > 1 ? (size_t)split * rb * 16 * bn * sizeof(float) : 0;  // bytes per tile
-      if (split > 1 && (!split_ws || tiles > 256 || tiles * split > cus || nb / split < 3 || split_ws_bytes < 1024 + tiles * part))
-        break;
-      const int rounds = (tiles * split + cus - 1) / cus;
-      const float cost = rounds * (0.42f + (nb + split - 1) / split * slab) +
-                         (split > 1 ? 1.8f + 0.33f * split + 1.8e-5f * (float)part : 0.f);
-      if (cost < best) best = cost, columns = bn, a.split = split;
-    }
-  }
+  const W4Plan p = plan_w4(M, N, K, split_ws != nullptr, split_ws_bytes);
+  const int columns = p.columns;
+  a.split = p.split;
   a.part = nullptr;
   a.part_cnt = nullptr;
   const dim3 grid((N + columns - 1) / columns, a.split);
@@ -574,4 +583,13 @@ int sx_launch_gemm_w4_qkv_rope(const void* X, const sx_w4_matrix* qkv, int hq, i
   a.k = static_cast<unsigned short*>(k);
   a.v = static_cast<unsigned short*>(v);
   return launch_w4(a, X, qkv, ns, 3, group, nullptr, ns[0] + ns[1] + ns[2], M, K, SX_GEMM_QKV_ROPE, split_ws, split_ws_bytes, st);
+}
+
+extern "C" int sx_gemm_w4a16_plan(int32_t M, int32_t N, int32_t K, size_t workspace_bytes, int32_t* tile_columns, int32_t* k_parts) {
+  if (!tile_columns || !k_parts) return SX_ERR_NULL;
+  if (M < 1 || M > 128 || N < 1 || K < BK || K % BK != 0) return SX_ERR_SHAPE;
+  const W4Plan p = plan_w4(M, N, K, workspace_bytes != 0, workspace_bytes);
+  *tile_columns = p.columns;
+  *k_parts = p.split;
+  return SX_OK;
 }
