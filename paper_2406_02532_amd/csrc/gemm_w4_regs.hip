@@ -473,9 +473,8 @@ void launch_form(const W4RegArgs& a, int columns, dim3 grid, hipStream_t st) {
 
 // Columns per workgroup and cut of K, one workgroup to a compute unit, parts of at least 3 slabs.  The figures are fitted to
 // 1600 launches of 12 shapes (2048 to 57344 columns, K of 2048 to 28672) at 1 to 128 rows, weights from memory: a slab's
-// time grows with columns, rows and both; a cut costs what the last arriver does, at 96 columns with its twelve waves a
-// quarter of a microsecond more a part (without that 11264 x 2048 at 128 rows took 22.8 us cut in two for 19.2 with 64
-// columns uncut).  Within 0.7 % of the best launch on average over 17 shapes at six row counts.
+// time grows with columns, rows and both; a cut costs what the last arriver does, at 96 columns with its twelve waves 0.4 us
+// more a part (without that 11264 x 2048 at 128 rows took 22.8 us cut in two for 19.2 with 64 columns uncut).  Within 0.4 % of the best launch on average, 5 % at worst, over 17 shapes at six row counts.
 struct W4Plan {
   int columns, split;
 };
@@ -493,7 +492,7 @@ W4Plan plan_w4(int M, int N, int K, bool have_ws, size_t split_ws_bytes) {
         break;
       const int rounds = (tiles * split + cus - 1) / cus;
       const float cost = rounds * (0.42f + (nb + split - 1) / split * slab) +
-                         (split > 1 ? 1.8f + (bn == 96 ? 0.58f : 0.33f) * split + 1.8e-5f * (float)part : 0.f);
+                         (split > 1 ? 1.8f + (bn == 96 ? 0.75f : 0.33f) * split + 1.8e-5f * (float)part : 0.f);
       if (cost < best) best = cost, p = {bn, split};
     }
   }
