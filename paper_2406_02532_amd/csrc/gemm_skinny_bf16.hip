@@ -12,8 +12,10 @@
 // as many bytes as of W.  Hence:
 //   the tile has as many blocks of 16 rows as M asks for (1, 2, 4, 5, 7 or 8), whose room goes to further stages (up to five);
 //   96 columns where 128 leave a third of the chip idle (gate|up of 2 x 11008: 172 tiles or 230);
-//   of 96 columns on, W goes past the caches' other contents (nontemporal), which leaves X there.  With 64 columns, cut, that
-//   was 2 to 7 % slower.
+//   of 96 columns on, W goes past the caches' other contents (nontemporal), which leaves X there (without it, at 100 rows: head
+//   of 32000 51.4 us for 47.4, 7B gate|up 38.4 for 36.4, 70B down 99 for 89).  With 64 columns, cut, that was 2 to 7 % slower, and
+//   so it is with a single matrix that the last-level cache still holds from the call before: 7B gate|up over and over, 100 rows,
+//   35.8 us for 33.2, and 31 with the kernel before; a model's layers do not meet that.
 // Weights from memory, us, the kernel before (128 rows of X always, 64 or 128 columns, three or four stages) -> now, at 16,
 // 64, 100 and 128 rows: 7B O 13.4 -> 10.2, 14.0 -> 11.7, 14.6 -> 14.1, 15.1 -> 15.1; down 24.7 -> 18.7, 25.8 -> 22.3, 27.3 ->
 // 27.6, 29.6 -> 29.6; gate|up 36.7 -> 29.8, 39.4 -> 32.2, 42.2 -> 38.2, 45.5 -> 39.9; head of 32000 47.1 -> 43.5, 48.4 -> 43.8,
@@ -218,29 +220,45 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
 #undef SX_COPY
 #undef SX_WAIT
 
-  // ---- the tile is dealt out anew through LDS, block after block of 16 x 16 as the lanes hold them: block b = j NCB + column
-  // block belongs to wave b % NW (pairs: their number, likewise)
-  auto slot = [&](int b) -> unsigned char* {
-    constexpr int PER_STAGE = kStage / 1024;
-    const int stage = b / PER_STAGE;
-    return (stage == 0 ? st0 : stage == 1 ? st1 : stage == 2 ? st2 : stage == 3 ? st3 : st4) +
-           (b - stage * PER_STAGE) * 1024 + lane * 16;
+  // ---- which 16 x 16 blocks of the tile are this wave's from here on; block b = row block * NCB + column block.  Columns in pairs
+  // go by unit, two blocks side by side.  A wave of two column blocks keeps its own (row blocks past the last one are the last
+  // again, with the same sums, and store nothing), unless the waves' row blocks are too uneven; otherwise the waves leave theirs
+  // in LDS, as the lanes hold them, and take every NW-th unit.  (All dealt out anew, head of 32000 x 768 at 100 rows 15.8 us, 768
+  // x 3072 of gate|up 3 % more; none, 2048 x 2048 at 32 rows 7.8 us for 7.5, four row groups sharing two blocks.)
+  constexpr int PER = kPairs ? 2 : 1;                        // blocks of a unit
+  constexpr int UNITS = BLOCKS / PER;
+  constexpr bool kDeal = WB != 2 || RW * RG * 5 > RB * 6;
+  constexpr int NU = kDeal ? (UNITS + NW - 1) / NW : RW * WB / PER;  // per wave
+  auto unit_ok = [&](int u) { return kDeal ? wave + u * NW < UNITS : RW * wr + u * PER / WB < RB; };
+  auto unit = [&](int u) {
+    return kDeal ? min(wave + u * NW, UNITS - 1)
+                 : min(RW * wr + u * PER / WB, RB - 1) * (NCB / PER) + wc * (WB / PER) + u % (WB / PER);
   };
-  static_assert(BLOCKS <= S * (kStage / 1024), "a block lies in one stage");
-#pragma unroll
-  for (int i = 0; i < WB; ++i)
-#pragma unroll
-    for (int j = 0; j < RW; ++j)
-      if (RB % RG == 0 || RW * wr + j < RB) *reinterpret_cast<f32x4*>(slot((RW * wr + j) * NCB + WB * wc + i)) = acc[i][j];
-  __syncthreads();
-  constexpr int PER = kPairs ? 2 : 1;                        // blocks of a unit, side by side in a row of blocks
-  constexpr int UNITS = BLOCKS / PER, NU = (UNITS + NW - 1) / NW;  // per wave
   f32x4 v[NU][PER];
+  if constexpr (kDeal) {
+    auto slot = [&](int b) -> unsigned char* {
+      constexpr int PER_STAGE = kStage / 1024;
+      const int stage = b / PER_STAGE;
+      return (stage == 0 ? st0 : stage == 1 ? st1 : stage == 2 ? st2 : stage == 3 ? st3 : st4) +
+             (b - stage * PER_STAGE) * 1024 + lane * 16;
+    };
+    static_assert(BLOCKS <= S * (kStage / 1024), "a block lies in one stage");
 #pragma unroll
-  for (int u = 0; u < NU; ++u)
+    for (int i = 0; i < WB; ++i)
 #pragma unroll
-    for (int e = 0; e < PER; ++e)
-      v[u][e] = *reinterpret_cast<const f32x4*>(slot(min(wave + u * NW, UNITS - 1) * PER + e));
+      for (int j = 0; j < RW; ++j)
+        if (RB % RG == 0 || RW * wr + j < RB) *reinterpret_cast<f32x4*>(slot((RW * wr + j) * NCB + WB * wc + i)) = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+      for (int e = 0; e < PER; ++e) v[u][e] = *reinterpret_cast<const f32x4*>(slot(unit(u) * PER + e));
+  } else {
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+#pragma unroll
+      for (int e = 0; e < PER; ++e) v[u][e] = acc[(u * PER + e) % WB][u * PER / WB];
+  }
 
   // ---- K split: partial sums meet in memory, the last workgroup to arrive adds them in part order
   // (device-scope stores and loads, stores complete before the counter's device-scope atomic is issued)
@@ -253,7 +271,7 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
     for (int u = 0; u < NU; ++u)
 #pragma unroll
       for (int e = 0; e < PER; ++e) {
-        const int b = min(wave + u * NW, UNITS - 1) * PER + e;
+        const int b = unit(u) * PER + e;
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[u][e]), pres,
                                                all + (unsigned)kpart * (kPartFloats * 4u) + b * 1024, 0, kScopeDevice);
       }
@@ -284,7 +302,7 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
           for (int e = 0; e < PER; ++e)
             x[u][e] = __builtin_bit_cast(
                 f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                           pres, all + (unsigned)p * (kPartFloats * 4u) + (min(wave + u * NW, UNITS - 1) * PER + e) * 1024, 0,
+                           pres, all + (unsigned)p * (kPartFloats * 4u) + (unit(u) * PER + e) * 1024, 0,
                            kScopeDevice));
       }
 #pragma unroll
@@ -301,8 +319,8 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
   if constexpr (MODE == SX_GEMM_SWIGLU) {
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int b = wave + u * NW, m = b / (NCB / 2) * 16 + l16, f = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
-      if (b >= UNITS || m >= a.M || f >= a.N) continue;
+      const int b = unit(u), m = b / (NCB / 2) * 16 + l16, f = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
+      if (!unit_ok(u) || m >= a.M || f >= a.N) continue;
       float h[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) h[e] = silu_mul_bf16_bound(v[u][0][e], v[u][PER - 1][e]);
@@ -324,15 +342,15 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
     f32x4 t[NU][2];
 #pragma unroll
     for (int u = 0; u < NU; ++u) {  // all rows' angles are requested before the first is used
-      const int b = min(wave + u * NW, UNITS - 1), p = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
+      const int b = unit(u), p = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
       const f32x4* c = reinterpret_cast<const f32x4*>(a.cs + (size_t)min(b / (NCB / 2) * 16 + l16, a.M - 1) * 64 + (p & 63));
       t[u][0] = c[0];
       t[u][1] = c[1];
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int b = wave + u * NW, m = b / (NCB / 2) * 16 + l16, p = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
-      if (b >= UNITS || m >= a.M || 2 * p >= a.N) continue;
+      const int b = unit(u), m = b / (NCB / 2) * 16 + l16, p = tile_n * (BN / 2) + b % (NCB / 2) * 16 + 4 * lq;
+      if (!unit_ok(u) || m >= a.M || 2 * p >= a.N) continue;
       const int head = p >> 6;
       const bool is_v = head >= hq + hkv;
       const int nheads = head < hq ? hq : hkv, first_head = is_v ? hq + hkv : head >= hq ? hq : 0;
@@ -360,14 +378,14 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
     if (MODE == SX_GEMM_RESIDUAL) {
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
-        const int b = min(wave + u * NW, UNITS - 1), m = min(b / NCB * 16 + l16, a.M - 1);
+        const int b = unit(u), m = min(b / NCB * 16 + l16, a.M - 1);
         r[u] = *reinterpret_cast<const f32x4*>(Y + (size_t)m * a.N + min(tile_n * BN + b % NCB * 16 + 4 * lq, a.N - 4));
       }
     }
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int b = wave + u * NW, m = b / NCB * 16 + l16, n = tile_n * BN + b % NCB * 16 + 4 * lq;
-      if (b >= UNITS) continue;
+      const int b = unit(u), m = b / NCB * 16 + l16, n = tile_n * BN + b % NCB * 16 + 4 * lq;
+      if (!unit_ok(u)) continue;
       if (m >= a.M || n >= a.N) continue;
       f32x4 x = v[u][0];
       if (MODE == SX_GEMM_RESIDUAL) x += r[u];
@@ -377,8 +395,8 @@ __global__ __launch_bounds__(64 * CG * RG) void gemm_skinny_bf16_kernel(SkinnyAr
     float* Y = static_cast<float*>(a.Y);
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
-      const int b = wave + u * NW, m = b / NCB * 16 + l16, n = tile_n * BN + b % NCB * 16 + 4 * lq;
-      if (b >= UNITS || m >= a.M) continue;
+      const int b = unit(u), m = b / NCB * 16 + l16, n = tile_n * BN + b % NCB * 16 + 4 * lq;
+      if (!unit_ok(u) || m >= a.M) continue;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (n + e < a.N) {
@@ -413,8 +431,9 @@ SkinnyPlan plan_skinny(int M, int cols, int K, bool pairs, bool have_ws, size_t 
       const int rounds = (tiles * split + cus - 1) / cus;
       const float unit = rounds * ((nb + split - 1) / split) * (rb * 2048 + bn * 128) / 63e3f;
       const float weights = (float)tiles * nb * bn * 128 / 5.2e6f;
-      const float cost = 2.1f * rounds + sqrtf(unit * unit + weights * weights) +
-                         (split > 1 ? 1.3f + 0.07f * split + 2.5e-5f * (float)part : 0.f);
+      float cost = 2.1f * rounds + sqrtf(unit * unit + weights * weights) +
+                   (split > 1 ? 1.3f + 0.07f * split + 2.5e-5f * (float)part : 0.f);
+      if (split > 1 && bn == 128 && rb == 8) cost *= 1.01f;  // four stages instead of five: 8192 x 8192 at 128 rows 39.9 us, 64 columns 38.6
       if (cost < best) best = cost, p = {bn, split};
     }
   }
