@@ -42,6 +42,7 @@ WIDE_SHAPES = [
     (2, 134, 5408, 4096, 160, "all", False), (2, 793, 2376, 3072, 128, "none", False),
     (2, 514, 13096, 3072, 192, "tail", False), (2, 404, 16424, 3072, 224, "tail", False),
     (2, 484, 16568, 4096, 256, "tail", False), (2, 1926, 6024, 3072, 256, "tail", True),
+    (0, 2424, 2346, 8192, 224, "all", False), (0, 233, 16480, 6144, 256, "all", False),
     (0, 2251, 1040, 5120, 160, "all", True), (2, 2251, 520, 5120, 160, "all", True), (2, 780, 9376, 2560, 160, "tail", True),
     # what the suite has run all along, whatever the height
     (0, 160, 520, 192, None, None, None), (0, 161, 72, 1088, None, None, None), (0, 192, 512, 64, None, None, None),
@@ -60,8 +61,35 @@ QKV_SHAPES = [
     (1543, 3072, 16, 2, 128, "none", True), (1282, 64, 16, 16, 160, "none", False), (1541, 64, 32, 4, 160, "none", True),
     (2054, 3072, 64, 8, 192, "none", False), (961, 64, 64, 8, 192, "none", False), (961, 64, 64, 16, 224, "none", False),
     (1025, 64, 64, 16, 224, "none", False), (1794, 64, 4, 2, 128, "none", True), (1838, 64, 4, 2, 256, "none", True),
-    (2305, 64, 112, 16, 256, "none", False), (1983, 3072, 80, 8, 256, "tail", True)
+    (2305, 64, 112, 16, 256, "none", False), (1983, 3072, 80, 8, 256, "tail", True),
+    (1601, 3584, 16, 2, 160, "all", False), (2252, 5120, 8, 1, 160, "all", True), (1921, 6144, 16, 2, 192, "all", False),
+    (1319, 3072, 64, 16, 192, "tail", False), (1539, 5120, 64, 8, 224, "tail", False)
 ]
 
-# at most 128 rows: the narrow kernel's tiles of 64 and of 128 columns, whole and with K cut
-FEW_ROWS_QKV_SHAPES = [(1, 64, 1, 1), (128, 4096, 32, 32), (100, 8192, 64, 8), (65, 192, 112, 16), (128, 512, 8, 1), (33, 1088, 4, 2)]
+# at most 128 rows: (rows, K, query heads, KV heads, columns of the narrow kernel's tiles, whether K is cut)
+FEW_ROWS_QKV_SHAPES = [(1, 64, 1, 1, 64, False), (128, 4096, 32, 32, 96, True), (100, 8192, 64, 8, 128, True),
+                       (65, 192, 112, 16, 96, False), (128, 512, 8, 1, 64, False), (33, 1088, 4, 2, 64, False),
+                       (100, 1536, 1, 1, 64, True), (100, 64, 128, 64, 128, False)]
+
+# The narrow kernel at every number of row blocks, (mode, N, K) or (3, K, query heads, KV heads), then columns of a tile and
+# whether K is cut, the same at any number of rows: K of one slab, of less than the stages hold, of one slab more than they
+# hold twice over; ragged columns, rows of Y that are whole quads and not
+NARROW_SHAPES = [
+    (0, 72, 64, 64, False), (0, 250, 1536, 64, True), (1, 1000, 2048, 64, True), (0, 250, 704, 64, False),
+    (0, 16500, 192, 128, False), (1, 8257, 4096, 128, True), (2, 40, 64, 64, False), (2, 1500, 4096, 64, True),
+    (2, 8200, 192, 96, False), (2, 2760, 4096, 96, True), (2, 14000, 320, 128, False), (2, 4132, 5120, 128, True),
+]
+NARROW_QKV_SHAPES = [
+    (3, 64, 1, 1, 64, False), (3, 1536, 1, 1, 64, True), (3, 192, 112, 16, 96, False), (3, 5120, 32, 8, 96, True),
+    (3, 64, 128, 64, 128, False), (3, 6144, 64, 8, 128, True),
+]
+# 4-bit products (N, K, group) and models of one layer (d_model, query heads, KV heads, d_ffn), whose products pair their columns
+W4_SHAPES = [
+    (250, 384, 128, 64, False), (3072, 4096, 512, 64, True), (20500, 512, 64, 96, False), (10884, 4096, 128, 96, True),
+    (30010, 256, 256, 128, False), (10200, 8192, 128, 128, True),
+]
+W4_PAIR_SHAPES = [
+    (128, 1, 1, 128, 64, False), (2048, 1, 1, 128, 64, True), (128, 128, 16, 8320, 96, False), (4096, 64, 16, 5504, 96, True),
+    (128, 128, 64, 12416, 128, False), (3072, 64, 8, 4224, 128, True),
+]
+ROW_BLOCK_EDGES = [1, 16, 17, 32, 33, 64, 65, 80, 81, 112, 113, 128]
