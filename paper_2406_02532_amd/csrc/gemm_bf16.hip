@@ -18,7 +18,7 @@
 // both fit the 160 KB at JB = 4 and 5.  From JB = 6 on W has three and X two (160 KB to the byte at JB = 8): X is small
 // and comes from L2, it is the weights that are late.  As two stages of both, now three of W: a slab of 192 rows 1.40 -> 1.04 us, of 224 1.48 -> 1.16
 // and of 256 1.50 -> 1.30; 70B gate|up at 512 rows 417 -> 361 us, 7B gate|up at 396 rows 99 -> 74, 32000 columns, K = 4096,
-// at 337 rows 109 -> 84; 250 products of the 1B to 70B shapes at 129 to 2500 rows take 0.96 of the time on average.
+// at 337 rows 109 -> 84; 850 products of the 1B to 70B shapes at 129 to 2400 rows take 0.95 of the time on average.
 //
 // Global -> LDS without registers.  Operand slabs are copied by buffer loads that write LDS
 // directly (16 bytes per lane, a wave fills 1 KB of consecutive LDS per instruction), so the K loop

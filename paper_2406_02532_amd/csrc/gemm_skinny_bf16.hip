@@ -17,10 +17,10 @@
 //   so it is with a single matrix that the last-level cache still holds from the call before: 7B gate|up over and over, 100 rows,
 //   35.8 us for 33.2, and 31 with the kernel before; a model's layers do not meet that.
 // Weights from memory, us, the kernel before (128 rows of X always, 64 or 128 columns, three or four stages) -> now, at 16,
-// 64, 100 and 128 rows: 7B O 13.4 -> 10.2, 14.0 -> 11.7, 14.6 -> 14.1, 15.1 -> 15.1; down 24.7 -> 18.7, 25.8 -> 22.3, 27.3 ->
-// 27.6, 29.6 -> 29.6; gate|up 36.7 -> 29.8, 39.4 -> 32.2, 42.2 -> 38.2, 45.5 -> 39.9; head of 32000 47.1 -> 43.5, 48.4 -> 43.8,
-// 50.7 -> 47.4, 53.6 -> 51.4; 70B O 32.5 -> 26.3, 34.0 -> 28.3, 35.7 -> 34.1, 37.8 -> 37.5; down 89.3 -> 72.3, 94.4 -> 79.4, 100.3
-// -> 90.6, 105.5 -> 97.0.  Fourteen shapes at 7 row counts: 0.86 of the time; 5632-wide gate|up at 128 rows 2 % more.
+// 64, 100 and 128 rows: 7B QKV 33.4 -> 23.2, 34.5 -> 26.4, 35.8 -> 29.2, 37.1 -> 31.1; O 14.0 -> 10.5, 14.8 -> 12.1, 15.5 -> 14.6,
+// 16.1 -> 15.7; gate|up 34.7 -> 30.0, 38.1 -> 31.8, 41.6 -> 36.0, 45.1 -> 38.5; down 25.1 -> 19.0, 26.2 -> 22.4, 27.8 -> 27.4, 30.1
+// -> 29.4; head of 32000 45.2 -> 43.1, 47.5 -> 42.2, 50.1 -> 47.0, 52.8 -> 49.3; 70B O 33.1 -> 25.9, 35.1 -> 28.9, 37.0 -> 34.8,
+// 38.9 -> 38.8; down 89.5 -> 71.8, 94.7 -> 79.4, 102.0 -> 89.6, 107.2 -> 97.2.  Nineteen shapes at 13 row counts: 0.85 of the time.
 // Measured and not kept: W straight into registers in the layout of the MFMA operand (a load then touches 16 rows, 64 bytes
 // each, and the address unit bounds it: head at 100 rows 59 us); 32 columns (7B O at 16 rows 9.2, no better from 64 rows on); a
 // walk that starts at the same slab everywhere (see the rotation below).

@@ -489,8 +489,10 @@ int sx_launch_tree_attn_bf16(const void* q, const void* k_tree, const void* v_tr
     int s = cus / wgs;
     if (s > 8) s = 8;
     if (s > npre / 2) s = npre / 2;
-    // what a share costs besides its tiles: the partial results, the counter, and reading them back (3.7 us in four shares; when
-    // it was a launch, 128 nodes, 64 / 32 heads, 300 prefix keys in two shares took 17.1 us, whole 14.7)
+    // What a share costs besides its tiles: the partial results, the counter, and reading them back.  The 6 was fitted when that
+    // was a launch of 5.4 us (128 nodes, 64 / 32 heads, 300 prefix keys in two shares took 17.1 us, whole 14.7); it is 3.7 us in
+    // four shares now, and prefixes of some 256 to 500 keys are left whole that would gain (100 nodes, 32 heads: 400 keys, whole,
+    // 16.0 us, 520, shared, 14.4).
     if (npre * (s - 1) < 6 * s) s = 1;
     const size_t nrow = (size_t)Tq * Hq;
     if (s > 1 && split_ws_bytes >= (size_t)s * nrow * (DH + 2) * sizeof(float)) {
