@@ -19,7 +19,7 @@
 // at 32 bytes each); beyond that a compute unit's own slab, 0.58 us plus 0.08 per block of rows at 128 columns: X read from LDS
 // by every column group, the dequantisation and the MFMAs, which hardly overlap.  So: no more row blocks than M asks for; X
 // three slabs ahead in four stages (a barrier waits only for its own slab's operations, by count), whose swizzle keeps the
-// fragment reads off each other's banks (conflicts 52 % of the cycles in which the LDS is busy with row & 15, 17 % now); codes
+// fragment reads off each other's banks (conflicts half of the cycles in which the LDS is busy with row & 15, 5 to 14 % now); codes
 // converted from their bytes in place (the compiler extracted each one first, 6 more instructions a word); scales and zero
 // points of up to 48 groups fetched into LDS at a time, side by side; the words of two slabs, which share their lines, fetched
 // together.  Weights from memory, us, the kernel before (128 rows always, 128 or 64 columns) -> now, at 16, 64, 100 and 128
